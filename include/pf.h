@@ -62,10 +62,10 @@ const char *pf_status_str(pf_status s);
 
 /* Which kernel family would serve these dimensions.  Host only, no GPU needed.
  *   0  unsupported (pf_delta_fwd would return PF_ERR_UNSUPPORTED)
- *   1  generic path: one workgroup per (b, h), fp32 vector arithmetic, chunk state in LDS; both
- *      dtypes, any d_k, d_v, r; the chunk is halved until its working set fits 160 KiB of LDS next
- *      to the fp32 state (unsupported only when not even one token does); L need not be a
- *      multiple of chunk (the tail is a shorter last chunk)
+ *   1  generic path: the recurrence token by token in fp32 vector arithmetic, rows of the state in
+ *      registers; both dtypes, any d_k, d_v, r; the chunk bounds the tokens staged in LDS at a time
+ *      and is halved until the working set of the chunk-wise form (Theorem 3.2) would fit 160 KiB
+ *      of LDS next to an fp32 state (unsupported only when not even one token does); any L
  *   2  MFMA path (PF_BF16 only): d_k in {64, 128}, d_v any multiple of 16 (the state is split into
  *      tiles of 16 or 32 rows of d_v, so d_v need not equal d_k), and a flow block (see
  *      pf_delta_fwd_block) with block * r in {64, 128, 256}, block in {32, 64, 128}.  Any L: the
@@ -87,7 +87,8 @@ int pf_delta_fwd_supported(int d_k, int d_v, int r, int chunk, pf_dtype dt);
  * square of the block; below 32 tokens the fixed cost of a block outweighs that.  The flow over a chunk
  * is the composition of the flows over consecutive pieces of it (Section 3.1), so O and S_L are the
  * same function of the inputs either way; only the blocking of the arithmetic, hence its rounding,
- * differs.  On the generic path: the requested chunk, halved until its working set fits LDS.  0 when
+ * differs.  On the generic path: the most tokens whose inputs are staged at a time (the
+ * requested chunk, halved as described at pf_delta_fwd_supported).  0 when
  * pf_delta_fwd_supported(...) is 0.  Host only. */
 int pf_delta_fwd_block(int d_k, int d_v, int r, int chunk, pf_dtype dt);
 

@@ -1,184 +1,454 @@
-// Generic path: one workgroup per (b, h), fp32 vector arithmetic, the chunk's working set in
-// LDS.  Serves PF_F32 and every shape the MFMA path has no instance for (any d_k, d_v, r,
-// chunk that fits LDS; a shorter last chunk when L is not a multiple of chunk).
+// Generic path: the recurrence itself (Section 3.1 of ParallelFlow, arXiv 2504.00492), token by token, in
+// fp32 vector arithmetic with the state in registers.  Serves PF_F32, every shape the MFMA path has
+// no instance for (any d_k, d_v, r), sequences shorter than one flow block (the step-by-step use of
+// the forward: a few tokens in, the state in and out) and the L % block tokens a flow block leaves over.
 //
-// Per chunk it takes the steps of Theorem 3.2 (ParallelFlow, arXiv 2504.00492) in delta
-// variables, n = (tokens in chunk) * r virtual tokens:
-//   G      = M (.) diag(beta) K K^T          M strict in time               (system matrix - Id)
-//   [W|U'] = (Id + G)^{-1} [beta K | beta V]  by forward substitution, token by token
-//            (Proposition 3.3; the r rows of one token do not see each other)
-//   U_eff  = U' - W S^T                      (U + W S_0^T of Theorem 3.2)
-//   O      = Q S^T + (Mbar (.) Q K^T) U_eff   Mbar inclusive in time       (flow truncated at t)
-//   S     += U_eff^T K                       (S_1 of Theorem 3.2)
+//   delta rule   u_j = beta_j (v_j - S k_j),   S += sum_j u_j k_j^T,   o = S q
+//   drivers      u_j = atil_j + S a_j,         S += sum_j u_j b_j^T,   o = S q
 //
-// The same kernel serves the general low-rank drivers of Section 3.1,
-//   S_t = S_{t-1} + S_{t-1} A_t B_t^T + Atil_t B_t^T,
-// by loading (K, beta K, beta V) := (-B, A, -Atil): Theorem 3.2's Id - M (.) A B^T is then
-// Id + M (.) (A)(-B)^T, its U + W S_0^T is -(U_eff), and every later line is unchanged.
+// Rows of S are independent (the recurrence multiplies S from the right), so a wavefront owns 64 / LPR
+// rows of one head, LPR lanes to a row, CS columns of it in each lane's registers, and nothing but
+// inputs and outputs ever leaves the registers between tokens.  The sums over a row are a butterfly of
+// LPR lanes in DPP moves.  k (a, b), q, v, beta of a block of tokens are staged in LDS as fp32 by the whole
+// workgroup (one read from memory for all its rows) while the block before is computed; the readout of
+// token t and the products S k of token t + 1 both see S_t, so their sums run side by side.
+//
+// What bounds it: with few rows the dependent chain of a token (CS fused multiply-adds, the butterfly, u,
+// CS more: about 100 to 200 cycles), with many rows the vector ALU; with few tokens the state's own
+// traffic.  The form of Theorem 3.2 with a chunk in LDS that stood here before did 3 to 4 times the
+// arithmetic out of LDS and a workgroup barrier per token of the substitution: 32 heads x 2048 tokens,
+// d = 64, fp32: 10.5 ms; 1024 heads x 1 token, d = 128, r = 2, bf16: 0.24 ms.
 #include "pf_internal.h"
 #include "pf_common.h"
 
 namespace pf {
 
-template <typename T> __device__ __forceinline__ float load_as_f32(const T *p, size_t i);
-template <> __device__ __forceinline__ float load_as_f32<float>(const float *p, size_t i) { return p[i]; }
-template <> __device__ __forceinline__ float load_as_f32<uint16_t>(const uint16_t *p, size_t i)
+namespace {
+
+template <typename T> __device__ __forceinline__ float as_f32(T v);
+template <> __device__ __forceinline__ float as_f32<float>(float v) { return v; }
+template <> __device__ __forceinline__ float as_f32<uint16_t>(uint16_t v) { return bf16_bits_to_f32(v); }
+template <typename T> __device__ __forceinline__ T from_f32(float v);
+template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
+template <> __device__ __forceinline__ uint16_t from_f32<uint16_t>(float v)
 {
-    return bf16_bits_to_f32(p[i]);
-}
-template <typename T> __device__ __forceinline__ void store_from_f32(T *p, size_t i, float v);
-template <> __device__ __forceinline__ void store_from_f32<float>(float *p, size_t i, float v) { p[i] = v; }
-template <> __device__ __forceinline__ void store_from_f32<uint16_t>(uint16_t *p, size_t i, float v)
-{
-    bf16 b = (bf16)v;
-    p[i] = __builtin_bit_cast(uint16_t, b);
+    const bf16 b = (bf16)v;
+    return __builtin_bit_cast(uint16_t, b);
 }
 
-// LDS plan (floats), identical on host and device.
-struct GenericPlan {
-    int ldk, ldv, ldn;          // padded row pitches
-    size_t oS, oK, oW, oU, oQ, oG, oP, total;
-};
-__host__ __device__ inline GenericPlan generic_plan(int dk, int dv, int r, int chunk)
+// 16 bytes of elements as they lie in memory -> fp32 in LDS
+__device__ __forceinline__ void put16(float *dst, u32x4 w, float)
 {
-    GenericPlan p;
-    const int n = chunk * r;
-    p.ldk = dk + 1; p.ldv = dv + 1; p.ldn = n + 1;
-    size_t o = 0;
-    p.oS = o; o += (size_t)dv * p.ldk;
-    p.oK = o; o += (size_t)n * p.ldk;
-    p.oW = o; o += (size_t)n * p.ldk;
-    p.oU = o; o += (size_t)n * p.ldv;
-    p.oQ = o; o += (size_t)chunk * p.ldk;
-    p.oG = o; o += (size_t)n * p.ldn;
-    p.oP = o; o += (size_t)chunk * p.ldn;
-    p.total = o;
+    *reinterpret_cast<u32x4 *>(dst) = w;
+}
+__device__ __forceinline__ void put16(float *dst, u32x4 w, uint16_t)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            v[2 * i] = __uint_as_float(w[2 * h + i] << 16);
+            v[2 * i + 1] = __uint_as_float(w[2 * h + i] & 0xffff0000u);
+        }
+        *reinterpret_cast<f32x4 *>(dst + 4 * h) = v;
+    }
+}
+
+template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// sum over the LPR neighbouring lanes of a row, in every one of them
+template <int LPR> __device__ __forceinline__ float row_sum(float v)
+{
+    static_assert(LPR == 4 || LPR == 8 || LPR == 16 || LPR == 64, "lanes per row");
+    v = dpp_add<0xB1>(v);                        // quad_perm [1 0 3 2]
+    v = dpp_add<0x4E>(v);                        // quad_perm [2 3 0 1]
+    if (LPR >= 8) v = dpp_add<0x141>(v);         // row_half_mirror
+    if (LPR >= 16) v = dpp_add<0x140>(v);        // row_mirror
+    if (LPR >= 64) {
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+    }
+    return v;
+}
+
+constexpr int kPre = 6;      // 16-byte pieces of rows a thread carries for the next block of tokens
+constexpr int kPreV = 4;     // values a thread carries for it
+
+}  // namespace
+
+// How one call is cut up: filled in by the host, uniform over the grid.
+struct GenericPlan {
+    int lpr, cs;        // lanes per row, columns per lane (cs = 0: state rows in LDS, see generic_long_rows)
+    int waves;          // wavefronts per workgroup
+    int tb;             // tokens staged at a time
+    int prefetch;       // the next block's inputs fit the registers a thread carries
+    int vpr;            // pieces per row (16 bytes each when vec, else one element each)
+    int vec;            // rows are whole 16-byte pieces
+    int tiles;          // workgroups per head
+    size_t lds;
+};
+
+template <typename T> struct GenericArgs {
+    const T *Q, *K, *V, *beta;
+    const float *S0;
+    T *O;
+    float *SL;
+    int heads, L, dk, dv, r, t0, product;
+};
+
+namespace {
+
+// R: ranks held side by side (their products with the state all see the state before the token); R = 1
+// with nsub > 1 is the product form (the sub-updates of a token one after another); R = 0 takes any r.
+template <typename T, bool kDrivers, int LPR, int CS, int R>
+__device__ __forceinline__ void generic_rows(const GenericArgs<T> &a, const GenericPlan &pl, float *smem)
+{
+    constexpr int VEC = 16 / sizeof(T), CV = CS / 4, DKP = LPR * CS, RPW = 64 / LPR;
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane % LPR, rr = lane / LPR;
+    const int rowsWG = pl.waves * RPW;
+    // workgroups of one head are `heads` apart in blockIdx (one XCD's L2 when heads is a multiple of 8)
+    const size_t head = blockIdx.x % (unsigned)a.heads;
+    const int base = (int)(blockIdx.x / (unsigned)a.heads) * rowsWG;
+    const int rowl = wave * RPW + rr, row = base + rowl;
+    const bool live = row < a.dv;
+    const int L = a.L, dk = a.dk, dv = a.dv, r = a.r, tb = pl.tb;
+    const int nsub = R == 1 ? r : 1;                 // r == 1, or the product form
+    const T *Qh = a.Q + head * (size_t)L * dk;
+    const T *Kh = a.K + head * (size_t)L * r * dk;
+    const T *Ah = kDrivers ? a.beta + head * (size_t)L * r * dk : Kh;   // rows that multiply the state
+    const T *Vh = a.V + head * (size_t)L * r * dv;
+    const T *bh = a.beta + head * (size_t)L * r;
+    T *Oh = a.O + head * (size_t)L * dv;
+
+    // LDS: rows that multiply the state, (drivers: rows of the update,) q; v; beta; o; u (R = 0)
+    const int krows = tb * r, urow0 = kDrivers ? krows : 0, qrow0 = urow0 + krows, nrows = qrow0 + tb;
+    float *rows = smem, *vs = rows + (size_t)nrows * DKP, *bs = vs + (size_t)krows * rowsWG;
+    float *os = bs + (kDrivers ? 0 : krows), *us = os + (size_t)tb * rowsWG + (size_t)rowl * r;
+
+    float S[CS];
+    {
+        const float *s0 = a.S0 ? a.S0 + (head * (size_t)dv + (live ? row : 0)) * dk : nullptr;
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            const int x = 4 * (c + LPR * i);
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (s0 && live) {
+                if (dk % 4 == 0) {
+                    if (x < dk) v = *reinterpret_cast<const f32x4 *>(s0 + x);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (x + e < dk) v[e] = s0[x + e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) S[4 * i + e] = v[e];
+        }
+    }
+    // columns beyond d_k are staged as zeros, once
+    if (dk < DKP)
+        for (int i = tid; i < nrows * (DKP - dk); i += nthr) rows[(i / (DKP - dk)) * DKP + dk + i % (DKP - dk)] = 0.f;
+
+    // source of staged row i of the block that starts at token t (rows beyond its `cl` tokens: its first row)
+    auto row_src = [&](int i, int t, int cl) -> const T * {
+        if (i >= qrow0) return Qh + (size_t)(t + (i - qrow0 < cl ? i - qrow0 : 0)) * dk;
+        const bool second = kDrivers && i >= urow0;
+        const int j = second ? i - urow0 : i;
+        return (second ? Kh : Ah) + ((size_t)t * r + (j < cl * r ? j : 0)) * dk;
+    };
+    const int rpp = nthr / pl.vpr > 0 ? nthr / pl.vpr : 1;      // rows per pass of the workgroup
+    const int pr0 = tid / pl.vpr, px = tid % pl.vpr;
+    u32x4 pre[kPre];
+    T prev[kPreV], preb{};
+    auto fetch = [&](int t) {                                   // prefetch == 1: rows are whole pieces
+        const int cl = L - t < tb ? L - t : tb;
+#pragma unroll
+        for (int q = 0; q < kPre; ++q) {
+            const int i = pr0 + q * rpp;
+            if (pr0 < rpp && i < nrows) pre[q] = *reinterpret_cast<const u32x4 *>(row_src(i, t, cl) + px * VEC);
+        }
+#pragma unroll
+        for (int q = 0; q < kPreV; ++q) {
+            const int i = tid + q * nthr;
+            if (i < krows * rowsWG) {
+                const int j = i / rowsWG, m = i % rowsWG;
+                prev[q] = Vh[((size_t)t * r + (j < cl * r ? j : 0)) * dv + (base + m < dv ? base + m : 0)];
+            }
+        }
+        if (!kDrivers && tid < krows) preb = bh[(size_t)t * r + (tid < cl * r ? tid : 0)];
+    };
+    auto stage = [&](int t) {
+        if (pl.prefetch) {
+#pragma unroll
+            for (int q = 0; q < kPre; ++q) {
+                const int i = pr0 + q * rpp;
+                if (pr0 < rpp && i < nrows) put16(rows + (size_t)i * DKP + px * VEC, pre[q], T{});
+            }
+#pragma unroll
+            for (int q = 0; q < kPreV; ++q) {
+                const int i = tid + q * nthr;
+                if (i < krows * rowsWG) vs[i] = as_f32(prev[q]);
+            }
+            if (!kDrivers && tid < krows) bs[tid] = as_f32(preb);
+            return;
+        }
+        const int cl = L - t < tb ? L - t : tb;
+        for (int i0 = 0; i0 < nrows; i0 += rpp)
+            for (int x = px; x < pl.vpr; x += nthr) {
+                const int i = i0 + pr0;
+                if (pr0 >= rpp || i >= nrows) continue;
+                const T *p = row_src(i, t, cl);
+                if (pl.vec) put16(rows + (size_t)i * DKP + x * VEC, *reinterpret_cast<const u32x4 *>(p + x * VEC), T{});
+                else rows[(size_t)i * DKP + x] = as_f32(p[x]);
+            }
+        for (int i = tid; i < cl * r * rowsWG; i += nthr) {
+            const int j = i / rowsWG, m = i % rowsWG;
+            vs[i] = base + m < dv ? as_f32(Vh[((size_t)t * r + j) * dv + base + m]) : 0.f;
+        }
+        if (!kDrivers)
+            for (int i = tid; i < cl * r; i += nthr) bs[i] = as_f32(bh[(size_t)t * r + i]);
+    };
+    auto load_row = [&](int i, float (&x)[CS]) {
+#pragma unroll
+        for (int q = 0; q < CV; ++q) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(rows + (size_t)i * DKP + 4 * (c + LPR * q));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * q + e] = v[e];
+        }
+    };
+    auto dot = [&](const float (&x)[CS]) {                      // two partial sums: half the dependent chain
+        float s0 = S[0] * x[0], s1 = S[1] * x[1];
+#pragma unroll
+        for (int i = 2; i < CS; i += 2) {
+            s0 = fmaf(S[i], x[i], s0);
+            s1 = fmaf(S[i + 1], x[i + 1], s1);
+        }
+        return s0 + s1;
+    };
+
+    if (pl.prefetch && a.t0 < L) fetch(a.t0);
+    for (int t0 = a.t0; t0 < L; t0 += tb) {
+        const int cl = L - t0 < tb ? L - t0 : tb;
+        stage(t0);
+        __syncthreads();
+        if (pl.prefetch) fetch(t0 + tb < L ? t0 + tb : t0);
+        if constexpr (R > 0) {
+            const int steps = cl * nsub;                        // R = 1: virtual tokens
+            float kd[R][CS], w[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                load_row(j, kd[j]);
+                w[j] = row_sum<LPR>(dot(kd[j]));
+            }
+            int sub = 0, t = 0;
+#pragma unroll 1
+            for (int s = 0; s < steps; ++s) {
+                const int nx = s + 1 < steps ? s + 1 : s;
+                float kn[R][CS], ku[kDrivers ? R : 1][CS], q[CS], u[R];
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    if constexpr (kDrivers) load_row(urow0 + s * R + j, ku[j]);
+                    load_row(nx * R + j, kn[j]);
+                    const float v = vs[(s * R + j) * rowsWG + rowl];
+                    u[j] = kDrivers ? v + w[j] : bs[s * R + j] * (v - w[j]);
+                }
+                const bool out = ++sub == nsub;
+                if (out) {
+                    load_row(qrow0 + t, q);
+                    sub = 0;
+                }
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+#pragma unroll
+                    for (int i = 0; i < CS; ++i) S[i] = fmaf(u[j], kDrivers ? ku[kDrivers ? j : 0][i] : kd[j][i], S[i]);
+                float o = out ? dot(q) : 0.f;
+#pragma unroll
+                for (int j = 0; j < R; ++j) w[j] = dot(kn[j]);
+                if (out) {
+                    o = row_sum<LPR>(o);
+                    if (c == 0) os[t * rowsWG + rowl] = o;
+                    ++t;
+                }
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    w[j] = row_sum<LPR>(w[j]);
+#pragma unroll
+                    for (int i = 0; i < CS; ++i) kd[j][i] = kn[j][i];
+                }
+            }
+        } else {
+            for (int t = 0; t < cl; ++t) {
+                float x[CS];
+                for (int j = 0; j < r; ++j) {
+                    load_row(t * r + j, x);
+                    const float w = row_sum<LPR>(dot(x)), v = vs[(t * r + j) * rowsWG + rowl];
+                    if (c == 0) us[j] = kDrivers ? v + w : bs[t * r + j] * (v - w);
+                }
+                for (int j = 0; j < r; ++j) {
+                    load_row(urow0 + t * r + j, x);
+                    const float u = us[j];
+#pragma unroll
+                    for (int i = 0; i < CS; ++i) S[i] = fmaf(u, x[i], S[i]);
+                }
+                load_row(qrow0 + t, x);
+                const float o = row_sum<LPR>(dot(x));
+                if (c == 0) os[t * rowsWG + rowl] = o;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < cl * rowsWG; i += nthr) {
+            const int t = i / rowsWG, m = i % rowsWG;
+            if (base + m < dv) Oh[(size_t)(t0 + t) * dv + base + m] = from_f32<T>(os[i]);
+        }
+    }
+    if (a.SL && live) {
+        float *sl = a.SL + (head * (size_t)dv + row) * dk;
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            const int x = 4 * (c + LPR * i);
+            if (dk % 4 == 0) {
+                if (x < dk) *reinterpret_cast<f32x4 *>(sl + x) = f32x4{S[4 * i], S[4 * i + 1], S[4 * i + 2], S[4 * i + 3]};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (x + e < dk) sl[x + e] = S[4 * i + e];
+            }
+        }
+    }
+}
+
+// Rows too long for registers (d_k > 512) or too many ranks for the staging plan: a wavefront per row, the
+// row and the u_j of a token in LDS, operands straight from memory.
+template <typename T, bool kDrivers>
+__device__ __forceinline__ void generic_long_rows(const GenericArgs<T> &a, const GenericPlan &pl, float *smem)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const size_t head = blockIdx.x % (unsigned)a.heads;
+    const int row = (int)(blockIdx.x / (unsigned)a.heads) * pl.waves + wave;
+    if (row >= a.dv) return;                                   // whole wavefronts; no barrier below
+    const int L = a.L, dk = a.dk, dv = a.dv, r = a.r, nsub = a.product ? r : 1, rs = a.product ? 1 : r;
+    float *S = smem + (size_t)wave * (dk + r), *us = S + dk;
+    auto sum = [&](const T *x) {
+        float s = 0.f;
+        for (int i = lane; i < dk; i += 64) s = fmaf(S[i], as_f32(x[i]), s);
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+        return s;
+    };
+    for (int i = lane; i < dk; i += 64) S[i] = a.S0 ? a.S0[(head * (size_t)dv + row) * dk + i] : 0.f;
+    for (int t = a.t0; t < L; ++t) {
+        for (int sub = 0; sub < nsub; ++sub) {
+            const size_t v0 = (head * (size_t)L + t) * r + (size_t)sub * rs;
+            for (int j = 0; j < rs; ++j) {
+                const float w = sum((kDrivers ? a.beta : a.K) + (v0 + j) * dk), v = as_f32(a.V[(v0 + j) * dv + row]);
+                if (lane == 0) us[j] = kDrivers ? v + w : as_f32(a.beta[v0 + j]) * (v - w);
+            }
+            for (int j = 0; j < rs; ++j) {
+                const float u = us[j];
+                const T *k = a.K + (v0 + j) * dk;
+                for (int i = lane; i < dk; i += 64) S[i] = fmaf(u, as_f32(k[i]), S[i]);
+            }
+        }
+        const float o = sum(a.Q + (head * (size_t)L + t) * dk);
+        if (lane == 0) a.O[(head * (size_t)L + t) * dv + row] = from_f32<T>(o);
+    }
+    if (a.SL)
+        for (int i = lane; i < dk; i += 64) a.SL[(head * (size_t)dv + row) * dk + i] = S[i];
+}
+
+}  // namespace
+
+// kDrivers == false: (K, V, beta) are keys, values, betas of the delta rule.
+// kDrivers == true:  (K, V, beta) are (B, Atil, A) of the general recurrence (beta: [.., r, d_k]).
+// One overload per row shape, told apart by its last parameter, so that each gets registers of its own.
+template <int LPR, int CS, int R> struct RowShape {};
+struct LongRows {};
+
+#define PF_RANKS(X, LPR, CS) X(LPR, CS, 1) X(LPR, CS, 2) X(LPR, CS, 4) X(LPR, CS, 0)
+#define PF_ROW_SHAPES(X) \
+    PF_RANKS(X, 4, 4) PF_RANKS(X, 8, 4) PF_RANKS(X, 16, 4) PF_RANKS(X, 16, 8) PF_RANKS(X, 64, 4) PF_RANKS(X, 64, 8)
+
+#define X(LPR, CS, R)                                                                                           \
+    template <typename T, bool kDrivers>                                                                        \
+    __global__ __launch_bounds__(256) void generic_kernel(GenericArgs<T> a, GenericPlan pl, RowShape<LPR, CS, R>) \
+    {                                                                                                           \
+        extern __shared__ __attribute__((aligned(16))) float gsmem[];                                           \
+        generic_rows<T, kDrivers, LPR, CS, R>(a, pl, gsmem);                                                    \
+    }
+PF_ROW_SHAPES(X)
+#undef X
+
+template <typename T, bool kDrivers>
+__global__ __launch_bounds__(256) void generic_kernel(GenericArgs<T> a, GenericPlan pl, LongRows)
+{
+    extern __shared__ __attribute__((aligned(16))) float gsmem[];
+    generic_long_rows<T, kDrivers>(a, pl, gsmem);
+}
+
+namespace {
+
+// Lanes and columns by d_k (the smallest padded row that holds it), tokens per staging block by what a
+// thread can carry in registers for the next block, at most `chunk`, and by 64 KiB of LDS.
+GenericPlan plan_generic(int dk, int dv, int r, int chunk, int tokens, bool drivers, int esize)
+{
+    GenericPlan p{};
+    const int vec = 16 / esize;
+    p.vec = dk % vec == 0;
+    p.vpr = p.vec ? dk / vec : dk;
+    if (dk <= 16) { p.lpr = 4; p.cs = 4; }
+    else if (dk <= 32) { p.lpr = 8; p.cs = 4; }
+    else if (dk <= 64) { p.lpr = 16; p.cs = 4; }
+    else if (dk <= 128) { p.lpr = 16; p.cs = 8; }
+    else if (dk <= 256) { p.lpr = 64; p.cs = 4; }
+    else if (dk <= 512) { p.lpr = 64; p.cs = 8; }
+    const int cap = chunk < tokens ? chunk : (tokens > 0 ? tokens : 1);
+    if (p.cs) {
+        const int rpw = 64 / p.lpr, dkp = p.lpr * p.cs;
+        p.waves = (dv + rpw - 1) / rpw < 4 ? (dv + rpw - 1) / rpw : 4;
+        const int nthr = 64 * p.waves, rows_wg = p.waves * rpw, rpp = nthr / p.vpr;
+        auto lds = [&](int tb) {
+            const size_t k = (size_t)tb * r;
+            return 4 * ((k * (drivers ? 2 : 1) + tb) * dkp + k * rows_wg + (drivers ? 0 : k) + (size_t)tb * rows_wg +
+                        (size_t)rows_wg * r);
+        };
+        auto carried = [&](int tb) {
+            const size_t k = (size_t)tb * r, rows = k * (drivers ? 2 : 1) + tb;
+            return p.vec && rpp > 0 && rows <= (size_t)kPre * rpp && k * rows_wg <= (size_t)kPreV * nthr && k <= (size_t)nthr;
+        };
+        int tb = cap;
+        while (tb > 1 && !(carried(tb) && lds(tb) <= 65536)) tb = tb > 16 ? tb - tb / 4 : tb - 1;
+        p.prefetch = carried(tb) && lds(tb) <= 65536;
+        if (!p.prefetch) {
+            tb = cap;
+            while (tb > 1 && lds(tb) > 65536) tb = (tb + 1) / 2;
+        }
+        p.tb = tb;
+        p.lds = lds(tb);
+        p.tiles = (dv + rows_wg - 1) / rows_wg;
+    }
+    if (!p.cs || p.lds > kMaxLdsBytes) {
+        p.cs = 0;
+        const size_t per_wave = 4 * ((size_t)dk + r);
+        p.waves = 4;
+        while (p.waves > 1 && p.waves * per_wave > kMaxLdsBytes) p.waves /= 2;
+        p.lds = p.waves * per_wave;
+        p.tiles = (dv + p.waves - 1) / p.waves;
+    }
     return p;
 }
 
-// rs = rows of the system that are solved together and do not see each other: r for the paper's
-// additive rank-r increment (Theorem 3.2's mask, strict in time), 1 for the product form, in
-// which the r sub-updates of a token are applied one after another (mask strict in the virtual
-// token).  The readout mask is the same in both.
-// kDrivers == false: (K, V, beta) are keys, values, betas of the delta rule.
-// kDrivers == true:  (K, V, beta) are (B, Atil, A) of the general recurrence (beta: [.., r, d_k]).
-template <typename T, bool kDrivers>
-__global__ __launch_bounds__(256) void generic_kernel(const T *__restrict__ Q, const T *__restrict__ K,
-                                                      const T *__restrict__ V, const T *__restrict__ beta,
-                                                      const float *S0, T *__restrict__ O, float *SL,
-                                                      int L, int dk, int dv, int r, int chunk, int t0,
-                                                      int rs)
-{
-    extern __shared__ float smem[];
-    const GenericPlan pl = generic_plan(dk, dv, r, chunk);
-    float *S = smem + pl.oS, *Kc = smem + pl.oK, *Wc = smem + pl.oW, *Uc = smem + pl.oU;
-    float *Qc = smem + pl.oQ, *G = smem + pl.oG, *Pm = smem + pl.oP;
-    const int ldk = pl.ldk, ldv = pl.ldv, ldn = pl.ldn;
-    const int tid = threadIdx.x, nth = blockDim.x;
-    const size_t head = blockIdx.x;
-    const T *Qh = Q + head * (size_t)L * dk;
-    const T *Kh = K + head * (size_t)L * r * dk;
-    const T *Vh = V + head * (size_t)L * r * dv;
-    const T *bh = beta + head * (size_t)L * r * (kDrivers ? dk : 1);
-    T *Oh = O + head * (size_t)L * dv;
+}  // namespace
 
-    for (int i = tid; i < dv * dk; i += nth) {
-        const int m = i / dk, x = i % dk;
-        S[m * ldk + x] = S0 ? S0[head * (size_t)dv * dk + i] : 0.0f;
-    }
-    __syncthreads();
-
-    for (int c0 = t0; c0 < L; c0 += chunk) {   // tokens before t0 belong to another kernel
-        const int cl = min(chunk, L - c0);   // tokens in this chunk (shorter tail allowed)
-        const int n = cl * r;                // virtual tokens in this chunk
-        // ---- load: K, W = beta K, U = beta V, Q
-        for (int i = tid; i < n * dk; i += nth) {
-            const int row = i / dk, x = i % dk;
-            const float kv = load_as_f32(Kh, ((size_t)c0 * r + row) * dk + x);
-            if (kDrivers) {
-                Kc[row * ldk + x] = -kv;
-                Wc[row * ldk + x] = load_as_f32(bh, ((size_t)c0 * r + row) * dk + x);
-            } else {
-                Kc[row * ldk + x] = kv;
-                Wc[row * ldk + x] = load_as_f32(bh, (size_t)c0 * r + row) * kv;
-            }
-        }
-        for (int i = tid; i < n * dv; i += nth) {
-            const int row = i / dv, m = i % dv;
-            const float vv = load_as_f32(Vh, ((size_t)c0 * r + row) * dv + m);
-            Uc[row * ldv + m] = kDrivers ? -vv : load_as_f32(bh, (size_t)c0 * r + row) * vv;
-        }
-        for (int i = tid; i < cl * dk; i += nth) {
-            const int t = i / dk, x = i % dk;
-            Qc[t * ldk + x] = load_as_f32(Qh, ((size_t)c0 + t) * dk + x);
-        }
-        __syncthreads();
-        // ---- G = M (.) (beta K) K^T  and  P = Mbar (.) Q K^T   (W still holds beta K here)
-        for (int i = tid; i < n * n; i += nth) {
-            const int row = i / n, col = i % n;
-            float acc = 0.0f;
-            if (col / rs < row / rs)
-                for (int x = 0; x < dk; ++x) acc = fmaf(Wc[row * ldk + x], Kc[col * ldk + x], acc);
-            G[row * ldn + col] = acc;
-        }
-        for (int i = tid; i < cl * n; i += nth) {
-            const int t = i / n, col = i % n;
-            float acc = 0.0f;
-            if (col / r <= t)
-                for (int x = 0; x < dk; ++x) acc = fmaf(Qc[t * ldk + x], Kc[col * ldk + x], acc);
-            Pm[t * ldn + col] = acc;
-        }
-        __syncthreads();
-        // ---- forward substitution, rs rows at a time (one token, or one virtual token)
-        const int ncol = dk + dv;
-        for (int t = 1; t < n / rs; ++t) {
-            for (int i = tid; i < rs * ncol; i += nth) {
-                const int row = t * rs + i / ncol, col = i % ncol;
-                float acc = 0.0f;
-                if (col < dk) {
-                    for (int j = 0; j < t * rs; ++j) acc = fmaf(G[row * ldn + j], Wc[j * ldk + col], acc);
-                    Wc[row * ldk + col] -= acc;
-                } else {
-                    const int m = col - dk;
-                    for (int j = 0; j < t * rs; ++j) acc = fmaf(G[row * ldn + j], Uc[j * ldv + m], acc);
-                    Uc[row * ldv + m] -= acc;
-                }
-            }
-            __syncthreads();
-        }
-        // ---- U_eff = U' - W S^T
-        for (int i = tid; i < n * dv; i += nth) {
-            const int row = i / dv, m = i % dv;
-            float acc = 0.0f;
-            for (int x = 0; x < dk; ++x) acc = fmaf(Wc[row * ldk + x], S[m * ldk + x], acc);
-            Uc[row * ldv + m] -= acc;
-        }
-        __syncthreads();
-        // ---- O = Q S^T + P U_eff
-        for (int i = tid; i < cl * dv; i += nth) {
-            const int t = i / dv, m = i % dv;
-            float acc = 0.0f;
-            for (int x = 0; x < dk; ++x) acc = fmaf(Qc[t * ldk + x], S[m * ldk + x], acc);
-            for (int j = 0; j < (t + 1) * r; ++j) acc = fmaf(Pm[t * ldn + j], Uc[j * ldv + m], acc);
-            store_from_f32(Oh, ((size_t)c0 + t) * dv + m, acc);
-        }
-        __syncthreads();
-        // ---- S += U_eff^T K
-        for (int i = tid; i < dv * dk; i += nth) {
-            const int m = i / dk, x = i % dk;
-            float acc = S[m * ldk + x];
-            for (int j = 0; j < n; ++j) acc = fmaf(Uc[j * ldv + m], Kc[j * ldk + x], acc);
-            S[m * ldk + x] = acc;
-        }
-        __syncthreads();
-    }
-    if (SL)
-        for (int i = tid; i < dv * dk; i += nth) SL[head * (size_t)dv * dk + i] = S[(i / dk) * ldk + i % dk];
-}
-
+// LDS of the chunk-wise form of Theorem 3.2 at these dimensions (S, K, W, U, Q, G, P in fp32): what
+// pf_delta_fwd_block and the family query size chunks by.  The recurrence above needs less.
 size_t generic_lds_bytes(int dk, int dv, int r, int chunk)
 {
-    return generic_plan(dk, dv, r, chunk).total * sizeof(float);
+    const size_t n = (size_t)chunk * r;
+    return 4 * ((size_t)(dv + 2 * n + chunk) * (dk + 1) + n * (dv + 1) + (n + chunk) * (n + 1));
 }
 
 template <typename T, bool kDrivers>
@@ -186,15 +456,29 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
                                           const float *S0, void *O, float *SL, int heads, int L, int dk, int dv,
                                           int r, int chunk, int t0, bool product, hipStream_t stream)
 {
-    const size_t lds = generic_lds_bytes(dk, dv, r, chunk);
-    auto kern = generic_kernel<T, kDrivers>;
-    // the opt-in is for the largest size any call may ask for, so that it is made once per device
-    static std::atomic<uint64_t> armed{0};
-    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), kMaxLdsBytes);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(heads), dim3(256), lds, stream, (const T *)Q, (const T *)K, (const T *)V,
-                       (const T *)beta, S0, (T *)O, SL, L, dk, dv, r, chunk, t0, product ? 1 : r);
-    return hipGetLastError();
+    const GenericPlan pl = plan_generic(dk, dv, r, chunk, L - t0, kDrivers, (int)sizeof(T));
+    if (pl.lds > kMaxLdsBytes || (long long)heads * pl.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    const GenericArgs<T> a{(const T *)Q, (const T *)K, (const T *)V, (const T *)beta, S0, (T *)O, SL,
+                           heads, L, dk, dv, r, t0, product ? 1 : 0};
+    const int ranks = product ? 1 : r;
+    auto launch = [&](auto shape) -> hipError_t {
+        void (*kern)(GenericArgs<T>, GenericPlan, decltype(shape)) = generic_kernel<T, kDrivers>;
+        if (pl.lds > 65536) {
+            // the opt-in is for the largest size any call may ask for, so that it is made once per device
+            static std::atomic<uint64_t> armed{0};
+            hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), kMaxLdsBytes);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kern, dim3((unsigned)heads * pl.tiles), dim3(64 * pl.waves), pl.lds, stream, a, pl, shape);
+        return hipGetLastError();
+    };
+    if (pl.cs == 0) return launch(LongRows{});
+    const int rank_shape = ranks == 1 || ranks == 2 || ranks == 4 ? ranks : 0;
+#define X(LPR, CS, R) \
+    if (pl.lpr == LPR && pl.cs == CS && rank_shape == R) return launch(RowShape<LPR, CS, R>{});
+    PF_ROW_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_generic(const void *Q, const void *K, const void *V, const void *beta, const float *S0,
