@@ -14,6 +14,8 @@
 #include "pf_internal.h"
 #include "pf_common.h"
 
+#include <type_traits>
+
 namespace pf {
 
 __global__ __launch_bounds__(256) void segment_constants_kernel(bf16 *zeroV, float *ident, int n, int d)
@@ -31,58 +33,93 @@ hipError_t launch_segment_constants(void *zeroV, float *ident, int n, int d, hip
     return hipGetLastError();
 }
 
-// One workgroup owns kRows rows of the state of one head (rows are independent) and walks the
-// segments: S <- S P_s + H_s in fp32.  The rows live in LDS; a thread produces the columns
-// x = tid, tid + 256, ... of every row.
-constexpr int kComposeRows = 8;
+// One workgroup owns kComposeRows rows of the state of one head (rows are independent) and walks the segments:
+// S <- S P_s + H_s in fp32.  Thread (yg, x4) sums d / kComposeSplit values of y for 4 columns of every row; the
+// kComposeSplit partial sums meet in LDS.  A thread's piece of P_{s+1} is in registers before segment s is
+// summed: P does not depend on the state, so the chain over the segments never waits for memory.  What bounds it is
+// that chain (products and two barriers per segment).  One column per thread with P read as it was needed took
+// 273 us for 4 heads x 8 segments, d = 128.
+constexpr int kComposeRows = 4;
+constexpr int kComposeSplit = 16;
 
-__global__ __launch_bounds__(256) void segment_compose_kernel(const float *S0,
-                                                              const float *__restrict__ Pseg,
-                                                              const float *__restrict__ Hseg,
-                                                              float *__restrict__ Sin, float *SL, int G, int d)
+template <int D>
+__device__ __forceinline__ void segment_compose(const float *S0, const float *__restrict__ Pseg,
+                                                const float *__restrict__ Hseg, float *__restrict__ Sin, float *SL, int G)
 {
-    extern __shared__ float rows[];                    // [2][kComposeRows][d]
-    const int tiles = d / kComposeRows;
+    constexpr int X4 = D / 4, NTHR = X4 * kComposeSplit, YN = D / kComposeSplit;
+    static_assert(kComposeRows * D <= NTHR, "a thread per state element");
+    __shared__ __attribute__((aligned(16))) float cur[kComposeRows][D], part[kComposeSplit][kComposeRows][D];
+    const int tiles = D / kComposeRows;
     const size_t head = blockIdx.x / tiles;
     const int r0 = (blockIdx.x % tiles) * kComposeRows;
-    const int tid = threadIdx.x;
-    float *cur = rows, *nxt = rows + kComposeRows * d;
-    for (int i = tid; i < kComposeRows * d; i += 256)
-        cur[i] = S0 ? S0[head * (size_t)d * d + (size_t)(r0 + i / d) * d + i % d] : 0.0f;
-    __syncthreads();
-    for (int s = 0; s < G; ++s) {
-        const size_t seg = head * (size_t)G + s;
-        for (int i = tid; i < kComposeRows * d; i += 256)
-            Sin[seg * (size_t)d * d + (size_t)(r0 + i / d) * d + i % d] = cur[i];
-        const float *P = Pseg + seg * (size_t)d * d;
-        const float *H = Hseg + seg * (size_t)d * d;
-        for (int x = tid; x < d; x += 256) {
-            float acc[kComposeRows];
+    const int tid = threadIdx.x, x = 4 * (tid % X4), yg = tid / X4;
+    const bool own = tid < kComposeRows * D;           // the state element this thread adds up
+    const int om = own ? tid / D : 0, ox = tid % D;
+    const size_t oel = (size_t)(r0 + om) * D + ox;
+    float s = own && S0 ? S0[head * (size_t)D * D + oel] : 0.0f;
+    f32x4 p[YN];
+    float h = 0.0f;
+    auto fetch = [&](int g) {
+        const size_t seg = (head * (size_t)G + g) * D * D;
 #pragma unroll
-            for (int m = 0; m < kComposeRows; ++m) acc[m] = H[(size_t)(r0 + m) * d + x];
-            for (int y = 0; y < d; ++y) {
-                const float p = P[(size_t)y * d + x];   // coalesced over x
-#pragma unroll
-                for (int m = 0; m < kComposeRows; ++m) acc[m] = fmaf(cur[m * d + y], p, acc[m]);
-            }
-#pragma unroll
-            for (int m = 0; m < kComposeRows; ++m) nxt[m * d + x] = acc[m];
+        for (int i = 0; i < YN; ++i) p[i] = *reinterpret_cast<const f32x4 *>(Pseg + seg + (size_t)(yg * YN + i) * D + x);
+        h = Hseg[seg + oel];
+    };
+    fetch(0);
+    for (int g = 0; g < G; ++g) {
+        if (own) {
+            cur[om][ox] = s;
+            Sin[(head * (size_t)G + g) * D * D + oel] = s;
         }
+        s = h;
         __syncthreads();
-        float *t = cur; cur = nxt; nxt = t;
+        f32x4 acc[kComposeRows];
+#pragma unroll
+        for (int m = 0; m < kComposeRows; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < YN; ++i)
+#pragma unroll
+            for (int m = 0; m < kComposeRows; ++m) {
+                const float c = cur[m][yg * YN + i];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[m][e] = fmaf(c, p[i][e], acc[m][e]);
+            }
+        fetch(g + 1 < G ? g + 1 : g);
+#pragma unroll
+        for (int m = 0; m < kComposeRows; ++m) *reinterpret_cast<f32x4 *>(&part[yg][m][x]) = acc[m];
+        __syncthreads();
+        if (own) {
+#pragma unroll
+            for (int q = 0; q < kComposeSplit; ++q) s += part[q][om][ox];
+        }
     }
-    if (SL)
-        for (int i = tid; i < kComposeRows * d; i += 256)
-            SL[head * (size_t)d * d + (size_t)(r0 + i / d) * d + i % d] = cur[i];
+    if (SL && own) SL[head * (size_t)D * D + oel] = s;
 }
+
+// one overload per width, told apart by the last parameter
+#define PF_COMPOSE(D)                                                                                              \
+    __global__ __launch_bounds__(D / 4 * kComposeSplit) void segment_compose_kernel(                               \
+        const float *S0, const float *Pseg, const float *Hseg, float *Sin, float *SL, int G,                       \
+        std::integral_constant<int, D>)                                                                            \
+    {                                                                                                              \
+        segment_compose<D>(S0, Pseg, Hseg, Sin, SL, G);                                                            \
+    }
+PF_COMPOSE(64)
+PF_COMPOSE(128)
+#undef PF_COMPOSE
 
 hipError_t launch_segment_compose(const float *S0, const float *Pseg, const float *Hseg, float *Sin,
                                   float *SL, int heads, int G, int d, hipStream_t stream)
 {
-    if (d % kComposeRows != 0) return hipErrorInvalidValue;
-    const size_t lds = (size_t)2 * kComposeRows * d * sizeof(float);
-    hipLaunchKernelGGL(segment_compose_kernel, dim3((unsigned)(heads * (d / kComposeRows))), dim3(256), lds,
-                       stream, S0, Pseg, Hseg, Sin, SL, G, d);
+    const unsigned grid = (unsigned)(heads * (d / kComposeRows));
+    auto launch = [&](auto width) {
+        constexpr int D = decltype(width)::value;
+        void (*kern)(const float *, const float *, const float *, float *, float *, int, decltype(width)) = segment_compose_kernel;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(D / 4 * kComposeSplit), 0, stream, S0, Pseg, Hseg, Sin, SL, G, width);
+    };
+    if (d == 64) launch(std::integral_constant<int, 64>{});
+    else if (d == 128) launch(std::integral_constant<int, 128>{});
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
