@@ -1,0 +1,373 @@
+// Body of the scan kernel for flow blocks of 64 virtual tokens and tiles of 16 rows of S (the delta rule): one wavefront
+// runs the whole chain R -> U_eff -> S of the 16 rows by itself, out of registers.
+//
+// With S^T as accumulator tiles (rows d_k, columns the 16 rows of S) every product of a block takes the result of
+// the one before it as its B operand, and an accumulator tile is a B operand lane for lane (pf_common.h):
+//     R     = beta (.) (V - K S^T)     A operand: rows of K             B: S^T (bf16 copy in registers)
+//     U_eff = T R                      A operand: T tiles               B: R
+//     S^T  += K^T U_eff                A operand: K^T, transposing read  B: U_eff
+// so neither R, U_eff nor S passes through LDS on the chain, and the chain needs no barrier inside a block.  Row
+// tiles of S^T are numbered so that lane group g of tiles 2 ks and 2 ks + 1 holds d_k = 32 ks + 8 g .. + 7: the
+// joined pair then pairs with 16 consecutive bytes of a row of K.
+//
+// A workgroup has one such state wave per 16 rows and four helper waves.  Two of them (stagers) load K, V tile, beta
+// and the T tiles of a later block straight into a ring of LDS slots, the other two (readers) compute the readout of
+// the block before,
+//     O^T = S Q^T + U_eff^T P^T,
+// from the copies of S and U_eff that the state wave leaves in LDS in operand form.  One barrier per block.
+//
+// What bounds it: at d = 64 the state wave (38 MFMAs at d = 128, 22 at d = 64, and the latencies between the three
+// products: about 1300 cycles a block); at d = 128 with the readout the 35 KB a block brings into the compute unit, at
+// about 18 bytes a cycle (1900 cycles; the stagers then wait to issue, while the state wave waits at the barrier).
+// Against the split of the chain over four waves that pf_scan.hip keeps for the other shapes (three barriers a block), us:
+//   32 heads x 65536 tokens, r = 2, d = 128   1822 -> 1673      24 heads x 4096 tokens, r = 2, d = 64   66 -> 61
+//   32 heads x 2048 tokens, r = 1, d = 64     22.4 -> 20.8      32 segments x 4096 tokens, state only   92 -> 73
+// With 32 rows per workgroup both move the same 41 KB a block and the split is as fast (64 heads x 4096 tokens, r = 2:
+// 132.8 against 133.0), with 128 virtual tokens a block the operands of one wave do not fit its registers.
+#pragma once
+#include "pf_common.h"
+#include "pf_internal.h"
+#include "pf_layout.h"
+
+// keeps memory accesses in program order across it (register arithmetic may cross)
+#define LDS_FENCE() asm volatile("" ::: "memory")
+
+namespace pf {
+
+// K lies in LDS without padding, its 16-byte units permuted within a row (position = unit ^ swizzle of the row) so
+// that 16 rows at one unit (row operand) and 4 rows at 4 neighbouring units (transposing read) both touch
+// distinct banks.  With rows padded by 16 bytes the transposing reads were four-way conflicts.
+template <int D>
+__device__ __forceinline__ int k_swizzle(int row)
+{
+    static_assert(D == 64 || D == 128, "16-byte units per row");
+    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+}
+
+template <int D, int N, int C, int TV, bool RO>
+struct ChainPlan {
+    static constexpr int NS = TV / 16;                 // state waves
+    static constexpr int stagers = 2, readers = RO ? 2 : 0;
+    static constexpr int threads = 64 * (NS + stagers + readers);
+    static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
+    // one ring slot: K, V tile, T tiles, beta (32 bits each)
+    static constexpr size_t oV = (size_t)N * D * 2;
+    static constexpr size_t oT = oV + (size_t)N * TV * 2;
+    static constexpr size_t oB = oT + (size_t)NT * 1024;
+    static constexpr size_t slot = oB + (size_t)N * 4;
+    static constexpr size_t szX = RO ? (size_t)NS * (D / 32) * 1024 : 0;   // S of a block, operand tiles
+    static constexpr size_t szU = RO ? (size_t)NS * (N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
+    // two slots are being read (this block, and the rows and T of the next), the others are on their way from memory
+    static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU)) / slot);
+    static constexpr int kRing = fit < 6 ? fit : 6;
+    static constexpr size_t oX = kRing * slot;
+    static constexpr size_t oU = oX + 2 * szX;
+    static constexpr size_t total = oU + 2 * szU;
+    static constexpr bool kServes = N == 64 && TV == 16 && kRing >= 4;
+};
+
+// 16 bytes (4: 2 bytes, widened to 32 bits) per lane from memory to LDS; the LDS address is the wavefront's, lane l
+// writes behind lane l - 1.
+__device__ __forceinline__ void load_lds16(const bf16 *src, char *dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 2, 0, 0);
+}
+
+template <int D, int N, int C, int TV, bool RO>
+__device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const bf16 *V, const bf16 *beta,
+                                           const bf16 *Tt, const bf16 *Pt, const float *S0, bf16 *O, float *SL,
+                                           int nchains, int NC, int tail, int vmul, int s0mul, int dv, char *smem)
+{
+    using Pl = ChainPlan<D, N, C, TV, RO>;
+    constexpr int NS = Pl::NS, NT = Pl::NT, kRing = Pl::kRing;
+    constexpr int R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, MD = D / 16, CT = C / 16;
+    constexpr int NSt = Pl::stagers;
+
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const int tile = blockIdx.x / nchains;             // workgroups of one head: one XCD (see the launcher)
+    const size_t chain = blockIdx.x % nchains;
+    const size_t c0 = chain * (size_t)NC;
+    // `tail` tokens of every head belong to another kernel; vmul, s0mul = 0: one block at V, one matrix at S0 for all
+    Q += chain * (size_t)tail * D;
+    K += chain * (size_t)tail * R * D;
+    V += (size_t)vmul * chain * (size_t)tail * R * dv + tile * TV;
+    beta += chain * (size_t)tail * R;
+    bf16 *Xs = reinterpret_cast<bf16 *>(smem + Pl::oX), *Us = reinterpret_cast<bf16 *>(smem + Pl::oU);
+    constexpr int XB = (int)(Pl::szX / 2), UB = (int)(Pl::szU / 2);   // elements of one buffer
+
+    if (wave < NS) {
+        // -------------------------------------------------------------- state waves
+        __builtin_amdgcn_s_setprio(3);                 // the helpers of this SIMD fill what the chain leaves
+        auto dk0 = [&](int mt) { return 32 * (mt >> 1) + 8 * g + 4 * (mt & 1); };
+        const size_t srow = (size_t)(tile * TV + 16 * wave + r16) * D;
+        f32x4 sacc[MD];
+#pragma unroll
+        for (int mt = 0; mt < MD; ++mt) {
+            sacc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (S0) sacc[mt] = *reinterpret_cast<const f32x4 *>(S0 + (size_t)s0mul * chain * (size_t)dv * D + srow + dk0(mt));
+        }
+        // byte offsets in a slot: row operand of K by k-step, transposing read of K by pair of d_k tiles
+        int kr0[NKS], kt0[NKS];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            kr0[ks] = r16 * D * 2 + ((4 * ks + g) ^ k_swizzle<D>(r16)) * 16;
+            kt0[ks] = (4 * g + (r16 >> 2)) * D * 2 + ((4 * ks + (r16 & 3)) ^ k_swizzle<D>(4 * g + (r16 >> 2))) * 16;
+        }
+        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 16 * wave + 4 * (r16 & 3)) * 2;
+        const int tt0 = (int)Pl::oT + lane * 16, bt0 = (int)Pl::oB + 16 * g;
+        auto at8 = [&](int off) { return *reinterpret_cast<const bf16x8 *>(smem + off); };
+
+        // Operands of a block are read from its slot ahead of their use: K^T during R, rows of K, V, beta and T of the
+        // next block during the update of S.  The order below is the order of issue (kInOrder keeps the compiler from
+        // gathering the reads behind the products): every LDS read and every conversion lies in the shadow of products.
+        // Reads gathered at the end of a block cost 0.1 us a block.
+#define kInOrder() __builtin_amdgcn_sched_barrier(0)
+        constexpr int NM = NKT * MD;                   // products of R, and of the update
+        static_assert(NM == MT * NKS && MT == 4, "one operand of K^T is read per product of R");
+        bf16x8 aK[MT][NKS], tA[NT], aT[NKT][MD];
+        bf16x4 vt[MT];
+        u32x4 bt[MT];                                  // bf16 in the low half
+        f32x4 vneg[MT], bw[MT];                        // -V and beta, widened
+        auto read_kt = [&](int base, int i) {
+            const int kt = i / MD, mt = i % MD;
+            const bf16 *p = reinterpret_cast<const bf16 *>(smem + base + kt0[mt >> 1] + 32 * kt * D * 2 + 8 * (mt & 1));
+            aT[kt][mt] = join(lds_read_tr4(p), lds_read_tr4(p + 16 * D));
+        };
+        constexpr int kAhead = 2 * MT + MT * NKS + NT, kPer = (kAhead + NM - 1) / NM;
+        auto read_ahead = [&](int base, int i) {
+            if (i < MT) vt[i] = lds_read_tr4(reinterpret_cast<const bf16 *>(smem + base + vt0 + 16 * i * TV * 2));
+            else if (i < 2 * MT) bt[i - MT] = *reinterpret_cast<const u32x4 *>(smem + base + bt0 + 64 * (i - MT));
+            else if (i < 2 * MT + MT * NKS) {
+                const int mt = (i - 2 * MT) / NKS, ks = (i - 2 * MT) % NKS;
+                aK[mt][ks] = at8(base + kr0[ks] + 16 * mt * D * 2);
+            } else if (i < kAhead) tA[i - 2 * MT - MT * NKS] = at8(base + tt0 + (i - 2 * MT - MT * NKS) * 1024);
+        };
+        auto widen = [&](int mt) {
+            const u32x2 m = __builtin_bit_cast(u32x2, vt[mt]) ^ 0x80008000u;
+            vneg[mt] = __builtin_bit_cast(f32x4, u32x4{m[0] << 16, m[0] & 0xffff0000u, m[1] << 16, m[1] & 0xffff0000u});
+            bw[mt] = __builtin_bit_cast(f32x4, bt[mt] << 16);
+            asm volatile("" : "+v"(vneg[mt]), "+v"(bw[mt]));   // here, not at the use
+        };
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) read_ahead(0, i);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) widen(mt);
+
+        int slot = 0;
+#pragma unroll 1
+        for (int ch = 0; ch < NC; ++ch) {
+            const int base = slot * (int)Pl::slot;
+            slot = slot == kRing - 1 ? 0 : slot + 1;
+            const int ahead = slot * (int)Pl::slot;    // (after the last block: some slot, not used)
+            bf16x8 bS[NKS], bR[NKT], bU[NKT];
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) bS[ks] = join(cvt4(sacc[2 * ks]), cvt4(sacc[2 * ks + 1]));
+            kInOrder();
+            // ---- R = beta (.) (V - K S^T), from K S^T - V; the first pair of row tiles is finished inside the second
+            f32x4 acc[MT], u[MT];
+            auto epilogue = [&](int kt) {
+                bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
+            };
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = vneg[mt];
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                const int mt = 2 * (i / (2 * NKS)) + (i & 1), ks = (i / 2) % NKS;
+                acc[mt] = mfma16(aK[mt][ks], bS[ks], acc[mt]);
+                read_kt(base, i);
+                if constexpr (RO)
+                    if (i < NKS) st8(&Xs[(ch & 1) * XB + (wave * NKS + i) * 512 + lane * 8], bS[i]);
+                if (i == 2 * NKS + NKS - 1) epilogue(0);
+                kInOrder();
+            }
+            // ---- U_eff = T R, lower block-triangular
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) u[mt] = mfma16(tA[t_tile_index(mt, 0)], bR[0], f32x4{0.f, 0.f, 0.f, 0.f});
+            kInOrder();
+            epilogue(1);
+            kInOrder();
+#pragma unroll
+            for (int mt = 2; mt < MT; ++mt) u[mt] = mfma16(tA[t_tile_index(mt, 1)], bR[1], u[mt]);
+            bU[0] = join(cvt4(u[0]), cvt4(u[1]));
+            kInOrder();
+            // ---- S^T += K^T U_eff
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+                const int kt = i / MD, mt = i % MD;
+                if (i == MD) bU[1] = join(cvt4(u[2]), cvt4(u[3]));
+                sacc[mt] = mfma16(aT[kt][mt], bU[kt], sacc[mt]);
+                if constexpr (RO)
+                    if (mt == 0) st8(&Us[(ch & 1) * UB + (wave * NKT + kt) * 512 + lane * 8], bU[kt]);
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) read_ahead(ahead, kPer * i + q);
+                if (kt == 1 && mt % (MD / MT) == 0) widen(mt / (MD / MT));
+                kInOrder();
+            }
+            __syncthreads();
+        }
+#undef kInOrder
+        if (SL) {
+#pragma unroll
+            for (int mt = 0; mt < MD; ++mt)
+                *reinterpret_cast<f32x4 *>(SL + chain * (size_t)dv * D + srow + dk0(mt)) = sacc[mt];
+        }
+        return;
+    }
+
+    // ------------------------------------------------------------------ helper waves
+    constexpr std::integral_constant<int, 0> k0{};
+    constexpr std::integral_constant<int, 1> k1{};
+    constexpr std::integral_constant<int, 2> k2{};
+    // Blocks in groups (one block per register set) without a branch inside: a branch around a load or store makes
+    // every later wait assume the shorter queue.
+    auto for_blocks = [&](auto Gc, auto f) {
+        constexpr int G = decltype(Gc)::value;
+        static_assert(G == 2 || G == 3, "register sets");
+        int ch = 0;
+#pragma unroll 1
+        for (; ch + G <= NC; ch += G) {
+            f(ch, k0);
+            f(ch + 1, k1);
+            if constexpr (G == 3) f(ch + 2, k2);
+        }
+        if (ch < NC) f(ch, k0);
+        if constexpr (G == 3)
+            if (ch + 1 < NC) f(ch + 1, k1);
+    };
+    auto clamp = [&](int ch) { return c0 + (size_t)(ch < NC ? ch : NC - 1); };
+
+    if (wave < NS + NSt) {
+        // The stagers' loads go straight to LDS.  Pieces of 64 x 16 bytes, dealt to the stagers one by one.
+        const int H = wave - NS;
+        constexpr int VPR = D / 8, PPR = TV / 8;                     // 16-byte units per row of K, of the V tile
+        constexpr int KQ = N * VPR / 64 / NSt, VQ = N * PPR / 64 / NSt, TQ = NT / NSt;
+        constexpr int kLoads = KQ + VQ + TQ + 1;                     // loads of a stager per block
+        static_assert(N * VPR % (64 * NSt) == 0 && N * PPR % (64 * NSt) == 0 && NT % NSt == 0 && N == 64, "whole pieces");
+        static_assert((kRing - 3) * kLoads < 64, "vmcnt");
+        int ksrc[KQ], vsrc[VQ], tsrc[TQ];
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+            const int v = (H + NSt * q) * 64 + lane, row = v / VPR;
+            ksrc[q] = row * D + ((v % VPR) ^ k_swizzle<D>(row)) * 8;
+        }
+#pragma unroll
+        for (int q = 0; q < VQ; ++q) {
+            const int v = (H + NSt * q) * 64 + lane;
+            vsrc[q] = (v / PPR) * dv + (v % PPR) * 8;
+        }
+#pragma unroll
+        for (int q = 0; q < TQ; ++q) {                               // the tiles that exist, row by row
+            int mt = 0;
+            while (t_tile_index(mt + 1, 0) <= H + NSt * q) ++mt;
+            tsrc[q] = (int)full_tile_offset(NKT, mt, H + NSt * q - t_tile_index(mt, 0)) + lane * 8;
+        }
+        auto fetch = [&](int ch, int slot) {                         // (beyond the last block: the last once more)
+            const size_t cid = clamp(ch);
+            char *d = smem + slot * (int)Pl::slot;
+            const bf16 *Kg = K + cid * (size_t)N * D, *Vg = V + (size_t)vmul * cid * (size_t)N * dv, *Tg = Tt + cid * (size_t)N * N;
+#pragma unroll
+            for (int q = 0; q < KQ; ++q) load_lds16(Kg + ksrc[q], d + (H + NSt * q) * 1024);
+#pragma unroll
+            for (int q = 0; q < VQ; ++q) load_lds16(Vg + vsrc[q], d + Pl::oV + (H + NSt * q) * 1024);
+#pragma unroll
+            for (int q = 0; q < TQ; ++q) load_lds16(Tg + tsrc[q], d + Pl::oT + (H + NSt * q) * 1024);
+            load_lds2(beta + cid * (size_t)N + lane, d + Pl::oB);    // both stagers: the same values to the same place
+        };
+        // Loads return in order: all but the newest n blocks have landed.
+        auto landed_but = [&](auto Nc) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(Nc)::value * kLoads) : "memory");
+        };
+        if (NC > 0) {
+#pragma unroll
+            for (int b = 0; b < kRing - 1; ++b) fetch(b, b);
+            landed_but(std::integral_constant<int, kRing - 3>{});
+        }
+        __builtin_amdgcn_s_barrier();
+        int slot = kRing - 1;
+        // During block ch: request block ch + kRing - 1 into the slot that block ch - 1 left; blocks up to ch + 2 have
+        // landed at its end, because the state waves read the rows of block ch + 2 during block ch + 1.
+#pragma unroll 1
+        for (int ch = 0; ch < NC; ++ch) {
+            fetch(ch + kRing - 1, slot);
+            slot = slot == kRing - 1 ? 0 : slot + 1;
+            landed_but(std::integral_constant<int, kRing - 3>{});
+            __builtin_amdgcn_s_barrier();
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // nothing is under way to LDS when the wave ends
+        return;
+    }
+
+    // readers: token tiles w and CT - 1 - w (of two tiles: w) of all rows of the workgroup, a block behind the state
+    auto reader = [&](auto Wc) {
+        constexpr int W = decltype(Wc)::value, TN = CT / 2;
+        constexpr auto tok_tile = [](int i) constexpr { return i == 0 ? W : CT - 1 - W; };
+        // blocks of Q and P on their way in register sets
+        constexpr int kSets = 3;
+        bf16x8 bQ[kSets][TN][NKS], bP[kSets][TN][NKT];               // (P tiles above the causal mask do not exist)
+        auto fetch = [&](int ch, auto Sc) {
+            constexpr int S = decltype(Sc)::value;
+            const size_t cid = clamp(ch);
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    bQ[S][i][ks] = ld8(Q + cid * (size_t)C * D + (16 * tok_tile(i) + r16) * D + 32 * ks + 8 * g);
+#pragma unroll
+                for (int kt = 0; kt < NKT; ++kt)
+                    if (kt < p_ksteps(R, tok_tile(i))) bP[S][i][kt] = ld8(Pt + cid * (size_t)C * N + full_tile_offset(NKT, tok_tile(i), kt) + lane * 8);
+            }
+        };
+        if (NC > 0) {
+            fetch(0, k0);
+            fetch(1, k1);
+            if constexpr (kSets == 3) fetch(2, k2);
+        }
+        __syncthreads();
+        for_blocks(std::integral_constant<int, kSets>{}, [&](int ch, auto Sc) {
+            constexpr int S = decltype(Sc)::value;
+            __syncthreads();
+            bf16 *Oc = O + chain * (size_t)tail * dv + ((c0 + ch) * (size_t)C + r16) * dv + tile * TV + 4 * g;
+            const bf16 *X = Xs + (ch & 1) * XB + lane * 8, *U = Us + (ch & 1) * UB + lane * 8;
+            f32x4 o[NS][TN];
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                bf16x8 x[NKS], u[NKT];
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) x[ks] = ld8(X + (j * NKS + ks) * 512);
+#pragma unroll
+                for (int kt = 0; kt < NKT; ++kt) u[kt] = ld8(U + (j * NKT + kt) * 512);
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    o[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks) o[j][i] = mfma16(x[ks], bQ[S][i][ks], o[j][i]);
+#pragma unroll
+                    for (int kt = 0; kt < NKT; ++kt)
+                        if (kt < p_ksteps(R, tok_tile(i))) o[j][i] = mfma16(u[kt], bP[S][i][kt], o[j][i]);
+                }
+            }
+            LDS_FENCE();
+            fetch(ch + kSets, Sc);
+            LDS_FENCE();
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < NS; ++j) st4(Oc + (size_t)16 * tok_tile(i) * dv + 16 * j, cvt4(o[j][i]));
+            LDS_FENCE();
+        });
+    };
+    if constexpr (RO) {
+        if (wave == NS + NSt) reader(k0);
+        else reader(k1);
+    }
+}
+
+}  // namespace pf

@@ -46,13 +46,12 @@
 #include "pf_common.h"
 #include "pf_layout.h"
 
-#include <atomic>
+#include "pf_chain.h"
 
+#include <atomic>
 #include <type_traits>
 
 namespace pf {
-
-#define LDS_FENCE() asm volatile("" ::: "memory")
 
 constexpr int kScanRoleWaves = 4;                       // waves per role
 constexpr int kScanRoleThreads = 64 * kScanRoleWaves;
@@ -84,11 +83,12 @@ struct ScanLds {
 
 // RO: the readout O is wanted (false: only the state is advanced, for the per-segment passes of
 // the segment-parallel scan).
-template <int D, int N, int C, int TV, bool RO, bool GEN = false>
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+template <int D, int N, int C, int TV, bool RO, bool GEN>
+__device__ __forceinline__ void split_scan(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv,
+    char *smem)
 {
     // With GEN, K is the array of B rows, `beta` the array of A rows (n x d each) and V the array
     // of Atil rows: R = Atil + A S^T, U_eff = T R, S += U_eff^T B, O = Q S^T + P U_eff.
@@ -126,7 +126,6 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     static_assert(MT % 4 == 0 && (CT % 4 == 0 || CT < 4), "tiles are dealt evenly, or at most one token tile per wave");
     static_assert(N <= NTHR, "beta of a chunk is fetched by one pass");
 
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16 *Ks = reinterpret_cast<bf16 *>(smem + Ld::oKs);
     bf16 *Vs = reinterpret_cast<bf16 *>(smem + Ld::oVs);
     float *bs = reinterpret_cast<float *>(smem + Ld::oBs);
@@ -670,6 +669,29 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     }
 }
 
+// Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for tiles of 16
+// rows and 64 virtual tokens, where it is the faster one (figures there), else the split above.
+template <int D, int N, int C, int TV, bool RO, bool GEN>
+struct ScanBody {
+    using Chain = ChainPlan<D, N, C, TV, RO>;
+    static constexpr bool kChain = !GEN && Chain::kServes;
+    static constexpr size_t lds = kChain ? Chain::total : ScanLds<D, N, C, TV, GEN>::total;
+    static constexpr int threads = kChain ? Chain::threads : kScanThreads;
+};
+
+template <int D, int N, int C, int TV, bool RO, bool GEN = false>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: bounds of 256 and below bring in AGPR copies)
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if constexpr (ScanBody<D, N, C, TV, RO, GEN>::kChain)
+        chain_scan<D, N, C, TV, RO>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+    else
+        split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+}
+
 // ---------------------------------------------------------------------------- host side
 #ifndef PF_SCAN_INSTANCES
 #define PF_SCAN_INSTANCES(X) \
@@ -683,13 +705,13 @@ static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, co
                                        int heads, int NC, int tail, int vmul, int s0mul, int dv, hipStream_t stream)
 {
     auto kern = scan_kernel<D, N, C, TV, RO, GEN>;
-    constexpr size_t lds = ScanLds<D, N, C, TV, GEN>::total;
+    constexpr size_t lds = ScanBody<D, N, C, TV, RO, GEN>::lds;
     static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)heads * (dv / TV);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kScanThreads), lds, stream, (const bf16 *)Q,
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(ScanBody<D, N, C, TV, RO, GEN>::threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
                        (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, vmul, s0mul, dv);
     return hipGetLastError();
