@@ -38,9 +38,10 @@ struct WorkspacePlan {
 // Segments per head for the segment-parallel scan: 1 (plain hand-over chain per head) unless
 // the chains of the plain scan (heads x d_v tiles) would leave three quarters of the CUs idle
 // and there are enough blocks to cut.  Three passes of the scan kernel then run with
-// `segments` times as many chains.  Measured on 65536 tokens, d = 128, r = 2: eight segments
-// on 4 heads 0.96 ms against 1.75 ms, four segments on 8 heads 1.52 against 1.83 ms; two
-// segments (three passes over half the blocks each) cannot pay.
+// `segments` times as many chains.  Measured on 65536 tokens, d = 128, r = 2, whole forward: eight
+// segments on 4 heads 0.61 ms against 1.61 ms, four segments on 8 heads 1.18 against 1.69 ms; two
+// segments (three passes over half the blocks each: 0.57 us a block without the readout, 0.82 with it)
+// cannot pay.
 int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 {
     if (L % chunk != 0 || d != dv) return 1;     // (the composition kernel takes square states)
