@@ -251,7 +251,8 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
                 out = flow + ";pf::segment_constants_kernel;" + scan + ", false, false>;" + scan + ", false, false>;" +
                       "pf::segment_compose_kernel;" + scan + ", true, false>";
             else
-                out = flow + ";" + scan + ", true, false>";
+                out = flow + ";" + scan + ", true, false" +
+                      (n == 64 && pf::scan_dv_tile(heads, d_v, n) == 16 && !pf::scan_chain(heads, d_v, n) ? ", true>" : ">");
             if (tail) out += ";" + generic;
         }
     }

@@ -1,5 +1,6 @@
-// Body of the scan kernel for flow blocks of 64 virtual tokens and tiles of 16 rows of S (the delta rule): one wavefront
-// runs the whole chain R -> U_eff -> S of the 16 rows by itself, out of registers.
+// Body of the scan kernel for flow blocks of 64 virtual tokens and tiles of 16 rows of S (the delta rule), with at most
+// one workgroup per compute unit (scan_chain in pf_scan.hip): one wavefront runs the whole chain R -> U_eff -> S of the
+// 16 rows by itself, out of registers.
 //
 // With S^T as accumulator tiles (rows d_k, columns the 16 rows of S) every product of a block takes the result of
 // the one before it as its B operand, and an accumulator tile is a B operand lane for lane (pf_common.h):

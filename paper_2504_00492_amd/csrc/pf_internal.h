@@ -65,6 +65,8 @@ hipError_t launch_chunk_scan_general(const void *Q, const void *A, const void *A
 // a multiple of 16, 0 meaning d_v = d_k: V, O are dv wide and S0, S_L are dv x d.)
 // d_v rows of S one scan workgroup owns for these dimensions (the scan runs heads * dv / tile chains)
 int scan_dv_tile(int heads, int dv, int n);
+// whether the scan of these dimensions runs the chain of 16 rows in one wavefront (delta rule, 16-row tiles)
+bool scan_chain(int heads, int dv, int n);
 
 // ---- fused forward (pf_fused.hip): flow and scan of every block in one kernel, d = d_k = d_v,
 // n = chunk * r in {64, 128}.  Takes the first L / chunk whole blocks of every head.  Tdump / Pdump

@@ -670,16 +670,19 @@ __device__ __forceinline__ void split_scan(
 }
 
 // Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for tiles of 16
-// rows and 64 virtual tokens, where it is the faster one (figures there), else the split above.
-template <int D, int N, int C, int TV, bool RO, bool GEN>
+// rows and 64 virtual tokens, unless SPLIT asks for the split above (scan_chain says when), which serves the rest.
+template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT = false>
 struct ScanBody {
     using Chain = ChainPlan<D, N, C, TV, RO>;
-    static constexpr bool kChain = !GEN && Chain::kServes;
+    static constexpr bool kChain = !SPLIT && !GEN && Chain::kServes;
     static constexpr size_t lds = kChain ? Chain::total : ScanLds<D, N, C, TV, GEN>::total;
     static constexpr int threads = kChain ? Chain::threads : kScanThreads;
 };
 
-template <int D, int N, int C, int TV, bool RO, bool GEN = false>
+typedef void ScanFn(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *,
+                    float *, int, int, int, int, int, int);
+
+template <int D, int N, int C, int TV, bool RO, bool GEN>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: bounds of 256 and below bring in AGPR copies)
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
@@ -692,6 +695,18 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
         split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
 }
 
+// the split body of a shape that the chain serves as well
+template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv)
+{
+    static_assert(SPLIT && ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes have one body");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+}
+
 // ---------------------------------------------------------------------------- host side
 #ifndef PF_SCAN_INSTANCES
 #define PF_SCAN_INSTANCES(X) \
@@ -699,19 +714,22 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
     X(128, 64, 64) X(128, 64, 32) X(128, 128, 32) X(128, 128, 64) X(128, 128, 128) X(128, 256, 64) X(128, 256, 128)
 #endif
 
-template <int D, int N, int C, int TV, bool RO, bool GEN = false>
+template <int D, int N, int C, int TV, bool RO, bool GEN = false, bool SPLIT = false>
 static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                                        int heads, int NC, int tail, int vmul, int s0mul, int dv, hipStream_t stream)
 {
-    auto kern = scan_kernel<D, N, C, TV, RO, GEN>;
-    constexpr size_t lds = ScanBody<D, N, C, TV, RO, GEN>::lds;
+    using Body = ScanBody<D, N, C, TV, RO, GEN, SPLIT>;
+    ScanFn *kern;
+    if constexpr (SPLIT) kern = scan_kernel<D, N, C, TV, RO, GEN, true>;
+    else kern = scan_kernel<D, N, C, TV, RO, GEN>;
+    constexpr size_t lds = Body::lds;
     static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
     const unsigned grid = (unsigned)heads * (dv / TV);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(ScanBody<D, N, C, TV, RO, GEN>::threads), lds, stream, (const bf16 *)Q,
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
                        (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, vmul, s0mul, dv);
     return hipGetLastError();
@@ -725,11 +743,30 @@ int scan_dv_tile(int heads, int dv, int n)
     return (n < 256 && dv % 32 == 0 && (long long)heads * (dv / 32) >= (long long)device_cu_count()) ? 32 : 16;
 }
 
+// A compute unit holds one workgroup of the chain (the ring fills its LDS; at d = 64 a ring of four slots, 75 KB, took
+// the same time within 1 %), but two of the split: the chain where every workgroup has a compute unit of its own, the
+// split beyond.  Scan alone, 4096 tokens, us, split / chain:
+//                     d = 64, r = 2    d = 128, r = 2    d = 128, r = 1
+//   256 workgroups     81.5 / 78.5        113 / 102        60.8 / 57.1
+//   288                 107 / 126         159 / 186            -
+//   384                 141 / 211         178 / 228         109 / 114
+//   480                 179 / 223         243 / 262         157 / 151
+// and for d_v = 48, 2048 tokens, r = 2, 768 workgroups: d = 64 241 / 321, d = 128 403 / 437.
+bool scan_chain(int heads, int dv, int n)
+{
+    return n == 64 && scan_dv_tile(heads, dv, n) == 16 && (long long)heads * (dv / 16) <= (long long)device_cu_count();
+}
+
 template <int D, int N, int C, int TV>
 static hipError_t launch_scan_instance(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                                        int heads, int NC, int tail, int vmul, int s0mul, int dv, hipStream_t stream)
 {
+    if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
+        // (state-only passes run for scan_segments' choices, which never exceed the compute units)
+        if (O && !scan_chain(heads, dv, N))
+            return launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+    }
     return O ? launch_scan_ro<D, N, C, TV, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream)
              : launch_scan_ro<D, N, C, TV, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
 }
