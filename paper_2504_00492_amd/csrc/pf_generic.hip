@@ -59,7 +59,7 @@ template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
 {
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
-// sum over the LPR neighbouring lanes of a row, in every one of them
+// sum over the LPR neighbouring lanes of a row, in every one of them (the same bits: each step adds the same two numbers)
 template <int LPR> __device__ __forceinline__ float row_sum(float v)
 {
     static_assert(LPR == 4 || LPR == 8 || LPR == 16 || LPR == 64, "lanes per row");
@@ -286,7 +286,7 @@ __device__ __forceinline__ void generic_rows(const GenericArgs<T> &a, const Gene
                 for (int j = 0; j < r; ++j) {
                     load_row(t * r + j, x);
                     const float w = row_sum<LPR>(dot(x)), v = vs[(t * r + j) * rowsWG + rowl];
-                    if (c == 0) us[j] = kDrivers ? v + w : bs[t * r + j] * (v - w);
+                    us[j] = kDrivers ? v + w : bs[t * r + j] * (v - w);   // every lane: read back by the one that wrote it
                 }
                 for (int j = 0; j < r; ++j) {
                     load_row(urow0 + t * r + j, x);
@@ -345,7 +345,7 @@ __device__ __forceinline__ void generic_long_rows(const GenericArgs<T> &a, const
             const size_t v0 = (head * (size_t)L + t) * r + (size_t)sub * rs;
             for (int j = 0; j < rs; ++j) {
                 const float w = sum((kDrivers ? a.beta : a.K) + (v0 + j) * dk), v = as_f32(a.V[(v0 + j) * dv + row]);
-                if (lane == 0) us[j] = kDrivers ? v + w : as_f32(a.beta[v0 + j]) * (v - w);
+                us[j] = kDrivers ? v + w : as_f32(a.beta[v0 + j]) * (v - w);   // every lane: read back by the one that wrote it
             }
             for (int j = 0; j < rs; ++j) {
                 const float u = us[j];
