@@ -286,12 +286,19 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         auto landed_but = [&](auto Nc) {
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(Nc)::value * kLoads) : "memory");
         };
+        // The barrier alone, without the wait for every load that __syncthreads brings; to the compiler it does not touch
+        // memory, so the fences keep the loads of a later block, which reuse a slot, behind it.
+        auto barrier = [&] {
+            LDS_FENCE();
+            __builtin_amdgcn_s_barrier();
+            LDS_FENCE();
+        };
         if (NC > 0) {
 #pragma unroll
             for (int b = 0; b < kRing - 1; ++b) fetch(b, b);
             landed_but(std::integral_constant<int, kRing - 3>{});
         }
-        __builtin_amdgcn_s_barrier();
+        barrier();
         int slot = kRing - 1;
         // During block ch: request block ch + kRing - 1 into the slot that block ch - 1 left; blocks up to ch + 2 have
         // landed at its end, because the state waves read the rows of block ch + 2 during block ch + 1.
@@ -300,7 +307,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             fetch(ch + kRing - 1, slot);
             slot = slot == kRing - 1 ? 0 : slot + 1;
             landed_but(std::integral_constant<int, kRing - 3>{});
-            __builtin_amdgcn_s_barrier();
+            barrier();
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // nothing is under way to LDS when the wave ends
         return;
