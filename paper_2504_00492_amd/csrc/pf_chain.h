@@ -11,9 +11,9 @@
 // tiles of S^T are numbered so that lane group g of tiles 2 ks and 2 ks + 1 holds d_k = 32 ks + 8 g .. + 7: the
 // joined pair then pairs with 16 consecutive bytes of a row of K.
 //
-// A workgroup has one such state wave per 16 rows and four helper waves.  Two of them (stagers) load K, V tile, beta
-// and the T tiles of a later block straight into a ring of LDS slots, the other two (readers) compute the readout of
-// the block before,
+// A workgroup has one such state wave and helper waves.  Two of them (stagers) load K, V tile, beta and the T tiles of a
+// later block straight into a ring of six LDS slots, two more (readers, where O is wanted) compute the readout of the
+// block before,
 //     O^T = S Q^T + U_eff^T P^T,
 // from the copies of S and U_eff that the state wave leaves in LDS in operand form.  One barrier per block.
 //
@@ -30,9 +30,6 @@
 #include "pf_internal.h"
 #include "pf_layout.h"
 
-// keeps memory accesses in program order across it (register arithmetic may cross)
-#define LDS_FENCE() asm volatile("" ::: "memory")
-
 namespace pf {
 
 // K lies in LDS without padding, its 16-byte units permuted within a row (position = unit ^ swizzle of the row) so
@@ -47,17 +44,16 @@ __device__ __forceinline__ int k_swizzle(int row)
 
 template <int D, int N, int C, int TV, bool RO>
 struct ChainPlan {
-    static constexpr int NS = TV / 16;                 // state waves
     static constexpr int stagers = 2, readers = RO ? 2 : 0;
-    static constexpr int threads = 64 * (NS + stagers + readers);
+    static constexpr int threads = 64 * (1 + stagers + readers);
     static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
     // one ring slot: K, V tile, T tiles, beta (32 bits each)
     static constexpr size_t oV = (size_t)N * D * 2;
     static constexpr size_t oT = oV + (size_t)N * TV * 2;
     static constexpr size_t oB = oT + (size_t)NT * 1024;
     static constexpr size_t slot = oB + (size_t)N * 4;
-    static constexpr size_t szX = RO ? (size_t)NS * (D / 32) * 1024 : 0;   // S of a block, operand tiles
-    static constexpr size_t szU = RO ? (size_t)NS * (N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
+    static constexpr size_t szX = RO ? (size_t)(D / 32) * 1024 : 0;   // S of a block, operand tiles
+    static constexpr size_t szU = RO ? (size_t)(N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
     // two slots are being read (this block, and the rows and T of the next), the others are on their way from memory
     static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU)) / slot);
     static constexpr int kRing = fit < 6 ? fit : 6;
@@ -86,7 +82,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                                            int nchains, int NC, int tail, int vmul, int s0mul, int dv, char *smem)
 {
     using Pl = ChainPlan<D, N, C, TV, RO>;
-    constexpr int NS = Pl::NS, NT = Pl::NT, kRing = Pl::kRing;
+    constexpr int NT = Pl::NT, kRing = Pl::kRing;
     constexpr int R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, MD = D / 16, CT = C / 16;
     constexpr int NSt = Pl::stagers;
 
@@ -103,11 +99,11 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     bf16 *Xs = reinterpret_cast<bf16 *>(smem + Pl::oX), *Us = reinterpret_cast<bf16 *>(smem + Pl::oU);
     constexpr int XB = (int)(Pl::szX / 2), UB = (int)(Pl::szU / 2);   // elements of one buffer
 
-    if (wave < NS) {
-        // -------------------------------------------------------------- state waves
+    if (wave == 0) {
+        // -------------------------------------------------------------- state wave
         __builtin_amdgcn_s_setprio(3);                 // the helpers of this SIMD fill what the chain leaves
         auto dk0 = [&](int mt) { return 32 * (mt >> 1) + 8 * g + 4 * (mt & 1); };
-        const size_t srow = (size_t)(tile * TV + 16 * wave + r16) * D;
+        const size_t srow = (size_t)(tile * TV + r16) * D;
         f32x4 sacc[MD];
 #pragma unroll
         for (int mt = 0; mt < MD; ++mt) {
@@ -121,7 +117,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             kr0[ks] = r16 * D * 2 + ((4 * ks + g) ^ k_swizzle<D>(r16)) * 16;
             kt0[ks] = (4 * g + (r16 >> 2)) * D * 2 + ((4 * ks + (r16 & 3)) ^ k_swizzle<D>(4 * g + (r16 >> 2))) * 16;
         }
-        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 16 * wave + 4 * (r16 & 3)) * 2;
+        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 4 * (r16 & 3)) * 2;
         const int tt0 = (int)Pl::oT + lane * 16, bt0 = (int)Pl::oB + 16 * g;
         auto at8 = [&](int off) { return *reinterpret_cast<const bf16x8 *>(smem + off); };
 
@@ -185,7 +181,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 acc[mt] = mfma16(aK[mt][ks], bS[ks], acc[mt]);
                 read_kt(base, i);
                 if constexpr (RO)
-                    if (i < NKS) st8(&Xs[(ch & 1) * XB + (wave * NKS + i) * 512 + lane * 8], bS[i]);
+                    if (i < NKS) st8(&Xs[(ch & 1) * XB + i * 512 + lane * 8], bS[i]);
                 if (i == 2 * NKS + NKS - 1) epilogue(0);
                 kInOrder();
             }
@@ -206,7 +202,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 if (i == MD) bU[1] = join(cvt4(u[2]), cvt4(u[3]));
                 sacc[mt] = mfma16(aT[kt][mt], bU[kt], sacc[mt]);
                 if constexpr (RO)
-                    if (mt == 0) st8(&Us[(ch & 1) * UB + (wave * NKT + kt) * 512 + lane * 8], bU[kt]);
+                    if (mt == 0) st8(&Us[(ch & 1) * UB + kt * 512 + lane * 8], bU[kt]);
 #pragma unroll
                 for (int q = 0; q < kPer; ++q) read_ahead(ahead, kPer * i + q);
                 if (kt == 1 && mt % (MD / MT) == 0) widen(mt / (MD / MT));
@@ -227,27 +223,24 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     constexpr std::integral_constant<int, 0> k0{};
     constexpr std::integral_constant<int, 1> k1{};
     constexpr std::integral_constant<int, 2> k2{};
-    // Blocks in groups (one block per register set) without a branch inside: a branch around a load or store makes
-    // every later wait assume the shorter queue.
-    auto for_blocks = [&](auto Gc, auto f) {
-        constexpr int G = decltype(Gc)::value;
-        static_assert(G == 2 || G == 3, "register sets");
+    // Blocks in groups of three (one per register set of the readers) without a branch inside: a branch around a load or
+    // store makes every later wait assume the shorter queue.
+    auto for_blocks = [&](auto f) {
         int ch = 0;
 #pragma unroll 1
-        for (; ch + G <= NC; ch += G) {
+        for (; ch + 3 <= NC; ch += 3) {
             f(ch, k0);
             f(ch + 1, k1);
-            if constexpr (G == 3) f(ch + 2, k2);
+            f(ch + 2, k2);
         }
         if (ch < NC) f(ch, k0);
-        if constexpr (G == 3)
-            if (ch + 1 < NC) f(ch + 1, k1);
+        if (ch + 1 < NC) f(ch + 1, k1);
     };
     auto clamp = [&](int ch) { return c0 + (size_t)(ch < NC ? ch : NC - 1); };
 
-    if (wave < NS + NSt) {
+    if (wave < 1 + NSt) {
         // The stagers' loads go straight to LDS.  Pieces of 64 x 16 bytes, dealt to the stagers one by one.
-        const int H = wave - NS;
+        const int H = wave - 1;
         constexpr int VPR = D / 8, PPR = TV / 8;                     // 16-byte units per row of K, of the V tile
         constexpr int KQ = N * VPR / 64 / NSt, VQ = N * PPR / 64 / NSt, TQ = NT / NSt;
         constexpr int kLoads = KQ + VQ + TQ + 1;                     // loads of a stager per block
@@ -301,7 +294,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         barrier();
         int slot = kRing - 1;
         // During block ch: request block ch + kRing - 1 into the slot that block ch - 1 left; blocks up to ch + 2 have
-        // landed at its end, because the state waves read the rows of block ch + 2 during block ch + 1.
+        // landed at its end, because the state wave reads the rows of block ch + 2 during block ch + 1.
 #pragma unroll 1
         for (int ch = 0; ch < NC; ++ch) {
             fetch(ch + kRing - 1, slot);
@@ -313,12 +306,11 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         return;
     }
 
-    // readers: token tiles w and CT - 1 - w (of two tiles: w) of all rows of the workgroup, a block behind the state
+    // readers: token tiles w and CT - 1 - w (of two tiles: w), a block behind the state
     auto reader = [&](auto Wc) {
         constexpr int W = decltype(Wc)::value, TN = CT / 2;
         constexpr auto tok_tile = [](int i) constexpr { return i == 0 ? W : CT - 1 - W; };
-        // blocks of Q and P on their way in register sets
-        constexpr int kSets = 3;
+        constexpr int kSets = 3;                                     // blocks of Q and P on their way in register sets
         bf16x8 bQ[kSets][TN][NKS], bP[kSets][TN][NKT];               // (P tiles above the causal mask do not exist)
         auto fetch = [&](int ch, auto Sc) {
             constexpr int S = decltype(Sc)::value;
@@ -336,44 +328,39 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         if (NC > 0) {
             fetch(0, k0);
             fetch(1, k1);
-            if constexpr (kSets == 3) fetch(2, k2);
+            fetch(2, k2);
         }
         __syncthreads();
-        for_blocks(std::integral_constant<int, kSets>{}, [&](int ch, auto Sc) {
+        for_blocks([&](int ch, auto Sc) {
             constexpr int S = decltype(Sc)::value;
             __syncthreads();
             bf16 *Oc = O + chain * (size_t)tail * dv + ((c0 + ch) * (size_t)C + r16) * dv + tile * TV + 4 * g;
             const bf16 *X = Xs + (ch & 1) * XB + lane * 8, *U = Us + (ch & 1) * UB + lane * 8;
-            f32x4 o[NS][TN];
+            f32x4 o[TN];
+            bf16x8 x[NKS], u[NKT];
 #pragma unroll
-            for (int j = 0; j < NS; ++j) {
-                bf16x8 x[NKS], u[NKT];
+            for (int ks = 0; ks < NKS; ++ks) x[ks] = ld8(X + ks * 512);
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) x[ks] = ld8(X + (j * NKS + ks) * 512);
+            for (int kt = 0; kt < NKT; ++kt) u[kt] = ld8(U + kt * 512);
 #pragma unroll
-                for (int kt = 0; kt < NKT; ++kt) u[kt] = ld8(U + (j * NKT + kt) * 512);
+            for (int i = 0; i < TN; ++i) {
+                o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < TN; ++i) {
-                    o[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int ks = 0; ks < NKS; ++ks) o[i] = mfma16(x[ks], bQ[S][i][ks], o[i]);
 #pragma unroll
-                    for (int ks = 0; ks < NKS; ++ks) o[j][i] = mfma16(x[ks], bQ[S][i][ks], o[j][i]);
-#pragma unroll
-                    for (int kt = 0; kt < NKT; ++kt)
-                        if (kt < p_ksteps(R, tok_tile(i))) o[j][i] = mfma16(u[kt], bP[S][i][kt], o[j][i]);
-                }
+                for (int kt = 0; kt < NKT; ++kt)
+                    if (kt < p_ksteps(R, tok_tile(i))) o[i] = mfma16(u[kt], bP[S][i][kt], o[i]);
             }
             LDS_FENCE();
             fetch(ch + kSets, Sc);
             LDS_FENCE();
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < NS; ++j) st4(Oc + (size_t)16 * tok_tile(i) * dv + 16 * j, cvt4(o[j][i]));
+            for (int i = 0; i < TN; ++i) st4(Oc + (size_t)16 * tok_tile(i) * dv, cvt4(o[i]));
             LDS_FENCE();
         });
     };
     if constexpr (RO) {
-        if (wave == NS + NSt) reader(k0);
+        if (wave == 1 + NSt) reader(k0);
         else reader(k1);
     }
 }

@@ -57,8 +57,6 @@
 
 namespace pf {
 
-#define LDS_FENCE() asm volatile("" ::: "memory")
-
 constexpr int kFusedRoleWaves = 4;                       // waves per role
 constexpr int kFusedRoleThreads = 64 * kFusedRoleWaves;
 constexpr int kFusedThreads = 3 * kFusedRoleThreads;     // state, gram and aux waves
