@@ -20,7 +20,8 @@ cfg3a, cfg3b), each with its own K timed steps.  Per workload:
     8 TB/s = 312 flop/B), so it is algorithmic bytes (the q, k, v, beta it must read and the o
     it must write) per second against the 8 TB/s HBM peak.  "traffic" is the HBM bytes per launch
     that rocprofv3's counters saw for that kernel (profiles/hbm_traffic.json), taken over only if
-    the profiled kernel instantiation is the one this run launched (pf_delta_fwd_describe);
+    the profiled kernel instantiation is the one this run launched (pf_delta_fwd_describe) and the
+    kernels' code is still the profiled one (kernel_code_digest);
   * "requested_chunk": where pf_delta_fwd runs flow blocks shorter than the requested chunk, the
     two kernels timed at the requested chunk itself through the split entry points (null when no
     instance of that size exists);
@@ -34,8 +35,11 @@ Only one GPU is used; --gpus N with N > 1 exits with a message.
 from __future__ import annotations
 
 import argparse
+import glob
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 from concurrent.futures import ThreadPoolExecutor
@@ -86,6 +90,25 @@ def kernel_bytes_per_token_head(d, r, e):
     flow = e * d * (1 + r) + e * r                # q, k, beta
     scan = e * d * (2 + 2 * r) + e * r            # q, k, v, beta, o
     return flow, scan
+
+
+def kernel_code_digest(csrc=os.path.join(ROOT, "paper_2504_00492_amd", "csrc")):
+    """Digest of the code of the flow, scan and fused kernels (comments and white space left out): the name of an
+    instantiation does not say which body it has."""
+    files = [os.path.join(csrc, f) for f in ("pf_flow.hip", "pf_scan.hip", "pf_fused.hip")] + glob.glob(os.path.join(csrc, "*.h"))
+    h = hashlib.sha256()
+    for f in sorted(files):
+        with open(f) as src:
+            code = re.sub(r"//[^\n]*|/\*.*?\*/", "", src.read(), flags=re.S)
+        h.update((os.path.basename(f) + ":" + re.sub(r"\s+", "", code) + ";").encode())
+    return h.hexdigest()[:16]
+
+
+def profiled_traffic(table, workload, key, name, digest):
+    """HBM bytes per launch of kernel `key` from the committed counter passes; None unless they were taken of the
+    instantiation `name` built from the code with this digest."""
+    rec = table.get(workload, {}).get(key) if table.get("code_digest") == digest else None
+    return rec["bytes"] if isinstance(rec, dict) and rec.get("name") == name else None
 
 
 def device_inputs(synth, w, dev, torch):
@@ -222,10 +245,9 @@ def run_workload(pf, torch, w, inputs, args, traffic_table):
         roofline = {"bound": "hbm", "kernel": dom, "kernel_name": kernels[dom]["name"],
                     "achieved": kernels[dom]["alg_gbs"], "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": kernels[dom]["frac_hbm_peak"], "avg_kernel_ms": kernels[dom]["ms"], "traffic": None}
-        # counters of a profiled run count only if that run launched this very instantiation
+        digest = kernel_code_digest()
         for key, info in kernels.items():
-            rec = traffic_table.get(w.name, {}).get(key)
-            info["traffic"] = rec["bytes"] if isinstance(rec, dict) and rec.get("name") == info["name"] else None
+            info["traffic"] = profiled_traffic(traffic_table, w.name, key, info["name"], digest)
         roofline["traffic"] = kernels[dom]["traffic"]
         if kernels["flow_kernel"]["traffic"] and kernels["scan_kernel"]["traffic"]:
             roofline["traffic_both_kernels_over_min_bytes"] = (

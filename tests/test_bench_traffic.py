@@ -1,0 +1,30 @@
+"""bench.py reports counter figures of a profile only for the code that they were taken of (CPU only)."""
+import shutil
+
+from test_bench_formulas import bench  # noqa: F401  (fixture: imports bench.py)
+
+NAME = "pf::scan_kernel<128, 64, 32, 16, true, false>"
+
+
+def test_traffic_belongs_to_the_profiled_code(bench):  # noqa: F811
+    table = {"code_digest": "abc", "cfg4": {"scan_kernel": {"name": NAME, "bytes": 7}}}
+    assert bench.profiled_traffic(table, "cfg4", "scan_kernel", NAME, "abc") == 7
+    assert bench.profiled_traffic(table, "cfg4", "scan_kernel", NAME, "abd") is None             # other code, same name
+    assert bench.profiled_traffic(table, "cfg4", "scan_kernel", NAME[:-6] + "true>", "abc") is None
+    assert bench.profiled_traffic(table, "cfg2", "scan_kernel", NAME, "abc") is None
+    assert bench.profiled_traffic({"cfg4": table["cfg4"]}, "cfg4", "scan_kernel", NAME, "abc") is None   # code not recorded
+
+
+def test_digest_follows_the_code_and_nothing_else(bench, tmp_path):  # noqa: F811
+    import os
+    csrc = os.path.join(os.path.dirname(os.path.abspath(bench.__file__)), "paper_2504_00492_amd", "csrc")
+    copy = tmp_path / "csrc"
+    shutil.copytree(csrc, copy, ignore=shutil.ignore_patterns("*.o"))
+    digest = bench.kernel_code_digest()
+    assert bench.kernel_code_digest(str(copy)) == digest
+    chain = copy / "pf_chain.h"
+    text = chain.read_text()
+    chain.write_text("// a remark\n" + text.replace("\n", "\n\n") + "/* another\n one */\n")
+    assert bench.kernel_code_digest(str(copy)) == digest
+    chain.write_text(text.replace("fit < 6 ? fit : 6", "fit < 4 ? fit : 4"))
+    assert bench.kernel_code_digest(str(copy)) != digest
