@@ -84,7 +84,7 @@ int pf_delta_fwd_supported(int d_k, int d_v, int r, int chunk, pf_dtype dt);
  * among the blocks that have a kernel instance: the one of 64 virtual tokens (block * r) if it holds at
  * least 32 tokens; else the largest of at most 128 virtual tokens; else the largest there is (256
  * virtual tokens).  Small blocks are preferred because the per-block hand-over array grows with the
- * square of the block; below 32 tokens the fixed cost of a block outweighs that.  The flow over a chunk
+ * square of the block; blocks of fewer than 32 tokens have no instance.  The flow over a chunk
  * is the composition of the flows over consecutive pieces of it (Section 3.1), so O and S_L are the
  * same function of the inputs either way; only the blocking of the arithmetic, hence its rounding,
  * differs.  On the generic path: the most tokens whose inputs are staged at a time (the

@@ -38,10 +38,11 @@ struct WorkspacePlan {
 // Segments per head for the segment-parallel scan: 1 (plain hand-over chain per head) unless
 // the chains of the plain scan (heads x d_v tiles) would leave three quarters of the CUs idle
 // and there are enough blocks to cut.  Three passes of the scan kernel then run with
-// `segments` times as many chains.  Measured on 65536 tokens, d = 128, r = 2, whole forward: eight
-// segments on 4 heads 0.61 ms against 1.61 ms, four segments on 8 heads 1.18 against 1.69 ms; two
-// segments (three passes over half the blocks each: 0.57 us a block without the readout, 0.82 with it)
-// cannot pay.
+// `segments` times as many chains.  Whole forward, d = 128, r = 2, segments against one chain per head:
+// 4 heads x 65536 tokens (eight segments) 0.57 against 1.58 ms, 8 heads x 65536 (four) 1.12 against 1.70 ms,
+// 8 heads x 8192 0.150 against 0.186 ms, 1 head x 2048 48 against 51 us.  A block costs 0.55 us in a pass without
+// the readout, 0.67 with it and 0.75 in the plain scan, so G segments pay from 1.77 / G < 0.75 on: two cannot, three
+// would, but only powers of two are tried, on whole blocks that divide evenly.
 int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 {
     if (L % chunk != 0 || d != dv) return 1;     // (the composition kernel takes square states)
@@ -78,8 +79,9 @@ WorkspacePlan plan_workspace(int heads, int L, int d, int dv, int r, int chunk)
     return p;
 }
 
-// Tokens per chunk for the generic kernel when it takes the ragged tail of an MFMA-path call:
-// the largest power of two up to 16 whose working set fits LDS next to the fp32 state (0: none).
+// Tokens the generic kernel stages at a time when it takes the ragged tail of an MFMA-path call: the largest
+// power of two up to 16 that generic_lds_bytes admits (0: none, the call is refused; at the widths of that
+// path d_v beyond 288 to 304 for d_k = 128, 576 to 608 for d_k = 64, by r).
 int tail_chunk(int d, int dv, int r)
 {
     for (int c = 16; c >= 1; c /= 2)
@@ -90,12 +92,13 @@ int tail_chunk(int d, int dv, int r)
 // Tokens per flow block on the MFMA path: the requested chunk or chunk / 2^j (the flow over a
 // chunk is the composition of the flows over its pieces, Section 3.1).  Small blocks are preferred
 // where an instance exists: the hand-over array T grows with the square of the block and every d_v
-// tile of a head reads all of it.  Measured (ms per forward; 64 / 128 / 256 virtual tokens per
-// block): 64 heads x 4096 tokens, r = 2: 0.201 / 0.224 / -; 32 heads x 65536 tokens, r = 2:
-// 2.31 / 2.39 / 3.27; r = 1, d = 64: 0.039 / 0.042 / -.  Blocks of fewer than 32 tokens lose again
-// (r = 4: 16 tokens 0.542, 32 tokens 0.529, 64 tokens 0.752).  So: 64 virtual tokens if that is
-// at least 32 tokens, else at most 128 virtual tokens, else the largest block that has an
-// instance.  0 when no instance serves these dimensions.
+// tile of a head reads all of it.  Measured (us per forward; 64 / 128 / 256 virtual tokens per
+// block), d = 128: 64 heads x 4096 tokens, r = 2: 197 / 225 / 461; 32 heads x 65536, r = 2: 2180 / 2378 /
+// 3227; 32 heads x 8192, r = 4: - / 530 / 755; 32 heads x 2048, r = 1: 45 / 61 / -; d = 64: the same with r = 1
+// 34 / 37 / -, 32 heads x 4096, r = 2 95 / 93 / 142.  16 tokens with r = 4 (64 virtual tokens) took 542 against 529
+// in the scan of eight wavefronts; the chain in one wavefront, whose readout takes at least two token tiles,
+// has no such instance.  So: 64 virtual tokens if that is at least 32 tokens, else at most 128 virtual tokens,
+// else the largest block that has an instance.  0 when no instance serves these dimensions.
 template <typename Exists>
 int pick_block(int r, int chunk, Exists exists)
 {
@@ -117,8 +120,8 @@ int mfma_block(int d_k, int d_v, int r, int chunk, pf_dtype dt)
     return pick_block(r, chunk, [&](int n, int c) { return pf::mfma_instance_exists(d_k, n, c); });
 }
 
-// The same choice for the general drivers (measured: 64 heads x 4096 tokens, r = 2: 0.270 ms with
-// blocks of 64 virtual tokens, 0.317 ms with 128); their instances end at 128 virtual tokens.
+// The same choice for the general drivers (64 heads x 4096 tokens, r = 2: 0.270 ms with blocks of 64
+// virtual tokens, 0.317 ms with 128); their instances end at 128 virtual tokens.
 int mfma_general_block(int d_k, int d_v, int r, int chunk, pf_dtype dt)
 {
     if (dt != PF_BF16 || d_v % 16 != 0) return 0;
@@ -131,10 +134,9 @@ bool split_instance(int d_k, int d_v, int r, int chunk)
     return d_v % 16 == 0 && (long long)chunk * r <= 4096 && pf::mfma_instance_exists(d_k, chunk * r, chunk);
 }
 
-// Tokens per chunk on the generic path: the requested chunk when its working set fits LDS next
-// to the fp32 state, else the chunk halved until it does (the flow over a chunk is the composition
-// of the flows over its pieces; the generic kernel takes a shorter last piece anyway).  0 when
-// not even one token fits (the state alone is too large).
+// Tokens per chunk on the generic path: the requested chunk when generic_lds_bytes (the working set of the
+// chunk-wise form next to an fp32 state) fits 160 KiB, else the chunk halved until it does.  0 when not even
+// one token does (the state alone is too large).
 int generic_block(int d_k, int d_v, int r, int chunk)
 {
     if (d_k > 65536 || d_v > 65536 || r > 65536) return 0;

@@ -17,14 +17,18 @@
 //     O^T = S Q^T + U_eff^T P^T,
 // from the copies of S and U_eff that the state wave leaves in LDS in operand form.  One barrier per block.
 //
-// What bounds it: at d = 64 the state wave (38 MFMAs at d = 128, 22 at d = 64, and the latencies between the three
-// products: about 1300 cycles a block); at d = 128 with the readout the 35 KB a block brings into the compute unit, at
-// about 18 bytes a cycle (1900 cycles; the stagers then wait to issue, while the state wave waits at the barrier).
+// What bounds it: at d = 64, and without the readout, the state wave (22 MFMAs at d = 64, 38 at d = 128, and the latencies
+// between the three products: about 1100 and 1300 cycles a block).  At d = 128 with the readout a block takes 1940 cycles,
+// because its 35 KB come in at 18 bytes a cycle: the stagers wait to issue, while the state wave waits at the barrier.
+// Counters (32 heads x 65536 tokens): 330 read requests a block and compute unit, 114 of them on their way at any time,
+// 670 cycles each (15 % of them miss L2, 1300 cycles).  It is the latency under this load, not the width of a path:
+// reads that hit in L2, from all compute units at once, come in at 50 bytes a cycle.
 // Against the split of the chain over four waves that pf_scan.hip keeps for the other shapes (three barriers a block), us:
 //   32 heads x 65536 tokens, r = 2, d = 128   1822 -> 1673      24 heads x 4096 tokens, r = 2, d = 64   66 -> 61
 //   32 heads x 2048 tokens, r = 1, d = 64     22.4 -> 20.8      32 segments x 4096 tokens, state only   92 -> 73
-// With 32 rows per workgroup both move the same 41 KB a block and the split is as fast (64 heads x 4096 tokens, r = 2:
-// 132.8 against 133.0), with 128 virtual tokens a block the operands of one wave do not fit its registers.
+// (all with at most one workgroup per compute unit).  With 32 rows per workgroup both move the same 41 KB a block and the
+// split is as fast (64 heads x 4096 tokens, r = 2: 132.8 against 133.0), with 128 virtual tokens a block the operands of
+// one wave do not fit its registers.
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"

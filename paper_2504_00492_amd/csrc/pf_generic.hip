@@ -13,11 +13,17 @@
 // workgroup (one read from memory for all its rows) while the block before is computed; the readout of
 // token t and the products S k of token t + 1 both see S_t, so their sums run side by side.
 //
-// What bounds it: with few rows the dependent chain of a token (CS fused multiply-adds, the butterfly, u,
-// CS more: about 100 to 200 cycles), with many rows the vector ALU; with few tokens the state's own
-// traffic.  The form of Theorem 3.2 with a chunk in LDS that stood here before did 3 to 4 times the
-// arithmetic out of LDS and a workgroup barrier per token of the substitution: 32 heads x 2048 tokens,
-// d = 64, fp32: 10.5 ms; 1024 heads x 1 token, d = 128, r = 2, bf16: 0.24 ms.
+// What bounds it: with few rows the one wavefront of a SIMD, token after token.  32 heads x 2048 tokens,
+// d = 64, r = 1, fp32: 0.43 ms, 490 cycles a token; in 58 % of them it issues (39 vector, 20 scalar, 5 LDS
+// instructions), in 36 % it waits (LDS reads of the same token, sums over a row); drivers, 8 heads x 500
+// tokens, d_k = 32, r = 2: 0.127 ms, 620 cycles a token, 56 % and 39 %.  With few tokens the state's
+// own traffic and the few loads in flight (1024 heads x 1 token, d = 128, r = 2, bf16: 51 us at 139
+// registers, three waves a SIMD).  Ranks without a shape of their own take the u_j through LDS, one rank
+// after the other (the first shape with r = 3: 1.19 ms, r = 4: 0.82, r = 8: 2.69), and rows too long for
+// registers are read from memory at every use (32 heads x 512 tokens, d_v = 32, fp32: d_k = 512, r = 2
+// 0.37 ms, d_k = 520 4.14 ms).  The form of Theorem 3.2 with a chunk in LDS that stood here before did 3 to 4
+// times the arithmetic out of LDS and a workgroup barrier per token of the substitution: 10.5 ms for the
+// first shape, 0.24 ms for the one token.
 #include "pf_internal.h"
 #include "pf_common.h"
 
@@ -443,8 +449,9 @@ GenericPlan plan_generic(int dk, int dv, int r, int chunk, int tokens, bool driv
 
 }  // namespace
 
-// LDS of the chunk-wise form of Theorem 3.2 at these dimensions (S, K, W, U, Q, G, P in fp32): what
-// pf_delta_fwd_block and the family query size chunks by.  The recurrence above needs less.
+// LDS of the chunk-wise form of Theorem 3.2 at these dimensions (S, K, W, U, Q, G, P in fp32).  No kernel
+// here needs it, the recurrence above takes less at any chunk; it is the documented line of the interface
+// between dimensions that are taken and refused, and of the chunk that pf_delta_fwd_block names.
 size_t generic_lds_bytes(int dk, int dv, int r, int chunk)
 {
     const size_t n = (size_t)chunk * r;

@@ -11,7 +11,11 @@
 //     S_c+1 = S_c + U_eff^T K             TV x d       (S_1 of Theorem 3.2)
 //
 // Only R -> U_eff -> S_c+1 is a chain from one chunk to the next; the readout O_c hangs off it.
-// The workgroup therefore has two kinds of wavefronts, one of each per SIMD:
+// Two bodies follow from that.  The chain in one wavefront (pf_chain.h) takes tiles of 16 rows with blocks of 64
+// virtual tokens, up to one workgroup per compute unit (scan_chain).  The split over several wavefronts below takes
+// the rest: 32 rows, other blocks, general drivers, more workgroups.
+//
+// The workgroup of the split has two kinds of wavefronts, one of each per SIMD:
 //
 //   state waves (0..3)  run the chain: R (interval 0), U_eff (interval 1), S update (interval 2).
 //                       Their global loads are their own T tiles, straight into MFMA operand
@@ -110,15 +114,16 @@ __device__ __forceinline__ void split_scan(
     // U_eff as operands, so it costs them no LDS reads but Q), else the io waves.
     // Register sets for the operands that come straight from global memory: two (two blocks of
     // loads in flight) where the registers allow, else one.
-    // (measured on blocks of 64 virtual tokens, 64 heads x 4096 / 32 heads x 65536 tokens: one set
-    // 0.144 / 1.90 ms, two sets 0.136 / 1.79 ms, four sets 0.142 / 2.07 ms)
+    // (blocks of 64 virtual tokens, 64 heads x 4096 tokens in tiles of 32 rows / 32 heads x 65536 in tiles of 16, which
+    // the chain takes by now: one set 0.144 / 1.90 ms, two sets 0.136 / 1.79 ms, four sets 0.142 / 2.07 ms)
     constexpr int kSets = (!GEN && N <= 128 && !(D == 128 && N == 128 && C == 128 && TV == 32)) ? 2 : 1;
     // Recomputing the per-lane offsets every step costs about 100 integer instructions per wave
     // and step but keeps them out of the registers.  Where registers are plentiful (blocks of 64
     // virtual tokens with 32-row tiles, or d = 64) hoisting them wins: 64 heads x 4096 tokens,
-    // d = 128: scan 0.130 against 0.136 ms; d = 64: 0.0276 against 0.0292 ms.  With 16-row tiles at
-    // d = 128 it loses (1.85 against 1.78 ms on 32 heads x 65536 tokens), with 128 virtual tokens
-    // per block too (0.410 against 0.398 ms), and the 32-row instances there would spill.
+    // d = 128: scan 0.130 against 0.136 ms; 32 heads x 2048 tokens, d = 64, 16-row tiles (a shape of the chain by
+    // now): 0.0276 against 0.0292 ms.  With 16-row tiles at d = 128 it lost (32 heads x 65536 tokens, before the chain:
+    // 1.85 against 1.78 ms), with 128 virtual tokens per block too (0.410 against 0.398 ms), and the 32-row instances
+    // there would spill.
     constexpr bool kLaunder = !(N <= 64 && (TV == 32 || D == 64));
     constexpr bool kStateReadout = RO && N <= 128;
     constexpr bool kIoReadout = RO && N > 128;
