@@ -1,7 +1,9 @@
-// Generic path: the recurrence itself (Section 3.1 of ParallelFlow, arXiv 2504.00492), token by token, in
-// fp32 vector arithmetic with the state in registers.  Serves PF_F32, every shape the MFMA path has
-// no instance for (any d_k, d_v, r), sequences shorter than one flow block (the step-by-step use of
-// the forward: a few tokens in, the state in and out) and the L % block tokens a flow block leaves over.
+// Generic path: the recurrence itself (Section 3.1 of ParallelFlow, arXiv 2504.00492) in fp32.  Serves PF_F32, every
+// shape the MFMA path has no instance for (any d_k, d_v, r), sequences shorter than one flow block (the
+// step-by-step use of the forward: a few tokens in, the state in and out) and the L % block tokens a flow block
+// leaves over.  Two bodies: rows of up to 128 columns with more than a few tokens go 16 virtual tokens at a time
+// through the fp32 matrix instruction (pf_generic_block.h; block_pays says when), the rest token by token in vector
+// arithmetic with the state in registers, below.
 //
 //   delta rule   u_j = beta_j (v_j - S k_j),   S += sum_j u_j k_j^T,   o = S q
 //   drivers      u_j = atil_j + S a_j,         S += sum_j u_j b_j^T,   o = S q
@@ -13,34 +15,20 @@
 // workgroup (one read from memory for all its rows) while the block before is computed; the readout of
 // token t and the products S k of token t + 1 both see S_t, so their sums run side by side.
 //
-// What bounds it: with few rows the one wavefront of a SIMD, token after token.  32 heads x 2048 tokens,
-// d = 64, r = 1, fp32: 0.43 ms, 490 cycles a token; in 58 % of them it issues (39 vector, 20 scalar, 5 LDS
-// instructions), in 36 % it waits (LDS reads of the same token, sums over a row); drivers, 8 heads x 500
-// tokens, d_k = 32, r = 2: 0.127 ms, 620 cycles a token, 56 % and 39 %.  With few tokens the state's
-// own traffic and the few loads in flight (1024 heads x 1 token, d = 128, r = 2, bf16: 51 us at 139
-// registers, three waves a SIMD).  Ranks without a shape of their own take the u_j through LDS, one rank
-// after the other (the first shape with r = 3: 1.19 ms, r = 4: 0.82, r = 8: 2.69), and rows too long for
-// registers are read from memory at every use (32 heads x 512 tokens, d_v = 32, fp32: d_k = 512, r = 2
-// 0.37 ms, d_k = 520 4.14 ms).  The form of Theorem 3.2 with a chunk in LDS that stood here before did 3 to 4
-// times the arithmetic out of LDS and a workgroup barrier per token of the substitution: 10.5 ms for the
-// first shape, 0.24 ms for the one token.
+// What bounds it: with few tokens the state's own traffic and the few loads in flight (1024 heads x 1 token, d = 128,
+// r = 2, bf16: 51 us at 139 registers, three waves a SIMD).  Ranks without a shape of their own take the u_j through
+// LDS, one rank after the other, and rows too long for registers are read from memory at every use (32 heads x 512
+// tokens, d_v = 32, fp32: d_k = 512, r = 2 0.37 ms, d_k = 520 4.14 ms).
 #include "pf_internal.h"
 #include "pf_common.h"
+#include "pf_generic.h"
+#include "pf_generic_block.h"
+
+#include <type_traits>
 
 namespace pf {
 
 namespace {
-
-template <typename T> __device__ __forceinline__ float as_f32(T v);
-template <> __device__ __forceinline__ float as_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ float as_f32<uint16_t>(uint16_t v) { return bf16_bits_to_f32(v); }
-template <typename T> __device__ __forceinline__ T from_f32(float v);
-template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ uint16_t from_f32<uint16_t>(float v)
-{
-    const bf16 b = (bf16)v;
-    return __builtin_bit_cast(uint16_t, b);
-}
 
 // 16 bytes of elements as they lie in memory -> fp32 in LDS
 __device__ __forceinline__ void put16(float *dst, u32x4 w, float)
@@ -95,14 +83,6 @@ struct GenericPlan {
     int vec;            // rows are whole 16-byte pieces
     int tiles;          // workgroups per head
     size_t lds;
-};
-
-template <typename T> struct GenericArgs {
-    const T *Q, *K, *V, *beta;
-    const float *S0;
-    T *O;
-    float *SL;
-    int heads, L, dk, dv, r, t0, product;
 };
 
 namespace {
@@ -373,6 +353,7 @@ __device__ __forceinline__ void generic_long_rows(const GenericArgs<T> &a, const
 // One overload per row shape, told apart by its last parameter, so that each gets registers of its own.
 template <int LPR, int CS, int R> struct RowShape {};
 struct LongRows {};
+template <int DT> struct BlockShape {};          // d_k padded to 16 DT (pf_generic_block.h)
 
 #define PF_RANKS(X, LPR, CS) X(LPR, CS, 1) X(LPR, CS, 2) X(LPR, CS, 4) X(LPR, CS, 0)
 #define PF_ROW_SHAPES(X) \
@@ -386,6 +367,17 @@ struct LongRows {};
         generic_rows<T, kDrivers, LPR, CS, R>(a, pl, gsmem);                                                    \
     }
 PF_ROW_SHAPES(X)
+#undef X
+
+#define PF_BLOCK_SHAPES(X) X(1) X(2) X(3) X(4) X(6) X(8)
+#define X(DT)                                                                                          \
+    template <typename T, bool kDrivers>                                                               \
+    __global__ __launch_bounds__((BlockLds<kDrivers, DT>::threads)) void generic_kernel(GenericArgs<T> a, int C, BlockShape<DT>) \
+    {                                                                                                  \
+        extern __shared__ __attribute__((aligned(16))) float gsmem[];                                  \
+        generic_block<T, kDrivers, DT>(a, C, gsmem);                                                   \
+    }
+PF_BLOCK_SHAPES(X)
 #undef X
 
 template <typename T, bool kDrivers>
@@ -447,6 +439,25 @@ GenericPlan plan_generic(int dk, int dv, int r, int chunk, int tokens, bool driv
     return p;
 }
 
+// Tiles of 16 columns that hold d_k, for the body that takes 16 virtual tokens at a time (0: no instance).
+int block_tiles(int dk, int r)
+{
+    if (dk > 128 || r > kBlockVT) return 0;
+    const int dt = (dk + 15) / 16;
+    return dt <= 4 ? dt : (dt <= 6 ? 6 : 8);
+}
+
+// Whether that body serves the call.  A workgroup costs it 5 to 7 us before the second block of tokens and a compute unit
+// holds one or two of them, so it pays from about 24 virtual tokens a round of workgroups on.  Token by token / by blocks, us:
+//   8 heads, d = 128, r = 2, 12 tokens 8.1 / 8.0, 16 tokens 9.1 / 8.0; d = 64, 16 tokens 7.8 / 6.4, 32 tokens r = 1 11.0 / 6.4
+//   128 heads (four rounds), d = 128, r = 1, 32 tokens 21.3 / 28.7;   1024 heads, d = 128, r = 2, 16 tokens 115 / 225
+//   64 heads (two rounds), d = 128, 1000 tokens 335 / 184;   32 heads, d = 64, 2048 tokens 492 / 106
+bool block_pays(long long workgroups, size_t lds, long long virtual_tokens)
+{
+    const long long at_once = (long long)device_cu_count() * (2 * lds <= kMaxLdsBytes ? 2 : 1);
+    return virtual_tokens > 24 * ((workgroups + at_once - 1) / at_once);
+}
+
 }  // namespace
 
 // LDS of the chunk-wise form of Theorem 3.2 at these dimensions (S, K, W, U, Q, G, P in fp32).  No kernel
@@ -463,10 +474,34 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
                                           const float *S0, void *O, float *SL, int heads, int L, int dk, int dv,
                                           int r, int chunk, int t0, bool product, hipStream_t stream)
 {
-    const GenericPlan pl = plan_generic(dk, dv, r, chunk, L - t0, kDrivers, (int)sizeof(T));
-    if (pl.lds > kMaxLdsBytes || (long long)heads * pl.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const GenericArgs<T> a{(const T *)Q, (const T *)K, (const T *)V, (const T *)beta, S0, (T *)O, SL,
                            heads, L, dk, dv, r, t0, product ? 1 : 0};
+    bool taken = false;
+    hipError_t done = hipSuccess;
+    auto blocks = [&](auto dt) {
+        using Ld = BlockLds<kDrivers, decltype(dt)::value>;
+        using Shape = BlockShape<decltype(dt)::value>;
+        const long long grid = (long long)heads * ((dv + 15) / 16);
+        if (grid > 0x7fffffffLL || !block_pays(grid, Ld::bytes, (long long)(L - t0) * r)) return;
+        taken = true;
+        void (*kern)(GenericArgs<T>, int, Shape) = generic_kernel<T, kDrivers>;
+        if (Ld::bytes > 65536) {
+            static std::atomic<uint64_t> armed{0};
+            done = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Ld::bytes);
+            if (done != hipSuccess) return;
+        }
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Ld::threads), Ld::bytes, stream, a, kBlockVT / r, Shape{});
+        done = hipGetLastError();
+    };
+    switch (block_tiles(dk, r)) {
+#define X(N) case N: blocks(std::integral_constant<int, N>{}); break;
+        PF_BLOCK_SHAPES(X)
+#undef X
+    default: break;
+    }
+    if (taken) return done;
+    const GenericPlan pl = plan_generic(dk, dv, r, chunk, L - t0, kDrivers, (int)sizeof(T));
+    if (pl.lds > kMaxLdsBytes || (long long)heads * pl.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const int ranks = product ? 1 : r;
     auto launch = [&](auto shape) -> hipError_t {
         void (*kern)(GenericArgs<T>, GenericPlan, decltype(shape)) = generic_kernel<T, kDrivers>;

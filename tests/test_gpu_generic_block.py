@@ -1,0 +1,99 @@
+"""The generic kernel's body of 16 virtual tokens at a time, against the fp64 oracle: every padded width and its edges,
+ranks that fill a block, leave rows of it empty or fill it with one token, remainders of the last block, fewer blocks than
+helper waves and one more, rows that are not whole pieces of four elements, d_v that does not fill its tiles, and what an
+infinity or NaN of one token reaches.  Bars: a few roundings of 2^-24 per token, measured 1.0e-7 to 2.2e-7 at these
+sizes, times the growth that near-reflections allow; bf16 inputs add the rounding of O to bf16 (2^-9 / sqrt(3))."""
+import numpy as np
+import pytest
+
+from paper_2504_00492_amd import synth
+from gpu_util import flat_heads, rel_l2, to_device
+
+pytestmark = pytest.mark.gpu
+BAR = {"f32": 1e-6, "bf16": 2e-3}
+
+
+def _run(w, inp, product):
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    dev = to_device(w, inp)
+    O, SL = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=w.chunk, product=product)
+    torch.cuda.synchronize()
+    return flat_heads(O.float().cpu().numpy()), flat_heads(SL.cpu().numpy())
+
+
+@pytest.mark.parametrize("product", [False, True])
+@pytest.mark.parametrize("dtype,heads,L,dk,dv,r", [
+    ("f32", 1, 25, 16, 16, 1), ("f32", 2, 64, 16, 16, 1), ("f32", 3, 127, 16, 5, 1), ("f32", 2, 145, 16, 48, 1),
+    ("f32", 2, 60, 17, 7, 2), ("f32", 2, 129, 32, 33, 1), ("f32", 3, 50, 24, 70, 3), ("f32", 2, 30, 33, 16, 4),
+    ("f32", 2, 75, 48, 20, 2), ("f32", 2, 40, 52, 64, 5), ("f32", 2, 161, 64, 64, 1), ("f32", 1, 33, 60, 40, 7),
+    ("f32", 2, 81, 96, 128, 1), ("f32", 1, 29, 65, 9, 3), ("f32", 2, 97, 128, 40, 2), ("f32", 1, 70, 128, 128, 1),
+    ("f32", 1, 9, 100, 30, 16), ("f32", 1, 12, 31, 18, 11), ("f32", 300, 80, 16, 16, 1), ("f32", 160, 60, 64, 64, 2),
+    ("bf16", 2, 60, 24, 40, 2), ("bf16", 1, 57, 128, 128, 1), ("bf16", 2, 31, 64, 48, 2), ("bf16", 2, 45, 36, 18, 3),
+])
+def test_blocks(oracle, dtype, heads, L, dk, dv, r, product):
+    w = synth.Workload("block", dtype, 1, heads, L, dk, dv, r, 16 if dtype == "f32" else 64, seed=L + dk, s0_std=0.2,
+                       reflect_frac=0.05)
+    print(f"[case] generic blocks {dtype} heads={heads} d=({dk},{dv}) r={r} L={L} product={product}", flush=True)
+    inp = synth.make_inputs(w)
+    O, SL = _run(w, inp, product)
+    ref = oracle.delta_product_fwd if product else oracle.delta_fwd
+    Oref, SLref = ref(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    print(f"        O {rel_l2(O, Oref):.2e} S_L {rel_l2(SL, SLref):.2e}", flush=True)
+    assert rel_l2(O, Oref) <= BAR[dtype]
+    assert rel_l2(SL, SLref) <= BAR["f32"]
+
+
+@pytest.mark.parametrize("dtype,L,dk,dv,r", [
+    ("f32", 60, 16, 20, 1), ("f32", 41, 32, 48, 2), ("f32", 30, 45, 9, 3), ("f32", 90, 64, 64, 1), ("f32", 26, 100, 33, 4),
+    ("f32", 40, 128, 20, 2), ("f32", 8, 64, 16, 13), ("bf16", 70, 24, 40, 2), ("bf16", 33, 80, 18, 1),
+])
+def test_blocks_of_drivers(oracle, dtype, L, dk, dv, r):
+    """General drivers near the delta form, A and B independent of each other."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    N = 2
+    rng = np.random.default_rng(1000 * dk + r)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    unit = lambda *s: (lambda x: x / np.linalg.norm(x, axis=-1, keepdims=True))(rng.standard_normal(s))
+    k, beta = unit(N, L, r, dk), 1.0 / (1.0 + np.exp(-rng.standard_normal((N, L, r, 1)))) / max(1, r / 4)
+    up = lambda a: torch.from_numpy(a.astype(np.float32)).to("cuda:0").to(tdt)[None].contiguous()
+    tq, tat = up(rng.standard_normal((N, L, dk)) / np.sqrt(dk)), up(rng.standard_normal((N, L, r, dv)) / np.sqrt(dv))
+    ta, tb = up(beta * (k + 0.3 * unit(N, L, r, dk))), up(-(k + 0.3 * unit(N, L, r, dk)))
+    S0 = (0.2 * rng.standard_normal((N, dv, dk))).astype(np.float32)
+    print(f"[case] generic blocks of drivers {dtype} d=({dk},{dv}) r={r} L={L}", flush=True)
+    state = torch.from_numpy(S0).to("cuda:0")[None].contiguous()
+    O, SL = pf.flow_fwd(tq, ta, tat, tb, state, chunk=4)
+    torch.cuda.synchronize()
+    back = lambda t: t[0].float().cpu().numpy().astype(np.float64)
+    for h in range(N):
+        Oref, SLref = oracle.flow_head(back(ta)[h], back(tat)[h], back(tb)[h], back(tq)[h], S0[h].astype(np.float64))
+        assert rel_l2(back(O)[h], Oref) <= BAR[dtype]
+        assert rel_l2(back(SL)[h], SLref) <= BAR["f32"]
+
+
+@pytest.mark.parametrize("where", ["V", "K", "beta", "S0"])
+@pytest.mark.parametrize("r,t,value", [(1, 21, float("nan")), (1, 40, float("inf")), (2, 19, float("inf")), (3, 7, float("nan"))])
+def test_what_is_no_number_reaches_no_earlier_token(oracle, where, r, t, value):
+    """An infinity or NaN of token t (S0: of one row) leaves the tokens before t (the other rows) as they are."""
+    L, dk, dv = 50, 32, 20
+    w = synth.Workload("nan", "f32", 1, 2, L, dk, dv, r, 16, seed=5, s0_std=0.2)
+    inp = {k: (None if v is None else np.array(v, copy=True)) for k, v in synth.make_inputs(w).items()}
+    Oref, SLref = oracle.delta_fwd(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    print(f"[case] generic blocks, {value} in {where}, r={r}", flush=True)
+    if where == "S0":
+        inp["S0"][0, 3, 2] = value
+    else:
+        inp[where][(0, t, 0, 1) if where != "beta" else (0, t, 0)] = value
+    O, SL = _run(w, inp, False)
+    assert rel_l2(O[1], Oref[1]) <= BAR["f32"] and rel_l2(SL[1], SLref[1]) <= BAR["f32"]
+    if where == "S0":
+        rest = np.arange(dv) != 3
+        assert rel_l2(O[0][:, rest], Oref[0][:, rest]) <= BAR["f32"] and not np.isfinite(O[0][:, 3]).any()
+    else:
+        assert rel_l2(O[0, :t], Oref[0, :t]) <= BAR["f32"]
+        bad = ~np.isfinite(O[0, t:])
+        assert bad[:, 1].all() if where == "V" else bad.all()
+        if where == "V":                           # one row of the state
+            rest = np.arange(dv) != 1
+            assert rel_l2(O[0][:, rest], Oref[0][:, rest]) <= BAR["f32"]
