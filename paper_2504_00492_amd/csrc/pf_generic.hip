@@ -1,7 +1,7 @@
 // Generic path: the recurrence itself (Section 3.1 of ParallelFlow, arXiv 2504.00492) in fp32.  Serves PF_F32, every
 // shape the MFMA path has no instance for (any d_k, d_v, r), sequences shorter than one flow block (the
 // step-by-step use of the forward: a few tokens in, the state in and out) and the L % block tokens a flow block
-// leaves over.  Two bodies: rows of up to 128 columns with more than a few tokens go 16 virtual tokens at a time
+// leaves over.  Two forms: rows of up to 128 columns with more than a few tokens go 16 virtual tokens at a time
 // through the fp32 matrix instruction (pf_generic_block.h; block_pays says when), the rest token by token in vector
 // arithmetic with the state in registers, below.
 //
@@ -15,8 +15,9 @@
 // workgroup (one read from memory for all its rows) while the block before is computed; the readout of
 // token t and the products S k of token t + 1 both see S_t, so their sums run side by side.
 //
-// What bounds it: with few tokens the state's own traffic and the few loads in flight (1024 heads x 1 token, d = 128,
-// r = 2, bf16: 51 us at 139 registers, three waves a SIMD).  Ranks without a shape of their own take the u_j through
+// Few tokens against a state that many wavefronts share out have a body of their own (generic_few; few_tokens says when).
+//
+// What bounds it: one wavefront per SIMD, token after token.  Ranks without a shape of their own take the u_j through
 // LDS, one rank after the other, and rows too long for registers are read from memory at every use (32 heads x 512
 // tokens, d_v = 32, fp32: d_k = 512, r = 2 0.37 ms, d_k = 520 4.14 ms).
 #include "pf_internal.h"
@@ -307,6 +308,134 @@ __device__ __forceinline__ void generic_rows(const GenericArgs<T> &a, const Gene
     }
 }
 
+// A few tokens: a wavefront owns kFewRows rows of S, 16 lanes to a row, and asks for all of them at once; k (a, b) and q of a
+// token come straight from memory into the registers of the lanes that need them (every wavefront of a head reads the
+// same ones, out of L2), one token ahead.  No LDS, no barrier, and 8 KB of S per wavefront in flight at d_k = 128, where
+// the body above has 2 KB and waits for its staging in between.  Bounded by the state's
+// traffic: 1024 heads x 1 token, d = 128, r = 2 are 134 MB in 24 us (5.6 TB/s; 42 us in the body above).
+constexpr int kFewRows = 16;
+
+template <typename T, bool kDrivers, int CS, int R>
+__device__ __forceinline__ void generic_few(const GenericArgs<T> &a)
+{
+    constexpr int LPR = 16, CV = CS / 4, NG = kFewRows * LPR / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane % LPR, rr = lane / LPR;
+    const size_t head = blockIdx.x % (unsigned)a.heads;
+    const int base = ((int)(blockIdx.x / (unsigned)a.heads) * (int)(blockDim.x >> 6) + wave) * kFewRows;
+    if (base >= a.dv) return;                                  // whole wavefronts; no barrier below
+    const int L = a.L, dk = a.dk, dv = a.dv, r = a.r;
+    const int nsub = R == 1 ? r : 1;                           // r == 1, or the product form
+    const T *Qh = a.Q + head * (size_t)L * dk;
+    const T *Kh = a.K + head * (size_t)L * r * dk;
+    const T *Ah = kDrivers ? a.beta + head * (size_t)L * r * dk : Kh;
+    const T *Vh = a.V + head * (size_t)L * r * dv;
+    const T *bh = a.beta + head * (size_t)L * r;
+    T *Oh = a.O + head * (size_t)L * dv;
+    f32x4 S[NG][CV];
+    int row[NG];
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+        row[n] = base + n * (64 / LPR) + rr;
+        const float *s0 = a.S0 ? a.S0 + (head * (size_t)dv + (row[n] < dv ? row[n] : dv - 1)) * dk : nullptr;
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            const int x = 4 * (c + LPR * i);
+            S[n][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (s0 && x < dk) S[n][i] = *reinterpret_cast<const f32x4 *>(s0 + x);
+        }
+    }
+    struct Token {
+        Raw4<T> k[R][CV], u[kDrivers ? R : 1][CV], q[CV];
+        T v[R][NG], b[R];
+    };
+    // virtual tokens s R .. s R + R - 1 (sub-update s % nsub of token s / nsub)
+    auto fetch = [&](int s, Token &t) {
+        const size_t v0 = (size_t)s * R;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+#pragma unroll
+            for (int i = 0; i < CV; ++i) {
+                const int x = 4 * (c + LPR * i), xx = x < dk ? x : 0;
+                t.k[j][i] = *reinterpret_cast<const Raw4<T> *>(Ah + (v0 + j) * dk + xx);
+                if constexpr (kDrivers) t.u[j][i] = *reinterpret_cast<const Raw4<T> *>(Kh + (v0 + j) * dk + xx);
+            }
+#pragma unroll
+            for (int n = 0; n < NG; ++n) t.v[j][n] = Vh[(v0 + j) * dv + (row[n] < dv ? row[n] : dv - 1)];
+            if constexpr (!kDrivers) t.b[j] = bh[v0 + j];
+        }
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            const int x = 4 * (c + LPR * i);
+            t.q[i] = *reinterpret_cast<const Raw4<T> *>(Qh + (size_t)(s / nsub) * dk + (x < dk ? x : 0));
+        }
+    };
+    auto dot = [&](const f32x4 (&x)[CV], const f32x4 (&y)[CV]) {
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < CV; ++i) {
+            s0 = fmaf(x[i][0], y[i][0], s0);
+            s1 = fmaf(x[i][1], y[i][1], s1);
+            s0 = fmaf(x[i][2], y[i][2], s0);
+            s1 = fmaf(x[i][3], y[i][3], s1);
+        }
+        return row_sum<LPR>(s0 + s1);
+    };
+    // columns beyond d_k were read from column 0: zero in the rows of the token, as they are in S
+    auto widen = [&](const Raw4<T> (&x)[CV], f32x4 (&y)[CV]) {
+#pragma unroll
+        for (int i = 0; i < CV; ++i) y[i] = 4 * (c + LPR * i) < dk ? x[i].widen() : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    const int steps = L * nsub;
+    auto step = [&](int s, const Token &t) {
+        f32x4 k[R][CV], q[CV];
+        float u[R][NG];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            widen(t.k[j], k[j]);
+#pragma unroll
+            for (int n = 0; n < NG; ++n) {
+                const float w = dot(S[n], k[j]), v = as_f32(t.v[j][n]);
+                u[j][n] = kDrivers ? v + w : as_f32(t.b[j]) * (v - w);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if constexpr (kDrivers) widen(t.u[j], k[j]);
+#pragma unroll
+            for (int n = 0; n < NG; ++n)
+#pragma unroll
+                for (int i = 0; i < CV; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) S[n][i][e] = fmaf(u[j][n], k[j][i][e], S[n][i][e]);
+        }
+        if (nsub == 1 || (s + 1) % nsub == 0) {
+            widen(t.q, q);
+#pragma unroll
+            for (int n = 0; n < NG; ++n) {
+                const float o = dot(S[n], q);
+                if (c == 0 && row[n] < dv) Oh[(size_t)(s / nsub) * dv + row[n]] = from_f32<T>(o);
+            }
+        }
+    };
+    Token even, odd;
+    fetch(0, even);
+    for (int s = 0; s < steps; s += 2) {
+        fetch(s + 1 < steps ? s + 1 : s, odd);
+        step(s, even);
+        if (s + 1 >= steps) break;
+        fetch(s + 2 < steps ? s + 2 : s + 1, even);
+        step(s + 1, odd);
+    }
+    if (a.SL)
+#pragma unroll
+        for (int n = 0; n < NG; ++n)
+#pragma unroll
+            for (int i = 0; i < CV; ++i) {
+                const int x = 4 * (c + LPR * i);
+                if (row[n] < dv && x < dk) *reinterpret_cast<f32x4 *>(a.SL + (head * (size_t)dv + row[n]) * dk + x) = S[n][i];
+            }
+}
+
 // Rows too long for registers (d_k > 512) or too many ranks for the staging plan: a wavefront per row, the
 // row and the u_j of a token in LDS, operands straight from memory.
 template <typename T, bool kDrivers>
@@ -353,6 +482,7 @@ __device__ __forceinline__ void generic_long_rows(const GenericArgs<T> &a, const
 // One overload per row shape, told apart by its last parameter, so that each gets registers of its own.
 template <int LPR, int CS, int R> struct RowShape {};
 struct LongRows {};
+template <int CS, int R> struct FewTokens {};     // 16 lanes to a row, CS columns a lane
 template <int DT> struct BlockShape {};          // d_k padded to 16 DT (pf_generic_block.h)
 
 #define PF_RANKS(X, LPR, CS) X(LPR, CS, 1) X(LPR, CS, 2) X(LPR, CS, 4) X(LPR, CS, 0)
@@ -367,6 +497,16 @@ template <int DT> struct BlockShape {};          // d_k padded to 16 DT (pf_gene
         generic_rows<T, kDrivers, LPR, CS, R>(a, pl, gsmem);                                                    \
     }
 PF_ROW_SHAPES(X)
+#undef X
+
+#define PF_FEW_SHAPES(X) X(4, 1) X(4, 2) X(4, 4) X(8, 1) X(8, 2) X(8, 4)
+#define X(CS, R)                                                                                       \
+    template <typename T, bool kDrivers>                                                               \
+    __global__ __launch_bounds__(256) void generic_kernel(GenericArgs<T> a, FewTokens<CS, R>)          \
+    {                                                                                                  \
+        generic_few<T, kDrivers, CS, R>(a);                                                            \
+    }
+PF_FEW_SHAPES(X)
 #undef X
 
 #define PF_BLOCK_SHAPES(X) X(1) X(2) X(3) X(4) X(6) X(8)
@@ -439,6 +579,19 @@ GenericPlan plan_generic(int dk, int dv, int r, int chunk, int tokens, bool driv
     return p;
 }
 
+// Whether the body for a few tokens serves the call (steps: virtual tokens in the product form, else tokens).  It waits
+// for every token's rows to come out of L2, which many wavefronts hide from each other and few do not.  The body above /
+// this one, us, d = 128, r = 2, bf16:
+//   1024 heads   1 token 42.0 / 24.1    4 50.6 / 32.0    8 65.2 / 46.2    12 82.5 / 61.4
+//   128 heads    1 token  8.4 /  5.1    4 10.2 /  7.6    8 12.8 / 11.0    16, r = 1 12.9 / 16.1
+//   8 heads      1 token  5.1 /  4.5    2  4.8 /  4.8    4  5.4 /  6.4     8  6.6 / 9.8
+// and d = 64 (half the wavefronts): 1024 heads 1 token 17.4 / 7.3, 16 r = 1 30.0 / 26.4; 128 heads 4 5.6 / 5.5, 8 6.8 / 8.0.
+bool few_tokens(int heads, int dk, int dv, int steps)
+{
+    const long long waves = (long long)heads * ((dv + kFewRows - 1) / kFewRows);
+    return dk > 32 && dk <= 128 && dk % 4 == 0 && steps >= 1 && steps <= 16 && (steps <= 2 || steps <= waves / 128);
+}
+
 // Tiles of 16 columns that hold d_k, for the body that takes 16 virtual tokens at a time (0: no instance).
 int block_tiles(int dk, int r)
 {
@@ -476,6 +629,7 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
 {
     const GenericArgs<T> a{(const T *)Q, (const T *)K, (const T *)V, (const T *)beta, S0, (T *)O, SL,
                            heads, L, dk, dv, r, t0, product ? 1 : 0};
+    const int ranks = product ? 1 : r;
     bool taken = false;
     hipError_t done = hipSuccess;
     auto blocks = [&](auto dt) {
@@ -500,9 +654,21 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
     default: break;
     }
     if (taken) return done;
+    if (t0 == 0 && L <= 16 && few_tokens(heads, dk, dv, L * (r / ranks)) && (ranks == 1 || ranks == 2 || ranks == 4)) {
+        const int per_wg = 4 * kFewRows, tiles = (dv + per_wg - 1) / per_wg;
+        if ((long long)heads * tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+        auto launch = [&](auto shape) -> hipError_t {
+            void (*kern)(GenericArgs<T>, decltype(shape)) = generic_kernel<T, kDrivers>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)heads * tiles), dim3(256), 0, stream, a, shape);
+            return hipGetLastError();
+        };
+#define X(CS, R) \
+        if ((dk > 64 ? 8 : 4) == CS && ranks == R) return launch(FewTokens<CS, R>{});
+        PF_FEW_SHAPES(X)
+#undef X
+    }
     const GenericPlan pl = plan_generic(dk, dv, r, chunk, L - t0, kDrivers, (int)sizeof(T));
     if (pl.lds > kMaxLdsBytes || (long long)heads * pl.tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-    const int ranks = product ? 1 : r;
     auto launch = [&](auto shape) -> hipError_t {
         void (*kern)(GenericArgs<T>, GenericPlan, decltype(shape)) = generic_kernel<T, kDrivers>;
         if (pl.lds > 65536) {

@@ -72,6 +72,32 @@ def test_blocks_of_drivers(oracle, dtype, L, dk, dv, r):
         assert rel_l2(back(SL)[h], SLref) <= BAR["f32"]
 
 
+@pytest.mark.parametrize("product", [False, True])
+@pytest.mark.parametrize("dtype,heads,L,dk,dv,r", [
+    ("bf16", 3, 1, 128, 128, 2), ("bf16", 2, 2, 36, 5, 1), ("bf16", 40, 1, 64, 70, 4), ("bf16", 128, 8, 128, 128, 1),
+    ("bf16", 300, 16, 64, 128, 1), ("bf16", 520, 5, 128, 64, 2), ("f32", 1, 1, 100, 33, 1), ("f32", 3, 2, 60, 16, 2),
+    ("f32", 600, 4, 44, 20, 4), ("f32", 260, 15, 64, 128, 1), ("f32", 130, 3, 128, 128, 4),
+])
+def test_a_few_tokens(oracle, dtype, heads, L, dk, dv, r, product):
+    """The body that keeps 16 rows a wavefront and reads the tokens as it goes: both widths, padded columns, rows that do
+    not fill a wavefront, odd and even numbers of steps; a state handed in that is also the one handed out."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    w = synth.Workload("few", dtype, 1, heads, L, dk, dv, r, 64, seed=heads + L, s0_std=0.2, reflect_frac=0.05)
+    print(f"[case] a few tokens {dtype} heads={heads} d=({dk},{dv}) r={r} L={L} product={product}", flush=True)
+    inp = synth.make_inputs(w)
+    dev = to_device(w, inp)
+    O, state = torch.empty(1, heads, L, dv, dtype=dev["Q"].dtype, device="cuda:0"), dev["S0"].clone()
+    call = pf.pf_delta_product_fwd if product else pf.pf_delta_fwd
+    st = call(dev["Q"], dev["K"], dev["V"], dev["beta"], state, O, state, 1, heads, L, dk, dv, r, 64 if dtype == "bf16" else 4,
+              pf.PF_BF16 if dtype == "bf16" else pf.PF_F32, None, 0, None)
+    assert st == pf.PF_OK
+    torch.cuda.synchronize()
+    Oref, SLref = (oracle.delta_product_fwd if product else oracle.delta_fwd)(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    assert rel_l2(flat_heads(O.float().cpu().numpy()), Oref) <= BAR[dtype]
+    assert rel_l2(flat_heads(state.cpu().numpy()), SLref) <= BAR["f32"]
+
+
 @pytest.mark.parametrize("where", ["V", "K", "beta", "S0"])
 @pytest.mark.parametrize("r,t,value", [(1, 21, float("nan")), (1, 40, float("inf")), (2, 19, float("inf")), (3, 7, float("nan"))])
 def test_what_is_no_number_reaches_no_earlier_token(oracle, where, r, t, value):
