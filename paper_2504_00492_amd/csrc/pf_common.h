@@ -37,6 +37,16 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// 16x16x16: slot (g, e) of the contraction is 4 g + e.  The instruction takes its bf16 operands as 16-bit integers; the
+// pair of packed conversions is made opaque before that reinterpretation, otherwise the conversion is done element by
+// element and repacked.
+__device__ __forceinline__ f32x4 mfma16k(bf16x4 a, bf16x4 b, f32x4 c)
+{
+    u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+    asm volatile("" : "+v"(ua), "+v"(ub));
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, ua), __builtin_bit_cast(s16x4, ub), c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b)
 {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);

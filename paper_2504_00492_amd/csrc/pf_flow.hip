@@ -1,6 +1,6 @@
 // Chunk-flow kernel: step 2 of Section 3 of ParallelFlow (arXiv 2504.00492), "parallel
-// compute".  Persistent workgroups (8 wavefronts) walk the (b, h, chunk) triples; chunks do not
-// depend on each other.
+// compute".  Persistent workgroups walk the (b, h, chunk) triples; chunks do not depend on each other.  Blocks of 64
+// virtual tokens go one to a wavefront (pf_flow_wave.h); the body below, one block to a workgroup of 8, takes the rest.
 //
 // In delta variables (Remark in Section 3.1: A = beta k, Atil = -beta v, B = -k) Theorem 3.2
 // reads, with n = chunk * r virtual tokens and M strict in time,
@@ -32,8 +32,10 @@
 #include "pf_internal.h"
 #include "pf_common.h"
 #include "pf_layout.h"
+#include "pf_flow_wave.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace pf {
 
@@ -63,10 +65,10 @@ struct FlowLds {
     static constexpr size_t total = oUn + szUn;
 };
 
-template <int D, int N, int C, bool GEN = false>
-__global__ __launch_bounds__(kFlowThreads) void flow_kernel(
+template <int D, int N, int C, bool GEN>
+__device__ __forceinline__ void flow_workgroup(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
-    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift)
+    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift, char *smem)
 {
     // With GEN, K is the array of B rows and `beta` the array of A rows (n x d, like K); the
     // system matrix is Id - M (.) A B^T and P = Mbar (.) Q B^T (Theorem 3.2 as printed).
@@ -81,7 +83,6 @@ __global__ __launch_bounds__(kFlowThreads) void flow_kernel(
     static_assert(32 % R == 0 && N % 32 == 0 && C % 16 == 0 && D % 32 == 0, "tile shapes");
     static_assert(SPW <= 2, "a wave owns at most two slices");
 
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16 *Ks = reinterpret_cast<bf16 *>(smem + Ld::oKs);             // column side of the Gram: K, or B
     bf16 *As = GEN ? Ks + N * KP : Ks;                               // row side: K, or A
     float *bs = reinterpret_cast<float *>(smem + Ld::oBs);
@@ -378,6 +379,29 @@ __global__ __launch_bounds__(kFlowThreads) void flow_kernel(
     }
 }
 
+// Which body serves an instance, with its LDS, workgroup size and workgroups a compute unit.
+template <int D, int N, int C, bool GEN>
+struct FlowBody {
+    static constexpr bool kWave = N == 64;
+    static constexpr size_t lds = kWave ? FlowWavePlan::lds : FlowLds<D, N, C, GEN>::total;
+    static constexpr int threads = kWave ? FlowWavePlan::threads : kFlowThreads;
+    // (waves a SIMD of the body of one wavefront per block: as its operands in registers allow)
+    static constexpr int at_once = kWave ? (D == 64 ? 3 : (GEN ? 1 : 2)) : (2 * lds <= kMaxLdsBytes ? 2 : 1);
+    static constexpr int blocks = kWave ? FlowWavePlan::waves : 1;      // that a workgroup holds at a time
+};
+
+template <int D, int N, int C, bool GEN = false>
+__global__ __launch_bounds__((FlowBody<D, N, C, GEN>::threads), (FlowBody<D, N, C, GEN>::kWave ? FlowBody<D, N, C, GEN>::at_once : 1)) void flow_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
+    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if constexpr (FlowBody<D, N, C, GEN>::kWave)
+        flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, reinterpret_cast<float *>(smem));
+    else
+        flow_workgroup<D, N, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, smem);
+}
+
 // ---------------------------------------------------------------------------- host side
 #define PF_FLOW_INSTANCES(X) \
     X(64, 64, 64) X(64, 64, 32) X(64, 128, 32) X(64, 128, 64) X(64, 128, 128) X(64, 256, 64) X(64, 256, 128) \
@@ -399,17 +423,16 @@ static hipError_t launch_flow_instance(const void *Q, const void *K, const void 
     int mask_shift = 0;
     if (!product)
         while ((1 << mask_shift) < N / C) ++mask_shift;
-    constexpr size_t lds = FlowLds<D, N, C, GEN>::total;
-    static_assert(lds <= kMaxLdsBytes, "flow kernel LDS plan exceeds the CU");
+    using Body = FlowBody<D, N, C, GEN>;
+    static_assert(Body::lds <= kMaxLdsBytes, "flow kernel LDS plan exceeds the CU");
     static std::atomic<uint64_t> armed{0};
-    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
+    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Body::lds);
     if (e != hipSuccess) return e;
-    // Persistent grid: as many workgroups as the chip holds at once (LDS decides how many per
-    // CU, at most two), each walking its share of the chunks.
-    const size_t per_cu = kMaxLdsBytes / lds ? kMaxLdsBytes / lds : 1;
-    const size_t resident = (size_t)device_cu_count() * (per_cu > 2 ? 2 : per_cu);
-    const unsigned grid = (unsigned)(nchunks < resident ? nchunks : resident);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kFlowThreads), lds, stream, (const bf16 *)Q,
+    // Persistent grid: as many workgroups as the chip holds at once, each walking its share of the chunks.
+    const size_t resident = (size_t)device_cu_count() * Body::at_once;
+    const size_t want = (nchunks + Body::blocks - 1) / Body::blocks;
+    const unsigned grid = (unsigned)(want < resident ? want : resident);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift);
     return hipGetLastError();
 }

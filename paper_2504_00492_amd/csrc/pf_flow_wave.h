@@ -1,0 +1,196 @@
+// Body of the chunk-flow kernel for blocks of 64 virtual tokens: one wavefront per block, no barrier, and nothing but the
+// inverse of the diagonal tiles through LDS.
+//
+// The rows of K of a block fit one wavefront's registers as MFMA operands, and the layout that serves them as rows of the
+// Gram serves them as columns, so G and K Q^T come out of registers alone.  What follows is the block substitution of
+// Proposition 3.3 on 16 x 16 tiles, run on the transposed system (Id + G)^T X = Id, X = T^T, from the last tile up:
+//     X_js = T_jj^T ( - sum_{j < i <= s} G_ij^T X_is ),     X_ss = T_ss^T.
+// An accumulator tile of G is, lane for lane, the A operand of its transpose, and an accumulator tile of X the B operand
+// of the next product (16x16x16 MFMA, contraction index 4 g + e), so the substitution moves nothing between lanes
+// either.  Two accumulator tiles of X, one upon the other, are a tile of T as the scan reads it (pf_layout.h).
+// T_jj = (Id + G_jj)^{-1}: forward substitution in fp32 on the vector ALU, four tiles at a time, a column per lane.
+//
+// What bounds it: HBM (64 heads x 4096 tokens, d = 128, r = 2: 278 MB in 49 us, 5.7 TB/s; 32 heads x 65536: 2.2 GB in
+// 432 us).  The rows of the next block are asked for as soon as the block before has had its two sets of products, and
+// eight wavefronts a compute unit at different steps keep the loads going.  The workgroup of eight wavefronts per block
+// that serves the larger blocks (pf_flow.hip) had work for two to four of them here and six barriers; flow alone, us,
+// that body / this one:
+//   64 heads x 4096, d = 128, r = 2    70.5 / 49.0        32 x 2048, d = 64, r = 1    11.2 / 7.4
+//   32 x 65536, d = 128, r = 2          532 / 432         24 x 4096, d = 64, r = 2    26.3 / 14.0
+//   4 x 32768, d = 128, r = 2          37.2 / 28.2        32 x 2944, d = 128, r = 1   18.4 / 18.8 (one block a wavefront)
+#pragma once
+#include "pf_common.h"
+#include "pf_internal.h"
+#include "pf_layout.h"
+
+#include <type_traits>
+
+namespace pf {
+
+struct FlowWavePlan {
+    static constexpr int waves = 4, threads = 64 * waves;
+    static constexpr int NP = 20;                                      // row pitch of a tile in LDS
+    static constexpr int floats = 4 * 16 * NP + 64;                    // of a wavefront: diagonal tiles, row factors
+    static constexpr size_t lds = (size_t)waves * floats * 4;
+};
+
+template <int D, int C, bool GEN>
+__device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
+                                          bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail,
+                                          int mask_shift, float *smem)
+{
+    constexpr int N = 64, R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, CT = C / 16, NP = FlowWavePlan::NP;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    float *Ns = smem + wave * FlowWavePlan::floats, *bs = Ns + 4 * 16 * NP;
+    constexpr auto tri = [](int i, int j) constexpr { return i * (i + 1) / 2 + j; };   // tiles on and below the diagonal
+
+    bf16x8 aK[MT][NKS], aA[GEN ? MT : 1][NKS], bQ[CT][NKS];
+    bf16 breg = (bf16)0.0f;
+    // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: block c of the compact
+    // numbering starts (c / NC) * tail tokens further on in Q, K, beta.
+    auto fetch = [&](size_t c) {
+        const size_t skew = tail ? (c / (size_t)NC) * (size_t)tail : (size_t)0;
+        const bf16 *Kg = K + (c * N + skew * R) * D, *Qg = Q + (c * C + skew) * D;
+        const uint32_t at = (uint32_t)(r16 * D + 8 * g);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                aK[m][ks] = ld8(Kg + at + 16 * m * D + 32 * ks);
+                if constexpr (GEN) aA[m][ks] = ld8(beta + (c * N + skew * R) * D + at + 16 * m * D + 32 * ks);
+            }
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) bQ[t][ks] = ld8(Qg + at + 16 * t * D + 32 * ks);
+        if constexpr (!GEN) breg = beta[c * N + skew * R + lane];
+    };
+
+    const unsigned blocks = (unsigned)nchunks, step = gridDim.x * FlowWavePlan::waves;
+    unsigned cid = blockIdx.x * FlowWavePlan::waves + wave;
+    if (cid >= blocks) return;                         // whole wavefronts; no barrier below
+    fetch(cid);
+#pragma unroll 1
+    for (; cid < blocks; cid += step) {
+        bf16 *Ttg = Tt + (size_t)cid * N * N, *Ptg = Pt + (size_t)cid * C * N;
+        // ---- row factor of the system matrix: beta_i for the delta rule (G_ij = beta_i k_i . k_j); -1 for general
+        // drivers (G_ij = -a_i . b_j)
+        f32x4 b[MT];
+        if constexpr (!GEN) {
+            bs[lane] = (float)breg;
+            LDS_FENCE();
+#pragma unroll
+            for (int i = 0; i < MT; ++i) b[i] = *reinterpret_cast<const f32x4 *>(&bs[16 * i + 4 * g]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) b[i] = f32x4{-1.f, -1.f, -1.f, -1.f};
+        }
+        // ---- G, lower tiles
+        f32x4 G[tri(MT, 0)];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) acc = mfma16(GEN ? aA[GEN ? i : 0][ks] : aK[i][ks], aK[j][ks], acc);
+                G[tri(i, j)] = acc;
+            }
+        // ---- P = Mbar (.) Q K^T, from K Q^T
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int kt = 0; kt < NKT; ++kt) {
+                if (kt >= p_ksteps(R, t)) continue;
+                f32x4 acc[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks) acc[h] = mfma16(aK[2 * kt + h][ks], bQ[t][ks], acc[h]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)        // readout mask, inclusive in time
+                        if (32 * kt + 16 * h + 15 >= R * 16 * t) acc[h][e] = (32 * kt + 16 * h + 4 * g + e) / R > 16 * t + r16 ? 0.0f : acc[h][e];
+                }
+                st8(Ptg + full_tile_offset(NKT, t, kt) + lane * 8, join(cvt4(acc[0]), cvt4(acc[1])));
+            }
+        // ---- the next block's inputs, unconditionally (the last block's again)
+        fetch(cid + step < blocks ? cid + step : cid);
+        // ---- diagonal tiles to LDS, strictly lower in time; the others as operands of -G^T
+        bf16x4 nG[tri(MT, 0)];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                // rows and columns compared by token, i.e. by virtual token >> log2(R); mask_shift = 0 compares
+                // virtual tokens themselves (the r sub-updates of a token then see each other, one after another)
+                const bool seen = (r16 >> mask_shift) < ((4 * g + e) >> mask_shift);
+                Ns[(16 * i + 4 * g + e) * NP + r16] = seen ? G[tri(i, i)][e] * b[i][e] : 0.0f;
+            }
+#pragma unroll
+            for (int j = 0; j < i; ++j) nG[tri(i, j)] = cvt4(G[tri(i, j)] * -b[i]);
+        }
+        // ---- T_jj: lane group g inverts tile g, a column per lane; by columns, so that products do not wait for each other
+        {
+            const float *n = Ns + 16 * g * NP;
+            float t[16];
+            auto rows = [&](auto I0c, auto I1c) {
+                constexpr int I0 = decltype(I0c)::value, I1 = decltype(I1c)::value;
+                f32x4 x[I1 - I0][4];
+                LDS_FENCE();
+#pragma unroll
+                for (int i = I0; i < I1; ++i)
+#pragma unroll
+                    for (int j = 0; j < i; j += 4) x[i - I0][j / 4] = *reinterpret_cast<const f32x4 *>(&n[i * NP + j]);
+                LDS_FENCE();
+#pragma unroll
+                for (int i = I0; i < I1; ++i) t[i] = i == r16 ? 1.f : 0.f;
+#pragma unroll
+                for (int j = 0; j < I1 - 1; ++j)
+#pragma unroll
+                    for (int i = j + 1 > I0 ? j + 1 : I0; i < I1; ++i) t[i] = fmaf(-x[i - I0][j / 4][j & 3], t[j], t[i]);
+            };
+            rows(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+            rows(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
+            rows(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
+#pragma unroll
+            for (int i = 0; i < 16; ++i) Ns[(16 * g + i) * NP + r16] = t[i];
+            LDS_FENCE();
+        }
+        // ---- X, column by column of tiles
+        f32x4 Xd[MT];                                      // T_ss^T
+        bf16x4 To[MT];                                     // T_jj as operand of its transpose
+#pragma unroll
+        for (int s = 0; s < MT; ++s) {
+            Xd[s] = *reinterpret_cast<const f32x4 *>(&Ns[(16 * s + r16) * NP + 4 * g]);
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = Ns[(16 * s + 4 * g + e) * NP + r16];
+            To[s] = cvt4(v);
+        }
+        LDS_FENCE();
+#pragma unroll
+        for (int s = 0; s < MT; ++s) {
+            bf16x4 X[MT];
+            X[s] = cvt4(Xd[s]);
+#pragma unroll
+            for (int j = s - 1; j >= 0; --j) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f}, x = acc;
+#pragma unroll
+                for (int i = j + 1; i <= s; ++i) acc = mfma16k(nG[tri(i, j)], X[i], acc);
+                x = mfma16k(To[j], cvt4(acc), x);
+                X[j] = cvt4(x);
+            }
+#pragma unroll
+            for (int kt = 0; 2 * kt <= s; ++kt) {
+                bf16x4 z;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = (bf16)0.0f;
+                st8(Ttg + full_tile_offset(NKT, s, kt) + lane * 8, join(X[2 * kt], 2 * kt + 1 <= s ? X[2 * kt + 1] : z));
+            }
+        }
+    }
+}
+
+}  // namespace pf

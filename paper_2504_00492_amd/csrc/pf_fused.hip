@@ -61,16 +61,6 @@ constexpr int kFusedRoleWaves = 4;                       // waves per role
 constexpr int kFusedRoleThreads = 64 * kFusedRoleWaves;
 constexpr int kFusedThreads = 3 * kFusedRoleThreads;     // state, gram and aux waves
 
-// 16 x 16 x 16 product.  The instruction takes its bf16 operands as 16-bit integers; the pair of
-// packed conversions is made opaque before that reinterpretation, otherwise the conversion is done
-// element by element and repacked.
-__device__ __forceinline__ f32x4 mfma16k(bf16x4 a, bf16x4 b, f32x4 c)
-{
-    u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
-    asm volatile("" : "+v"(ua), "+v"(ub));
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, ua), __builtin_bit_cast(s16x4, ub), c, 0, 0, 0);
-}
-
 template <int D, int N, int C, int TV>
 struct FusedLds {
     static constexpr int R = N / C, NB = N / 32, MT = N / 16, CT = C / 16;
