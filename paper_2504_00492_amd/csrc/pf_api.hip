@@ -301,9 +301,10 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
     {
         float *Smid = tail ? reinterpret_cast<float *>(ws + wp.oS) : S_L;
         const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
+        const bool fold = pf::scan_chain(heads * wp.segments, d_v, block * r);
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             // Segment-parallel scan (no tail here): every segment of every head is a chain of
             // its own.  What a segment does to a zero state, then its propagator (identity in,
@@ -314,18 +315,18 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
             float *Sin = reinterpret_cast<float *>(ws + wp.oSin), *ident = reinterpret_cast<float *>(ws + wp.oI);
             e = pf::launch_segment_constants(ws + wp.oZ, ident, block * r, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, nullptr, nullptr, Hseg, vh, Ls, d_k, r, block, s);
+            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, nullptr, nullptr, Hseg, vh, Ls, d_k, r, block, s, fold);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, ws + wp.oZ, beta, Tt, Pt, ident, nullptr, Pseg, vh, Ls, d_k, r, block, s, 0, 0);
+            e = pf::launch_chunk_scan(Q, K, ws + wp.oZ, beta, Tt, Pt, ident, nullptr, Pseg, vh, Ls, d_k, r, block, s, fold, 0, 0);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             e = pf::launch_segment_compose(S0, Pseg, Hseg, Sin, S_L, heads, G, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, block, s);
+            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, block, s, fold);
             return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
         } else {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, block, s, 1, 1, d_v);
+            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, block, s, fold, 1, 1, d_v);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
         }
         state = Smid;
@@ -531,7 +532,7 @@ pf_status pf_delta_chunk_scan(const void *Q, const void *K, const void *V, const
         !aligned16(Pt) || !aligned16(S0) || !aligned16(O) || !aligned16(S_L))
         return PF_ERR_ALIGN;
     hipError_t e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, S_L, B * H, L, d_k, r, chunk,
-                                         static_cast<hipStream_t>(stream), 1, 1, d_v);
+                                         static_cast<hipStream_t>(stream), false, 1, 1, d_v);
     return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
 }
 

@@ -80,7 +80,9 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
                                      (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 2, 0, 0);
 }
 
-template <int D, int N, int C, int TV, bool RO>
+// FOLD: Tt holds -T diag(beta) (launch_chunk_flow), so that the chain takes K S^T - V as it comes out of the products: no
+// beta, no factor, and V goes in as a product with -Id.
+template <int D, int N, int C, int TV, bool RO, bool FOLD>
 __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const bf16 *V, const bf16 *beta,
                                            const bf16 *Tt, const bf16 *Pt, const float *S0, bf16 *O, float *SL,
                                            int nchains, int NC, int tail, int vmul, int s0mul, int dv, char *smem)
@@ -134,23 +136,29 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         static_assert(NM == MT * NKS && MT == 4, "one operand of K^T is read per product of R");
         bf16x8 aK[MT][NKS], tA[NT], aT[NKT][MD];
         bf16x4 vt[MT];
-        u32x4 bt[MT];                                  // bf16 in the low half
-        f32x4 vneg[MT], bw[MT];                        // -V and beta, widened
+        u32x4 bt[FOLD ? 1 : MT];                       // bf16 in the low half
+        f32x4 vneg[FOLD ? 1 : MT], bw[FOLD ? 1 : MT];  // -V and beta, widened
+        bf16x8 nI[2];                                  // -Id on the first, on the second half of a k-step
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) nI[h][e] = (bf16)(e / 4 == h && 4 * g + (e & 3) == r16 ? -1.0f : 0.0f);
         auto read_kt = [&](int base, int i) {
             const int kt = i / MD, mt = i % MD;
             const bf16 *p = reinterpret_cast<const bf16 *>(smem + base + kt0[mt >> 1] + 32 * kt * D * 2 + 8 * (mt & 1));
             aT[kt][mt] = join(lds_read_tr4(p), lds_read_tr4(p + 16 * D));
         };
-        constexpr int kAhead = 2 * MT + MT * NKS + NT, kPer = (kAhead + NM - 1) / NM;
+        constexpr int kVB = FOLD ? MT : 2 * MT, kAhead = kVB + MT * NKS + NT, kPer = (kAhead + NM - 1) / NM;
         auto read_ahead = [&](int base, int i) {
             if (i < MT) vt[i] = lds_read_tr4(reinterpret_cast<const bf16 *>(smem + base + vt0 + 16 * i * TV * 2));
-            else if (i < 2 * MT) bt[i - MT] = *reinterpret_cast<const u32x4 *>(smem + base + bt0 + 64 * (i - MT));
-            else if (i < 2 * MT + MT * NKS) {
-                const int mt = (i - 2 * MT) / NKS, ks = (i - 2 * MT) % NKS;
+            else if (i < kVB) bt[FOLD ? 0 : i - MT] = *reinterpret_cast<const u32x4 *>(smem + base + bt0 + 64 * (i - MT));
+            else if (i < kVB + MT * NKS) {
+                const int mt = (i - kVB) / NKS, ks = (i - kVB) % NKS;
                 aK[mt][ks] = at8(base + kr0[ks] + 16 * mt * D * 2);
-            } else if (i < kAhead) tA[i - 2 * MT - MT * NKS] = at8(base + tt0 + (i - 2 * MT - MT * NKS) * 1024);
+            } else if (i < kAhead) tA[i - kVB - MT * NKS] = at8(base + tt0 + (i - kVB - MT * NKS) * 1024);
         };
         auto widen = [&](int mt) {
+            if constexpr (FOLD) return;
             const u32x2 m = __builtin_bit_cast(u32x2, vt[mt]) ^ 0x80008000u;
             vneg[mt] = __builtin_bit_cast(f32x4, u32x4{m[0] << 16, m[0] & 0xffff0000u, m[1] << 16, m[1] & 0xffff0000u});
             bw[mt] = __builtin_bit_cast(f32x4, bt[mt] << 16);
@@ -175,10 +183,14 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             // ---- R = beta (.) (V - K S^T), from K S^T - V; the first pair of row tiles is finished inside the second
             f32x4 acc[MT], u[MT];
             auto epilogue = [&](int kt) {
-                bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
+                if constexpr (FOLD) bR[kt] = join(cvt4(acc[2 * kt]), cvt4(acc[2 * kt + 1]));
+                else bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
             };
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[mt] = vneg[mt];
+            for (int mt = 0; mt < MT; ++mt) {
+                if constexpr (FOLD) acc[mt] = mfma16(nI[mt & 1], join(vt[mt & ~1], vt[mt | 1]), f32x4{0.f, 0.f, 0.f, 0.f});
+                else acc[mt] = vneg[mt];
+            }
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 const int mt = 2 * (i / (2 * NKS)) + (i & 1), ks = (i / 2) % NKS;
@@ -247,7 +259,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         const int H = wave - 1;
         constexpr int VPR = D / 8, PPR = TV / 8;                     // 16-byte units per row of K, of the V tile
         constexpr int KQ = N * VPR / 64 / NSt, VQ = N * PPR / 64 / NSt, TQ = NT / NSt;
-        constexpr int kLoads = KQ + VQ + TQ + 1;                     // loads of a stager per block
+        constexpr int kLoads = KQ + VQ + TQ + (FOLD ? 0 : 1);                     // loads of a stager per block
         static_assert(N * VPR % (64 * NSt) == 0 && N * PPR % (64 * NSt) == 0 && NT % NSt == 0 && N == 64, "whole pieces");
         static_assert((kRing - 3) * kLoads < 64, "vmcnt");
         int ksrc[KQ], vsrc[VQ], tsrc[TQ];
@@ -277,7 +289,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             for (int q = 0; q < VQ; ++q) load_lds16(Vg + vsrc[q], d + Pl::oV + (H + NSt * q) * 1024);
 #pragma unroll
             for (int q = 0; q < TQ; ++q) load_lds16(Tg + tsrc[q], d + Pl::oT + (H + NSt * q) * 1024);
-            load_lds2(beta + cid * (size_t)N + lane, d + Pl::oB);    // both stagers: the same values to the same place
+            if constexpr (!FOLD) load_lds2(beta + cid * (size_t)N + lane, d + Pl::oB);    // both stagers: the same values to the same place
         };
         // Loads return in order: all but the newest n blocks have landed.
         auto landed_but = [&](auto Nc) {

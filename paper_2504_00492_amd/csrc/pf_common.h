@@ -47,6 +47,10 @@ __device__ __forceinline__ f32x4 mfma16k(bf16x4 a, bf16x4 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, ua), __builtin_bit_cast(s16x4, ub), c, 0, 0, 0);
 }
 
+// fp32, 16x16x4: A[r16][g], B[g][r16]; with step e standing for index 4 g + e, element e of an accumulator tile is the B
+// operand of step e, and of its transpose the A operand.
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b)
 {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);

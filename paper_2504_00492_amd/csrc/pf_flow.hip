@@ -386,18 +386,18 @@ struct FlowBody {
     static constexpr size_t lds = kWave ? FlowWavePlan::lds : FlowLds<D, N, C, GEN>::total;
     static constexpr int threads = kWave ? FlowWavePlan::threads : kFlowThreads;
     // (waves a SIMD of the body of one wavefront per block: as its operands in registers allow)
-    static constexpr int at_once = kWave ? (D == 64 ? 3 : (GEN ? 1 : 2)) : (2 * lds <= kMaxLdsBytes ? 2 : 1);
+    static constexpr int at_once = kWave ? (GEN && D == 128 ? 1 : 2) : (2 * lds <= kMaxLdsBytes ? 2 : 1);
     static constexpr int blocks = kWave ? FlowWavePlan::waves : 1;      // that a workgroup holds at a time
 };
 
 template <int D, int N, int C, bool GEN = false>
 __global__ __launch_bounds__((FlowBody<D, N, C, GEN>::threads), (FlowBody<D, N, C, GEN>::kWave ? FlowBody<D, N, C, GEN>::at_once : 1)) void flow_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
-    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift)
+    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift, int fold)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (FlowBody<D, N, C, GEN>::kWave)
-        flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, reinterpret_cast<float *>(smem));
+        flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, fold, reinterpret_cast<float *>(smem));
     else
         flow_workgroup<D, N, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, smem);
 }
@@ -417,7 +417,7 @@ bool mfma_instance_exists(int d, int n, int chunk)
 
 template <int D, int N, int C, bool GEN = false>
 static hipError_t launch_flow_instance(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
-                                       size_t nchunks, int NC, int tail, bool product, hipStream_t stream)
+                                       size_t nchunks, int NC, int tail, bool product, bool fold, hipStream_t stream)
 {
     auto kern = flow_kernel<D, N, C, GEN>;
     int mask_shift = 0;
@@ -433,21 +433,22 @@ static hipError_t launch_flow_instance(const void *Q, const void *K, const void 
     const size_t want = (nchunks + Body::blocks - 1) / Body::blocks;
     const unsigned grid = (unsigned)(want < resident ? want : resident);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
-                       (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift);
+                       (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift, fold ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
-                             int heads, int L, int d, int r, int chunk, hipStream_t stream, bool product)
+                             int heads, int L, int d, int r, int chunk, hipStream_t stream, bool product, bool fold)
 {
     const int NC = L / chunk, tail = L % chunk;   // the tail tokens of every head are skipped
     const size_t nchunks = (size_t)heads * NC;
     if (nchunks == 0) return hipSuccess;
     if (nchunks > 0x7fffffffull) return hipErrorInvalidValue;
     const int n = chunk * r;
+    if (fold && n != 64) return hipErrorInvalidValue;
 #define X(DD, NN, CC)                                                                        \
     if (d == DD && n == NN && chunk == CC)                                                    \
-        return launch_flow_instance<DD, NN, CC>(Q, K, beta, Tt, Pt, nchunks, NC, tail, product, stream);
+        return launch_flow_instance<DD, NN, CC>(Q, K, beta, Tt, Pt, nchunks, NC, tail, product, fold, stream);
     PF_FLOW_INSTANCES(X)
 #undef X
     return hipErrorInvalidValue;
@@ -466,7 +467,7 @@ hipError_t launch_chunk_flow_general(const void *Q, const void *A, const void *B
 #define X(DD, NN, CC)                                                                                    \
     if constexpr (NN <= 128) {                                                                            \
         if (d == DD && n == NN && chunk == CC)                                                            \
-            return launch_flow_instance<DD, NN, CC, true>(Q, Bm, A, Tt, Pt, nchunks, NC, tail, false, stream); \
+            return launch_flow_instance<DD, NN, CC, true>(Q, Bm, A, Tt, Pt, nchunks, NC, tail, false, false, stream); \
     }
     PF_FLOW_INSTANCES(X)
 #undef X

@@ -5,19 +5,21 @@
 // Gram serves them as columns, so G and K Q^T come out of registers alone.  What follows is the block substitution of
 // Proposition 3.3 on 16 x 16 tiles, run on the transposed system (Id + G)^T X = Id, X = T^T, from the last tile up:
 //     X_js = T_jj^T ( - sum_{j < i <= s} G_ij^T X_is ),     X_ss = T_ss^T.
-// An accumulator tile of G is, lane for lane, the A operand of its transpose, and an accumulator tile of X the B operand
-// of the next product (16x16x16 MFMA, contraction index 4 g + e), so the substitution moves nothing between lanes
-// either.  Two accumulator tiles of X, one upon the other, are a tile of T as the scan reads it (pf_layout.h).
+// An accumulator tile of G is, element for element, the A operand of its transpose for the fp32 instruction, and an
+// accumulator tile of X the B operand of the next product (mfma4), so the substitution moves nothing between lanes
+// either, and T is rounded to bf16 once, when it is stored: with G, X and T_jj rounded to bf16 as operands the flow took
+// 1 us less on every shape below and the forward was 1 % further from 64 bits (O 4.54e-3 against 4.49e-3 before this
+// body and 4.42e-3 now, 20 heads x 8192 tokens, d = 128, r = 2).  Two accumulator tiles of X, one upon the other, are a tile of T as the scan reads it (pf_layout.h).
 // T_jj = (Id + G_jj)^{-1}: forward substitution in fp32 on the vector ALU, four tiles at a time, a column per lane.
 //
-// What bounds it: HBM (64 heads x 4096 tokens, d = 128, r = 2: 278 MB in 49 us, 5.7 TB/s; 32 heads x 65536: 2.2 GB in
-// 432 us).  The rows of the next block are asked for as soon as the block before has had its two sets of products, and
-// eight wavefronts a compute unit at different steps keep the loads going.  The workgroup of eight wavefronts per block
-// that serves the larger blocks (pf_flow.hip) had work for two to four of them here and six barriers; flow alone, us,
-// that body / this one:
-//   64 heads x 4096, d = 128, r = 2    70.5 / 49.0        32 x 2048, d = 64, r = 1    11.2 / 7.4
-//   32 x 65536, d = 128, r = 2          532 / 432         24 x 4096, d = 64, r = 2    26.3 / 14.0
-//   4 x 32768, d = 128, r = 2          37.2 / 28.2        32 x 2944, d = 128, r = 1   18.4 / 18.8 (one block a wavefront)
+// What bounds it: HBM (64 heads x 4096 tokens, d = 128, r = 2: 278 MB in 45 us, 6.2 TB/s; 32 heads x 65536: 2.2 GB in
+// 433 us).  The rows of the next block are asked for as soon as the block before has had its two sets of products, and
+// eight wavefronts a compute unit at different steps keep the loads going (at d = 64 a third workgroup a compute unit
+// would spill).  The workgroup of eight wavefronts per block that serves the larger blocks (pf_flow.hip) had work for
+// two to four of them here and six barriers; flow alone, us, that body / this one:
+//   64 heads x 4096, d = 128, r = 2    70.2 / 45.1        32 x 2048, d = 64, r = 1    11.2 / 7.9
+//   32 x 65536, d = 128, r = 2          533 / 433         24 x 4096, d = 64, r = 2    26.1 / 13.9
+//   4 x 32768, d = 128, r = 2          36.6 / 24.1        32 x 2944, d = 128, r = 1   18.1 / 18.0 (one block a wavefront)
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"
@@ -37,7 +39,7 @@ struct FlowWavePlan {
 template <int D, int C, bool GEN>
 __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
                                           bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail,
-                                          int mask_shift, float *smem)
+                                          int mask_shift, int fold, float *smem)
 {
     constexpr int N = 64, R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, CT = C / 16, NP = FlowWavePlan::NP;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -72,7 +74,7 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
     if (cid >= blocks) return;                         // whole wavefronts; no barrier below
     fetch(cid);
 #pragma unroll 1
-    for (; cid < blocks; cid += step) {
+    for (bool more = true; more; cid += step) {
         bf16 *Ttg = Tt + (size_t)cid * N * N, *Ptg = Pt + (size_t)cid * C * N;
         // ---- row factor of the system matrix: beta_i for the delta rule (G_ij = beta_i k_i . k_j); -1 for general
         // drivers (G_ij = -a_i . b_j)
@@ -115,10 +117,11 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
                 }
                 st8(Ptg + full_tile_offset(NKT, t, kt) + lane * 8, join(cvt4(acc[0]), cvt4(acc[1])));
             }
-        // ---- the next block's inputs, unconditionally (the last block's again)
-        fetch(cid + step < blocks ? cid + step : cid);
+        // ---- the next block's inputs
+        more = cid + step < blocks;
+        if (more) fetch(cid + step);
         // ---- diagonal tiles to LDS, strictly lower in time; the others as operands of -G^T
-        bf16x4 nG[tri(MT, 0)];
+        f32x4 nG[tri(MT, 0)];
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
 #pragma unroll
@@ -129,7 +132,7 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
                 Ns[(16 * i + 4 * g + e) * NP + r16] = seen ? G[tri(i, i)][e] * b[i][e] : 0.0f;
             }
 #pragma unroll
-            for (int j = 0; j < i; ++j) nG[tri(i, j)] = cvt4(G[tri(i, j)] * -b[i]);
+            for (int j = 0; j < i; ++j) nG[tri(i, j)] = G[tri(i, j)] * -b[i];
         }
         // ---- T_jj: lane group g inverts tile g, a column per lane; by columns, so that products do not wait for each other
         {
@@ -158,36 +161,43 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
             for (int i = 0; i < 16; ++i) Ns[(16 * g + i) * NP + r16] = t[i];
             LDS_FENCE();
         }
-        // ---- X, column by column of tiles
+        // ---- X, column by column of tiles; handed over as it is, or as -T diag(beta)
+        f32x4 sc[MT];
+#pragma unroll
+        for (int j = 0; j < MT; ++j) sc[j] = fold ? -b[j] : f32x4{1.f, 1.f, 1.f, 1.f};
         f32x4 Xd[MT];                                      // T_ss^T
-        bf16x4 To[MT];                                     // T_jj as operand of its transpose
+        f32x4 To[MT];                                      // T_jj as operand of its transpose
 #pragma unroll
         for (int s = 0; s < MT; ++s) {
             Xd[s] = *reinterpret_cast<const f32x4 *>(&Ns[(16 * s + r16) * NP + 4 * g]);
-            f32x4 v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = Ns[(16 * s + 4 * g + e) * NP + r16];
-            To[s] = cvt4(v);
+            for (int e = 0; e < 4; ++e) To[s][e] = Ns[(16 * s + 4 * g + e) * NP + r16];
         }
         LDS_FENCE();
 #pragma unroll
         for (int s = 0; s < MT; ++s) {
-            bf16x4 X[MT];
-            X[s] = cvt4(Xd[s]);
+            f32x4 X[MT];
+            bf16x4 out[MT];                                // (as handed over)
+            X[s] = Xd[s];
+            out[s] = cvt4(Xd[s] * sc[s]);
 #pragma unroll
             for (int j = s - 1; j >= 0; --j) {
                 f32x4 acc = {0.f, 0.f, 0.f, 0.f}, x = acc;
 #pragma unroll
-                for (int i = j + 1; i <= s; ++i) acc = mfma16k(nG[tri(i, j)], X[i], acc);
-                x = mfma16k(To[j], cvt4(acc), x);
-                X[j] = cvt4(x);
+                for (int i = j + 1; i <= s; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc = mfma4(nG[tri(i, j)][e], X[i][e], acc);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x = mfma4(To[j][e], acc[e], x);
+                X[j] = x;
+                out[j] = cvt4(x * sc[j]);
             }
 #pragma unroll
             for (int kt = 0; 2 * kt <= s; ++kt) {
                 bf16x4 z;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) z[e] = (bf16)0.0f;
-                st8(Ttg + full_tile_offset(NKT, s, kt) + lane * 8, join(X[2 * kt], 2 * kt + 1 <= s ? X[2 * kt + 1] : z));
+                st8(Ttg + full_tile_offset(NKT, s, kt) + lane * 8, join(out[2 * kt], 2 * kt + 1 <= s ? out[2 * kt + 1] : z));
             }
         }
     }

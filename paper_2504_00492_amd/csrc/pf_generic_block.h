@@ -70,8 +70,6 @@ struct BlockLds {
     }
 };
 
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
 // A sum of products in N sums that are added up at the end: rounded less often, and neighbours do not wait for each other.
 template <int N>
 struct Sums {

@@ -46,13 +46,15 @@ hipError_t launch_generic_drivers(const void *Q, const void *A, const void *Atil
 // ---- MFMA path (pf_flow.hip, pf_scan.hip); d = d_k = d_v, n = chunk * r.  Both launchers take
 // the first L / chunk whole blocks of every head (heads L tokens apart) and leave the tail alone.
 bool mfma_instance_exists(int d, int n, int chunk);
+// fold (blocks of 64 virtual tokens): Tt receives -T diag(beta), rounded once, the form that the chain in one wavefront
+// takes (launch_chunk_scan, folded, where scan_chain says that it serves the call) instead of T and beta.
 hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
-                             bool product = false);
+                             bool product = false, bool fold = false);
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta,
                              const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
-                             int vmul = 1, int s0mul = 1, int dv = 0);
+                             bool folded = false, int vmul = 1, int s0mul = 1, int dv = 0);
 // The same two kernels for the general drivers (A, Atil, B) of Section 3.1 (rows of A, B: d wide,
 // of Atil: dv wide); instances with at most 128 virtual tokens per block.
 bool mfma_general_instance_exists(int d, int n, int chunk);

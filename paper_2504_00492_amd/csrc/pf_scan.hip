@@ -695,7 +695,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (ScanBody<D, N, C, TV, RO, GEN>::kChain)
-        chain_scan<D, N, C, TV, RO>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+        chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
     else
         split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
 }
@@ -710,6 +710,19 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     static_assert(SPLIT && ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+}
+
+// the chain on T itself, as the split entry points hand it over
+struct PlainT {};
+template <int D, int N, int C, int TV, bool RO, bool GEN>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv, PlainT)
+{
+    static_assert(ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes take T as it is");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    chain_scan<D, N, C, TV, RO, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -765,12 +778,28 @@ bool scan_chain(int heads, int dv, int n)
 template <int D, int N, int C, int TV>
 static hipError_t launch_scan_instance(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                                       int heads, int NC, int tail, int vmul, int s0mul, int dv, hipStream_t stream)
+                                       int heads, int NC, int tail, int vmul, int s0mul, int dv, bool folded, hipStream_t stream)
 {
     if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
         // (state-only passes run for scan_segments' choices, which never exceed the compute units)
         if (O && !scan_chain(heads, dv, N))
-            return launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+            return folded ? hipErrorInvalidValue
+                          : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+        if (!folded) {
+            if (!O) return hipErrorInvalidValue;
+            using Body = ScanBody<D, N, C, TV, true, false>;
+            void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *,
+                         float *, int, int, int, int, int, int, PlainT) = scan_kernel<D, N, C, TV, true, false>;
+            static std::atomic<uint64_t> armed{0};
+            hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Body::lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / TV)), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
+                               (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt, (const bf16 *)Pt, S0,
+                               (bf16 *)O, SL, heads, NC, tail, vmul, s0mul, dv, PlainT{});
+            return hipGetLastError();
+        }
+    } else if (folded) {
+        return hipErrorInvalidValue;
     }
     return O ? launch_scan_ro<D, N, C, TV, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream)
              : launch_scan_ro<D, N, C, TV, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
@@ -778,7 +807,7 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
 
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt,
                              const void *Pt, const float *S0, void *O, float *SL, int heads, int L, int d,
-                             int r, int chunk, hipStream_t stream, int vmul, int s0mul, int dv)
+                             int r, int chunk, hipStream_t stream, bool folded, int vmul, int s0mul, int dv)
 {
     const int NC = L / chunk, tail = L % chunk;   // the tail tokens of every head are skipped
     const int n = chunk * r;
@@ -789,9 +818,9 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
     if (d == DD && n == NN && chunk == CC) {                                                                \
         if constexpr (NN < 256) {                                                                           \
             if (wide)                                                                                       \
-                return launch_scan_instance<DD, NN, CC, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream); \
+                return launch_scan_instance<DD, NN, CC, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream); \
         }                                                                                                   \
-        return launch_scan_instance<DD, NN, CC, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);   \
+        return launch_scan_instance<DD, NN, CC, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream);   \
     }
     PF_SCAN_INSTANCES(X)
 #undef X
