@@ -38,11 +38,9 @@ struct WorkspacePlan {
 // Segments per head for the segment-parallel scan: 1 (plain hand-over chain per head) unless
 // the chains of the plain scan (heads x d_v tiles) would leave three quarters of the CUs idle
 // and there are enough blocks to cut.  Three passes of the scan kernel then run with
-// `segments` times as many chains.  Whole forward, d = 128, r = 2, segments against one chain per head:
-// 4 heads x 65536 tokens (eight segments) 0.57 against 1.58 ms, 8 heads x 65536 (four) 1.12 against 1.70 ms,
-// 8 heads x 8192 0.150 against 0.186 ms, 1 head x 2048 48 against 51 us.  A block costs 0.55 us in a pass without
-// the readout, 0.67 with it and 0.75 in the plain scan, so G segments pay from 1.77 / G < 0.75 on: two cannot, three
-// would, but only powers of two are tried, on whole blocks that divide evenly.
+// `segments` times as many chains.  A block costs 0.55 us in a pass without the readout, 0.67 with it and 0.75 in the
+// plain scan, so G segments pay from 1.77 / G < 0.75 on: two cannot, three would, but only powers of two are tried, on
+// whole blocks that divide evenly.
 int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 {
     if (L % chunk != 0 || d != dv) return 1;     // (the composition kernel takes square states)
@@ -53,6 +51,21 @@ int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
     int G = 1;
     while (2 * G * chains <= cus && NC % (2 * G) == 0 && NC / (2 * G) >= 4) G *= 2;
     return G >= 4 ? G : 1;
+}
+
+// Long segments of blocks of 64 virtual tokens are cut once more, and a workgroup takes two tiles of 16 rows: the two
+// read the same K, Q, T, P once, and a block of a pass takes hardly longer than with one tile.  Whole forward, d = 128,
+// r = 2, us, as scan_segments / cut once more:
+//   4 heads x 32768 tokens  238 / 173     8 x 65536  1078 / 698     1 x 131072  261 / 226     8 x 8192  127 / 97
+// and d = 64, r = 2, 16 x 65536 886 / 641.  The composition over the segments of a head is a chain of its own (1.4 us a
+// segment at d = 128): with 16 blocks a segment 2 heads x 65536, d = 64, r = 1 83 / 92, with 2 1 x 2048 47.7 / 50.0.
+// What the segments write (P, H) goes to where O will be, which holds it from 4 d tokens a segment on; the states they
+// start from, to the place that scan_segments' number of them has for all three.
+constexpr int kLongSegment = 32;                 // blocks
+bool cut_once_more(int segments, int L, int d, int r, int chunk)
+{
+    const int G = 2 * segments;
+    return segments > 1 && chunk * r == 64 && (L / chunk) % G == 0 && L / chunk / G >= kLongSegment && L / G >= 4 * d;
 }
 // L tokens per head of which the first L - L % chunk (whole flow blocks) go through the MFMA
 // kernels; when a tail remains, a state buffer carries S from them to the kernel of the tail.
@@ -244,11 +257,11 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
             out = generic;
         } else {
             const int heads = B * H, n = block * r;
-            const int G = scan_segments(heads, L, d_k, d_v, r, block);
+            const int G = scan_segments(heads, L, d_k, d_v, r, block);   // (cut once more or not: the same tiles of 16 rows)
             const std::string dims = std::to_string(d_k) + ", " + std::to_string(n) + ", " + std::to_string(block);
             const std::string flow = "pf::flow_kernel<" + dims + ", false>";
             const std::string scan = "pf::scan_kernel<" + dims + ", " +
-                                     std::to_string(pf::scan_dv_tile(heads * G, d_v, n));
+                                     std::to_string(G > 1 && n == 64 ? 16 : pf::scan_dv_tile(heads * G, d_v, n));
             if (G > 1)
                 out = flow + ";pf::segment_constants_kernel;" + scan + ", false, false>;" + scan + ", false, false>;" +
                       "pf::segment_compose_kernel;" + scan + ", true, false>";
@@ -301,7 +314,7 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
     {
         float *Smid = tail ? reinterpret_cast<float *>(ws + wp.oS) : S_L;
         const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
-        const bool fold = pf::scan_chain(heads * wp.segments, d_v, block * r);
+        const bool fold = wp.segments > 1 ? block * r == 64 : pf::scan_chain(heads, d_v, block * r);
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);
@@ -310,18 +323,24 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
             // its own.  What a segment does to a zero state, then its propagator (identity in,
             // zero values), then the composition over the segments of a head, then the real
             // pass of every segment from its true incoming state.
-            const int G = wp.segments, vh = heads * G, Ls = L / G;
-            float *Hseg = reinterpret_cast<float *>(ws + wp.oH), *Pseg = reinterpret_cast<float *>(ws + wp.oG);
-            float *Sin = reinterpret_cast<float *>(ws + wp.oSin), *ident = reinterpret_cast<float *>(ws + wp.oI);
+            const bool twice = cut_once_more(wp.segments, L, d_k, r, block);
+            const int G = twice ? 2 * wp.segments : wp.segments, vh = heads * G, Ls = L / G;
+            float *Hseg = twice ? static_cast<float *>(O) : reinterpret_cast<float *>(ws + wp.oH);
+            float *Pseg = twice ? Hseg + (size_t)vh * d_k * d_k : reinterpret_cast<float *>(ws + wp.oG);
+            float *Sin = reinterpret_cast<float *>(ws + (twice ? wp.oH : wp.oSin)), *ident = reinterpret_cast<float *>(ws + wp.oI);
             e = pf::launch_segment_constants(ws + wp.oZ, ident, block * r, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, nullptr, nullptr, Hseg, vh, Ls, d_k, r, block, s, fold);
+            auto pass = [&](const void *values, const float *from, void *out, float *to, int vmul, int s0mul) {
+                return twice ? pf::launch_segment_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, block, s, vmul, s0mul)
+                            : pf::launch_chunk_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, block, s, fold, vmul, s0mul);
+            };
+            e = pass(V, nullptr, nullptr, Hseg, 1, 1);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, ws + wp.oZ, beta, Tt, Pt, ident, nullptr, Pseg, vh, Ls, d_k, r, block, s, fold, 0, 0);
+            e = pass(ws + wp.oZ, ident, nullptr, Pseg, 0, 0);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             e = pf::launch_segment_compose(S0, Pseg, Hseg, Sin, S_L, heads, G, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, block, s, fold);
+            e = pass(V, Sin, O, nullptr, 1, 1);
             return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
         } else {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);

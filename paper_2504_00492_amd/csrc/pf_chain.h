@@ -48,23 +48,23 @@ __device__ __forceinline__ int k_swizzle(int row)
 
 template <int D, int N, int C, int TV, bool RO>
 struct ChainPlan {
-    static constexpr int stagers = 2, readers = RO ? 2 : 0;
-    static constexpr int threads = 64 * (1 + stagers + readers);
+    static constexpr int states = TV / 16, stagers = 2, readers = RO ? 2 : 0;   // wavefronts of each role
+    static constexpr int threads = 64 * (states + stagers + readers);
     static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
     // one ring slot: K, V tile, T tiles, beta (32 bits each)
     static constexpr size_t oV = (size_t)N * D * 2;
     static constexpr size_t oT = oV + (size_t)N * TV * 2;
     static constexpr size_t oB = oT + (size_t)NT * 1024;
     static constexpr size_t slot = oB + (size_t)N * 4;
-    static constexpr size_t szX = RO ? (size_t)(D / 32) * 1024 : 0;   // S of a block, operand tiles
-    static constexpr size_t szU = RO ? (size_t)(N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
+    static constexpr size_t szX = RO ? (size_t)states * (D / 32) * 1024 : 0;   // S of a block, operand tiles
+    static constexpr size_t szU = RO ? (size_t)states * (N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
     // two slots are being read (this block, and the rows and T of the next), the others are on their way from memory
     static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU)) / slot);
     static constexpr int kRing = fit < 6 ? fit : 6;
     static constexpr size_t oX = kRing * slot;
     static constexpr size_t oU = oX + 2 * szX;
     static constexpr size_t total = oU + 2 * szU;
-    static constexpr bool kServes = N == 64 && TV == 16 && kRing >= 4;
+    static constexpr bool kServes = N == 64 && (TV == 16 || TV == 32) && kRing >= 4;
 };
 
 // 16 bytes (4: 2 bytes, widened to 32 bits) per lane from memory to LDS; the LDS address is the wavefront's, lane l
@@ -90,7 +90,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     using Pl = ChainPlan<D, N, C, TV, RO>;
     constexpr int NT = Pl::NT, kRing = Pl::kRing;
     constexpr int R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, MD = D / 16, CT = C / 16;
-    constexpr int NSt = Pl::stagers;
+    constexpr int NSS = Pl::states, NSt = Pl::stagers;
 
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
@@ -105,11 +105,11 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     bf16 *Xs = reinterpret_cast<bf16 *>(smem + Pl::oX), *Us = reinterpret_cast<bf16 *>(smem + Pl::oU);
     constexpr int XB = (int)(Pl::szX / 2), UB = (int)(Pl::szU / 2);   // elements of one buffer
 
-    if (wave == 0) {
-        // -------------------------------------------------------------- state wave
+    if (wave < NSS) {
+        // -------------------------------------------------------------- state waves, 16 rows each
         __builtin_amdgcn_s_setprio(3);                 // the helpers of this SIMD fill what the chain leaves
         auto dk0 = [&](int mt) { return 32 * (mt >> 1) + 8 * g + 4 * (mt & 1); };
-        const size_t srow = (size_t)(tile * TV + r16) * D;
+        const size_t srow = (size_t)(tile * TV + 16 * wave + r16) * D;
         f32x4 sacc[MD];
 #pragma unroll
         for (int mt = 0; mt < MD; ++mt) {
@@ -123,7 +123,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             kr0[ks] = r16 * D * 2 + ((4 * ks + g) ^ k_swizzle<D>(r16)) * 16;
             kt0[ks] = (4 * g + (r16 >> 2)) * D * 2 + ((4 * ks + (r16 & 3)) ^ k_swizzle<D>(4 * g + (r16 >> 2))) * 16;
         }
-        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 4 * (r16 & 3)) * 2;
+        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 16 * wave + 4 * (r16 & 3)) * 2;
         const int tt0 = (int)Pl::oT + lane * 16, bt0 = (int)Pl::oB + 16 * g;
         auto at8 = [&](int off) { return *reinterpret_cast<const bf16x8 *>(smem + off); };
 
@@ -197,7 +197,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 acc[mt] = mfma16(aK[mt][ks], bS[ks], acc[mt]);
                 read_kt(base, i);
                 if constexpr (RO)
-                    if (i < NKS) st8(&Xs[(ch & 1) * XB + i * 512 + lane * 8], bS[i]);
+                    if (i < NKS) st8(&Xs[(ch & 1) * XB + (wave * NKS + i) * 512 + lane * 8], bS[i]);
                 if (i == 2 * NKS + NKS - 1) epilogue(0);
                 kInOrder();
             }
@@ -218,7 +218,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 if (i == MD) bU[1] = join(cvt4(u[2]), cvt4(u[3]));
                 sacc[mt] = mfma16(aT[kt][mt], bU[kt], sacc[mt]);
                 if constexpr (RO)
-                    if (mt == 0) st8(&Us[(ch & 1) * UB + kt * 512 + lane * 8], bU[kt]);
+                    if (mt == 0) st8(&Us[(ch & 1) * UB + (wave * NKT + kt) * 512 + lane * 8], bU[kt]);
 #pragma unroll
                 for (int q = 0; q < kPer; ++q) read_ahead(ahead, kPer * i + q);
                 if (kt == 1 && mt % (MD / MT) == 0) widen(mt / (MD / MT));
@@ -254,9 +254,9 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     };
     auto clamp = [&](int ch) { return c0 + (size_t)(ch < NC ? ch : NC - 1); };
 
-    if (wave < 1 + NSt) {
+    if (wave < NSS + NSt) {
         // The stagers' loads go straight to LDS.  Pieces of 64 x 16 bytes, dealt to the stagers one by one.
-        const int H = wave - 1;
+        const int H = wave - NSS;
         constexpr int VPR = D / 8, PPR = TV / 8;                     // 16-byte units per row of K, of the V tile
         constexpr int KQ = N * VPR / 64 / NSt, VQ = N * PPR / 64 / NSt, TQ = NT / NSt;
         constexpr int kLoads = KQ + VQ + TQ + (FOLD ? 0 : 1);                     // loads of a stager per block
@@ -352,31 +352,36 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             __syncthreads();
             bf16 *Oc = O + chain * (size_t)tail * dv + ((c0 + ch) * (size_t)C + r16) * dv + tile * TV + 4 * g;
             const bf16 *X = Xs + (ch & 1) * XB + lane * 8, *U = Us + (ch & 1) * UB + lane * 8;
-            f32x4 o[TN];
-            bf16x8 x[NKS], u[NKT];
+            f32x4 o[NSS][TN];
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) x[ks] = ld8(X + ks * 512);
+            for (int w = 0; w < NSS; ++w) {
+                bf16x8 x[NKS], u[NKT];
 #pragma unroll
-            for (int kt = 0; kt < NKT; ++kt) u[kt] = ld8(U + kt * 512);
+                for (int ks = 0; ks < NKS; ++ks) x[ks] = ld8(X + (w * NKS + ks) * 512);
 #pragma unroll
-            for (int i = 0; i < TN; ++i) {
-                o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int kt = 0; kt < NKT; ++kt) u[kt] = ld8(U + (w * NKT + kt) * 512);
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) o[i] = mfma16(x[ks], bQ[S][i][ks], o[i]);
+                for (int i = 0; i < TN; ++i) {
+                    o[w][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kt = 0; kt < NKT; ++kt)
-                    if (kt < p_ksteps(R, tok_tile(i))) o[i] = mfma16(u[kt], bP[S][i][kt], o[i]);
+                    for (int ks = 0; ks < NKS; ++ks) o[w][i] = mfma16(x[ks], bQ[S][i][ks], o[w][i]);
+#pragma unroll
+                    for (int kt = 0; kt < NKT; ++kt)
+                        if (kt < p_ksteps(R, tok_tile(i))) o[w][i] = mfma16(u[kt], bP[S][i][kt], o[w][i]);
+                }
             }
             LDS_FENCE();
             fetch(ch + kSets, Sc);
             LDS_FENCE();
 #pragma unroll
-            for (int i = 0; i < TN; ++i) st4(Oc + (size_t)16 * tok_tile(i) * dv, cvt4(o[i]));
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int w = 0; w < NSS; ++w) st4(Oc + (size_t)16 * tok_tile(i) * dv + 16 * w, cvt4(o[w][i]));
             LDS_FENCE();
         });
     };
     if constexpr (RO) {
-        if (wave == 1 + NSt) reader(k0);
+        if (wave == NSS + NSt) reader(k0);
         else reader(k1);
     }
 }

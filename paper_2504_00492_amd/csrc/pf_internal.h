@@ -55,6 +55,11 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
                              const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
                              bool folded = false, int vmul = 1, int s0mul = 1, int dv = 0);
+// The chain with 32 rows of S to a workgroup (blocks of 64 virtual tokens, -T diag(beta) handed over, d = d_k = d_v, whole
+// blocks): the passes of the segment-parallel scan.
+hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                               const float *S0, void *O, float *SL, int heads, int L, int d, int r, int chunk,
+                               hipStream_t stream, int vmul = 1, int s0mul = 1);
 // The same two kernels for the general drivers (A, Atil, B) of Section 3.1 (rows of A, B: d wide,
 // of Atil: dv wide); instances with at most 128 virtual tokens per block.
 bool mfma_general_instance_exists(int d, int n, int chunk);

@@ -679,7 +679,7 @@ __device__ __forceinline__ void split_scan(
 template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT = false>
 struct ScanBody {
     using Chain = ChainPlan<D, N, C, TV, RO>;
-    static constexpr bool kChain = !SPLIT && !GEN && Chain::kServes;
+    static constexpr bool kChain = !SPLIT && !GEN && TV == 16 && Chain::kServes;
     static constexpr size_t lds = kChain ? Chain::total : ScanLds<D, N, C, TV, GEN>::total;
     static constexpr int threads = kChain ? Chain::threads : kScanThreads;
 };
@@ -710,6 +710,19 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     static_assert(SPLIT && ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+}
+
+// the chain with two tiles to a workgroup, a state wave each
+struct TwoTiles {};
+template <int D, int N, int C, int TV, bool RO, bool GEN>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv, TwoTiles)
+{
+    static_assert(TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
 }
 
 // the chain on T itself, as the split entry points hand it over
@@ -753,6 +766,24 @@ static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, co
     return hipGetLastError();
 }
 
+// the chain under one of its tags, ROWS rows of S to a workgroup
+template <int D, int N, int C, int ROWS, bool RO, typename Tag>
+static hipError_t launch_chain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                               const float *S0, void *O, float *SL, int heads, int NC, int tail, int vmul, int s0mul, int dv,
+                               hipStream_t stream)
+{
+    using Pl = ChainPlan<D, N, C, ROWS, RO>;
+    void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *, float *,
+                 int, int, int, int, int, int, Tag) = scan_kernel<D, N, C, 16, RO, false>;
+    static std::atomic<uint64_t> armed{0};
+    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / ROWS)), dim3(Pl::threads), Pl::total, stream, (const bf16 *)Q,
+                       (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt, (const bf16 *)Pt, S0, (bf16 *)O, SL,
+                       heads, NC, tail, vmul, s0mul, dv, Tag{});
+    return hipGetLastError();
+}
+
 int scan_dv_tile(int heads, int dv, int n)
 {
     // 32 rows when that already gives at least one workgroup per CU, else 16 rows (twice the
@@ -787,16 +818,7 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
                           : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
         if (!folded) {
             if (!O) return hipErrorInvalidValue;
-            using Body = ScanBody<D, N, C, TV, true, false>;
-            void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *,
-                         float *, int, int, int, int, int, int, PlainT) = scan_kernel<D, N, C, TV, true, false>;
-            static std::atomic<uint64_t> armed{0};
-            hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Body::lds);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / TV)), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
-                               (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt, (const bf16 *)Pt, S0,
-                               (bf16 *)O, SL, heads, NC, tail, vmul, s0mul, dv, PlainT{});
-            return hipGetLastError();
+            return launch_chain<D, N, C, TV, true, PlainT>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
         }
     } else if (folded) {
         return hipErrorInvalidValue;
@@ -821,6 +843,23 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
                 return launch_scan_instance<DD, NN, CC, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream); \
         }                                                                                                   \
         return launch_scan_instance<DD, NN, CC, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream);   \
+    }
+    PF_SCAN_INSTANCES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                               const float *S0, void *O, float *SL, int heads, int L, int d, int r, int chunk,
+                               hipStream_t stream, int vmul, int s0mul)
+{
+    const int NC = L / chunk, n = chunk * r;
+    if (L % chunk != 0 || n != 64 || d % 32 != 0 || (long long)heads * (d / 32) > 0x7fffffffLL) return hipErrorInvalidValue;
+#define X(DD, NN, CC)                                                                                      \
+    if constexpr (NN == 64) {                                                                               \
+        if (d == DD && chunk == CC)                                                                         \
+            return O ? launch_chain<DD, NN, CC, 32, true, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream) \
+                     : launch_chain<DD, NN, CC, 32, false, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream); \
     }
     PF_SCAN_INSTANCES(X)
 #undef X

@@ -39,3 +39,25 @@ def test_block_counts(oracle, blocks, tail, r, dk, dv):
 def test_segments(oracle, d, r, L):
     names = _check(oracle, 2, L, d, d, r, 7)
     assert "pf::segment_compose_kernel" in names
+
+
+@pytest.mark.parametrize("heads,d,r,L,product", [(8, 128, 2, 8192, False), (16, 64, 1, 16384, False), (8, 128, 1, 16384, True),
+                                                 (14, 64, 2, 8192, True)])
+def test_segments_cut_once_more(oracle, heads, d, r, L, product):
+    """Segments of 32 blocks with two tiles of 16 rows to a workgroup: what they write lies where O will be; the state is
+    handed in and out in place."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    w = synth.Workload("twice", "bf16", 1, heads, L, d, d, r, 64, seed=heads, s0_std=0.2, reflect_frac=0.05)
+    print(f"[case] segments cut once more heads={heads} L={L} d={d} r={r} product={product}", flush=True)
+    inp = synth.make_inputs(w)
+    dev = to_device(w, inp)
+    need = pf.pf_delta_fwd_workspace_bytes(1, heads, L, d, d, r, 64, pf.PF_BF16)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    O, state = torch.empty(1, heads, L, d, dtype=torch.bfloat16, device="cuda:0"), dev["S0"].clone()
+    call = pf.pf_delta_product_fwd if product else pf.pf_delta_fwd
+    assert call(dev["Q"], dev["K"], dev["V"], dev["beta"], state, O, state, 1, heads, L, d, d, r, 64, pf.PF_BF16, ws, need, None) == pf.PF_OK
+    torch.cuda.synchronize()
+    Oref, SLref = (oracle.delta_product_fwd if product else oracle.delta_fwd)(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    SLn, SLref = state.cpu().numpy().reshape(heads, d, d), np.asarray(SLref).reshape(heads, d, d)
+    assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
