@@ -67,6 +67,13 @@ bool cut_once_more(int segments, int L, int d, int r, int chunk)
     const int G = 2 * segments;
     return segments > 1 && chunk * r == 64 && (L / chunk) % G == 0 && L / chunk / G >= kLongSegment && L / G >= 4 * d;
 }
+// Whether blocks of 128 virtual tokens (32 tokens, r = 4) run as two blocks of 64 each: where the chain in one wavefront
+// serves those.  T of a block shrinks to its two diagonal quarters.
+bool run_in_halves(int heads, int dv, int r, int block, int segments)
+{
+    return r == 4 && block == 32 && (segments > 1 || pf::scan_chain(heads, dv, 64));
+}
+
 // L tokens per head of which the first L - L % chunk (whole flow blocks) go through the MFMA
 // kernels; when a tail remains, a state buffer carries S from them to the kernel of the tail.
 WorkspacePlan plan_workspace(int heads, int L, int d, int dv, int r, int chunk)
@@ -314,16 +321,18 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
     {
         float *Smid = tail ? reinterpret_cast<float *>(ws + wp.oS) : S_L;
         const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
-        const bool fold = wp.segments > 1 ? block * r == 64 : pf::scan_chain(heads, d_v, block * r);
+        const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
+        const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
+        const bool fold = wp.segments > 1 ? sub * r == 64 : pf::scan_chain(heads, d_v, sub * r);
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             // Segment-parallel scan (no tail here): every segment of every head is a chain of
             // its own.  What a segment does to a zero state, then its propagator (identity in,
             // zero values), then the composition over the segments of a head, then the real
             // pass of every segment from its true incoming state.
-            const bool twice = cut_once_more(wp.segments, L, d_k, r, block);
+            const bool twice = cut_once_more(wp.segments, L, d_k, r, sub);
             const int G = twice ? 2 * wp.segments : wp.segments, vh = heads * G, Ls = L / G;
             float *Hseg = twice ? static_cast<float *>(O) : reinterpret_cast<float *>(ws + wp.oH);
             float *Pseg = twice ? Hseg + (size_t)vh * d_k * d_k : reinterpret_cast<float *>(ws + wp.oG);
@@ -331,8 +340,8 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
             e = pf::launch_segment_constants(ws + wp.oZ, ident, block * r, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             auto pass = [&](const void *values, const float *from, void *out, float *to, int vmul, int s0mul) {
-                return twice ? pf::launch_segment_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, block, s, vmul, s0mul)
-                            : pf::launch_chunk_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, block, s, fold, vmul, s0mul);
+                return twice ? pf::launch_segment_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, sub, s, vmul, s0mul)
+                            : pf::launch_chunk_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, sub, s, fold, vmul, s0mul);
             };
             e = pass(V, nullptr, nullptr, Hseg, 1, 1);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
@@ -343,9 +352,9 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
             e = pass(V, Sin, O, nullptr, 1, 1);
             return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
         } else {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, block, s, product, fold);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, block, s, fold, 1, 1, d_v);
+            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, sub, s, fold, 1, 1, d_v, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
         }
         state = Smid;

@@ -48,7 +48,7 @@ __device__ __forceinline__ int k_swizzle(int row)
 
 template <int D, int N, int C, int TV, bool RO>
 struct ChainPlan {
-    static constexpr int states = TV / 16, stagers = 2, readers = RO ? 2 : 0;   // wavefronts of each role
+    static constexpr int states = TV / 16, stagers = 2, readers = !RO ? 0 : (C >= 32 ? 2 : 1);   // wavefronts of each role
     static constexpr int threads = 64 * (states + stagers + readers);
     static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
     // one ring slot: K, V tile, T tiles, beta (32 bits each)
@@ -322,9 +322,9 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         return;
     }
 
-    // readers: token tiles w and CT - 1 - w (of two tiles: w), a block behind the state
+    // readers: token tiles w and CT - 1 - w (of two tiles: w; of one: one reader), a block behind the state
     auto reader = [&](auto Wc) {
-        constexpr int W = decltype(Wc)::value, TN = CT / 2;
+        constexpr int W = decltype(Wc)::value, TN = CT < 2 ? 1 : CT / 2;
         constexpr auto tok_tile = [](int i) constexpr { return i == 0 ? W : CT - 1 - W; };
         constexpr int kSets = 3;                                     // blocks of Q and P on their way in register sets
         bf16x8 bQ[kSets][TN][NKS], bP[kSets][TN][NKT];               // (P tiles above the causal mask do not exist)
@@ -381,8 +381,8 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         });
     };
     if constexpr (RO) {
-        if (wave == NSS + NSt) reader(k0);
-        else reader(k1);
+        if (Pl::readers == 1 || wave == NSS + NSt) reader(k0);
+        else if constexpr (Pl::readers == 2) reader(k1);
     }
 }
 

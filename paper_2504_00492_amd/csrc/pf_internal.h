@@ -50,11 +50,13 @@ bool mfma_instance_exists(int d, int n, int chunk);
 // takes (launch_chunk_scan, folded, where scan_chain says that it serves the call) instead of T and beta.
 hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
-                             bool product = false, bool fold = false);
+                             bool product = false, bool fold = false, int unit = 0);
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta,
                              const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
-                             bool folded = false, int vmul = 1, int s0mul = 1, int dv = 0);
+                             bool folded = false, int vmul = 1, int s0mul = 1, int dv = 0, int unit = 0);
+// unit (0: chunk): the whole blocks of a head are counted in this many tokens.  chunk = 16 with r = 4 and unit = 32 runs
+// the two halves of a block of 128 virtual tokens as blocks of 64 (fold only: the chain has no other form of them).
 // The chain with 32 rows of S to a workgroup (blocks of 64 virtual tokens, -T diag(beta) handed over, d = d_k = d_v, whole
 // blocks): the passes of the segment-parallel scan.
 hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,

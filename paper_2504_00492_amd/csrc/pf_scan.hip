@@ -725,6 +725,24 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
 }
 
+// blocks of 128 virtual tokens and 32 tokens (r = 4) as two blocks of 64 each, one tile or two to a workgroup
+template <int TILES> struct Halves {};
+#define PF_HALVES(TILES)                                                                                                     \
+    template <int D, int N, int C, int TV, bool RO, bool GEN>                                                                \
+    __global__ __launch_bounds__(kScanThreads) void scan_kernel(                                                             \
+        const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ beta,   \
+        const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt, const float *S0, bf16 *__restrict__ O, float *SL,          \
+        int nchains, int NC, int tail, int vmul, int s0mul, int dv, Halves<TILES>)                                           \
+    {                                                                                                                        \
+        static_assert(N == 128 && TV == 16 && !GEN, "halves of 64 virtual tokens");                                          \
+        extern __shared__ __attribute__((aligned(16))) char smem[];                                                          \
+        chain_scan<D, N / 2, C / 2, 16 * TILES, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul,  \
+                                                          dv, smem);                                                         \
+    }
+PF_HALVES(1)
+PF_HALVES(2)
+#undef PF_HALVES
+
 // the chain on T itself, as the split entry points hand it over
 struct PlainT {};
 template <int D, int N, int C, int TV, bool RO, bool GEN>
@@ -766,15 +784,16 @@ static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, co
     return hipGetLastError();
 }
 
-// the chain under one of its tags, ROWS rows of S to a workgroup
-template <int D, int N, int C, int ROWS, bool RO, typename Tag>
+// the chain of N virtual tokens a block under one of its tags, ROWS rows of S to a workgroup; `of` blocks make one of the
+// kernel's name
+template <int D, int N, int C, int ROWS, bool RO, typename Tag, int of = 1>
 static hipError_t launch_chain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
                                const float *S0, void *O, float *SL, int heads, int NC, int tail, int vmul, int s0mul, int dv,
                                hipStream_t stream)
 {
     using Pl = ChainPlan<D, N, C, ROWS, RO>;
     void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *, float *,
-                 int, int, int, int, int, int, Tag) = scan_kernel<D, N, C, 16, RO, false>;
+                 int, int, int, int, int, int, Tag) = scan_kernel<D, N * of, C * of, 16, RO, false>;
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
     if (e != hipSuccess) return e;
@@ -829,12 +848,23 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
 
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt,
                              const void *Pt, const float *S0, void *O, float *SL, int heads, int L, int d,
-                             int r, int chunk, hipStream_t stream, bool folded, int vmul, int s0mul, int dv)
+                             int r, int chunk, hipStream_t stream, bool folded, int vmul, int s0mul, int dv, int unit)
 {
-    const int NC = L / chunk, tail = L % chunk;   // the tail tokens of every head are skipped
+    if (unit <= 0) unit = chunk;
+    const int NC = L / unit * (unit / chunk), tail = L % unit;   // the tail tokens of every head are skipped
     const int n = chunk * r;
     if (dv <= 0) dv = d;
     if (dv % 16 != 0 || (long long)heads * (dv / 16) > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (n == 64 && chunk == 16) {                  // halves of a block of 32 tokens
+        if (!folded) return hipErrorInvalidValue;
+#define X(DD)                                                                                                                 \
+        if (d == DD)                                                                                                          \
+            return O ? launch_chain<DD, 64, 16, 16, true, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream) \
+                     : launch_chain<DD, 64, 16, 16, false, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+        X(64) X(128)
+#undef X
+        return hipErrorInvalidValue;
+    }
     const bool wide = scan_dv_tile(heads, dv, n) == 32;
 #define X(DD, NN, CC)                                                                                      \
     if (d == DD && n == NN && chunk == CC) {                                                                \
@@ -862,6 +892,12 @@ hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, cons
                      : launch_chain<DD, NN, CC, 32, false, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream); \
     }
     PF_SCAN_INSTANCES(X)
+#undef X
+#define X(DD)                                                                                                                 \
+    if (d == DD && chunk == 16)                                                                                               \
+        return O ? launch_chain<DD, 64, 16, 32, true, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream) \
+                 : launch_chain<DD, 64, 16, 32, false, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream);
+    X(64) X(128)
 #undef X
     return hipErrorInvalidValue;
 }

@@ -61,3 +61,18 @@ def test_segments_cut_once_more(oracle, heads, d, r, L, product):
     Oref, SLref = (oracle.delta_product_fwd if product else oracle.delta_fwd)(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
     SLn, SLref = state.cpu().numpy().reshape(heads, d, d), np.asarray(SLref).reshape(heads, d, d)
     assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (64, 48)])
+@pytest.mark.parametrize("blocks,tail", [(1, 0), (2, 31), (3, 16), (5, 1), (8, 0)])
+def test_rank_4_in_halves(oracle, blocks, tail, dk, dv):
+    """Blocks of 32 tokens and 128 virtual tokens run as two of 64: one token tile a half, one reader, a tail of up to 31
+    tokens behind the whole blocks (which a half of it would fit), d_v apart from d_k."""
+    names = _check(oracle, 3, blocks * 32 + tail, dk, dv, 4, 10 * blocks + tail)
+    assert names[0] == f"pf::flow_kernel<{dk}, 128, 32, false>" and f"pf::scan_kernel<{dk}, 128, 32, 16, true, false>" in names
+
+
+@pytest.mark.parametrize("heads,d,L", [(2, 128, 2048), (8, 64, 16384)])
+def test_rank_4_segments(oracle, heads, d, L):
+    """Segments of halves, with one tile and (cut once more) with two tiles to a workgroup."""
+    assert "pf::segment_compose_kernel" in _check(oracle, heads, L, d, d, 4, 3)
