@@ -10,16 +10,18 @@
 // either, and T is rounded to bf16 once, when it is stored: with G, X and T_jj rounded to bf16 as operands the flow took
 // 1 us less on every shape below and the forward was 1 % further from 64 bits (O 4.54e-3 against 4.49e-3 before this
 // body and 4.42e-3 now, 20 heads x 8192 tokens, d = 128, r = 2).  Two accumulator tiles of X, one upon the other, are a tile of T as the scan reads it (pf_layout.h).
-// T_jj = (Id + G_jj)^{-1}: forward substitution in fp32 on the vector ALU, four tiles at a time, a column per lane.
+// T_jj = (Id + G_jj)^{-1}: forward substitution in fp32 on the vector ALU, four tiles at a time, a column per lane;
+// the rows of G_jj come in 16 reads and go round by DPP (as operands that all lanes read out of LDS, 40 reads of 16 bytes,
+// 32 x 2944 below took 18.0 us: the chain of one block is all it has).
 //
 // What bounds it: HBM (64 heads x 4096 tokens, d = 128, r = 2: 278 MB in 45 us, 6.2 TB/s; 32 heads x 65536: 2.2 GB in
 // 433 us).  The rows of the next block are asked for as soon as the block before has had its two sets of products, and
 // eight wavefronts a compute unit at different steps keep the loads going (at d = 64 a third workgroup a compute unit
 // would spill).  The workgroup of eight wavefronts per block that serves the larger blocks (pf_flow.hip) had work for
 // two to four of them here and six barriers; flow alone, us, that body / this one:
-//   64 heads x 4096, d = 128, r = 2    70.2 / 45.1        32 x 2048, d = 64, r = 1    11.2 / 7.9
-//   32 x 65536, d = 128, r = 2          533 / 433         24 x 4096, d = 64, r = 2    26.1 / 13.9
-//   4 x 32768, d = 128, r = 2          36.6 / 24.1        32 x 2944, d = 128, r = 1   18.1 / 18.0 (one block a wavefront)
+//   64 heads x 4096, d = 128, r = 2    70.2 / 44.7        32 x 2048, d = 64, r = 1    11.2 / 7.9
+//   32 x 65536, d = 128, r = 2          533 / 432         24 x 4096, d = 64, r = 2    26.1 / 13.6
+//   4 x 32768, d = 128, r = 2          36.6 / 23.8        32 x 2944, d = 128, r = 1   18.1 / 14.9 (one block a wavefront)
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"
@@ -35,6 +37,55 @@ struct FlowWavePlan {
     static constexpr int floats = 4 * 16 * NP + 64;                    // of a wavefront: diagonal tiles, row factors
     static constexpr size_t lds = (size_t)waves * floats * 4;
 };
+
+// t[i] -= (n[i] of lane J of a row of 16 lanes) * y for M <= 8 rows: DPP row_newbcast inside the product (written as a move, the
+// compiler keeps it one and hoists all of them into registers).  The compiler does not look for hazards inside: the s_nop gives
+// the two wait states between a register written just before, for instance by a copy, and its use by DPP.
+template <int J, int M>
+__device__ __forceinline__ void minus_rows(const float *n, float *t, float y)
+{
+#define PF_L(k) "\n\tv_fmac_f32_dpp %[t" #k "], -%[n" #k "], %[y] row_newbcast:%c[j] row_mask:0xf bank_mask:0xf"
+#define PF_T(k) [t##k] "+&v"(t[k])
+#define PF_N(k) [n##k] "v"(n[k])
+#define PF_Y [y] "v"(y), [j] "n"(J)
+    static_assert(M >= 1 && M <= 8);
+    if constexpr (M == 8) {
+        asm("s_nop 1" PF_L(0) PF_L(1) PF_L(2) PF_L(3) PF_L(4) PF_L(5) PF_L(6) PF_L(7)
+            : PF_T(0), PF_T(1), PF_T(2), PF_T(3), PF_T(4), PF_T(5), PF_T(6), PF_T(7)
+            : PF_N(0), PF_N(1), PF_N(2), PF_N(3), PF_N(4), PF_N(5), PF_N(6), PF_N(7), PF_Y);
+    } else if constexpr (M >= 4) {
+        asm("s_nop 1" PF_L(0) PF_L(1) PF_L(2) PF_L(3)
+            : PF_T(0), PF_T(1), PF_T(2), PF_T(3) : PF_N(0), PF_N(1), PF_N(2), PF_N(3), PF_Y);
+        if constexpr (M > 4) minus_rows<J, M - 4>(n + 4, t + 4, y);
+    } else if constexpr (M == 3) {
+        asm("s_nop 1" PF_L(0) PF_L(1) PF_L(2) : PF_T(0), PF_T(1), PF_T(2) : PF_N(0), PF_N(1), PF_N(2), PF_Y);
+    } else if constexpr (M == 2) {
+        asm("s_nop 1" PF_L(0) PF_L(1) : PF_T(0), PF_T(1) : PF_N(0), PF_N(1), PF_Y);
+    } else {
+        asm("s_nop 1" PF_L(0) : PF_T(0) : PF_N(0), PF_Y);
+    }
+#undef PF_L
+#undef PF_T
+#undef PF_N
+#undef PF_Y
+}
+
+// T = (Id + N)^{-1}, N strictly lower 16 x 16, by forward substitution: lane c of a row of 16 lanes holds element c of row i of N
+// in n[i] and column c of T in t.  By columns, so that products do not wait for each other.
+template <int J = 0>
+__device__ __forceinline__ void substitute_rows(const float (&n)[16], float (&t)[16], int c)
+{
+    if constexpr (J == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i] = i == c ? 1.f : 0.f;
+    }
+    if constexpr (J < 15) {
+        constexpr int M = 15 - J, B = M < 8 ? M : 8;
+        if constexpr (M > 8) minus_rows<J, M - 8>(n + J + 1, t + J + 1, t[J]);
+        minus_rows<J, B>(n + 16 - B, t + 16 - B, t[J]);
+        substitute_rows<J + 1>(n, t, c);
+    }
+}
 
 template <int D, int C, bool GEN>
 __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
@@ -134,29 +185,13 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
 #pragma unroll
             for (int j = 0; j < i; ++j) nG[tri(i, j)] = G[tri(i, j)] * -b[i];
         }
-        // ---- T_jj: lane group g inverts tile g, a column per lane; by columns, so that products do not wait for each other
+        // ---- T_jj: lane group g inverts tile g, a column per lane
         {
-            const float *n = Ns + 16 * g * NP;
-            float t[16];
-            auto rows = [&](auto I0c, auto I1c) {
-                constexpr int I0 = decltype(I0c)::value, I1 = decltype(I1c)::value;
-                f32x4 x[I1 - I0][4];
-                LDS_FENCE();
+            float n[16], t[16];
+            LDS_FENCE();
 #pragma unroll
-                for (int i = I0; i < I1; ++i)
-#pragma unroll
-                    for (int j = 0; j < i; j += 4) x[i - I0][j / 4] = *reinterpret_cast<const f32x4 *>(&n[i * NP + j]);
-                LDS_FENCE();
-#pragma unroll
-                for (int i = I0; i < I1; ++i) t[i] = i == r16 ? 1.f : 0.f;
-#pragma unroll
-                for (int j = 0; j < I1 - 1; ++j)
-#pragma unroll
-                    for (int i = j + 1 > I0 ? j + 1 : I0; i < I1; ++i) t[i] = fmaf(-x[i - I0][j / 4][j & 3], t[j], t[i]);
-            };
-            rows(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
-            rows(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
-            rows(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
+            for (int i = 1; i < 16; ++i) n[i] = Ns[(16 * g + i) * NP + r16];
+            substitute_rows(n, t, r16);
 #pragma unroll
             for (int i = 0; i < 16; ++i) Ns[(16 * g + i) * NP + r16] = t[i];
             LDS_FENCE();
