@@ -99,7 +99,8 @@ def _ptr(x):
 def _stream_handle(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        # the handle of torch.cuda.current_stream(), without the Stream object around it (2.9 us of a call's 13.5)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -250,23 +251,25 @@ def delta_fwd(Q, K, V, beta, S0=None, *, chunk: int, workspace=None, stream=None
             raise ValueError("inputs must be contiguous")
     B, H, L, r, d_k = K.shape
     d_v = V.shape[-1]
-    if Q.dtype == torch.float32:
+    dtype, device, f32 = Q.dtype, Q.device, torch.float32
+    if dtype == f32:
         dt = PF_F32
-    elif Q.dtype == torch.bfloat16:
+    elif dtype == torch.bfloat16:
         dt = PF_BF16
     else:
         raise ValueError("dtype must be float32 or bfloat16")
-    if not (K.dtype == V.dtype == beta.dtype == Q.dtype):
+    if not (K.dtype == V.dtype == beta.dtype == dtype):
         raise ValueError("Q, K, V, beta must share one dtype")
     if Q.shape != (B, H, L, d_k) or V.shape != (B, H, L, r, d_v) or beta.shape != (B, H, L, r):
         raise ValueError("inconsistent shapes")
-    if S0 is not None and (S0.dtype != torch.float32 or S0.shape != (B, H, d_v, d_k) or not S0.is_contiguous()):
+    if S0 is not None and (S0.dtype != f32 or S0.shape != (B, H, d_v, d_k) or not S0.is_contiguous()):
         raise ValueError("S0 must be contiguous float32 [B,H,dv,dk]")
-    O = torch.empty((B, H, L, d_v), dtype=Q.dtype, device=Q.device)
-    S_L = torch.empty((B, H, d_v, d_k), dtype=torch.float32, device=Q.device)
-    need = pf_delta_fwd_workspace_bytes(B, H, L, d_k, d_v, r, chunk, dt)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    O = torch.empty((B, H, L, d_v), dtype=dtype, device=device)
+    S_L = torch.empty((B, H, d_v, d_k), dtype=f32, device=device)
+    if workspace is None:
+        need = pf_delta_fwd_workspace_bytes(B, H, L, d_k, d_v, r, chunk, dt)
+        if need > 0:
+            workspace = torch.empty(need, dtype=torch.uint8, device=device)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     call = pf_delta_product_fwd if product else pf_delta_fwd
     st = call(Q, K, V, beta, S0, O, S_L, B, H, L, d_k, d_v, r, chunk, dt, workspace, wbytes, stream)
