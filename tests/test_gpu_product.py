@@ -112,6 +112,31 @@ def test_beta_exponential_matches_closed_form(pf, dtype, dk):
     assert pf.pf_beta_exponential(Kd, bd, bd, B, H, L, dk, r, 9) == pf.PF_ERR_UNSUPPORTED
 
 
+# a wavefront takes 64 rows of 128 bytes or 32 of 256: one row, remainders, whole wavefronts and workgroups, one row more
+@pytest.mark.parametrize("dtype,dk", [("f32", 32), ("f32", 64), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("rows", [1, 7, 31, 33, 63, 65, 128, 256, 257])
+def test_beta_exponential_rows_of_a_wavefront(pf, dtype, dk, rows):
+    import torch
+    from oracle import chunk_flow_ref as cf
+    print(f"[case] beta_exponential dtype={dtype} d_k={dk} rows={rows}", flush=True)
+    rng = np.random.default_rng(11 * rows + dk)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    K = torch.from_numpy((rng.standard_normal((1, 1, rows, 1, dk)) * rng.uniform(0.0, 1.5, (1, 1, rows, 1, 1))).astype(np.float32))
+    K[0, 0, rows // 2] = 0.0
+    beta = torch.from_numpy(rng.uniform(0.0, 3.0, (1, 1, rows, 1)).astype(np.float32))
+    Kd, bd = K.to("cuda:0").to(tdt).contiguous(), beta.to("cuda:0").to(tdt).contiguous()
+    out = torch.full((rows + 64,), float("nan"), device="cuda:0", dtype=tdt)
+    assert pf.pf_beta_exponential(Kd, bd, out, 1, 1, rows, dk, 1, pf.PF_F32 if dtype == "f32" else pf.PF_BF16) == pf.PF_OK
+    torch.cuda.synchronize()
+    ref = cf.exp_rank1_beta(Kd.float().cpu().numpy(), bd.float().cpu().numpy()).reshape(rows)
+    got = out.float().cpu().numpy().astype(np.float64)
+    # fp32: |k|^2 is a sum of d_k products in a tree (16 roundings at most), beta_eff changes by no more than it does;
+    # bf16: one rounding of the result
+    bar = 2e-6 if dtype == "f32" else 2.0 ** -8
+    assert np.all(np.abs(got[:rows] - ref) <= bar * np.abs(ref) + 1e-30)
+    assert np.all(np.isnan(got[rows:]))                          # nothing behind the last row
+
+
 def test_exponential_product_flow_end_to_end(pf):
     """pf_beta_exponential followed by pf_delta_product_fwd is the product of exponentials of
     Section 3.3 with its inputs: checked against scipy's expm of every rank-1 increment's augmented
