@@ -29,7 +29,8 @@ constexpr size_t kAlign = 256;
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Offsets (bytes) of the two per-chunk arrays inside the MFMA path's workspace.
+// Offsets (bytes) of the arrays inside the MFMA path's workspace.  (oZ, oI: nothing lies there any more; a program that asked
+// for the size once still finds it enough, and the same.)
 struct WorkspacePlan {
     size_t oT, oP, oS, oZ, oI, oH, oG, oSin, total;
     int segments;
@@ -37,10 +38,10 @@ struct WorkspacePlan {
 
 // Segments per head for the segment-parallel scan: 1 (plain hand-over chain per head) unless
 // the chains of the plain scan (heads x d_v tiles) would leave three quarters of the CUs idle
-// and there are enough blocks to cut.  Three passes of the scan kernel then run with
-// `segments` times as many chains.  A block costs 0.55 us in a pass without the readout, 0.67 with it and 0.75 in the
-// plain scan, so G segments pay from 1.77 / G < 0.75 on: two cannot, three would, but only powers of two are tried, on
-// whole blocks that divide evenly.
+// and there are enough blocks to cut.  Two passes of the scan kernel (launch_segment_maps, then the readout) then run with
+// `segments` times as many chains.  A block costs 0.6 us in the first, 0.67 with the readout and 0.75 in the plain scan, so
+// G segments pay from 1.27 / G + composition < 0.75 on: two would by little, and only with three quarters of the compute
+// units idle is the gain worth what a call's workspace grows by; powers of two, on whole blocks that divide evenly.
 int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 {
     if (L % chunk != 0 || d != dv) return 1;     // (the composition kernel takes square states)
@@ -56,9 +57,10 @@ int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 // Long segments of blocks of 64 virtual tokens are cut once more, and a workgroup takes two tiles of 16 rows: the two
 // read the same K, Q, T, P once, and a block of a pass takes hardly longer than with one tile.  Whole forward, d = 128,
 // r = 2, us, as scan_segments / cut once more:
-//   4 heads x 32768 tokens  238 / 173     8 x 65536  1078 / 698     1 x 131072  261 / 226     8 x 8192  127 / 97
-// and d = 64, r = 2, 16 x 65536 886 / 641.  The composition over the segments of a head is a chain of its own (1.4 us a
-// segment at d = 128): with 16 blocks a segment 2 heads x 65536, d = 64, r = 1 83 / 92, with 2 1 x 2048 47.7 / 50.0.
+//   4 heads x 32768 tokens  192 / 163     8 x 65536  812 / 573     1 x 131072  211 / 205     8 x 8192  102 / 88
+// and d = 64, r = 2, 16 x 65536 715 / 549.  The composition over the segments of a head is a chain of its own (1.4 us a
+// segment at d = 128): with 16 blocks a segment 2 heads x 65536, d = 64, r = 1 72 / 87, 2 x 16384 77 / 88, and 4 x 16384,
+// r = 1 78.3 / 75.6, 8 x 4096 63.8 / 61.1.
 // What the segments write (P, H) goes to where O will be, which holds it from 4 d tokens a segment on; the states they
 // start from, to the place that scan_segments' number of them has for all three.
 constexpr int kLongSegment = 32;                 // blocks
@@ -270,7 +272,7 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
             const std::string scan = "pf::scan_kernel<" + dims + ", " +
                                      std::to_string(G > 1 && n == 64 ? 16 : pf::scan_dv_tile(heads * G, d_v, n));
             if (G > 1)
-                out = flow + ";pf::segment_constants_kernel;" + scan + ", false, false>;" + scan + ", false, false>;" +
+                out = flow + ";" + scan + ", false, false>;" + scan + ", false, false>;" +
                       "pf::segment_compose_kernel;" + scan + ", true, false>";
             else
                 out = flow + ";" + scan + ", true, false" +
@@ -323,38 +325,30 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
         const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
         const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
         const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
-        const bool fold = wp.segments > 1 ? sub * r == 64 : pf::scan_chain(heads, d_v, sub * r);
+        const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r);
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            // Segment-parallel scan (no tail here): every segment of every head is a chain of
-            // its own.  What a segment does to a zero state, then its propagator (identity in,
-            // zero values), then the composition over the segments of a head, then the real
-            // pass of every segment from its true incoming state.
+            // Segment-parallel scan (no tail here, and blocks of 64 virtual tokens: pick_block): every segment of every
+            // head is a chain of its own.  What a segment does to a zero state and its propagator, then the composition
+            // over the segments of a head, then the real pass of every segment from its true incoming state.
             const bool twice = cut_once_more(wp.segments, L, d_k, r, sub);
             const int G = twice ? 2 * wp.segments : wp.segments, vh = heads * G, Ls = L / G;
             float *Hseg = twice ? static_cast<float *>(O) : reinterpret_cast<float *>(ws + wp.oH);
             float *Pseg = twice ? Hseg + (size_t)vh * d_k * d_k : reinterpret_cast<float *>(ws + wp.oG);
-            float *Sin = reinterpret_cast<float *>(ws + (twice ? wp.oH : wp.oSin)), *ident = reinterpret_cast<float *>(ws + wp.oI);
-            e = pf::launch_segment_constants(ws + wp.oZ, ident, block * r, d_k, s);
-            if (e != hipSuccess) return PF_ERR_LAUNCH;
-            auto pass = [&](const void *values, const float *from, void *out, float *to, int vmul, int s0mul) {
-                return twice ? pf::launch_segment_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, sub, s, vmul, s0mul)
-                            : pf::launch_chunk_scan(Q, K, values, beta, Tt, Pt, from, out, to, vh, Ls, d_k, r, sub, s, fold, vmul, s0mul);
-            };
-            e = pass(V, nullptr, nullptr, Hseg, 1, 1);
-            if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pass(ws + wp.oZ, ident, nullptr, Pseg, 0, 0);
+            float *Sin = reinterpret_cast<float *>(ws + (twice ? wp.oH : wp.oSin));
+            e = pf::launch_segment_maps(K, V, Tt, Hseg, Pseg, vh, Ls, d_k, r, sub, s, twice);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             e = pf::launch_segment_compose(S0, Pseg, Hseg, Sin, S_L, heads, G, d_k, s);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pass(V, Sin, O, nullptr, 1, 1);
+            e = twice ? pf::launch_segment_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, sub, s)
+                      : pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, sub, s, true);
             return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
         } else {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
-            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, sub, s, fold, 1, 1, d_v, block);
+            e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, sub, s, fold, d_v, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
         }
         state = Smid;
@@ -560,7 +554,7 @@ pf_status pf_delta_chunk_scan(const void *Q, const void *K, const void *V, const
         !aligned16(Pt) || !aligned16(S0) || !aligned16(O) || !aligned16(S_L))
         return PF_ERR_ALIGN;
     hipError_t e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, S_L, B * H, L, d_k, r, chunk,
-                                         static_cast<hipStream_t>(stream), false, 1, 1, d_v);
+                                         static_cast<hipStream_t>(stream), false, d_v);
     return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
 }
 

@@ -46,9 +46,17 @@ __device__ __forceinline__ int k_swizzle(int row)
     return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
 }
 
-template <int D, int N, int C, int TV, bool RO>
+// PAIR (state only): two sets of TV rows of one segment, the rows of its state from zero with V and the rows of its
+// propagator, from the identity, without: they have a zero tile in LDS for V (so that an infinity in V stays out of the
+// propagator).  Both read the same K and T, which a workgroup loads once: with two tiles, a state wave per SIMD, a block
+// takes 1.0 us where the two passes took 0.7 us each (4 heads x 32768 tokens, d = 128, r = 2: 2 x 44.8 us -> 2 x 35.7 for
+// half of the blocks each); what bounds it is LDS, four waves reading 42 KB a block each.  Whole forward, us, passes one
+// after the other / PAIR:
+//   d = 128, r = 2   4 heads x 32768  180 / 163    8 x 65536  685 / 570    1 x 131072  224 / 205    8 x 8192  97 / 87
+//   d = 64           16 x 65536, r = 2  645 / 542    2 x 65536, r = 1  84 / 72    8 x 2048, r = 1  33.0 / 28.7
+template <int D, int N, int C, int TV, bool RO, bool PAIR = false>
 struct ChainPlan {
-    static constexpr int states = TV / 16, stagers = 2, readers = !RO ? 0 : (C >= 32 ? 2 : 1);   // wavefronts of each role
+    static constexpr int states = (PAIR ? 2 : 1) * (TV / 16), stagers = 2, readers = !RO ? 0 : (C >= 32 ? 2 : 1);   // wavefronts of each role
     static constexpr int threads = 64 * (states + stagers + readers);
     static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
     // one ring slot: K, V tile, T tiles, beta (32 bits each)
@@ -59,11 +67,14 @@ struct ChainPlan {
     static constexpr size_t szX = RO ? (size_t)states * (D / 32) * 1024 : 0;   // S of a block, operand tiles
     static constexpr size_t szU = RO ? (size_t)states * (N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
     // two slots are being read (this block, and the rows and T of the next), the others are on their way from memory
-    static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU)) / slot);
+    static constexpr size_t szZ = PAIR ? (size_t)N * TV * 2 : 0;
+    static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU) - szZ) / slot);
     static constexpr int kRing = fit < 6 ? fit : 6;
     static constexpr size_t oX = kRing * slot;
     static constexpr size_t oU = oX + 2 * szX;
-    static constexpr size_t total = oU + 2 * szU;
+    static constexpr size_t oZ = oU + 2 * szU;
+    static constexpr size_t total = oZ + szZ;
+    static_assert(!(PAIR && RO), "a propagator has no readout");
     static constexpr bool kServes = N == 64 && (TV == 16 || TV == 32) && kRing >= 4;
 };
 
@@ -82,12 +93,15 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 
 // FOLD: Tt holds -T diag(beta) (launch_chunk_flow), so that the chain takes K S^T - V as it comes out of the products: no
 // beta, no factor, and V goes in as a product with -Id.
-template <int D, int N, int C, int TV, bool RO, bool FOLD>
+// PAIR: `stride` blocks a chain, of which this call takes NC from `first` on.  The rows of the state are in and out at SL, those
+// of the propagator at SP; from the first block on they start as zeros and as the identity.
+template <int D, int N, int C, int TV, bool RO, bool FOLD, bool PAIR = false>
 __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const bf16 *V, const bf16 *beta,
                                            const bf16 *Tt, const bf16 *Pt, const float *S0, bf16 *O, float *SL,
-                                           int nchains, int NC, int tail, int vmul, int s0mul, int dv, char *smem)
+                                           int nchains, int NC, int tail, int dv, char *smem,
+                                           float *SP = nullptr, int stride = 0, int first = 0)
 {
-    using Pl = ChainPlan<D, N, C, TV, RO>;
+    using Pl = ChainPlan<D, N, C, TV, RO, PAIR>;
     constexpr int NT = Pl::NT, kRing = Pl::kRing;
     constexpr int R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, MD = D / 16, CT = C / 16;
     constexpr int NSS = Pl::states, NSt = Pl::stagers;
@@ -96,11 +110,11 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
     const int tile = blockIdx.x / nchains;             // workgroups of one head: one XCD (see the launcher)
     const size_t chain = blockIdx.x % nchains;
-    const size_t c0 = chain * (size_t)NC;
-    // `tail` tokens of every head belong to another kernel; vmul, s0mul = 0: one block at V, one matrix at S0 for all
+    const size_t c0 = PAIR ? chain * (size_t)stride + (size_t)first : chain * (size_t)NC;
+    // `tail` tokens of every head belong to another kernel
     Q += chain * (size_t)tail * D;
     K += chain * (size_t)tail * R * D;
-    V += (size_t)vmul * chain * (size_t)tail * R * dv + tile * TV;
+    V += chain * (size_t)tail * R * dv + tile * TV;
     beta += chain * (size_t)tail * R;
     bf16 *Xs = reinterpret_cast<bf16 *>(smem + Pl::oX), *Us = reinterpret_cast<bf16 *>(smem + Pl::oU);
     constexpr int XB = (int)(Pl::szX / 2), UB = (int)(Pl::szU / 2);   // elements of one buffer
@@ -109,12 +123,22 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         // -------------------------------------------------------------- state waves, 16 rows each
         __builtin_amdgcn_s_setprio(3);                 // the helpers of this SIMD fill what the chain leaves
         auto dk0 = [&](int mt) { return 32 * (mt >> 1) + 8 * g + 4 * (mt & 1); };
-        const size_t srow = (size_t)(tile * TV + 16 * wave + r16) * D;
+        const bool prop = PAIR && wave >= NSS / 2;         // rows of the propagator
+        const int rowt = PAIR ? wave % (NSS / 2) : wave;   // 16 rows of the tile
+        const int row = tile * TV + 16 * rowt + r16;
+        const size_t srow = (size_t)row * D;
+        float *const out = prop ? SP : SL;
         f32x4 sacc[MD];
 #pragma unroll
         for (int mt = 0; mt < MD; ++mt) {
             sacc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (S0) sacc[mt] = *reinterpret_cast<const f32x4 *>(S0 + (size_t)s0mul * chain * (size_t)dv * D + srow + dk0(mt));
+            if constexpr (PAIR) {
+                if (first) sacc[mt] = *reinterpret_cast<const f32x4 *>(out + chain * (size_t)dv * D + srow + dk0(mt));
+                else if (prop) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sacc[mt][e] = dk0(mt) + e == row ? 1.0f : 0.0f;
+                }
+            } else if (S0) sacc[mt] = *reinterpret_cast<const f32x4 *>(S0 + chain * (size_t)dv * D + srow + dk0(mt));
         }
         // byte offsets in a slot: row operand of K by k-step, transposing read of K by pair of d_k tiles
         int kr0[NKS], kt0[NKS];
@@ -123,7 +147,14 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             kr0[ks] = r16 * D * 2 + ((4 * ks + g) ^ k_swizzle<D>(r16)) * 16;
             kt0[ks] = (4 * g + (r16 >> 2)) * D * 2 + ((4 * ks + (r16 & 3)) ^ k_swizzle<D>(4 * g + (r16 >> 2))) * 16;
         }
-        const int vt0 = (int)Pl::oV + ((4 * g + (r16 >> 2)) * TV + 16 * wave + 4 * (r16 & 3)) * 2;
+        const int vt0 = (int)(prop ? Pl::oZ : Pl::oV) + ((4 * g + (r16 >> 2)) * TV + 16 * rowt + 4 * (r16 & 3)) * 2;
+        if constexpr (PAIR) {
+            if (prop) {
+#pragma unroll
+                for (int i = 0; i < N / 16; ++i)           // the columns of V that this wave reads
+                    *reinterpret_cast<u32x2 *>(smem + vt0 + 16 * i * TV * 2) = u32x2{0, 0};
+            }
+        }
         const int tt0 = (int)Pl::oT + lane * 16, bt0 = (int)Pl::oB + 16 * g;
         auto at8 = [&](int off) { return *reinterpret_cast<const bf16x8 *>(smem + off); };
 
@@ -150,7 +181,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         };
         constexpr int kVB = FOLD ? MT : 2 * MT, kAhead = kVB + MT * NKS + NT, kPer = (kAhead + NM - 1) / NM;
         auto read_ahead = [&](int base, int i) {
-            if (i < MT) vt[i] = lds_read_tr4(reinterpret_cast<const bf16 *>(smem + base + vt0 + 16 * i * TV * 2));
+            if (i < MT) vt[i] = lds_read_tr4(reinterpret_cast<const bf16 *>(smem + (prop ? 0 : base) + vt0 + 16 * i * TV * 2));
             else if (i < kVB) bt[FOLD ? 0 : i - MT] = *reinterpret_cast<const u32x4 *>(smem + base + bt0 + 64 * (i - MT));
             else if (i < kVB + MT * NKS) {
                 const int mt = (i - kVB) / NKS, ks = (i - kVB) % NKS;
@@ -227,10 +258,10 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
             __syncthreads();
         }
 #undef kInOrder
-        if (SL) {
+        if (out) {
 #pragma unroll
             for (int mt = 0; mt < MD; ++mt)
-                *reinterpret_cast<f32x4 *>(SL + chain * (size_t)dv * D + srow + dk0(mt)) = sacc[mt];
+                *reinterpret_cast<f32x4 *>(out + chain * (size_t)dv * D + srow + dk0(mt)) = sacc[mt];
         }
         return;
     }
@@ -282,7 +313,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         auto fetch = [&](int ch, int slot) {                         // (beyond the last block: the last once more)
             const size_t cid = clamp(ch);
             char *d = smem + slot * (int)Pl::slot;
-            const bf16 *Kg = K + cid * (size_t)N * D, *Vg = V + (size_t)vmul * cid * (size_t)N * dv, *Tg = Tt + cid * (size_t)N * N;
+            const bf16 *Kg = K + cid * (size_t)N * D, *Vg = V + cid * (size_t)N * dv, *Tg = Tt + cid * (size_t)N * N;
 #pragma unroll
             for (int q = 0; q < KQ; ++q) load_lds16(Kg + ksrc[q], d + (H + NSt * q) * 1024);
 #pragma unroll

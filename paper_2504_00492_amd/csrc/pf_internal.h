@@ -54,14 +54,18 @@ hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, voi
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta,
                              const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
-                             bool folded = false, int vmul = 1, int s0mul = 1, int dv = 0, int unit = 0);
+                             bool folded = false, int dv = 0, int unit = 0);
 // unit (0: chunk): the whole blocks of a head are counted in this many tokens.  chunk = 16 with r = 4 and unit = 32 runs
 // the two halves of a block of 128 virtual tokens as blocks of 64 (fold only: the chain has no other form of them).
 // The chain with 32 rows of S to a workgroup (blocks of 64 virtual tokens, -T diag(beta) handed over, d = d_k = d_v, whole
-// blocks): the passes of the segment-parallel scan.
+// blocks): the last pass of the segment-parallel scan.
 hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
                                const float *S0, void *O, float *SL, int heads, int L, int d, int r, int chunk,
-                               hipStream_t stream, int vmul = 1, int s0mul = 1);
+                               hipStream_t stream);
+// For every segment (heads of them, L tokens each): H, its state from zero, and P, its propagator, in two launches of the
+// chain, the first blocks and the rest; two_tiles: 32 rows of each to a workgroup, else 16.
+hipError_t launch_segment_maps(const void *K, const void *V, const void *Tt, float *H, float *P, int heads, int L, int d, int r,
+                               int chunk, hipStream_t stream, bool two_tiles);
 // The same two kernels for the general drivers (A, Atil, B) of Section 3.1 (rows of A, B: d wide,
 // of Atil: dv wide); instances with at most 128 virtual tokens per block.
 bool mfma_general_instance_exists(int d, int n, int chunk);
@@ -70,7 +74,7 @@ hipError_t launch_chunk_flow_general(const void *Q, const void *A, const void *B
 hipError_t launch_chunk_scan_general(const void *Q, const void *A, const void *Atil, const void *Bm, const void *Tt,
                                      const void *Pt, const float *S0, void *O, float *SL, int heads, int L, int d,
                                      int dv, int r, int chunk, hipStream_t stream);
-// (O may be NULL: the state is advanced and S_L written, nothing is read out.  d = d_k; dv = d_v,
+// (d = d_k; dv = d_v,
 // a multiple of 16, 0 meaning d_v = d_k: V, O are dv wide and S0, S_L are dv x d.)
 // d_v rows of S one scan workgroup owns for these dimensions (the scan runs heads * dv / tile chains)
 int scan_dv_tile(int heads, int dv, int n);
@@ -86,9 +90,7 @@ hipError_t launch_fused(const void *Q, const void *K, const void *V, const void 
                         float *SL, void *Tdump, void *Pdump, int heads, int L, int d, int r, int chunk,
                         bool product, hipStream_t stream);
 
-// ---- segment-parallel scan (pf_segments.hip): S0 / V constants and the composition of segments
-// writes an n x d block of bf16 zeros at zeroV and the d x d fp32 identity at ident
-hipError_t launch_segment_constants(void *zeroV, float *ident, int n, int d, hipStream_t stream);
+// ---- segment-parallel scan (pf_segments.hip): the composition of segments
 // per head: Sin[0] = S0 (or 0); Sin[s+1] = Sin[s] Pseg[s] + Hseg[s]; S_L = Sin[G] (if not NULL)
 hipError_t launch_segment_compose(const float *S0, const float *Pseg, const float *Hseg, float *Sin,
                                   float *SL, int heads, int G, int d, hipStream_t stream);

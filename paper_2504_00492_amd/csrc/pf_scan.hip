@@ -85,13 +85,11 @@ struct ScanLds {
     static constexpr size_t total = oOb + (size_t)C * OP * 2;
 };
 
-// RO: the readout O is wanted (false: only the state is advanced, for the per-segment passes of
-// the segment-parallel scan).
-template <int D, int N, int C, int TV, bool RO, bool GEN>
+template <int D, int N, int C, int TV, bool GEN>
 __device__ __forceinline__ void split_scan(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv,
     char *smem)
 {
     // With GEN, K is the array of B rows, `beta` the array of A rows (n x d each) and V the array
@@ -125,8 +123,8 @@ __device__ __forceinline__ void split_scan(
     // 1.85 against 1.78 ms), with 128 virtual tokens per block too (0.410 against 0.398 ms), and the 32-row instances
     // there would spill.
     constexpr bool kLaunder = !(N <= 64 && (TV == 32 || D == 64));
-    constexpr bool kStateReadout = RO && N <= 128;
-    constexpr bool kIoReadout = RO && N > 128;
+    constexpr bool kStateReadout = N <= 128;
+    constexpr bool kIoReadout = N > 128;
     static_assert(D % 64 == 0 && TV % 16 == 0 && N % 32 == 0, "tile shapes");
     static_assert(MT % 4 == 0 && (CT % 4 == 0 || CT < 4), "tiles are dealt evenly, or at most one token tile per wave");
     static_assert(N <= NTHR, "beta of a chunk is fetched by one pass");
@@ -150,12 +148,9 @@ __device__ __forceinline__ void split_scan(
     const size_t c0 = chain * (size_t)NC;
     // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: in Q, K,
     // V, beta, O this head starts chain * tail tokens after its place in the compact numbering.
-    // vmul = 0 makes every block of every chain read the same n x d block at V (a block of
-    // zeros turns the kernel into the propagator of the transitions alone); s0mul = 0 makes
-    // every chain start from the same d x d matrix at S0 (the identity, for that propagator).
     Q += chain * (size_t)tail * D;
     K += chain * (size_t)tail * R * D;
-    V += (size_t)vmul * chain * (size_t)tail * R * dv;
+    V += chain * (size_t)tail * R * dv;
     beta += chain * (size_t)tail * R * (GEN ? D : 1);
     if (O) O += chain * (size_t)tail * dv;
 
@@ -175,7 +170,7 @@ __device__ __forceinline__ void split_scan(
             for (int nt = 0; nt < NNT; ++nt) {
                 const int mt = W * MPW + a;
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                if (S0) v = *reinterpret_cast<const f32x4 *>(S0 + (size_t)s0mul * chain * (size_t)dv * D +
+                if (S0) v = *reinterpret_cast<const f32x4 *>(S0 + chain * (size_t)dv * D +
                                                              (size_t)(dv0 + 16 * nt + r16) * D + 16 * mt + 4 * g);
                 sacc[a][nt] = v;
                 st4(&Sb[(16 * nt + r16) * SP + 16 * mt + 4 * g], cvt4(v));
@@ -478,7 +473,7 @@ __device__ __forceinline__ void split_scan(
         };
         auto fetch_vqb = [&](size_t cid, auto Sc) {
             constexpr int S = decltype(Sc)::value % kSets;
-            const bf16 *Vg = V + (size_t)vmul * cid * (size_t)N * dv + dv0;
+            const bf16 *Vg = V + cid * (size_t)N * dv + dv0;
 #pragma unroll
             for (int q = 0; q < VV; ++q) {
                 int v = tb + NTHR * q;
@@ -533,7 +528,6 @@ __device__ __forceinline__ void split_scan(
         };
         // the O tile of one chunk (chunk tokens x TV features), LDS -> its rows of O
         auto copy_out = [&](size_t cid) {
-            if constexpr (!RO) return;
             bf16 *Oc = O + cid * (size_t)C * dv;
 #pragma unroll
             for (int q = 0; q < OV; ++q) {
@@ -685,19 +679,19 @@ struct ScanBody {
 };
 
 typedef void ScanFn(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *,
-                    float *, int, int, int, int, int, int);
+                    float *, int, int, int, int);
 
 template <int D, int N, int C, int TV, bool RO, bool GEN>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: bounds of 256 and below bring in AGPR copies)
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (ScanBody<D, N, C, TV, RO, GEN>::kChain)
-        chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+        chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
-        split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // the split body of a shape that the chain serves as well
@@ -705,11 +699,11 @@ template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
 {
     static_assert(SPLIT && ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    split_scan<D, N, C, TV, RO, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+    split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // the chain with two tiles to a workgroup, a state wave each
@@ -718,11 +712,11 @@ template <int D, int N, int C, int TV, bool RO, bool GEN>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv, TwoTiles)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, TwoTiles)
 {
     static_assert(TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // blocks of 128 virtual tokens and 32 tokens (r = 4) as two blocks of 64 each, one tile or two to a workgroup
@@ -732,16 +726,36 @@ template <int TILES> struct Halves {};
     __global__ __launch_bounds__(kScanThreads) void scan_kernel(                                                             \
         const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ beta,   \
         const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt, const float *S0, bf16 *__restrict__ O, float *SL,          \
-        int nchains, int NC, int tail, int vmul, int s0mul, int dv, Halves<TILES>)                                           \
+        int nchains, int NC, int tail, int dv, Halves<TILES>)                                           \
     {                                                                                                                        \
         static_assert(N == 128 && TV == 16 && !GEN, "halves of 64 virtual tokens");                                          \
         extern __shared__ __attribute__((aligned(16))) char smem[];                                                          \
-        chain_scan<D, N / 2, C / 2, 16 * TILES, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul,  \
+        chain_scan<D, N / 2, C / 2, 16 * TILES, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail,  \
                                                           dv, smem);                                                         \
     }
 PF_HALVES(1)
 PF_HALVES(2)
 #undef PF_HALVES
+
+// the state of a segment from zero and its propagator side by side (ChainPlan, PAIR): TILES tiles of each to a workgroup, OF
+// blocks one of the kernel's name
+template <int TILES, int OF> struct Pair {};
+#define PF_PAIR(TILES, OF)                                                                                                   \
+    template <int D, int N, int C, int TV, bool RO, bool GEN>                                                                \
+    __global__ __launch_bounds__(kScanThreads) void scan_kernel(                                                             \
+        const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ Tt, float *H, float *P,             \
+        int nchains, int NC, int stride, int first, Pair<TILES, OF>)                                                         \
+    {                                                                                                                        \
+        static_assert(TV == 16 && !RO && !GEN && N == 64 * OF, "blocks of 64 virtual tokens");                               \
+        extern __shared__ __attribute__((aligned(16))) char smem[];                                                          \
+        chain_scan<D, 64, C / OF, 16 * TILES, false, true, true>(nullptr, K, V, nullptr, Tt, nullptr, nullptr, nullptr, H,   \
+                                                                nchains, NC, 0, D, smem, P, stride, first);                  \
+    }
+PF_PAIR(1, 1)
+PF_PAIR(2, 1)
+PF_PAIR(1, 2)
+PF_PAIR(2, 2)
+#undef PF_PAIR
 
 // the chain on T itself, as the split entry points hand it over
 struct PlainT {};
@@ -749,11 +763,11 @@ template <int D, int N, int C, int TV, bool RO, bool GEN>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int vmul, int s0mul, int dv, PlainT)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, PlainT)
 {
     static_assert(ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes take T as it is");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    chain_scan<D, N, C, TV, RO, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, vmul, s0mul, dv, smem);
+    chain_scan<D, N, C, TV, RO, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -766,7 +780,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
 template <int D, int N, int C, int TV, bool RO, bool GEN = false, bool SPLIT = false>
 static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                                       int heads, int NC, int tail, int vmul, int s0mul, int dv, hipStream_t stream)
+                                       int heads, int NC, int tail, int dv, hipStream_t stream)
 {
     using Body = ScanBody<D, N, C, TV, RO, GEN, SPLIT>;
     ScanFn *kern;
@@ -780,26 +794,26 @@ static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, co
     const unsigned grid = (unsigned)heads * (dv / TV);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
-                       (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, vmul, s0mul, dv);
+                       (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, dv);
     return hipGetLastError();
 }
 
 // the chain of N virtual tokens a block under one of its tags, ROWS rows of S to a workgroup; `of` blocks make one of the
 // kernel's name
-template <int D, int N, int C, int ROWS, bool RO, typename Tag, int of = 1>
+template <int D, int N, int C, int ROWS, typename Tag, int of = 1>
 static hipError_t launch_chain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
-                               const float *S0, void *O, float *SL, int heads, int NC, int tail, int vmul, int s0mul, int dv,
+                               const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv,
                                hipStream_t stream)
 {
-    using Pl = ChainPlan<D, N, C, ROWS, RO>;
+    using Pl = ChainPlan<D, N, C, ROWS, true>;
     void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *, float *,
-                 int, int, int, int, int, int, Tag) = scan_kernel<D, N * of, C * of, 16, RO, false>;
+                 int, int, int, int, Tag) = scan_kernel<D, N * of, C * of, 16, true, false>;
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / ROWS)), dim3(Pl::threads), Pl::total, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt, (const bf16 *)Pt, S0, (bf16 *)O, SL,
-                       heads, NC, tail, vmul, s0mul, dv, Tag{});
+                       heads, NC, tail, dv, Tag{});
     return hipGetLastError();
 }
 
@@ -828,39 +842,34 @@ bool scan_chain(int heads, int dv, int n)
 template <int D, int N, int C, int TV>
 static hipError_t launch_scan_instance(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                                       int heads, int NC, int tail, int vmul, int s0mul, int dv, bool folded, hipStream_t stream)
+                                       int heads, int NC, int tail, int dv, bool folded, hipStream_t stream)
 {
     if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
-        // (state-only passes run for scan_segments' choices, which never exceed the compute units)
-        if (O && !scan_chain(heads, dv, N))
+        if (!scan_chain(heads, dv, N))
             return folded ? hipErrorInvalidValue
-                          : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
-        if (!folded) {
-            if (!O) return hipErrorInvalidValue;
-            return launch_chain<D, N, C, TV, true, PlainT>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
-        }
+                          : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+        if (!folded)
+            return launch_chain<D, N, C, TV, PlainT>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
     } else if (folded) {
         return hipErrorInvalidValue;
     }
-    return O ? launch_scan_ro<D, N, C, TV, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream)
-             : launch_scan_ro<D, N, C, TV, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+    return launch_scan_ro<D, N, C, TV, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
 }
 
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt,
                              const void *Pt, const float *S0, void *O, float *SL, int heads, int L, int d,
-                             int r, int chunk, hipStream_t stream, bool folded, int vmul, int s0mul, int dv, int unit)
+                             int r, int chunk, hipStream_t stream, bool folded, int dv, int unit)
 {
     if (unit <= 0) unit = chunk;
     const int NC = L / unit * (unit / chunk), tail = L % unit;   // the tail tokens of every head are skipped
     const int n = chunk * r;
     if (dv <= 0) dv = d;
-    if (dv % 16 != 0 || (long long)heads * (dv / 16) > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (!O || dv % 16 != 0 || (long long)heads * (dv / 16) > 0x7fffffffLL) return hipErrorInvalidValue;   // (the state alone: launch_segment_maps)
     if (n == 64 && chunk == 16) {                  // halves of a block of 32 tokens
         if (!folded) return hipErrorInvalidValue;
 #define X(DD)                                                                                                                 \
         if (d == DD)                                                                                                          \
-            return O ? launch_chain<DD, 64, 16, 16, true, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream) \
-                     : launch_chain<DD, 64, 16, 16, false, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, stream);
+            return launch_chain<DD, 64, 16, 16, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         X(64) X(128)
 #undef X
         return hipErrorInvalidValue;
@@ -870,9 +879,9 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
     if (d == DD && n == NN && chunk == CC) {                                                                \
         if constexpr (NN < 256) {                                                                           \
             if (wide)                                                                                       \
-                return launch_scan_instance<DD, NN, CC, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream); \
+                return launch_scan_instance<DD, NN, CC, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, folded, stream); \
         }                                                                                                   \
-        return launch_scan_instance<DD, NN, CC, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, vmul, s0mul, dv, folded, stream);   \
+        return launch_scan_instance<DD, NN, CC, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, folded, stream);   \
     }
     PF_SCAN_INSTANCES(X)
 #undef X
@@ -881,23 +890,47 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
 
 hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
                                const float *S0, void *O, float *SL, int heads, int L, int d, int r, int chunk,
-                               hipStream_t stream, int vmul, int s0mul)
+                               hipStream_t stream)
 {
     const int NC = L / chunk, n = chunk * r;
-    if (L % chunk != 0 || n != 64 || d % 32 != 0 || (long long)heads * (d / 32) > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (!O || L % chunk != 0 || n != 64 || d % 32 != 0 || (long long)heads * (d / 32) > 0x7fffffffLL) return hipErrorInvalidValue;
 #define X(DD, NN, CC)                                                                                      \
     if constexpr (NN == 64) {                                                                               \
         if (d == DD && chunk == CC)                                                                         \
-            return O ? launch_chain<DD, NN, CC, 32, true, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream) \
-                     : launch_chain<DD, NN, CC, 32, false, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream); \
+            return launch_chain<DD, NN, CC, 32, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, d, stream); \
     }
     PF_SCAN_INSTANCES(X)
 #undef X
 #define X(DD)                                                                                                                 \
     if (d == DD && chunk == 16)                                                                                               \
-        return O ? launch_chain<DD, 64, 16, 32, true, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream) \
-                 : launch_chain<DD, 64, 16, 32, false, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, vmul, s0mul, d, stream);
+        return launch_chain<DD, 64, 16, 32, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, d, stream);
     X(64) X(128)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+template <int D, int C, int TILES, int OF>
+static hipError_t launch_pair(const void *K, const void *V, const void *Tt, float *H, float *P, int heads, int stride, int first,
+                              int NC, hipStream_t stream)
+{
+    using Pl = ChainPlan<D, 64, C, 16 * TILES, false, true>;
+    void (*kern)(const bf16 *, const bf16 *, const bf16 *, float *, float *, int, int, int, int, Pair<TILES, OF>) =
+        scan_kernel<D, 64 * OF, C * OF, 16, false, false>;
+    static std::atomic<uint64_t> armed{0};
+    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (D / (16 * TILES))), dim3(Pl::threads), Pl::total, stream, (const bf16 *)K,
+                       (const bf16 *)V, (const bf16 *)Tt, H, P, heads, NC, stride, first, Pair<TILES, OF>{});
+    return hipGetLastError();
+}
+
+hipError_t launch_segment_maps(const void *K, const void *V, const void *Tt, float *H, float *P, int heads, int L, int d, int r,
+                               int chunk, hipStream_t stream, bool two_tiles)
+{
+    const int NC = L / chunk, half = NC / 2;
+    if (L % chunk != 0 || chunk * r != 64 || half < 1 || (long long)heads * (d / 16) > 0x7fffffffLL) return hipErrorInvalidValue;
+#define X(DD, CC, OF)                                                                                          if (d == DD && chunk == CC) {                                                                                   auto run = [&](int first, int n) {                                                                              return two_tiles ? launch_pair<DD, CC, 2, OF>(K, V, Tt, H, P, heads, NC, first, n, stream)                                   : launch_pair<DD, CC, 1, OF>(K, V, Tt, H, P, heads, NC, first, n, stream);             };                                                                                                          const hipError_t e = run(0, half);                                                                          return e != hipSuccess ? e : run(half, NC - half);                                                      }
+    X(64, 64, 1) X(64, 32, 1) X(64, 16, 2) X(128, 64, 1) X(128, 32, 1) X(128, 16, 2)
 #undef X
     return hipErrorInvalidValue;
 }
@@ -915,8 +948,8 @@ hipError_t launch_chunk_scan_general(const void *Q, const void *A, const void *A
     if constexpr (NN <= 128) {                                                                              \
         if (d == DD && n == NN && chunk == CC) {                                                            \
             if (wide)                                                                                       \
-                return launch_scan_ro<DD, NN, CC, 32, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, 1, 1, dv, stream); \
-            return launch_scan_ro<DD, NN, CC, 16, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, 1, 1, dv, stream);     \
+                return launch_scan_ro<DD, NN, CC, 32, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream); \
+            return launch_scan_ro<DD, NN, CC, 16, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);     \
         }                                                                                                   \
     }
     PF_SCAN_INSTANCES(X)

@@ -7,31 +7,16 @@
 // with P_seg the ordered product of the segment's transitions (Proposition 2.1) and H_seg what
 // the segment writes into a zero state; affine maps compose, (P1, H1) then (P2, H2) =
 // (P1 P2, H1 P2 + H2).  Rows of the state evolve independently, so both come out of the
-// ordinary scan kernel: H_seg is its final state from S_0 = 0, and P_seg is its final state
-// when the rows of the identity are fed in as the initial state and the values are zero.  The
-// kernels here provide those two constants and the composition over the segments of a head;
-// a last pass of the scan kernel then runs every segment from its true incoming state.
+// chain of the scan kernel, side by side (ChainPlan, PAIR, in pf_chain.h): H_seg is its final state
+// from S_0 = 0, and P_seg is its final state when the rows of the identity are fed in and V is zero.
+// The kernel here is the composition over the segments of a head; a last pass of the scan kernel
+// then runs every segment from its true incoming state.
 #include "pf_internal.h"
 #include "pf_common.h"
 
 #include <type_traits>
 
 namespace pf {
-
-__global__ __launch_bounds__(256) void segment_constants_kernel(bf16 *zeroV, float *ident, int n, int d)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n * d) zeroV[i] = (bf16)0.0f;
-    if (i < d * d) ident[i] = (i / d == i % d) ? 1.0f : 0.0f;
-}
-
-hipError_t launch_segment_constants(void *zeroV, float *ident, int n, int d, hipStream_t stream)
-{
-    const int m = n * d > d * d ? n * d : d * d;
-    hipLaunchKernelGGL(segment_constants_kernel, dim3((m + 255) / 256), dim3(256), 0, stream,
-                       (bf16 *)zeroV, ident, n, d);
-    return hipGetLastError();
-}
 
 // One workgroup owns kComposeRows rows of the state of one head (rows are independent) and walks the segments:
 // S <- S P_s + H_s in fp32.  Thread (yg, x4) sums d / kComposeSplit values of y for 4 columns of every row; the

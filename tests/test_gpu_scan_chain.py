@@ -63,6 +63,26 @@ def test_segments_cut_once_more(oracle, heads, d, r, L, product):
     assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
 
 
+@pytest.mark.parametrize("d,r,L,chunk", [(128, 1, 2304, 64), (64, 2, 16384, 64), (128, 4, 2048, 64)])
+def test_segments_keep_columns_of_v_apart(d, r, L, chunk):
+    """The propagator of a segment runs beside the state of the same segment and must not see V: an infinity in one column of
+    V reaches that column of O and that row of S_L, and the others keep every bit."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    w = synth.Workload("inf", "bf16", 1, 2, L, d, d, r, chunk, seed=5, s0_std=0.2, reflect_frac=0.0)
+    print(f"[case] segments, infinity in V d={d} r={r} L={L}", flush=True)
+    dev = to_device(w, synth.make_inputs(w))
+    assert "pf::segment_compose_kernel" in pf.pf_delta_fwd_describe(1, 2, L, d, d, r, chunk, pf.PF_BF16)
+    O, S = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=chunk)
+    V = dev["V"].clone()
+    V[0, 0, L // 3, 0, 21] = float("inf")
+    Oi, Si = pf.delta_fwd(dev["Q"], dev["K"], V, dev["beta"], dev["S0"], chunk=chunk)
+    torch.cuda.synchronize()
+    keep = [j for j in range(d) if j != 21]
+    assert torch.equal(Oi[..., keep], O[..., keep]) and torch.equal(Si[:, :, keep], S[:, :, keep])
+    assert torch.equal(Oi[0, 1], O[0, 1]) and not torch.isfinite(Si[0, 0, 21]).all()
+
+
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 128), (64, 48)])
 @pytest.mark.parametrize("blocks,tail", [(1, 0), (2, 31), (3, 16), (5, 1), (8, 0)])
 def test_rank_4_in_halves(oracle, blocks, tail, dk, dv):
