@@ -18,27 +18,31 @@
 
 namespace pf {
 
-// One workgroup owns kComposeRows rows of the state of one head (rows are independent) and walks the segments:
+// One workgroup owns ROWS rows of the state of one head (rows are independent) and walks the segments:
 // S <- S P_s + H_s in fp32.  Thread (yg, x4) sums d / kComposeSplit values of y for 4 columns of every row; the
 // kComposeSplit partial sums meet in LDS.  A thread's piece of P_{s+1} is in registers before segment s is
 // summed: P does not depend on the state, so the chain over the segments never waits for memory.  What bounds it is
-// that chain (products and two barriers per segment).  One column per thread with P read as it was needed took
-// 273 us for 4 heads x 8 segments, d = 128.
-constexpr int kComposeRows = 4;
+// that chain (products and two barriers per segment; 64 KB of P a segment at d = 128).  One column per thread with P read
+// as it was needed took 273 us for 4 heads x 8 segments, d = 128.
+// Two rows where that gives no more workgroups than compute units, else four: half the products a step of the chain, but the
+// whole of P for each workgroup.  The same sums in the same order.  Whole forward, r = 2, us, four rows / two:
+//   d = 128   1 head x 131072 tokens  208 / 195    1 x 16384  76.9 / 72.3    2 x 16384  76.7 / 74.4    4 x 8192  68.1 / 66.7
+//             8 x 8192 (512 workgroups)  90.6 / 92.0         d = 64   2 x 32768  66.1 / 63.9
+// (32 partial sums instead of 16: no faster than two rows where those serve, and another order.)
 constexpr int kComposeSplit = 16;
 
-template <int D>
+template <int D, int ROWS>
 __device__ __forceinline__ void segment_compose(const float *S0, const float *__restrict__ Pseg,
                                                 const float *__restrict__ Hseg, float *__restrict__ Sin, float *SL, int G)
 {
     constexpr int X4 = D / 4, NTHR = X4 * kComposeSplit, YN = D / kComposeSplit;
-    static_assert(kComposeRows * D <= NTHR, "a thread per state element");
-    __shared__ __attribute__((aligned(16))) float cur[kComposeRows][D], part[kComposeSplit][kComposeRows][D];
-    const int tiles = D / kComposeRows;
+    static_assert(ROWS * D <= NTHR, "a thread per state element");
+    __shared__ __attribute__((aligned(16))) float cur[ROWS][D], part[kComposeSplit][ROWS][D];
+    const int tiles = D / ROWS;
     const size_t head = blockIdx.x / tiles;
-    const int r0 = (blockIdx.x % tiles) * kComposeRows;
+    const int r0 = (blockIdx.x % tiles) * ROWS;
     const int tid = threadIdx.x, x = 4 * (tid % X4), yg = tid / X4;
-    const bool own = tid < kComposeRows * D;           // the state element this thread adds up
+    const bool own = tid < ROWS * D;           // the state element this thread adds up
     const int om = own ? tid / D : 0, ox = tid % D;
     const size_t oel = (size_t)(r0 + om) * D + ox;
     float s = own && S0 ? S0[head * (size_t)D * D + oel] : 0.0f;
@@ -58,20 +62,20 @@ __device__ __forceinline__ void segment_compose(const float *S0, const float *__
         }
         s = h;
         __syncthreads();
-        f32x4 acc[kComposeRows];
+        f32x4 acc[ROWS];
 #pragma unroll
-        for (int m = 0; m < kComposeRows; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < ROWS; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < YN; ++i)
 #pragma unroll
-            for (int m = 0; m < kComposeRows; ++m) {
+            for (int m = 0; m < ROWS; ++m) {
                 const float c = cur[m][yg * YN + i];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[m][e] = fmaf(c, p[i][e], acc[m][e]);
             }
         fetch(g + 1 < G ? g + 1 : g);
 #pragma unroll
-        for (int m = 0; m < kComposeRows; ++m) *reinterpret_cast<f32x4 *>(&part[yg][m][x]) = acc[m];
+        for (int m = 0; m < ROWS; ++m) *reinterpret_cast<f32x4 *>(&part[yg][m][x]) = acc[m];
         __syncthreads();
         if (own) {
 #pragma unroll
@@ -81,31 +85,34 @@ __device__ __forceinline__ void segment_compose(const float *S0, const float *__
     if (SL && own) SL[head * (size_t)D * D + oel] = s;
 }
 
-// one overload per width, told apart by the last parameter
-#define PF_COMPOSE(D)                                                                                              \
+// one overload per width and number of rows, told apart by the last parameter
+template <int D_, int ROWS_> struct Compose { static constexpr int D = D_, ROWS = ROWS_; };
+#define PF_COMPOSE(D, ROWS)                                                                                        \
     __global__ __launch_bounds__(D / 4 * kComposeSplit) void segment_compose_kernel(                               \
-        const float *S0, const float *Pseg, const float *Hseg, float *Sin, float *SL, int G,                       \
-        std::integral_constant<int, D>)                                                                            \
+        const float *S0, const float *Pseg, const float *Hseg, float *Sin, float *SL, int G, Compose<D, ROWS>)     \
     {                                                                                                              \
-        segment_compose<D>(S0, Pseg, Hseg, Sin, SL, G);                                                            \
+        segment_compose<D, ROWS>(S0, Pseg, Hseg, Sin, SL, G);                                                      \
     }
-PF_COMPOSE(64)
-PF_COMPOSE(128)
+PF_COMPOSE(64, 2)
+PF_COMPOSE(64, 4)
+PF_COMPOSE(128, 2)
+PF_COMPOSE(128, 4)
 #undef PF_COMPOSE
 
 hipError_t launch_segment_compose(const float *S0, const float *Pseg, const float *Hseg, float *Sin,
                                   float *SL, int heads, int G, int d, hipStream_t stream)
 {
-    const unsigned grid = (unsigned)(heads * (d / kComposeRows));
-    auto launch = [&](auto width) {
-        constexpr int D = decltype(width)::value;
-        void (*kern)(const float *, const float *, const float *, float *, float *, int, decltype(width)) = segment_compose_kernel;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(D / 4 * kComposeSplit), 0, stream, S0, Pseg, Hseg, Sin, SL, G, width);
+    auto launch = [&](auto shape) {
+        using Shape = decltype(shape);
+        void (*kern)(const float *, const float *, const float *, float *, float *, int, Shape) = segment_compose_kernel;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(heads * (Shape::D / Shape::ROWS))), dim3(Shape::D / 4 * kComposeSplit), 0, stream,
+                           S0, Pseg, Hseg, Sin, SL, G, shape);
+        return hipGetLastError();
     };
-    if (d == 64) launch(std::integral_constant<int, 64>{});
-    else if (d == 128) launch(std::integral_constant<int, 128>{});
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    const bool two = (long long)heads * (d / 2) <= (long long)device_cu_count();
+    if (d == 64) return two ? launch(Compose<64, 2>{}) : launch(Compose<64, 4>{});
+    if (d == 128) return two ? launch(Compose<128, 2>{}) : launch(Compose<128, 4>{});
+    return hipErrorInvalidValue;
 }
 
 }  // namespace pf
