@@ -73,7 +73,7 @@ bool cut_once_more(int segments, int L, int d, int r, int chunk)
 // serves those.  T of a block shrinks to its two diagonal quarters.
 bool run_in_halves(int heads, int dv, int r, int block, int segments)
 {
-    return r == 4 && block == 32 && (segments > 1 || pf::scan_chain(heads, dv, 64));
+    return r == 4 && block == 32 && (segments > 1 || pf::scan_chain(heads, dv, 64) || pf::scan_two_tiles(heads, dv, 64));
 }
 
 // L tokens per head of which the first L - L % chunk (whole flow blocks) go through the MFMA
@@ -325,7 +325,7 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
         const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
         const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
         const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
-        const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r);
+        const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r) || pf::scan_two_tiles(heads, d_v, sub * r);
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);

@@ -47,7 +47,7 @@ hipError_t launch_generic_drivers(const void *Q, const void *A, const void *Atil
 // the first L / chunk whole blocks of every head (heads L tokens apart) and leave the tail alone.
 bool mfma_instance_exists(int d, int n, int chunk);
 // fold (blocks of 64 virtual tokens): Tt receives -T diag(beta), rounded once, the form that the chain in one wavefront
-// takes (launch_chunk_scan, folded, where scan_chain says that it serves the call) instead of T and beta.
+// takes (launch_chunk_scan, folded, where scan_chain or scan_two_tiles says that it serves the call) instead of T and beta.
 hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
                              bool product = false, bool fold = false, int unit = 0);
@@ -80,6 +80,8 @@ hipError_t launch_chunk_scan_general(const void *Q, const void *A, const void *A
 int scan_dv_tile(int heads, int dv, int n);
 // whether the scan of these dimensions runs the chain of 16 rows in one wavefront (delta rule, 16-row tiles)
 bool scan_chain(int heads, int dv, int n);
+// whether more tiles of 16 rows than that run it two to a workgroup (launch_chunk_scan, folded)
+bool scan_two_tiles(int heads, int dv, int n);
 
 // ---- fused forward (pf_fused.hip): flow and scan of every block in one kernel, d = d_k = d_v,
 // n = chunk * r in {64, 128}.  Takes the first L / chunk whole blocks of every head.  Tdump / Pdump

@@ -12,8 +12,8 @@
 //
 // Only R -> U_eff -> S_c+1 is a chain from one chunk to the next; the readout O_c hangs off it.
 // Two bodies follow from that.  The chain in one wavefront (pf_chain.h) takes tiles of 16 rows with blocks of 64
-// virtual tokens, up to one workgroup per compute unit (scan_chain).  The split over several wavefronts below takes
-// the rest: 32 rows, other blocks, general drivers, more workgroups.
+// virtual tokens, one or two to a workgroup, up to one workgroup per compute unit (scan_chain, scan_two_tiles).  The
+// split over several wavefronts below takes the rest: other blocks, general drivers, more workgroups, d_v = 16 mod 32.
 //
 // The workgroup of the split has two kinds of wavefronts, one of each per SIMD:
 //
@@ -669,7 +669,7 @@ __device__ __forceinline__ void split_scan(
 }
 
 // Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for tiles of 16
-// rows and 64 virtual tokens, unless SPLIT asks for the split above (scan_chain says when), which serves the rest.
+// rows and 64 virtual tokens, unless SPLIT asks for the split above (scan_chain and scan_two_tiles say when), which serves the rest.
 template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT = false>
 struct ScanBody {
     using Chain = ChainPlan<D, N, C, TV, RO>;
@@ -715,6 +715,17 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, TwoTiles)
 {
     static_assert(TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+}
+// (under the name of the body that served more tiles than compute units before: scan_two_tiles)
+template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT>
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, TwoTiles)
+{
+    static_assert(SPLIT && TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
@@ -800,14 +811,16 @@ static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, co
 
 // the chain of N virtual tokens a block under one of its tags, ROWS rows of S to a workgroup; `of` blocks make one of the
 // kernel's name
-template <int D, int N, int C, int ROWS, typename Tag, int of = 1>
+template <int D, int N, int C, int ROWS, typename Tag, int of = 1, bool SPLIT = false>
 static hipError_t launch_chain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
                                const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv,
                                hipStream_t stream)
 {
     using Pl = ChainPlan<D, N, C, ROWS, true>;
     void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *, float *,
-                 int, int, int, int, Tag) = scan_kernel<D, N * of, C * of, 16, true, false>;
+                 int, int, int, int, Tag);
+    if constexpr (SPLIT) kern = scan_kernel<D, N * of, C * of, 16, true, false, true>;
+    else kern = scan_kernel<D, N * of, C * of, 16, true, false>;
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
     if (e != hipSuccess) return e;
@@ -826,17 +839,25 @@ int scan_dv_tile(int heads, int dv, int n)
 }
 
 // A compute unit holds one workgroup of the chain (the ring fills its LDS; at d = 64 a ring of four slots, 75 KB, took
-// the same time within 1 %), but two of the split: the chain where every workgroup has a compute unit of its own, the
-// split beyond.  Scan alone, 4096 tokens, us, split / chain:
-//                     d = 64, r = 2    d = 128, r = 2    d = 128, r = 1
-//   256 workgroups     81.5 / 78.5        113 / 102        60.8 / 57.1
-//   288                 107 / 126         159 / 186            -
-//   384                 141 / 211         178 / 228         109 / 114
-//   480                 179 / 223         243 / 262         157 / 151
-// and for d_v = 48, 2048 tokens, r = 2, 768 workgroups: d = 64 241 / 321, d = 128 403 / 437.
+// the same time within 1 %), but two of the split: the chain where every workgroup has a compute unit of its own, and beyond
+// with two tiles to a workgroup where d_v allows, the split in the rest.  Whole forward, 4096 tokens, us, split / chain of one
+// tile / of two:
+//                              d = 64, r = 2          d = 64, r = 1       d = 128, r = 2         d = 128, r = 1
+//   256 tiles               113 / 110 /  -        30.6 / 29.2 / - (*)   117 /  99 /  -          79 /  74 /  -
+//   288                     142 / 162 / 129         96 /  98 / 70       191 / 202 / 136        135 / 136 /  86
+//   384                     183 / 254 / 153              -              207 / 252 / 150        133 / 137 /  87
+//   480                     234 / 279 / 175         70 /  69 / 49 (*)   288 / 298 / 188        183 / 184 / 122     ((*) 2048 tokens)
+// and r = 4 (the split on blocks of 128 virtual tokens, the chain on halves): d = 128, 288 tiles 498 / 416 / 252, 480
+// 655 / 531 / 309; d = 64, 384 tiles 587 / 438 / 261.  From 256 workgroups of two tiles on (64 heads, d = 128, r = 2) the
+// split of 32 rows is ahead again, 172.5 / 176.8.
 bool scan_chain(int heads, int dv, int n)
 {
     return n == 64 && scan_dv_tile(heads, dv, n) == 16 && (long long)heads * (dv / 16) <= (long long)device_cu_count();
+}
+
+bool scan_two_tiles(int heads, int dv, int n)
+{
+    return n == 64 && dv % 32 == 0 && scan_dv_tile(heads, dv, n) == 16 && !scan_chain(heads, dv, n);
 }
 
 template <int D, int N, int C, int TV>
@@ -845,6 +866,8 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
                                        int heads, int NC, int tail, int dv, bool folded, hipStream_t stream)
 {
     if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
+        if (folded && scan_two_tiles(heads, dv, N))
+            return launch_chain<D, N, C, 32, TwoTiles, 1, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         if (!scan_chain(heads, dv, N))
             return folded ? hipErrorInvalidValue
                           : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
@@ -869,7 +892,9 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
         if (!folded) return hipErrorInvalidValue;
 #define X(DD)                                                                                                                 \
         if (d == DD)                                                                                                          \
-            return launch_chain<DD, 64, 16, 16, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+            return scan_two_tiles(heads, dv, n)                                                                                   \
+                       ? launch_chain<DD, 64, 16, 32, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream) \
+                       : launch_chain<DD, 64, 16, 16, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         X(64) X(128)
 #undef X
         return hipErrorInvalidValue;

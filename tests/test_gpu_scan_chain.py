@@ -92,6 +92,14 @@ def test_rank_4_in_halves(oracle, blocks, tail, dk, dv):
     assert names[0] == f"pf::flow_kernel<{dk}, 128, 32, false>" and f"pf::scan_kernel<{dk}, 128, 32, 16, true, false>" in names
 
 
+@pytest.mark.parametrize("heads,dk,dv,r,L", [(65, 64, 64, 2, 32), (33, 128, 128, 1, 64 * 3), (22, 128, 192, 2, 32 * 4 + 9), (20, 64, 256, 1, 64 * 7 + 1),
+                                             (33, 128, 128, 4, 32 * 3), (65, 64, 64, 4, 32 * 2 + 21), (40, 64, 128, 4, 32 * 5)])
+def test_two_tiles_beyond_the_compute_units(oracle, heads, dk, dv, r, L):
+    """More tiles of 16 rows than compute units, two to a workgroup: one block up to more than the ring holds, tails, d_v apart
+    from d_k, halves of rank 4."""
+    _check(oracle, heads, L, dk, dv, r, heads + L)
+
+
 @pytest.mark.parametrize("heads,d,L", [(2, 128, 2048), (8, 64, 16384)])
 def test_rank_4_segments(oracle, heads, d, L):
     """Segments of halves, with one tile and (cut once more) with two tiles to a workgroup."""
