@@ -385,9 +385,9 @@ struct FlowBody {
     static constexpr bool kWave = N == 64;
     static constexpr size_t lds = kWave ? FlowWavePlan::lds : FlowLds<D, N, C, GEN>::total;
     static constexpr int threads = kWave ? FlowWavePlan::threads : kFlowThreads;
+    static constexpr int blocks = kWave ? FlowWavePlan::waves : 1;      // that a workgroup holds at a time
     // (waves a SIMD of the body of one wavefront per block: as its operands in registers allow)
     static constexpr int at_once = kWave ? (GEN && D == 128 ? 1 : 2) : (2 * lds <= kMaxLdsBytes ? 2 : 1);
-    static constexpr int blocks = kWave ? FlowWavePlan::waves : 1;      // that a workgroup holds at a time
 };
 
 template <int D, int N, int C, bool GEN = false>
@@ -442,7 +442,10 @@ static hipError_t launch_flow_instance(const void *Q, const void *K, const void 
     if (e != hipSuccess) return e;
     // Persistent grid: as many workgroups as the chip holds at once, each walking its share of the chunks.
     const size_t resident = (size_t)device_cu_count() * Body::at_once;
-    const size_t want = (nchunks + Body::blocks - 1) / Body::blocks;
+    // (Four blocks to a workgroup only beyond that: the four wavefronts of one get in each other's way.  8 to 256 blocks, us, four
+    // to a workgroup / one: d = 128, r = 1 7.5 to 7.9 / 4.8 to 5.1, r = 2 7.0 / 4.5, d = 64 5.6 to 6.4 / 4.1 to 4.5; 512 blocks
+    // 8.6 / 6.3; 1024, d = 128, r = 1 on 256 workgroups of four 9.4, on 512 of two 10.5.)
+    const size_t want = nchunks <= resident ? nchunks : (nchunks + Body::blocks - 1) / Body::blocks;
     const unsigned grid = (unsigned)(want < resident ? want : resident);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift, fold ? 1 : 0);

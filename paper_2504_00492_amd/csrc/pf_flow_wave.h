@@ -121,7 +121,9 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
     };
 
     const unsigned blocks = (unsigned)nchunks, step = gridDim.x * FlowWavePlan::waves;
-    unsigned cid = blockIdx.x * FlowWavePlan::waves + wave;
+    // no more blocks than workgroups: one to each; else neighbours in a workgroup (dealt a grid apart, 24 heads x 4096 tokens,
+    // d = 64, r = 2 took 15.6 us instead of 13.7)
+    unsigned cid = blocks <= gridDim.x ? blockIdx.x + gridDim.x * wave : blockIdx.x * FlowWavePlan::waves + wave;
     if (cid >= blocks) return;                         // whole wavefronts; no barrier below
     fetch(cid);
 #pragma unroll 1
