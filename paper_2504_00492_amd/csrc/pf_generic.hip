@@ -601,14 +601,31 @@ int block_tiles(int dk, int r)
 }
 
 // Whether that body serves the call.  A workgroup costs it 5 to 7 us before the second block of tokens and a compute unit
-// holds one or two of them, so it pays from about 24 virtual tokens a round of workgroups on.  Token by token / by blocks, us:
-//   8 heads, d = 128, r = 2, 12 tokens 8.1 / 8.0, 16 tokens 9.1 / 8.0; d = 64, 16 tokens 7.8 / 6.4, 32 tokens r = 1 11.0 / 6.4
-//   128 heads (four rounds), d = 128, r = 1, 32 tokens 21.3 / 28.7;   1024 heads, d = 128, r = 2, 16 tokens 115 / 225
-//   64 heads (two rounds), d = 128, 1000 tokens 335 / 184;   32 heads, d = 64, 2048 tokens 492 / 106
-bool block_pays(long long workgroups, size_t lds, long long virtual_tokens)
+// runs one at a time, while the rows' many wavefronts share one, and at r = 2 and 4 hold a token's products side by side (not in
+// the product form, which is taken as r = 3: 64 heads x 29 tokens, r = 4, d = 128, 45.5 / 48.5).  fp32, us, rows / blocks at virtual tokens a head:
+//                            12          24          48          96         192         384 (400: r = 1)
+//   256 workgroups
+//     d_k = 64, r = 1     6.9 / 6.0  10.0 / 6.7  15.2 / 7.4  26.3 / 10.3                 96.4 / 28.3
+//     d_k = 128, r = 2    6.7 / 7.3   8.5 / 8.3  12.8 / 9.2  20.0 / 14.8  35.8 / 23.6
+//     d_k = 64, r = 4                 6.7 / 6.6   9.0 / 7.3  14.4 / 9.9   23.1 / 15.9    41.6 / 26.5
+//   512 workgroups
+//     d_k = 64, r = 1     7.5 / 10.5 10.8 / 11.8 16.0 / 13.1 28.1 / 18.8                104.3 / 54.8
+//     d_k = 64, r = 2     6.8 / 10.5  8.3 / 11.8 11.8 / 12.9 18.6 / 18.5  32.1 / 30.0
+//     d_k = 64, r = 4                 7.9 / 11.7 10.6 / 13.1 16.9 / 18.4  27.3 / 29.9    49.9 / 51.1
+//     d_k = 128, r = 2    7.9 / 13.2  9.9 / 15.1 15.1 / 17.1 23.9 / 27.5  42.5 / 45.0   (800: 156.4 / 156.2)
+//   800 workgroups
+//     d_k = 64, r = 1     9.2 / 19.3 13.8 / 22.1 20.8 / 24.5 36.0 / 35.3                 129 / 108
+//     d_k = 128, r = 1   11.5 / 25.0 18.0 / 28.3 27.3 / 31.9 48.2 / 53.8                 175 / 165
+//     d_k = 64, r = 2                10.3 / 21.8 16.7 / 24.6 25.4 / 35.0  44.8 / 57.7
+// and r = 3 at 512: d_k = 64 72 tokens 19.3 / 17.5, d_k = 128 144 39.3 / 39.6; at 800, d_k = 64, 288 73.1 / 89.0.
+bool block_pays(long long workgroups, int dk, int ranks, long long virtual_tokens)
 {
-    const long long at_once = (long long)device_cu_count() * (2 * lds <= kMaxLdsBytes ? 2 : 1);
-    return virtual_tokens > 24 * ((workgroups + at_once - 1) / at_once);
+    const long long cus = device_cu_count(), rounds = (workgroups + cus - 1) / cus;
+    const bool together = ranks == 2 || ranks == 4, wide = dk > 64;
+    if (rounds == 1) return virtual_tokens > (together ? 20 : 12);
+    if (ranks == 1) return virtual_tokens > (rounds == 2 ? 32 : (wide ? 250 : 100));
+    if (rounds > 2 || ranks == 4) return false;
+    return ranks == 2 ? !wide && virtual_tokens > 100 : virtual_tokens > (wide ? 150 : 60);
 }
 
 }  // namespace
@@ -636,7 +653,7 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
         using Ld = BlockLds<kDrivers, decltype(dt)::value>;
         using Shape = BlockShape<decltype(dt)::value>;
         const long long grid = (long long)heads * ((dv + 15) / 16);
-        if (grid > 0x7fffffffLL || !block_pays(grid, Ld::bytes, (long long)(L - t0) * r)) return;
+        if (grid > 0x7fffffffLL || !block_pays(grid, dk, product && r > 1 ? 3 : r, (long long)(L - t0) * r)) return;
         taken = true;
         void (*kern)(GenericArgs<T>, int, Shape) = generic_kernel<T, kDrivers>;
         if (Ld::bytes > 65536) {
