@@ -62,8 +62,9 @@ const char *pf_status_str(pf_status s);
 
 /* Which kernel family would serve these dimensions.  Host only, no GPU needed.
  *   0  unsupported (pf_delta_fwd would return PF_ERR_UNSUPPORTED)
- *   1  generic path: the recurrence token by token in fp32 vector arithmetic, rows of the state in
- *      registers; both dtypes, any d_k, d_v, r; the chunk bounds the tokens staged in LDS at a time
+ *   1  generic path, fp32 throughout: the recurrence token by token in vector arithmetic, rows of the
+ *      state in registers, or 16 virtual tokens at a time on the fp32 matrix instruction where that is
+ *      faster (d_k up to 128); both dtypes, any d_k, d_v, r; the chunk bounds the tokens staged in LDS at a time
  *      and is halved until the working set of the chunk-wise form (Theorem 3.2) would fit 160 KiB
  *      of LDS next to an fp32 state (unsupported only when not even one token does); any L
  *   2  MFMA path (PF_BF16 only): d_k in {64, 128}, d_v any multiple of 16 (the state is split into

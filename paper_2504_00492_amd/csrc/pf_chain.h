@@ -1,6 +1,6 @@
 // Body of the scan kernel for flow blocks of 64 virtual tokens and tiles of 16 rows of S (the delta rule), with at most
-// one workgroup per compute unit (scan_chain in pf_scan.hip): one wavefront runs the whole chain R -> U_eff -> S of the
-// 16 rows by itself, out of registers.
+// one workgroup per compute unit (scan_chain, scan_two_tiles in pf_scan.hip): one wavefront runs the whole chain
+// R -> U_eff -> S of 16 rows by itself, out of registers.
 //
 // With S^T as accumulator tiles (rows d_k, columns the 16 rows of S) every product of a block takes the result of
 // the one before it as its B operand, and an accumulator tile is a B operand lane for lane (pf_common.h):
@@ -11,24 +11,28 @@
 // tiles of S^T are numbered so that lane group g of tiles 2 ks and 2 ks + 1 holds d_k = 32 ks + 8 g .. + 7: the
 // joined pair then pairs with 16 consecutive bytes of a row of K.
 //
-// A workgroup has one such state wave and helper waves.  Two of them (stagers) load K, V tile, beta and the T tiles of a
-// later block straight into a ring of six LDS slots, two more (readers, where O is wanted) compute the readout of the
-// block before,
+// A workgroup has one such state wave per tile of 16 rows (one tile, or two) and helper waves.  Two of them (stagers) load K,
+// the V tile and the T tiles of a later block straight into a ring of up to six LDS slots, two more (readers, where O is
+// wanted; one where a block holds 16 tokens) compute the readout of the block before,
 //     O^T = S Q^T + U_eff^T P^T,
-// from the copies of S and U_eff that the state wave leaves in LDS in operand form.  One barrier per block.
+// from the copies of S and U_eff that the state waves leave in LDS in operand form.  One barrier per block.
 //
-// What bounds it: at d = 64, and without the readout, the state wave (22 MFMAs at d = 64, 38 at d = 128, and the latencies
-// between the three products: about 1100 and 1300 cycles a block).  At d = 128 with the readout a block takes 1940 cycles,
-// because its 35 KB come in at 18 bytes a cycle: the stagers wait to issue, while the state wave waits at the barrier.
-// Counters (32 heads x 65536 tokens): 330 read requests a block and compute unit, 114 of them on their way at any time,
-// 670 cycles each (15 % of them miss L2, 1300 cycles).  It is the latency under this load, not the width of a path:
-// reads that hit in L2, from all compute units at once, come in at 50 bytes a cycle.
-// Against the split of the chain over four waves that pf_scan.hip keeps for the other shapes (three barriers a block), us:
-//   32 heads x 65536 tokens, r = 2, d = 128   1822 -> 1673      24 heads x 4096 tokens, r = 2, d = 64   66 -> 61
-//   32 heads x 2048 tokens, r = 1, d = 64     22.4 -> 20.8      32 segments x 4096 tokens, state only   92 -> 73
-// (all with at most one workgroup per compute unit).  With 32 rows per workgroup both move the same 41 KB a block and the
-// split is as fast (64 heads x 4096 tokens, r = 2: 132.8 against 133.0), with 128 virtual tokens a block the operands of
-// one wave do not fit its registers.
+// The flow kernel of the same call hands over -T diag(beta), rounded once (FOLD): beta and its widening are gone from the
+// state wave, and V enters as a product with -Id: 177 instructions a block at d = 128 where there were 235.  Whole forward,
+// 24 heads x 4096 tokens, d = 64, r = 2 89 -> 65 us, 4 heads x 32768, d = 128 277 -> 240 (both with the flow of
+// pf_flow_wave.h).  The split entry points hand over T itself and take the form without it.
+//
+// What bounds it: at d = 64 the state wave (26 MFMAs a block, and the latencies between the three products).  At d = 128
+// with the readout, 16 rows and 256 workgroups, the loads: a block takes 0.79 us, because its 35 KB come in at 18 bytes a
+// cycle, and the stagers wait to issue while the state wave waits at the barrier.  A compute unit has at most about 128 L2
+// lines on their way: 12 bytes a cycle where they come from HBM, 20 from the last-level cache, 42 from L2; a block's loads
+// alone take 0.79 us, 0.53 and 0.45, the state wave alone less.  Asking for a block's lines ahead of time in part (a wave, or
+// workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more elsewhere.
+//
+// Two tiles to a workgroup (scan_two_tiles and the segments) read K, Q, T, P once for 32 rows: a block takes hardly longer.
+// With at least 256 such workgroups the split of pf_scan.hip is ahead again (64 heads x 4096 tokens, d = 128, r = 2: whole
+// forward 172.5 us against 176.8).  With 128 virtual tokens a block the operands of one wave do not fit its registers:
+// blocks of rank 4 run as two halves (32 heads x 8192 tokens, r = 4 529 -> 436 us).
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"
