@@ -115,11 +115,9 @@ int tail_chunk(int d, int dv, int r)
 // chunk is the composition of the flows over its pieces, Section 3.1).  Small blocks are preferred
 // where an instance exists: the hand-over array T grows with the square of the block and every d_v
 // tile of a head reads all of it.  Measured (us per forward; 64 / 128 / 256 virtual tokens per
-// block), d = 128: 64 heads x 4096 tokens, r = 2: 197 / 225 / 461; 32 heads x 65536, r = 2: 2180 / 2378 /
-// 3227; 32 heads x 8192, r = 4: - / 530 / 755; 32 heads x 2048, r = 1: 45 / 61 / -; d = 64: the same with r = 1
-// 34 / 37 / -, 32 heads x 4096, r = 2 95 / 93 / 142.  16 tokens with r = 4 (64 virtual tokens) took 542 against 529
-// in the scan of eight wavefronts; the chain in one wavefront, whose readout takes at least two token tiles,
-// has no such instance.  So: 64 virtual tokens if that is at least 32 tokens, else at most 128 virtual tokens,
+// block), d = 128: 64 heads x 4096 tokens, r = 2: 180 / 225 / 461; 32 heads x 65536, r = 2: 2065 / 2378 / 3227; 32 heads x 8192,
+// r = 4: 438 (as halves of 128: run_in_halves) / 530 / 755; 32 heads x 2048, d = 64, r = 1: 28 / 37 / -.  Blocks of 16 tokens
+// have no instance of their own.  So: 64 virtual tokens if that is at least 32 tokens, else at most 128 virtual tokens,
 // else the largest block that has an instance.  0 when no instance serves these dimensions.
 template <typename Exists>
 int pick_block(int r, int chunk, Exists exists)
