@@ -9,7 +9,8 @@
 // accumulator tile of X the B operand of the next product (mfma4), so the substitution moves nothing between lanes
 // either, and T is rounded to bf16 once, when it is stored: with G, X and T_jj rounded to bf16 as operands the flow took
 // 1 us less on every shape below and the forward was 1 % further from 64 bits (O 4.54e-3 against 4.49e-3 before this
-// body and 4.42e-3 now, 20 heads x 8192 tokens, d = 128, r = 2).  Two accumulator tiles of X, one upon the other, are a tile of T as the scan reads it (pf_layout.h).
+// body and 4.42e-3 now, 20 heads x 8192 tokens, d = 128, r = 2).  Two accumulator tiles of X, one upon the other, are a
+// tile of T as the scan reads it (pf_layout.h).
 // T_jj = (Id + G_jj)^{-1}: forward substitution in fp32 on the vector ALU, four tiles at a time, a column per lane;
 // the rows of G_jj come in 16 reads and go round by DPP (as operands that all lanes read out of LDS, 40 reads of 16 bytes,
 // 32 x 2944 below took 18.0 us: the chain of one block is all it has).
