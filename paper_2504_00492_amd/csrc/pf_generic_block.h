@@ -88,8 +88,10 @@ struct Sums {
     }
 };
 
-// Between a product and a use of it in another basic block: the compiler (ROCm 7.2) was seen to place a copy of the
-// accumulator behind a join of branches without the wait states that reading it takes, and it got the old upper half.
+// Sixteen wait states between a product and a use of it behind a join of branches: the compiler (ROCm 7.2) counts the wait
+// states of its result along one path to the join only, the one through the code that the other jumps over, and a copy of
+// an accumulator there got the old upper half.  Products that cross a branch without it (os and ds, the branch for numbers
+// that are not finite) have enough of them on both paths as built: tests/test_wait_states.py follows all paths of all kernels.
 __device__ __forceinline__ void settle(f32x4 &v) { asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v)); }
 
 // four elements of a row as they lie in memory
