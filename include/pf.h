@@ -102,10 +102,13 @@ size_t pf_delta_fwd_workspace_bytes(int B, int H, int L, int d_k, int d_v, int r
  * launch order: the names of the kernel instantiations as a profiler prints them (template
  * arguments included, parameter lists left out), separated by ';', e.g.
  * "pf::flow_kernel<128, 64, 32, false>;pf::scan_kernel<128, 64, 32, 32, true, false>".  Template
- * arguments: d_k, virtual tokens per block, tokens per block; for the scan kernel then the d_v rows
- * one workgroup owns, whether it reads out O and whether the instance is the one for general
- * drivers, and a seventh, true, where more workgroups than compute units take the body without the
- * chain in one wavefront.  At most cap - 1
+ * arguments: d_k, virtual tokens and tokens of a block as it runs (with r = 4 a block of pf_delta_fwd_block
+ * tokens may run as two halves); for the scan and segment kernels then the rows one workgroup owns; for the
+ * scan kernel whether it reads out O, whether the instance is the one for general drivers, and a seventh, true,
+ * where the other of its two bodies runs: at 16 rows the one of eight wavefronts instead of the chain in one
+ * wavefront, at 32 rows the chain, two tiles of 16, instead of that one.  A name stands for one kernel of the
+ * library, but for the generic kernel: its bodies share theirs, because the choice depends on the form
+ * (pf_delta_fwd or pf_delta_product_fwd) as well, which is not an argument here.  At most cap - 1
  * characters and a terminating NUL are written to buf (buf may be NULL); the return value is the
  * length of the whole description (0 for unsupported or invalid dimensions).  Depends on the
  * compute-unit count of the current device where the d_v tile does (256 when no device answers).

@@ -263,18 +263,23 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
         if (fam == 1 || L < block) {
             out = generic;
         } else {
-            const int heads = B * H, n = block * r;
-            const int G = scan_segments(heads, L, d_k, d_v, r, block);   // (cut once more or not: the same tiles of 16 rows)
-            const std::string dims = std::to_string(d_k) + ", " + std::to_string(n) + ", " + std::to_string(block);
-            const std::string flow = "pf::flow_kernel<" + dims + ", false>";
-            const std::string scan = "pf::scan_kernel<" + dims + ", " +
-                                     std::to_string(G > 1 && n == 64 ? 16 : pf::scan_dv_tile(heads * G, d_v, n));
-            if (G > 1)
-                out = flow + ";" + scan + ", false, false>;" + scan + ", false, false>;" +
-                      "pf::segment_compose_kernel;" + scan + ", true, false>";
-            else
-                out = flow + ";" + scan + ", true, false" +
-                      (n == 64 && pf::scan_dv_tile(heads, d_v, n) == 16 && !pf::scan_chain(heads, d_v, n) ? ", true>" : ">");
+            const int heads = B * H, G = scan_segments(heads, L, d_k, d_v, r, block);
+            const int sub = run_in_halves(heads, d_v, r, block, G) ? block / 2 : block, n = sub * r;
+            const std::string dims = std::to_string(d_k) + ", " + std::to_string(n) + ", " + std::to_string(sub);
+            const std::string usual = ", true, false>", other = ", true, false, true>", scan = ";pf::scan_kernel<" + dims + ", ";
+            out = "pf::flow_kernel<" + dims + ", false>";
+            if (G > 1) {
+                const bool twice = cut_once_more(G, L, d_k, r, sub);
+                const std::string rows = twice ? "32" : "16", maps = ";pf::segment_maps_kernel<" + dims + ", " + rows + ">";
+                const std::string compose = ";pf::segment_compose_kernel<" + std::to_string(d_k) + ", " +
+                                            std::to_string(pf::segment_compose_rows(heads, d_k)) + ">";
+                out += maps + maps + compose + scan + rows + (twice ? other : usual);
+            } else if (pf::scan_two_tiles(heads, d_v, n)) {
+                out += scan + "32" + other;
+            } else {
+                const int rows = pf::scan_dv_tile(heads, d_v, n);
+                out += scan + std::to_string(rows) + (n == 64 && rows == 16 && !pf::scan_chain(heads, d_v, n) ? other : usual);
+            }
             if (tail) out += ";" + generic;
         }
     }

@@ -402,18 +402,6 @@ __global__ __launch_bounds__((FlowBody<D, N, C, GEN>::threads), (FlowBody<D, N, 
         flow_workgroup<D, N, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, smem);
 }
 
-// blocks of 128 virtual tokens and 32 tokens (r = 4) as two blocks of 64 each
-struct Halves {};
-template <int D, int N, int C, bool GEN = false>
-__global__ __launch_bounds__(FlowWavePlan::threads, 2) void flow_kernel(
-    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
-    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift, int fold, Halves)
-{
-    static_assert(N == 128 && !GEN, "halves of 64 virtual tokens");
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    flow_wave<D, C / 2, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, fold, reinterpret_cast<float *>(smem));
-}
-
 // ---------------------------------------------------------------------------- host side
 #define PF_FLOW_INSTANCES(X) \
     X(64, 64, 64) X(64, 64, 32) X(64, 128, 32) X(64, 128, 64) X(64, 128, 128) X(64, 256, 64) X(64, 256, 128) \
@@ -463,14 +451,13 @@ hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, voi
     const int n = chunk * r;
     if (n == 64 && chunk == 16) {                  // halves of a block of 32 tokens
         using Plan = FlowWavePlan;
-        void (*kern)(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int, int, Halves);
-        if (d == 64) kern = flow_kernel<64, 128, 32>;
-        else kern = flow_kernel<128, 128, 32>;
+        void (*kern)(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int, int) = flow_kernel<128, 64, 16>;
+        if (d == 64) kern = flow_kernel<64, 64, 16>;
         if ((d != 64 && d != 128) || Plan::lds > 65536) return hipErrorInvalidValue;
         const size_t resident = (size_t)device_cu_count() * 2, want = (nchunks + Plan::waves - 1) / Plan::waves;
         hipLaunchKernelGGL(kern, dim3((unsigned)(want < resident ? want : resident)), dim3(Plan::threads), Plan::lds, stream,
                            (const bf16 *)Q, (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail,
-                           product ? 0 : 2, fold ? 1 : 0, Halves{});
+                           product ? 0 : 2, fold ? 1 : 0);
         return hipGetLastError();
     }
     if (fold && n != 64) return hipErrorInvalidValue;

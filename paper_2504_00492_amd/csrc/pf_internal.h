@@ -93,6 +93,8 @@ hipError_t launch_fused(const void *Q, const void *K, const void *V, const void 
                         bool product, hipStream_t stream);
 
 // ---- segment-parallel scan (pf_segments.hip): the composition of segments
+// rows of the state that one of its workgroups owns
+int segment_compose_rows(int heads, int d);
 // per head: Sin[0] = S0 (or 0); Sin[s+1] = Sin[s] Pseg[s] + Hseg[s]; S_L = Sin[G] (if not NULL)
 hipError_t launch_segment_compose(const float *S0, const float *Pseg, const float *Hseg, float *Sin,
                                   float *SL, int heads, int G, int d, hipStream_t stream);

@@ -669,11 +669,12 @@ __device__ __forceinline__ void split_scan(
 }
 
 // Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for tiles of 16
-// rows and 64 virtual tokens, unless SPLIT asks for the split above (scan_chain and scan_two_tiles say when), which serves the rest.
-template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT = false>
+// rows and 64 virtual tokens, the split above for the rest; OTHER: the other one, the split at 16 rows, the chain with two
+// tiles at 32 (scan_chain and scan_two_tiles say when).
+template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER = false>
 struct ScanBody {
     using Chain = ChainPlan<D, N, C, TV, RO>;
-    static constexpr bool kChain = !SPLIT && !GEN && TV == 16 && Chain::kServes;
+    static constexpr bool kChain = !GEN && Chain::kServes && (TV == 16) != OTHER;
     static constexpr size_t lds = kChain ? Chain::total : ScanLds<D, N, C, TV, GEN>::total;
     static constexpr int threads = kChain ? Chain::threads : kScanThreads;
 };
@@ -694,91 +695,42 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
         split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
-// the split body of a shape that the chain serves as well
-template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT>
+// the other body of a shape that both serve: the split at 16 rows, the chain with two tiles of 16, a state wave each, at 32
+template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
     const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
 {
-    static_assert(SPLIT && ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes have one body");
+    static_assert(OTHER && !GEN && ChainPlan<D, N, C, TV, RO>::kServes, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+    if constexpr (TV == 32)
+        chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+    else
+        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
-// the chain with two tiles to a workgroup, a state wave each
-struct TwoTiles {};
-template <int D, int N, int C, int TV, bool RO, bool GEN>
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(
-    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
-    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, TwoTiles)
+// the state of a segment from zero and its propagator side by side (ChainPlan, PAIR), TV rows of each to a workgroup
+template <int D, int N, int C, int TV>
+__global__ __launch_bounds__(kScanThreads) void segment_maps_kernel(
+    const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ Tt, float *H, float *P,
+    int nchains, int NC, int stride, int first)
 {
-    static_assert(TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
-}
-// (under the name of the body that served more tiles than compute units before: scan_two_tiles)
-template <int D, int N, int C, int TV, bool RO, bool GEN, bool SPLIT>
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(
-    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
-    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, TwoTiles)
-{
-    static_assert(SPLIT && TV == 16 && !GEN && ChainPlan<D, N, C, 32, RO>::kServes, "blocks of 64 virtual tokens");
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    chain_scan<D, N, C, 32, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+    chain_scan<D, N, C, TV, false, true, true>(nullptr, K, V, nullptr, Tt, nullptr, nullptr, nullptr, H, nchains, NC, 0, D, smem,
+                                               P, stride, first);
 }
 
-// blocks of 128 virtual tokens and 32 tokens (r = 4) as two blocks of 64 each, one tile or two to a workgroup
-template <int TILES> struct Halves {};
-#define PF_HALVES(TILES)                                                                                                     \
-    template <int D, int N, int C, int TV, bool RO, bool GEN>                                                                \
-    __global__ __launch_bounds__(kScanThreads) void scan_kernel(                                                             \
-        const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ beta,   \
-        const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt, const float *S0, bf16 *__restrict__ O, float *SL,          \
-        int nchains, int NC, int tail, int dv, Halves<TILES>)                                           \
-    {                                                                                                                        \
-        static_assert(N == 128 && TV == 16 && !GEN, "halves of 64 virtual tokens");                                          \
-        extern __shared__ __attribute__((aligned(16))) char smem[];                                                          \
-        chain_scan<D, N / 2, C / 2, 16 * TILES, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail,  \
-                                                          dv, smem);                                                         \
-    }
-PF_HALVES(1)
-PF_HALVES(2)
-#undef PF_HALVES
-
-// the state of a segment from zero and its propagator side by side (ChainPlan, PAIR): TILES tiles of each to a workgroup, OF
-// blocks one of the kernel's name
-template <int TILES, int OF> struct Pair {};
-#define PF_PAIR(TILES, OF)                                                                                                   \
-    template <int D, int N, int C, int TV, bool RO, bool GEN>                                                                \
-    __global__ __launch_bounds__(kScanThreads) void scan_kernel(                                                             \
-        const bf16 *__restrict__ K, const bf16 *__restrict__ V, const bf16 *__restrict__ Tt, float *H, float *P,             \
-        int nchains, int NC, int stride, int first, Pair<TILES, OF>)                                                         \
-    {                                                                                                                        \
-        static_assert(TV == 16 && !RO && !GEN && N == 64 * OF, "blocks of 64 virtual tokens");                               \
-        extern __shared__ __attribute__((aligned(16))) char smem[];                                                          \
-        chain_scan<D, 64, C / OF, 16 * TILES, false, true, true>(nullptr, K, V, nullptr, Tt, nullptr, nullptr, nullptr, H,   \
-                                                                nchains, NC, 0, D, smem, P, stride, first);                  \
-    }
-PF_PAIR(1, 1)
-PF_PAIR(2, 1)
-PF_PAIR(1, 2)
-PF_PAIR(2, 2)
-#undef PF_PAIR
-
-// the chain on T itself, as the split entry points hand it over
-struct PlainT {};
-template <int D, int N, int C, int TV, bool RO, bool GEN>
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(
+// the chain on T itself, as callers of the split entry points hand it over
+template <int D, int N, int C>
+__global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, PlainT)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
 {
-    static_assert(ScanBody<D, N, C, TV, RO, GEN>::kChain, "the other shapes take T as it is");
+    static_assert(ScanBody<D, N, C, 16, true, false>::kChain, "the other shapes take T as it is");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    chain_scan<D, N, C, TV, RO, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+    chain_scan<D, N, C, 16, true, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -788,46 +740,40 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     X(128, 64, 64) X(128, 64, 32) X(128, 128, 32) X(128, 128, 64) X(128, 128, 128) X(128, 256, 64) X(128, 256, 128)
 #endif
 
-template <int D, int N, int C, int TV, bool RO, bool GEN = false, bool SPLIT = false>
-static hipError_t launch_scan_ro(const void *Q, const void *K, const void *V, const void *beta,
-                                       const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                                       int heads, int NC, int tail, int dv, hipStream_t stream)
+static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, int threads, size_t lds, const void *Q, const void *K,
+                         const void *V, const void *beta, const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
+                         int heads, int NC, int tail, int dv, hipStream_t stream)
 {
-    using Body = ScanBody<D, N, C, TV, RO, GEN, SPLIT>;
-    ScanFn *kern;
-    if constexpr (SPLIT) kern = scan_kernel<D, N, C, TV, RO, GEN, true>;
-    else kern = scan_kernel<D, N, C, TV, RO, GEN>;
-    constexpr size_t lds = Body::lds;
-    static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
-    static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
-    const unsigned grid = (unsigned)heads * (dv / TV);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), lds, stream, (const bf16 *)Q,
+    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / rows)), dim3(threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
                        (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, dv);
     return hipGetLastError();
 }
 
-// the chain of N virtual tokens a block under one of its tags, ROWS rows of S to a workgroup; `of` blocks make one of the
-// kernel's name
-template <int D, int N, int C, int ROWS, typename Tag, int of = 1, bool SPLIT = false>
-static hipError_t launch_chain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
-                               const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv,
-                               hipStream_t stream)
+// the body that is usual for TV rows to a workgroup, or (OTHER) the other one
+template <int D, int N, int C, int TV, bool GEN = false, bool OTHER = false>
+static hipError_t launch_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                              const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv, hipStream_t stream)
 {
-    using Pl = ChainPlan<D, N, C, ROWS, true>;
-    void (*kern)(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *, float *,
-                 int, int, int, int, Tag);
-    if constexpr (SPLIT) kern = scan_kernel<D, N * of, C * of, 16, true, false, true>;
-    else kern = scan_kernel<D, N * of, C * of, 16, true, false>;
+    using Body = ScanBody<D, N, C, TV, true, GEN, OTHER>;
+    static_assert(Body::lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
+    ScanFn *kern;
+    if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
+    else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / ROWS)), dim3(Pl::threads), Pl::total, stream, (const bf16 *)Q,
-                       (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt, (const bf16 *)Pt, S0, (bf16 *)O, SL,
-                       heads, NC, tail, dv, Tag{});
-    return hipGetLastError();
+    return launch(kern, armed, TV, Body::threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+}
+
+template <int D, int N, int C>
+static hipError_t launch_scan_plain(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                                    const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv, hipStream_t stream)
+{
+    using Pl = ChainPlan<D, N, C, 16, true>;
+    static std::atomic<uint64_t> armed{0};
+    return launch(scan_plain_kernel<D, N, C>, armed, 16, Pl::threads, Pl::total, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail,
+                  dv, stream);
 }
 
 int scan_dv_tile(int heads, int dv, int n)
@@ -867,16 +813,15 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
 {
     if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
         if (folded && scan_two_tiles(heads, dv, N))
-            return launch_chain<D, N, C, 32, TwoTiles, 1, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+            return launch_scan<D, N, C, 32, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         if (!scan_chain(heads, dv, N))
             return folded ? hipErrorInvalidValue
-                          : launch_scan_ro<D, N, C, TV, true, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
-        if (!folded)
-            return launch_chain<D, N, C, TV, PlainT>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+                          : launch_scan<D, N, C, TV, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+        if (!folded) return launch_scan_plain<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
     } else if (folded) {
         return hipErrorInvalidValue;
     }
-    return launch_scan_ro<D, N, C, TV, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    return launch_scan<D, N, C, TV>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
 }
 
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt,
@@ -890,11 +835,11 @@ hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const 
     if (!O || dv % 16 != 0 || (long long)heads * (dv / 16) > 0x7fffffffLL) return hipErrorInvalidValue;   // (the state alone: launch_segment_maps)
     if (n == 64 && chunk == 16) {                  // halves of a block of 32 tokens
         if (!folded) return hipErrorInvalidValue;
-#define X(DD)                                                                                                                 \
-        if (d == DD)                                                                                                          \
-            return scan_two_tiles(heads, dv, n)                                                                                   \
-                       ? launch_chain<DD, 64, 16, 32, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream) \
-                       : launch_chain<DD, 64, 16, 16, Halves<1>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+        const bool two = scan_two_tiles(heads, dv, n);
+#define X(DD)                                                                                                            \
+        if (d == DD)                                                                                                     \
+            return two ? launch_scan<DD, 64, 16, 32, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream) \
+                       : launch_scan<DD, 64, 16, 16>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         X(64) X(128)
 #undef X
         return hipErrorInvalidValue;
@@ -919,33 +864,25 @@ hipError_t launch_segment_scan(const void *Q, const void *K, const void *V, cons
 {
     const int NC = L / chunk, n = chunk * r;
     if (!O || L % chunk != 0 || n != 64 || d % 32 != 0 || (long long)heads * (d / 32) > 0x7fffffffLL) return hipErrorInvalidValue;
-#define X(DD, NN, CC)                                                                                      \
-    if constexpr (NN == 64) {                                                                               \
-        if (d == DD && chunk == CC)                                                                         \
-            return launch_chain<DD, NN, CC, 32, TwoTiles>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, d, stream); \
-    }
-    PF_SCAN_INSTANCES(X)
-#undef X
-#define X(DD)                                                                                                                 \
-    if (d == DD && chunk == 16)                                                                                               \
-        return launch_chain<DD, 64, 16, 32, Halves<2>, 2>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, d, stream);
-    X(64) X(128)
+#define X(DD, CC)            \
+    if (d == DD && chunk == CC) \
+        return launch_scan<DD, 64, CC, 32, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, 0, d, stream);
+    X(64, 64) X(64, 32) X(64, 16) X(128, 64) X(128, 32) X(128, 16)
 #undef X
     return hipErrorInvalidValue;
 }
 
-template <int D, int C, int TILES, int OF>
+template <int D, int C, int TV>
 static hipError_t launch_pair(const void *K, const void *V, const void *Tt, float *H, float *P, int heads, int stride, int first,
                               int NC, hipStream_t stream)
 {
-    using Pl = ChainPlan<D, 64, C, 16 * TILES, false, true>;
-    void (*kern)(const bf16 *, const bf16 *, const bf16 *, float *, float *, int, int, int, int, Pair<TILES, OF>) =
-        scan_kernel<D, 64 * OF, C * OF, 16, false, false>;
+    using Pl = ChainPlan<D, 64, C, TV, false, true>;
+    void (*kern)(const bf16 *, const bf16 *, const bf16 *, float *, float *, int, int, int, int) = segment_maps_kernel<D, 64, C, TV>;
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Pl::total);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (D / (16 * TILES))), dim3(Pl::threads), Pl::total, stream, (const bf16 *)K,
-                       (const bf16 *)V, (const bf16 *)Tt, H, P, heads, NC, stride, first, Pair<TILES, OF>{});
+    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (D / TV)), dim3(Pl::threads), Pl::total, stream, (const bf16 *)K,
+                       (const bf16 *)V, (const bf16 *)Tt, H, P, heads, NC, stride, first);
     return hipGetLastError();
 }
 
@@ -954,8 +891,17 @@ hipError_t launch_segment_maps(const void *K, const void *V, const void *Tt, flo
 {
     const int NC = L / chunk, half = NC / 2;
     if (L % chunk != 0 || chunk * r != 64 || half < 1 || (long long)heads * (d / 16) > 0x7fffffffLL) return hipErrorInvalidValue;
-#define X(DD, CC, OF)                                                                                          if (d == DD && chunk == CC) {                                                                                   auto run = [&](int first, int n) {                                                                              return two_tiles ? launch_pair<DD, CC, 2, OF>(K, V, Tt, H, P, heads, NC, first, n, stream)                                   : launch_pair<DD, CC, 1, OF>(K, V, Tt, H, P, heads, NC, first, n, stream);             };                                                                                                          const hipError_t e = run(0, half);                                                                          return e != hipSuccess ? e : run(half, NC - half);                                                      }
-    X(64, 64, 1) X(64, 32, 1) X(64, 16, 2) X(128, 64, 1) X(128, 32, 1) X(128, 16, 2)
+    auto both = [&](auto run) {
+        const hipError_t e = run(0, half);
+        return e != hipSuccess ? e : run(half, NC - half);
+    };
+#define X(DD, CC)                                                                                           \
+    if (d == DD && chunk == CC)                                                                             \
+        return both([&](int first, int n) {                                                                 \
+            return two_tiles ? launch_pair<DD, CC, 32>(K, V, Tt, H, P, heads, NC, first, n, stream)         \
+                             : launch_pair<DD, CC, 16>(K, V, Tt, H, P, heads, NC, first, n, stream);        \
+        });
+    X(64, 64) X(64, 32) X(64, 16) X(128, 64) X(128, 32) X(128, 16)
 #undef X
     return hipErrorInvalidValue;
 }
@@ -973,8 +919,8 @@ hipError_t launch_chunk_scan_general(const void *Q, const void *A, const void *A
     if constexpr (NN <= 128) {                                                                              \
         if (d == DD && n == NN && chunk == CC) {                                                            \
             if (wide)                                                                                       \
-                return launch_scan_ro<DD, NN, CC, 32, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream); \
-            return launch_scan_ro<DD, NN, CC, 16, true, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);     \
+                return launch_scan<DD, NN, CC, 32, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream); \
+            return launch_scan<DD, NN, CC, 16, true>(Q, Bm, Atil, A, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);     \
         }                                                                                                   \
     }
     PF_SCAN_INSTANCES(X)

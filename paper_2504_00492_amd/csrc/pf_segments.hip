@@ -14,8 +14,6 @@
 #include "pf_internal.h"
 #include "pf_common.h"
 
-#include <type_traits>
-
 namespace pf {
 
 // One workgroup owns ROWS rows of the state of one head (rows are independent) and walks the segments:
@@ -32,8 +30,8 @@ namespace pf {
 constexpr int kComposeSplit = 16;
 
 template <int D, int ROWS>
-__device__ __forceinline__ void segment_compose(const float *S0, const float *__restrict__ Pseg,
-                                                const float *__restrict__ Hseg, float *__restrict__ Sin, float *SL, int G)
+__global__ __launch_bounds__(D / 4 * kComposeSplit) void segment_compose_kernel(
+    const float *S0, const float *__restrict__ Pseg, const float *__restrict__ Hseg, float *__restrict__ Sin, float *SL, int G)
 {
     constexpr int X4 = D / 4, NTHR = X4 * kComposeSplit, YN = D / kComposeSplit;
     static_assert(ROWS * D <= NTHR, "a thread per state element");
@@ -85,33 +83,20 @@ __device__ __forceinline__ void segment_compose(const float *S0, const float *__
     if (SL && own) SL[head * (size_t)D * D + oel] = s;
 }
 
-// one overload per width and number of rows, told apart by the last parameter
-template <int D_, int ROWS_> struct Compose { static constexpr int D = D_, ROWS = ROWS_; };
-#define PF_COMPOSE(D, ROWS)                                                                                        \
-    __global__ __launch_bounds__(D / 4 * kComposeSplit) void segment_compose_kernel(                               \
-        const float *S0, const float *Pseg, const float *Hseg, float *Sin, float *SL, int G, Compose<D, ROWS>)     \
-    {                                                                                                              \
-        segment_compose<D, ROWS>(S0, Pseg, Hseg, Sin, SL, G);                                                      \
-    }
-PF_COMPOSE(64, 2)
-PF_COMPOSE(64, 4)
-PF_COMPOSE(128, 2)
-PF_COMPOSE(128, 4)
-#undef PF_COMPOSE
+int segment_compose_rows(int heads, int d) { return (long long)heads * (d / 2) <= (long long)device_cu_count() ? 2 : 4; }
 
 hipError_t launch_segment_compose(const float *S0, const float *Pseg, const float *Hseg, float *Sin,
                                   float *SL, int heads, int G, int d, hipStream_t stream)
 {
-    auto launch = [&](auto shape) {
-        using Shape = decltype(shape);
-        void (*kern)(const float *, const float *, const float *, float *, float *, int, Shape) = segment_compose_kernel;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(heads * (Shape::D / Shape::ROWS))), dim3(Shape::D / 4 * kComposeSplit), 0, stream,
-                           S0, Pseg, Hseg, Sin, SL, G, shape);
-        return hipGetLastError();
-    };
-    const bool two = (long long)heads * (d / 2) <= (long long)device_cu_count();
-    if (d == 64) return two ? launch(Compose<64, 2>{}) : launch(Compose<64, 4>{});
-    if (d == 128) return two ? launch(Compose<128, 2>{}) : launch(Compose<128, 4>{});
+    const int rows = segment_compose_rows(heads, d);
+#define X(D, ROWS)                                                                                                          \
+    if (d == D && rows == ROWS) {                                                                                           \
+        hipLaunchKernelGGL((segment_compose_kernel<D, ROWS>), dim3((unsigned)(heads * (D / ROWS))), dim3(D / 4 * kComposeSplit), \
+                           0, stream, S0, Pseg, Hseg, Sin, SL, G);                                                          \
+        return hipGetLastError();                                                                                           \
+    }
+    X(64, 2) X(64, 4) X(128, 2) X(128, 4)
+#undef X
     return hipErrorInvalidValue;
 }
 

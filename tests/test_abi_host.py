@@ -76,10 +76,15 @@ def test_describe_names_the_kernels_a_call_launches(pf):
     assert pf.pf_delta_fwd_describe(1, 32, 65536, 128, 128, 2, 128, BF) == [           # chunk 128 -> blocks of 32
         "pf::flow_kernel<128, 64, 32, false>", "pf::scan_kernel<128, 64, 32, 16, true, false>"]
     assert pf.pf_delta_fwd_describe(2, 16, 8192, 128, 128, 4, 64, BF) == [
-        "pf::flow_kernel<128, 128, 32, false>", "pf::scan_kernel<128, 128, 32, 16, true, false>"]
+        "pf::flow_kernel<128, 64, 16, false>", "pf::scan_kernel<128, 64, 16, 16, true, false>"]       # blocks of 32 in halves
+    assert pf.pf_delta_fwd_describe(4, 16, 8192, 128, 128, 4, 64, BF) == [              # many heads: whole blocks
+        "pf::flow_kernel<128, 128, 32, false>", "pf::scan_kernel<128, 128, 32, 32, true, false>"]
     seg = pf.pf_delta_fwd_describe(1, 4, 65536, 128, 128, 2, 64, BF)                    # few heads: segments
-    assert seg[0] == "pf::flow_kernel<128, 64, 32, false>" and seg[-1] == "pf::scan_kernel<128, 64, 32, 16, true, false>"
-    assert seg.count("pf::scan_kernel<128, 64, 32, 16, false, false>") == 2 and "pf::segment_compose_kernel" in seg
+    assert seg == ["pf::flow_kernel<128, 64, 32, false>"] + 2 * ["pf::segment_maps_kernel<128, 64, 32, 32>"] + [
+        "pf::segment_compose_kernel<128, 2>", "pf::scan_kernel<128, 64, 32, 32, true, false, true>"]
+    seg = pf.pf_delta_fwd_describe(1, 4, 2048, 128, 128, 2, 64, BF)                     # short segments: one tile to a workgroup
+    assert seg == ["pf::flow_kernel<128, 64, 32, false>"] + 2 * ["pf::segment_maps_kernel<128, 64, 32, 16>"] + [
+        "pf::segment_compose_kernel<128, 2>", "pf::scan_kernel<128, 64, 32, 16, true, false>"]
     assert pf.pf_delta_fwd_describe(1, 4, 100, 128, 128, 2, 64, BF)[-1] == "pf::generic_kernel<unsigned short, false>"
     assert pf.pf_delta_fwd_describe(1, 1, 64, 16, 16, 1, 16, F32) == ["pf::generic_kernel<float, false>"]
     assert pf.pf_delta_fwd_describe(1, 1, 64, 256, 256, 1, 16, F32) == []               # unsupported

@@ -38,7 +38,7 @@ def test_block_counts(oracle, blocks, tail, r, dk, dv):
 @pytest.mark.parametrize("d,r,L", [(64, 1, 2048), (64, 2, 1536), (128, 1, 2304)])
 def test_segments(oracle, d, r, L):
     names = _check(oracle, 2, L, d, d, r, 7)
-    assert "pf::segment_compose_kernel" in names
+    assert any(n.startswith("pf::segment_compose_kernel<") for n in names)
 
 
 @pytest.mark.parametrize("heads,d,r,L,product", [(8, 128, 2, 8192, False), (16, 64, 1, 16384, False), (8, 128, 1, 16384, True),
@@ -72,7 +72,7 @@ def test_segments_keep_columns_of_v_apart(d, r, L, chunk):
     w = synth.Workload("inf", "bf16", 1, 2, L, d, d, r, chunk, seed=5, s0_std=0.2, reflect_frac=0.0)
     print(f"[case] segments, infinity in V d={d} r={r} L={L}", flush=True)
     dev = to_device(w, synth.make_inputs(w))
-    assert "pf::segment_compose_kernel" in pf.pf_delta_fwd_describe(1, 2, L, d, d, r, chunk, pf.PF_BF16)
+    assert any(n.startswith("pf::segment_compose_kernel<") for n in pf.pf_delta_fwd_describe(1, 2, L, d, d, r, chunk, pf.PF_BF16))
     O, S = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=chunk)
     V = dev["V"].clone()
     V[0, 0, L // 3, 0, 21] = float("inf")
@@ -89,7 +89,7 @@ def test_rank_4_in_halves(oracle, blocks, tail, dk, dv):
     """Blocks of 32 tokens and 128 virtual tokens run as two of 64: one token tile a half, one reader, a tail of up to 31
     tokens behind the whole blocks (which a half of it would fit), d_v apart from d_k."""
     names = _check(oracle, 3, blocks * 32 + tail, dk, dv, 4, 10 * blocks + tail)
-    assert names[0] == f"pf::flow_kernel<{dk}, 128, 32, false>" and f"pf::scan_kernel<{dk}, 128, 32, 16, true, false>" in names
+    assert names[0] == f"pf::flow_kernel<{dk}, 64, 16, false>" and f"pf::scan_kernel<{dk}, 64, 16, 16, true, false>" in names
 
 
 @pytest.mark.parametrize("heads,dk,dv,r,L", [(65, 64, 64, 2, 32), (33, 128, 128, 1, 64 * 3), (22, 128, 192, 2, 32 * 4 + 9), (20, 64, 256, 1, 64 * 7 + 1),
@@ -103,4 +103,4 @@ def test_two_tiles_beyond_the_compute_units(oracle, heads, dk, dv, r, L):
 @pytest.mark.parametrize("heads,d,L", [(2, 128, 2048), (8, 64, 16384)])
 def test_rank_4_segments(oracle, heads, d, L):
     """Segments of halves, with one tile and (cut once more) with two tiles to a workgroup."""
-    assert "pf::segment_compose_kernel" in _check(oracle, heads, L, d, d, 4, 3)
+    assert any(n.startswith("pf::segment_compose_kernel<") for n in _check(oracle, heads, L, d, d, 4, 3))

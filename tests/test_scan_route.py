@@ -1,10 +1,15 @@
-"""Which body of the scan a call takes at 16-row tiles and blocks of 64 virtual tokens: the chain in one wavefront up to
-one workgroup per compute unit, the body of eight wavefronts (two workgroups a compute unit) beyond."""
+"""Which kernels a call launches, by name, and that a name tells which code ran.  Tiles of 16 rows and blocks of 64 virtual
+tokens take the chain in one wavefront: one tile to a workgroup up to one workgroup per compute unit, two beyond where d_v
+allows, and the body of eight wavefronts (two workgroups a compute unit) where it does not (d_v = 16 mod 32)."""
+import re
+import subprocess
+
 import numpy as np
 import pytest
 
 from paper_2504_00492_amd import synth
 from test_abi_host import pf  # noqa: F401  (fixture: builds / loads the library)
+from test_wait_states import _functions, _listings
 
 
 def _scan(pf, heads, L, dk, dv, r):  # noqa: F811
@@ -25,10 +30,60 @@ def test_body_by_workgroups(pf, dk, dv):  # noqa: F811
     for r in (1, 2):
         shape = f"pf::scan_kernel<{dk}, 64, {64 // r}, 16, true, false"
         assert _scan(pf, most, 640, dk, dv, r) == shape + ">"
-        assert _scan(pf, most + 1, 640, dk, dv, r) == shape + ", true>"
         if dv % 32:                              # no tiles of 32 rows: any number of heads
+            assert _scan(pf, most + 1, 640, dk, dv, r) == shape + ", true>"
             assert _scan(pf, 20 * most, 640, dk, dv, r) == shape + ", true>"
+        else:
+            assert _scan(pf, most + 1, 640, dk, dv, r) == f"pf::scan_kernel<{dk}, 64, {64 // r}, 32, true, false, true>"
     assert _scan(pf, 20 * most, 640, dk, 64, 2) == f"pf::scan_kernel<{dk}, 64, 32, 32, true, false>"
+
+
+# every branch of the dispatch: B * H, L, d_k, d_v, r, chunk
+SHAPES = [(32, 2048, 64, 64, 1, 64), (64, 4096, 128, 128, 2, 64), (32, 3001, 128, 128, 1, 64), (33, 256, 128, 128, 2, 64),
+          (65, 300, 64, 64, 1, 64), (100, 96, 64, 48, 2, 64), (32, 1024, 128, 128, 4, 128), (40, 96, 64, 128, 4, 64),
+          (20, 160, 64, 48, 4, 64), (64, 96, 128, 128, 4, 64), (100, 96, 64, 48, 4, 64), (2, 2048, 128, 128, 1, 64),
+          (8, 8192, 128, 128, 2, 64), (2, 2048, 64, 64, 4, 64), (8, 16384, 64, 64, 4, 64), (3, 40, 128, 128, 1, 64)]
+
+
+def _kernels(library, tmp_path):
+    """Names of the kernels in the library, without parameter lists, one for each kernel."""
+    names = []
+    for listing in _listings(tmp_path):
+        mangled = [name for name, body, _ in _functions(listing)]
+        plain = subprocess.run(["c++filt"], input="\n".join(mangled), capture_output=True, text=True, check=True).stdout.split("\n")
+        names += [re.sub(r"^void ", "", re.match(r"[^(]*", n).group(0)) for n in plain if n]
+    return names
+
+
+def test_a_name_stands_for_one_kernel(pf, tmp_path):  # noqa: F811
+    kernels = _kernels(pf, tmp_path)
+    for heads, L, dk, dv, r, chunk in SHAPES:
+        for name in pf.pf_delta_fwd_describe(1, heads, L, dk, dv, r, chunk, pf.PF_BF16):
+            if not name.startswith("pf::generic_kernel"):
+                assert kernels.count(name) == 1, (name, kernels.count(name))
+
+
+@pytest.mark.gpu
+def test_described_kernels_are_the_ones_that_run():
+    """Against the names that a profiler prints, in the order of the launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2504_00492_amd import binding as pf  # noqa: F811
+    gen, dev = torch.Generator(device="cuda:0").manual_seed(3), "cuda:0"
+    rand = lambda *s: 0.1 * torch.randn(s, generator=gen, device=dev)
+    inputs = [(rand(1, h, L, dk).bfloat16(), rand(1, h, L, r, dk).bfloat16(), rand(1, h, L, r, dv).bfloat16(), rand(1, h, L, r).bfloat16(), chunk)
+              for h, L, dk, dv, r, chunk in SHAPES]
+    for q, k, v, b, chunk in inputs:             # (first calls look up devices and kernels)
+        pf.delta_fwd(q, k, v, b, None, chunk=chunk)
+    torch.cuda.synchronize()
+    for shape, (q, k, v, b, chunk) in zip(SHAPES, inputs):
+        with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+            pf.delta_fwd(q, k, v, b, None, chunk=chunk)
+            torch.cuda.synchronize()
+        ran = sorted((e for e in p.events() if "pf::" in e.name), key=lambda e: e.time_range.start)
+        names = [re.sub(r"^void ", "", re.match(r"[^(]*", e.name).group(0)) for e in ran]
+        h, L, dk, dv, r, chunk = shape
+        assert names == pf.pf_delta_fwd_describe(1, h, L, dk, dv, r, chunk, pf.PF_BF16), shape
 
 
 @pytest.mark.gpu
@@ -40,7 +95,7 @@ def test_parity_beyond_the_compute_units(oracle, heads, L, dk, dv, r):
     from paper_2504_00492_amd import binding as pf  # noqa: F811
     w = synth.Workload("route", "bf16", 1, heads, L, dk, dv, r, 64, seed=heads, s0_std=0.2, reflect_frac=0.05)
     print(f"[case] scan beyond the compute units heads={heads} L={L} d=({dk},{dv}) r={r}", flush=True)
-    assert _scan(pf, heads, L, dk, dv, r).endswith("16, true, false, true>")
+    assert _scan(pf, heads, L, dk, dv, r).endswith("32, true, false, true>" if dv % 32 == 0 else "16, true, false, true>")
     inp = synth.make_inputs(w)
     dev = to_device(w, inp)
     O, SL = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64)
