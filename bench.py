@@ -12,10 +12,11 @@ cfg3a, cfg3b), each with its own K timed steps.  Per workload:
   * "ms_per_step" / "value": K steps timed after W warm-up steps and a settling period of
     further untimed steps (>= 0.15 s of GPU work; the clocks of this GPU need that long), and
     "ms_per_step_first_pass": the K steps timed right after the W warm-up steps, before settling;
-  * "kernels": each kernel's average duration, HIP events on the launch stream over K launches
-    through the split entry points (same kernels, same arguments, same input rotation), with its
-    algorithmic bytes and FLOPs against the HBM and bf16 MFMA peaks;
-  * "roofline": the dominant kernel against the roofline that bounds it.  Both kernels sit on the
+  * "kernels": the average duration of each kernel that pf_delta_fwd itself launches, from a trace
+    (torch.profiler) of further steps of the same loop, by the names of pf_delta_fwd_describe, with
+    its algorithmic bytes and FLOPs against the HBM and bf16 MFMA peaks; empty where the trace
+    does not hold exactly the described launches, or another profiler runs the program;
+  * "roofline": the dominant kernel (without "kernels": the whole step) against the roofline that bounds it.  Both kernels sit on the
     HBM side of the ridge (arithmetic intensity about 50-120 flop/B against 2500 TFLOP/s /
     8 TB/s = 312 flop/B), so it is algorithmic bytes (the q, k, v, beta it must read and the o
     it must write) per second against the 8 TB/s HBM peak.  "traffic" is the HBM bytes per launch
@@ -23,8 +24,8 @@ cfg3a, cfg3b), each with its own K timed steps.  Per workload:
     the profiled kernel instantiation is the one this run launched (pf_delta_fwd_describe) and the
     kernels' code is still the profiled one (kernel_code_digest);
   * "requested_chunk": where pf_delta_fwd runs flow blocks shorter than the requested chunk, the
-    two kernels timed at the requested chunk itself through the split entry points (null when no
-    instance of that size exists);
+    kernels of the split entry points timed at the requested chunk itself (null when no instance of
+    that size exists) beside the whole step at the library's blocks;
   * "fused_kernel": the one-kernel forward (pf_delta_fwd_fused) on the same blocks;
   * "general_drivers": the same forward through the general-driver kernels (pf_flow_fwd_mfma) on
     drivers of the same shape (A = -K / 2, Atil = V, B = K: two operand arrays instead of one).
@@ -133,10 +134,33 @@ def device_inputs(synth, w, dev, torch):
     return shp(Q), shp(K), shp(V), shp(beta), None if S0 is None else shp(S0)
 
 
+def launch_times(events, launched):
+    """Average microseconds of each launch of a step from a trace of several: events (start, name, duration) of this
+    library's kernels in any order, `launched` the names that a step launches, in order.  None unless the trace holds
+    those and nothing else."""
+    events, n = sorted(events), len(launched)
+    steps = len(events) // n if n else 0
+    if not steps or [name for _, name, _ in events] != steps * list(launched):
+        return None
+    return [sum(us for _, _, us in events[i::n]) / steps for i in range(n)]
+
+
+def trace_steps(torch, step, steps, launched):
+    """launch_times of `steps` calls of step(i).  Not under rocprofv3: one tracer of the GPU's queues at a time."""
+    if os.environ.get("ROCP_TOOL_LIBRARIES"):
+        return None
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        for i in range(steps):
+            step(i)
+        torch.cuda.synchronize()
+    kernels = [(e.time_range.start, re.sub(r"^void ", "", e.name.split("(")[0]), e.device_time) for e in p.events()]
+    return launch_times([k for k in kernels if k[1].startswith("pf::")], launched)
+
+
 def time_split(pf, torch, sets, S0, O, SL, dims, block, nwarm, steps, stream):
-    """Average duration of the flow and the scan kernel at flow blocks of `block` tokens: HIP events
-    on the launch stream around each launch through the split entry points, inputs rotated as in
-    the headline loop.  Returns (flow ms, scan ms)."""
+    """Average duration of pf_delta_chunk_flow and pf_delta_chunk_scan at flow blocks of `block` tokens: HIP events
+    on the launch stream around each launch, inputs rotated as in the headline loop.  Returns (flow ms, scan ms)."""
     B, H, L, dk, dv, r = dims
     n, NC = block * r, L // block
     dev = O.device
@@ -226,7 +250,6 @@ def run_workload(pf, torch, w, inputs, args, traffic_table):
     kernels, requested, fused, general = {}, None, None, None
     if fam == 2:
         dims = (B, H, L, dk, dv, r)
-        nwarm = min(args.warmup + settle_steps, 200)
 
         def kinfo(ms, fl, by, name):
             tf = fl * token_heads / (ms * 1e-3) / 1e12
@@ -235,30 +258,28 @@ def run_workload(pf, torch, w, inputs, args, traffic_table):
                     "alg_gbs": gb, "frac_hbm_peak": gb / PEAK_HBM_GBS,
                     "alg_bytes_per_launch": by * token_heads, "flop_per_alg_byte": fl / by}
 
-        name_of = lambda key: next((k for k in launched if k.startswith("pf::" + key)), None)
-        t_flow, t_scan = time_split(pf, torch, sets, S0, O, SL, dims, block, nwarm, args.steps, stream)
         f_flow, f_scan = kernel_flops_per_token_head(dk, r, block)
         b_flow, b_scan = kernel_bytes_per_token_head(dk, r, e)
-        kernels = {"flow_kernel": kinfo(t_flow, f_flow, b_flow, name_of("flow_kernel")),
-                   "scan_kernel": kinfo(t_scan, f_scan, b_scan, name_of("scan_kernel"))}
-        dom = "flow_kernel" if t_flow >= t_scan else "scan_kernel"
-        roofline = {"bound": "hbm", "kernel": dom, "kernel_name": kernels[dom]["name"],
-                    "achieved": kernels[dom]["alg_gbs"], "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                    "frac": kernels[dom]["frac_hbm_peak"], "avg_kernel_ms": kernels[dom]["ms"], "traffic": None}
-        digest = kernel_code_digest()
-        for key, info in kernels.items():
-            info["traffic"] = profiled_traffic(traffic_table, w.name, key, info["name"], digest)
-        roofline["traffic"] = kernels[dom]["traffic"]
-        if kernels["flow_kernel"]["traffic"] and kernels["scan_kernel"]["traffic"]:
-            roofline["traffic_both_kernels_over_min_bytes"] = (
-                (kernels["flow_kernel"]["traffic"] + kernels["scan_kernel"]["traffic"]) / min_bytes)
+        us = trace_steps(torch, step, max(10, min(args.steps, 100)), launched) if len(launched) == 2 else None
+        if us:                                   # (flow and scan; every workload here launches these two)
+            kernels = {"flow_kernel": kinfo(us[0] * 1e-3, f_flow, b_flow, launched[0]),
+                       "scan_kernel": kinfo(us[1] * 1e-3, f_scan, b_scan, launched[1])}
+            digest = kernel_code_digest()
+            for key, info in kernels.items():
+                info["traffic"] = profiled_traffic(traffic_table, w.name, key, info["name"], digest)
+        dom = max(kernels, key=lambda k: kernels[k]["ms"]) if kernels else "pf_delta_fwd"
+        top = kernels.get(dom) or kinfo(ms_per_step, f_flow + f_scan, min_bytes / token_heads, None)
+        roofline = {"bound": "hbm", "kernel": dom, "kernel_name": top["name"], "achieved": top["alg_gbs"], "peak": PEAK_HBM_GBS,
+                    "unit": "GB/s", "frac": top["frac_hbm_peak"], "avg_kernel_ms": top["ms"], "traffic": top.get("traffic")}
+        if kernels and all(k["traffic"] for k in kernels.values()):
+            roofline["traffic_both_kernels_over_min_bytes"] = sum(k["traffic"] for k in kernels.values()) / min_bytes
 
-        # the two kernels at the requested chunk itself, where the library runs shorter blocks
+        # the split entry points at the requested chunk itself, where the library runs shorter blocks
         if block != C:
             if pf.pf_delta_chunk_supported(dk, dv, r, C) and L % C == 0:
                 tf_, ts_ = time_split(pf, torch, sets, S0, O, SL, dims, C, 20, max(10, args.steps // 4), stream)
                 requested = {"chunk": C, "virtual_tokens": C * r, "flow_ms": tf_, "scan_ms": ts_,
-                             "ms_both": tf_ + ts_, "policy_block": block, "policy_ms_both": t_flow + t_scan}
+                             "ms_both": tf_ + ts_, "policy_block": block, "policy_ms_per_step": ms_per_step}
             else:
                 requested = {"chunk": C, "virtual_tokens": C * r, "ms_both": None, "policy_block": block,
                              "why": "no kernel instance for blocks of this many virtual tokens"}

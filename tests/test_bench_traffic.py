@@ -28,3 +28,13 @@ def test_digest_follows_the_code_and_nothing_else(bench, tmp_path):  # noqa: F81
     assert bench.kernel_code_digest(str(copy)) == digest
     chain.write_text(text.replace("fit < 6 ? fit : 6", "fit < 4 ? fit : 4"))
     assert bench.kernel_code_digest(str(copy)) != digest
+
+
+def test_launch_times_need_the_described_launches(bench):  # noqa: F811
+    names = ["pf::flow_kernel<64, 64, 64, false>", "pf::scan_kernel<64, 64, 64, 16, true, false>"]
+    trace = [(10, names[0], 2.0), (13, names[1], 5.0), (30, names[1], 7.0), (20, names[0], 4.0)]
+    assert bench.launch_times(trace, names) == [3.0, 6.0]
+    assert bench.launch_times(trace[:3], names) is None                     # a launch is missing
+    assert bench.launch_times(trace, names[:1]) is None                     # one that is not described
+    assert bench.launch_times(trace + [(40, names[1], 1.0), (41, names[0], 1.0)], names) is None   # another order
+    assert bench.launch_times([], names) is None and bench.launch_times(trace, []) is None
