@@ -356,8 +356,8 @@ __device__ __forceinline__ void generic_few(const GenericArgs<T> &a)
 #pragma unroll
             for (int i = 0; i < CV; ++i) {
                 const int x = 4 * (c + LPR * i), xx = x < dk ? x : 0;
-                t.k[j][i] = *reinterpret_cast<const Raw4<T> *>(Ah + (v0 + j) * dk + xx);
-                if constexpr (kDrivers) t.u[j][i] = *reinterpret_cast<const Raw4<T> *>(Kh + (v0 + j) * dk + xx);
+                t.k[j][i] = Raw4<T>::read(Ah + (v0 + j) * dk + xx);
+                if constexpr (kDrivers) t.u[j][i] = Raw4<T>::read(Kh + (v0 + j) * dk + xx);
             }
 #pragma unroll
             for (int n = 0; n < NG; ++n) t.v[j][n] = Vh[(v0 + j) * dv + (row[n] < dv ? row[n] : dv - 1)];
@@ -366,7 +366,7 @@ __device__ __forceinline__ void generic_few(const GenericArgs<T> &a)
 #pragma unroll
         for (int i = 0; i < CV; ++i) {
             const int x = 4 * (c + LPR * i);
-            t.q[i] = *reinterpret_cast<const Raw4<T> *>(Qh + (size_t)(s / nsub) * dk + (x < dk ? x : 0));
+            t.q[i] = Raw4<T>::read(Qh + (size_t)(s / nsub) * dk + (x < dk ? x : 0));
         }
     };
     auto dot = [&](const f32x4 (&x)[CV], const f32x4 (&y)[CV]) {

@@ -54,8 +54,9 @@ struct BlockLds {
     static constexpr int slot = oBt + 16;
     static constexpr int shares = 4 * NSW * 256;                       // of K S^T and of O^T, two blocks each
     // helper waves: eight where LDS has a slot for each of them and registers for three waves a SIMD suffice, else four
-    // (d_k = 128: six helpers 234 us, four 207 for 4 heads x 700 tokens, r = 3)
-    static constexpr int NH = DT <= 4 && 9 * slot + shares <= (int)(kMaxLdsBytes / 4) ? 8 : 4;
+    // (d_k = 128: six helpers 234 us, four 207 for 4 heads x 700 tokens, r = 3; drivers of d_k up to 48: eight spill, 130 us
+    // against 113 for 948 tokens, d_k = 48, d_v = 16 on two rounds of workgroups, 5 % in the middle of 169 shapes)
+    static constexpr int NH = DT <= 4 && !(kDrivers && DT == 3) && 9 * slot + shares <= (int)(kMaxLdsBytes / 4) ? 8 : 4;
     static constexpr int slots = NH + 1;                               // one in use, the others being prepared
     static constexpr int oR = slots * slot;                            // shares of K S^T
     static constexpr int oO = oR + 2 * NSW * 256;                      // shares of O^T
@@ -94,15 +95,17 @@ struct Sums {
 // that are not finite) have enough of them on both paths as built: tests/test_wait_states.py follows all paths of all kernels.
 __device__ __forceinline__ void settle(f32x4 &v) { asm volatile("s_nop 7\n\ts_nop 7" : "+v"(v)); }
 
-// four elements of a row as they lie in memory
+// four elements of a row as they lie in memory (read as a vector: a copy of the struct can stay a copy through scratch memory)
 template <typename T> struct Raw4;
 template <> struct Raw4<float> {
     f32x4 w;
+    __device__ static Raw4 read(const float *p) { return {*reinterpret_cast<const f32x4 *>(p)}; }
     __device__ f32x4 widen() const { return w; }
     __device__ static Raw4 narrow(f32x4 v) { return {v}; }
 };
 template <> struct Raw4<uint16_t> {
     u32x2 w;
+    __device__ static Raw4 read(const uint16_t *p) { return {*reinterpret_cast<const u32x2 *>(p)}; }
     __device__ f32x4 widen() const
     {
         return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xffff0000u), __uint_as_float(w[1] << 16),

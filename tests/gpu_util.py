@@ -97,6 +97,20 @@ def flat_heads(a):
     return a.reshape((-1,) + a.shape[2:])
 
 
+def kernels_of(call):
+    """Names of this library's kernels that call() launches, in order and with their parameter lists, as a profiler prints them
+    (the bodies of the generic kernel differ in the type of the last parameter)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    call()                                       # (a first call looks up devices and kernels)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        call()
+        torch.cuda.synchronize()
+    ran = sorted((e for e in p.events() if "pf::" in e.name), key=lambda e: e.time_range.start)
+    return [e.name for e in ran]
+
+
 # ---- decoding of the tiled operand arrays of pf_delta_chunk_flow (layouts: include/pf.h)
 def _lane_grid():
     lane = np.arange(64)

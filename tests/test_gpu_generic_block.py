@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2504_00492_amd import synth
-from gpu_util import flat_heads, rel_l2, to_device
+from gpu_util import flat_heads, kernels_of, rel_l2, to_device
 
 pytestmark = pytest.mark.gpu
 BAR = {"f32": 1e-6, "bf16": 2e-3}
@@ -96,6 +96,45 @@ def test_a_few_tokens(oracle, dtype, heads, L, dk, dv, r, product):
     Oref, SLref = (oracle.delta_product_fwd if product else oracle.delta_fwd)(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
     assert rel_l2(flat_heads(O.float().cpu().numpy()), Oref) <= BAR[dtype]
     assert rel_l2(flat_heads(state.cpu().numpy()), SLref) <= BAR["f32"]
+
+
+@pytest.mark.parametrize("dtype,heads,L,dk,dv,r", [
+    ("f32", 3, 1, 36, 5, 1), ("f32", 2, 2, 64, 40, 2), ("f32", 70, 1, 128, 100, 1), ("f32", 40, 2, 100, 70, 1), ("f32", 260, 15, 64, 128, 1),
+    ("f32", 300, 5, 128, 72, 2), ("f32", 300, 3, 100, 90, 4), ("f32", 250, 7, 128, 128, 1), ("bf16", 3, 1, 128, 48, 1),
+    ("bf16", 5, 2, 64, 16, 2), ("bf16", 260, 7, 64, 64, 4), ("bf16", 330, 3, 128, 112, 2), ("bf16", 280, 15, 128, 128, 1),
+])
+def test_a_few_tokens_of_drivers(oracle, dtype, heads, L, dk, dv, r):
+    """The same body on the rows of A and B: one token, two, odd numbers of them; a state that is handed out in place."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    rng = np.random.default_rng(100 * dk + 10 * r + L)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    unit = lambda *s: (lambda x: x / np.linalg.norm(x, axis=-1, keepdims=True))(rng.standard_normal(s))
+    k, beta = unit(heads, L, r, dk), 1.0 / (1.0 + np.exp(-rng.standard_normal((heads, L, r, 1))))
+    up = lambda a: torch.from_numpy(a.astype(np.float32)).to("cuda:0").to(tdt)[None].contiguous()
+    tq, tat = up(rng.standard_normal((heads, L, dk)) / np.sqrt(dk)), up(rng.standard_normal((heads, L, r, dv)) / np.sqrt(dv))
+    ta, tb = up(beta * (k + 0.3 * unit(heads, L, r, dk))), up(-(k + 0.3 * unit(heads, L, r, dk)))
+    S0 = (0.2 * rng.standard_normal((heads, dv, dk))).astype(np.float32)
+    print(f"[case] a few tokens of drivers {dtype} heads={heads} d=({dk},{dv}) r={r} L={L}", flush=True)
+    O, state = torch.empty(1, heads, L, dv, dtype=tdt, device="cuda:0"), None
+
+    def call():
+        nonlocal state
+        state = torch.from_numpy(S0).to("cuda:0")[None].contiguous()
+        if dtype == "f32":
+            st = pf.pf_flow_fwd(tq, ta, tat, tb, state, O, state, 1, heads, L, dk, dv, r, 16, pf.PF_F32)
+        else:
+            st = pf.pf_flow_fwd_mfma(tq, ta, tat, tb, state, O, state, 1, heads, L, dk, dv, r, 64, pf.PF_BF16, None, 0)
+        assert st == pf.PF_OK
+
+    name, = kernels_of(call)
+    assert "FewTokens<" in name, name
+    torch.cuda.synchronize()
+    back = lambda t: t[0].float().cpu().numpy().astype(np.float64)
+    q, at, a, b, o, s = (back(t) for t in (tq, tat, ta, tb, O, state))
+    ref = [oracle.flow_head(a[h], at[h], b[h], q[h], S0[h].astype(np.float64)) for h in range(heads)]
+    assert rel_l2(o, np.stack([x[0] for x in ref])) <= BAR[dtype]
+    assert rel_l2(s, np.stack([x[1] for x in ref])) <= BAR["f32"]
 
 
 @pytest.mark.parametrize("where", ["V", "K", "beta", "S0"])

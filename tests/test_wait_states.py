@@ -208,3 +208,12 @@ def test_no_kernel_uses_a_result_too_early(pf, tmp_path):  # noqa: F811
             early = missing_waits(body, labels)
             assert not early, (name, [(body[by], body[i], w) for (i, by), w in list(early.items())[:4]])
     assert kernels > 100
+
+
+def test_no_kernel_keeps_registers_in_memory(pf, tmp_path):  # noqa: F811
+    """Neither spills nor arrays that the compiler left in scratch memory."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    for listing in _listings(tmp_path):
+        for name, body, _ in _functions(listing):
+            assert not [t for t in body if t.startswith("scratch_")], name
