@@ -586,10 +586,20 @@ GenericPlan plan_generic(int dk, int dv, int r, int chunk, int tokens, bool driv
 //   128 heads    1 token  8.4 /  5.1    4 10.2 /  7.6    8 12.8 / 11.0    16, r = 1 12.9 / 16.1
 //   8 heads      1 token  5.1 /  4.5    2  4.8 /  4.8    4  5.4 /  6.4     8  6.6 / 9.8
 // and d = 64 (half the wavefronts): 1024 heads 1 token 17.4 / 7.3, 16 r = 1 30.0 / 26.4; 128 heads 4 5.6 / 5.5, 8 6.8 / 8.0.
-bool few_tokens(int heads, int dk, int dv, int steps)
+// Rows that a token brings cost it registers and time (operands: 1 at r = 1, d_k up to 64; rank 4, drivers' two arrays and
+// wider rows multiply it up to 16), and a wavefront with few of its 16 rows in use costs as much as a full one:
+//   8 operands, 2 tokens: d = 128, r = 4, 22 heads 5.9 / 6.5, 32 6.0 / 6.7; drivers d = 128, r = 2, 15 heads 5.2 / 5.6
+//   16: drivers, d = 128, r = 4, 8 heads, 1 token 5.1 / 5.6; fp32, d_v = 20, 574 heads, 8 tokens 28 / 37, d = 128, 508 heads, 4 48 / 37
+//   bf16, r = 1, d = 128, d_v = 100, 134 heads, 6 tokens 9.2 / 10.3
+//   d_v = 1 on 1358 heads, d_k = 128, r = 4, 7 tokens 11.7 / 23.3; d_v = 8, drivers, fp32, 1981 heads, 1 token 10.9 / 23.7
+bool few_tokens(int heads, int dk, int dv, int ranks, int steps, bool drivers, int esize)
 {
+    if (dk <= 32 || dk > 128 || dk % 4 != 0 || steps < 1 || steps > 16) return false;
     const long long waves = (long long)heads * ((dv + kFewRows - 1) / kFewRows);
-    return dk > 32 && dk <= 128 && dk % 4 == 0 && steps >= 1 && steps <= 16 && (steps <= 2 || steps <= waves / 128);
+    const bool wide = dk > 64, filled = dv >= kFewRows;
+    const int operands = ranks * (drivers ? 2 : 1) * (wide ? 2 : 1);
+    if (steps <= 2) return operands < 8 || steps * operands <= 8 || (filled && waves >= 300);
+    return filled && steps <= waves / (operands == 16 && esize == 4 ? 256 : (operands == 2 && wide && esize == 2 ? 160 : 128));
 }
 
 // Tiles of 16 columns that hold d_k, for the body that takes 16 virtual tokens at a time (0: no instance).
@@ -618,12 +628,26 @@ int block_tiles(int dk, int r)
 //     d_k = 128, r = 1   11.5 / 25.0 18.0 / 28.3 27.3 / 31.9 48.2 / 53.8                 175 / 165
 //     d_k = 64, r = 2                10.3 / 21.8 16.7 / 24.6 25.4 / 35.0  44.8 / 57.7
 // and r = 3 at 512: d_k = 64 72 tokens 19.3 / 17.5, d_k = 128 144 39.3 / 39.6; at 800, d_k = 64, 288 73.1 / 89.0.
-bool block_pays(long long workgroups, int dk, int ranks, long long virtual_tokens)
+// Rows of up to 32 columns cost the rows' body less, 8 or 16 of them to a wavefront: r = 1, bf16, chunk 64, four rounds of
+// workgroups d = 16 0.68 to 0.98 of its time, d = 32 0.31 to 1.15; six and seven 0.66 to 1.59; 12 to 16 1.3 to 2.7 (fp32 the
+// same: 1387 heads x 198 tokens, d_k = 16, d_v = 96 188 / 385).  The rows' body reads bf16 rows of no whole 16 bytes by elements: 698 heads
+// (six rounds) x 473 tokens, d = 20, 172 / 141, 601 x 334 118 / 91.
+// d_k that is no multiple of four is read element by element when it is staged, not requested ahead.  In bf16, beyond 16
+// columns, that pays with one round of workgroups, with two only while the inputs stay in L2, and more of them not:
+//   two rounds   d = 33, r = 1, 241 tokens 76 / 72, d = 31, 595 187 / 200, d = 17, 730 192 / 234, r = 2, 348 63 / 79,
+//                d = 127, 148 109 / 133        ten   1275 heads x 413, d = 17 168 / 636
+//   one, r = 4   d = 33, 140 tokens 29 / 16, d = 65, 980 236 / 255, d = 127, 676 258 / 275, 2092 816 / 901
+bool block_pays(long long workgroups, int dk, int ranks, long long virtual_tokens, int esize)
 {
     const long long cus = device_cu_count(), rounds = (workgroups + cus - 1) / cus;
     const bool together = ranks == 2 || ranks == 4, wide = dk > 64;
-    if (rounds == 1) return virtual_tokens > (together ? 20 : 12);
-    if (ranks == 1) return virtual_tokens > (rounds == 2 ? 32 : (wide ? 250 : 100));
+    if (esize == 2 && dk % 4 != 0 && dk > 16) {
+        if (rounds == 1) return virtual_tokens > (together ? 28 : 16) && (ranks != 4 || dk <= 32 || virtual_tokens <= 200);
+        return rounds == 2 && !together && !wide && virtual_tokens > 60 && virtual_tokens <= 200;
+    }
+    // (bf16: 16 heads x 12 tokens, d = 128, r = 2 8.3 / 8.8; drivers, d = 64, r = 4, 7 tokens 6.8 / 7.4)
+    if (rounds == 1) return virtual_tokens > (together ? (esize == 2 && dk >= 64 && dk % 8 == 0 ? 28 : 20) : 12);
+    if (ranks == 1) return virtual_tokens > (rounds == 2 ? 32 : (wide ? 250 : 100)) && (dk > 32 || rounds <= (esize == 2 && dk % 8 == 4 && virtual_tokens > 200 ? 6 : 4));
     if (rounds > 2 || ranks == 4) return false;
     return ranks == 2 ? !wide && virtual_tokens > 100 : virtual_tokens > (wide ? 150 : 60);
 }
@@ -653,7 +677,7 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
         using Ld = BlockLds<kDrivers, decltype(dt)::value>;
         using Shape = BlockShape<decltype(dt)::value>;
         const long long grid = (long long)heads * ((dv + 15) / 16);
-        if (grid > 0x7fffffffLL || !block_pays(grid, dk, product && r > 1 ? 3 : r, (long long)(L - t0) * r)) return;
+        if (grid > 0x7fffffffLL || !block_pays(grid, dk, product && r > 1 ? 3 : r, (long long)(L - t0) * r, (int)sizeof(T))) return;
         taken = true;
         void (*kern)(GenericArgs<T>, int, Shape) = generic_kernel<T, kDrivers>;
         if (Ld::bytes > 65536) {
@@ -671,7 +695,7 @@ static hipError_t launch_generic_instance(const void *Q, const void *K, const vo
     default: break;
     }
     if (taken) return done;
-    if (t0 == 0 && L <= 16 && few_tokens(heads, dk, dv, L * (r / ranks)) && (ranks == 1 || ranks == 2 || ranks == 4)) {
+    if (t0 == 0 && L <= 16 && few_tokens(heads, dk, dv, ranks, L * (r / ranks), kDrivers, (int)sizeof(T)) && (ranks == 1 || ranks == 2 || ranks == 4)) {
         const int per_wg = 4 * kFewRows, tiles = (dv + per_wg - 1) / per_wg;
         if ((long long)heads * tiles > 0x7fffffffLL) return hipErrorInvalidValue;
         auto launch = [&](auto shape) -> hipError_t {
