@@ -605,7 +605,7 @@ bool few_tokens(int heads, int dk, int dv, int ranks, int steps, bool drivers, i
 // Tiles of 16 columns that hold d_k, for the body that takes 16 virtual tokens at a time (0: no instance).
 int block_tiles(int dk, int r)
 {
-    if (dk > 128 || r > kBlockVT) return 0;
+    if (dk < 16 || dk > 128 || r > kBlockVT) return 0;    // (below: block_pays)
     const int dt = (dk + 15) / 16;
     return dt <= 4 ? dt : (dt <= 6 ? 6 : 8);
 }
@@ -637,8 +637,20 @@ int block_tiles(int dk, int r)
 //   two rounds   d = 33, r = 1, 241 tokens 76 / 72, d = 31, 595 187 / 200, d = 17, 730 192 / 234, r = 2, 348 63 / 79,
 //                d = 127, 148 109 / 133        ten   1275 heads x 413, d = 17 168 / 636
 //   one, r = 4   d = 33, 140 tokens 29 / 16, d = 65, 980 236 / 255, d = 127, 676 258 / 275, 2092 816 / 901
+// Where it would lose digits the rows' body stays, whatever the time.  A block sums a token's products more often (K S^T, T R, U^T P^T,
+// K^T U), which rounding S once a block makes up for from some tokens or columns on.  fp32, distance from 64 bits, blocks / rows, O and
+// S_L, the worse of delta rule, product form and drivers, with and without S_0, mean of 8 seeds and 16 heads:
+//                 16 tokens      24             32             40             48             64             128
+//   d_k = 12     1.17, 1.18    1.13, 1.02     1.13, 1.07     1.10, 0.99     1.10, 1.03     1.09, 1.01     1.07, 1.01
+//   d_k = 16     1.11, 1.06    1.06, 0.95     1.05, 0.96     1.03, 0.89     1.02, 0.92     1.00, 0.91     0.96, 0.88
+//   d_k = 20     1.10, 1.03    1.06, 0.93     1.03, 0.93     1.01, 0.87     0.99, 0.88     0.97, 0.86     0.92, 0.82
+//   d_k = 24     1.04, 1.00    1.01, 0.89     0.99, 0.89     0.98, 0.83     0.96, 0.84     0.93, 0.81     0.87, 0.76
+//   d_k = 64     1.01, 0.90    0.97, 0.81     0.94, 0.78     0.91, 0.73     0.88, 0.70     0.84, 0.66     0.73, 0.57
+//   d_k = 96     1.01, 0.89    0.99, 0.80     0.97, 0.76     0.93, 0.71     0.91, 0.68     0.85, 0.63     0.74, 0.54
+// (d_k = 8: 1.2 to 1.3 at any length.)  O in bf16 is rounded far above these; there S_L alone counts.
 bool block_pays(long long workgroups, int dk, int ranks, long long virtual_tokens, int esize)
 {
+    if (virtual_tokens <= (dk < 24 ? (esize == 4 ? 40 : 16) : (esize == 4 ? 16 : 0))) return false;
     const long long cus = device_cu_count(), rounds = (workgroups + cus - 1) / cus;
     const bool together = ranks == 2 || ranks == 4, wide = dk > 64;
     if (esize == 2 && dk % 4 != 0 && dk > 16) {

@@ -23,10 +23,12 @@
 // Why 16: one tile of the instruction is the smallest block that feeds it, and the chain of dependent products of a
 // block grows with the block.  What bounds it: that chain (about 1350 cycles a block of 16 at d_k = 64 with the helpers
 // idle: R, the exchange, U, S, each behind the latency of the one before), and the helpers that share its SIMDs and LDS.
-// Against the recurrence token by token (pf_generic.hip), fp32, us: 32 heads x 2048 tokens, d = 64, r = 1 492 -> 106;
-// drivers of 8 heads x 500 tokens, d_k = 32, d_v = 48, r = 2 127 -> 43; 64 heads x 1000, d = 128, r = 1 335 -> 184;
+// Against the recurrence token by token (pf_generic.hip), fp32, us: 32 heads x 2048 tokens, d = 64, r = 1 492 -> 110;
+// drivers of 8 heads x 500 tokens, d_k = 32, d_v = 48, r = 2 127 -> 45; 64 heads x 1000, d = 128, r = 1 335 -> 184;
 // 4 heads x 700, d = 128, r = 3 464 -> 197; 1 head x 64, d = 16 17.5 -> 6.  Error against 64 bits (2-norm of O, S_L): the
-// first of these 2.5e-7, 2.5e-7 -> 1.6e-7, 1.4e-7, because S is rounded once per block.
+// first of these 2.5e-7, 2.5e-7 -> 1.6e-7, 1.3e-7, because S is rounded once per block.  What a block adds, its sums, is kept
+// down by trees and by U = R + (T - Id) R: 3 % of the time (43.0 -> 44.6 us for the second of these), and without it few tokens
+// were further from 64 bits than token by token (block_pays in pf_generic.hip has what is left of that).
 #pragma once
 #include "pf_generic.h"
 #include "pf_internal.h"
@@ -184,6 +186,9 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
             to.p = f4(o + Ld::oP + lane * 4);
             if constexpr (!kDrivers) to.bt = f4(o + Ld::oBt + 4 * g);
         };
+        f32x4 one;                                         // this lane's elements of Id
+#pragma unroll
+        for (int e = 0; e < 4; ++e) one[e] = 4 * g + e == r16 ? 1.f : 0.f;
         Operands even, odd;
         barrier();
         read_block(0, even);
@@ -219,11 +224,13 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
             }
             slot = slot == Ld::slots - 1 ? 0 : slot + 1;
             read_block(slot, ahead);                       // (after the last block: some slot, not used)
+            // U = R + (T - Id) R: R, the largest term, is rounded once, not at every step of a sum
+            const f32x4 t = x.t - one;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) u.add(e, x.t[e], R[e]);
-            const f32x4 U = u.total();
+            for (int e = 0; e < 4; ++e) u.add(e, t[e], R[e]);
+            const f32x4 U = R + u.total();
             // the block's update is summed by itself: S is rounded once per block, not once per token
-            Sums<NA / 2> ds[TPW];
+            Sums<DT == 1 ? 4 : 2> ds[TPW];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -399,23 +406,32 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
         if constexpr (!kDrivers)
             if (lane < 16) smem[o + Ld::oBt + lane] = lane < n ? as_f32(rb) : 0.f;
     };
-    f32x4 acc, acc1;
-    constexpr int H1 = (DT + 1) / 2;
-    auto gram = [&](int o, int q0, int q1) {               // rows that multiply the state times rows of the update
-        if (q0 == 0) acc = acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    // x y^T over tiles Q0 .. Q1 - 1 of 16 columns, in pairs of pairs: the products of a tile in two sums of eight, their totals in
+    // a tree (in two sums over all of d_k = 128, O of 16 tokens from a zero state was 1.6 times as far from 64 bits as the rows'
+    // body has it, whose sums are trees as well)
+    auto dots = [&](auto self, int ox, int oy, auto Q0c, auto Q1c) -> f32x4 {
+        constexpr int Q0 = decltype(Q0c)::value, Q1 = decltype(Q1c)::value, M = (Q0 + Q1) / 2;
+        if constexpr (Q1 - Q0 > 1) {
+            const f32x4 lo = self(self, ox, oy, Q0c, std::integral_constant<int, M>{});
+            return lo + self(self, ox, oy, std::integral_constant<int, M>{}, Q1c);
+        } else {
+            const f32x4 x = f4(ox + r16 * KP + 16 * Q0 + 4 * g), y = f4(oy + r16 * KP + 16 * Q0 + 4 * g);
+            Sums<DT <= 2 ? 4 : 2> sum;
 #pragma unroll
-        for (int q = 0; q < DT; ++q) {
-            if (q < q0 || q >= q1) continue;
-            const f32x4 x = f4(o + Ld::oA + r16 * KP + 16 * q + 4 * g), y = f4(o + Ld::oB + r16 * KP + 16 * q + 4 * g);
-#pragma unroll
-            for (int e = 0; e < 4; e += 2) {
-                acc = mfma4(x[e], y[e], acc);
-                acc1 = mfma4(x[e + 1], y[e + 1], acc1);
-            }
+            for (int e = 0; e < 4; ++e) sum.add(e, x[e], y[e]);
+            return sum.total();
         }
     };
+    constexpr int H1 = (DT + 1) / 2;
+    constexpr std::integral_constant<int, 0> kFirst{};
+    constexpr std::integral_constant<int, H1> kHalf{};
+    constexpr std::integral_constant<int, DT> kLast{};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};                      // the first half of the columns, from one interval to the next
+    auto half = [&](int ox, int oy) { acc = dots(dots, ox, oy, kFirst, kHalf); };
+    auto whole = [&](int ox, int oy) {
+        if constexpr (H1 < DT) acc += dots(dots, ox, oy, kHalf, kLast);
+    };
     auto put_gram = [&](int o) {                           // the strictly lower part of the system matrix less the identity
-        acc += acc1;
         f32x4 b = {-1.f, -1.f, -1.f, -1.f};
         if constexpr (!kDrivers) b = f4(o + Ld::oBt + 4 * g);
 #pragma unroll
@@ -456,21 +472,7 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
         rows_of_t(o, t, std::integral_constant<int, 11>{}, std::integral_constant<int, 14>{});
         rows_of_t(o, t, std::integral_constant<int, 14>{}, std::integral_constant<int, kBlockVT>{});
     };
-    auto readout = [&](int o, int q0, int q1) {
-        if (q0 == 0) acc = acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < DT; ++q) {
-            if (q < q0 || q >= q1) continue;
-            const f32x4 x = f4(o + Ld::oB + r16 * KP + 16 * q + 4 * g), y = f4(o + Ld::oQ + r16 * KP + 16 * q + 4 * g);
-#pragma unroll
-            for (int e = 0; e < 4; e += 2) {
-                acc = mfma4(x[e], y[e], acc);
-                acc1 = mfma4(x[e + 1], y[e + 1], acc1);
-            }
-        }
-    };
     auto put_p = [&](int o) {
-        acc += acc1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = tok4[e] <= r16 ? acc[e] : 0.f;
         f4(o + Ld::oP + lane * 4) = acc;
@@ -496,11 +498,13 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
     if (h < NC) {
         const int o = h * Ld::slot;
         stage(h, o);
-        gram(o, 0, DT);
+        half(o + Ld::oA, o + Ld::oB);                      // rows that multiply the state times rows of the update
+        whole(o + Ld::oA, o + Ld::oB);
         put_gram(o);
         substitute_upper(o);
         substitute_lower(o);
-        readout(o, 0, DT);
+        half(o + Ld::oB, o + Ld::oQ);
+        whole(o + Ld::oB, o + Ld::oQ);
         put_p(o);
     }
     fetch(clamp(h + NH));
@@ -523,21 +527,17 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
             if (s0 <= 0 && have) stage(b, o);                                                \
             if (s0 <= 1 && 1 < s1) fetch(clamp(b + NH));                                     \
             if (have) {                                                                      \
-                if (s0 <= 1 && 1 < s1) gram(o, 0, H1);                                       \
+                if (s0 <= 1 && 1 < s1) half(o + Ld::oA, o + Ld::oB);                         \
                 if (s0 <= 2 && 2 < s1) {                                                     \
-                    gram(o, H1, DT);                                                         \
+                    whole(o + Ld::oA, o + Ld::oB);                                           \
                     put_gram(o);                                                             \
                 }                                                                            \
                 if (s0 <= 3 && 3 < s1) substitute_upper(o);                                  \
                 if (s0 <= 4 && 4 < s1) substitute_lower(o);                                  \
-                if (s0 <= 5 && 5 < s1) readout(o, 0, H1);                                    \
+                if (s0 <= 5 && 5 < s1) half(o + Ld::oB, o + Ld::oQ);                         \
                 if (s0 <= 6 && 6 < s1) {                                                     \
-                    readout(o, H1, DT);                                                      \
+                    whole(o + Ld::oB, o + Ld::oQ);                                           \
                     put_p(o);                                                                \
-                }                                                                            \
-                if ((s0 <= 1 && 1 < s1) || (s0 <= 5 && 5 < s1)) {                            \
-                    settle(acc);                                                             \
-                    settle(acc1);                                                            \
                 }                                                                            \
             }                                                                                \
             barrier();                                                                       \

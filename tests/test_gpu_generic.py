@@ -85,8 +85,13 @@ BODIES = [
     # bf16 rows that are not whole pieces of four: rounds, columns, ranks, lengths
     ("delta", "bf16", 354, 143, 17, 17, 1, 64, ROWS), ("delta", "bf16", 350, 143, 17, 16, 1, 64, BLOCKS), ("delta", "bf16", 300, 350, 17, 16, 1, 64, ROWS),
     ("delta", "bf16", 300, 143, 65, 16, 1, 64, ROWS), ("delta", "bf16", 24, 63, 33, 33, 4, 64, ROWS), ("delta", "bf16", 24, 50, 33, 33, 4, 64, BLOCKS),
-    ("delta", "bf16", 24, 63, 31, 31, 4, 64, BLOCKS), ("delta", "bf16", 354, 143, 15, 17, 1, 64, BLOCKS), ("delta", "f32", 354, 143, 17, 17, 1, 64, BLOCKS),
+    ("delta", "bf16", 24, 63, 31, 31, 4, 64, BLOCKS), ("delta", "bf16", 350, 143, 16, 16, 1, 64, BLOCKS), ("delta", "f32", 354, 143, 17, 17, 1, 64, BLOCKS),
     ("delta", "bf16", 13, 14, 127, 127, 1, 64, ROWS), ("delta", "bf16", 14, 13, 50, 50, 2, 64, ROWS),
+    # where a block would lose digits: fewer than 16 columns, few tokens of few columns
+    ("delta", "bf16", 354, 143, 15, 17, 1, 64, ROWS), ("delta", "f32", 3, 300, 15, 16, 1, 32, ROWS), ("drivers", "f32", 3, 150, 8, 16, 2, 16, ROWS),
+    ("delta", "f32", 3, 40, 16, 16, 1, 32, ROWS), ("delta", "f32", 3, 41, 16, 16, 1, 32, BLOCKS), ("delta", "f32", 3, 16, 24, 16, 1, 32, ROWS),
+    ("delta", "f32", 3, 17, 24, 16, 1, 32, BLOCKS), ("drivers", "f32", 3, 20, 20, 16, 2, 16, ROWS), ("drivers", "f32", 3, 21, 20, 16, 2, 16, BLOCKS),
+    ("delta", "bf16", 3, 16, 16, 16, 1, 64, ROWS), ("delta", "bf16", 3, 17, 16, 16, 1, 64, BLOCKS), ("delta", "bf16", 3, 13, 24, 16, 1, 64, BLOCKS),
     # one round, ranks 2 and 4
     ("delta", "bf16", 16, 14, 128, 128, 2, 64, ROWS), ("delta", "bf16", 16, 15, 128, 128, 2, 64, BLOCKS), ("delta", "f32", 16, 11, 128, 128, 2, 16, BLOCKS),
     # a few tokens: rank times width, wavefronts, rows that they fill
