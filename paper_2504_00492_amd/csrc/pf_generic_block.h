@@ -23,11 +23,11 @@
 // Why 16: one tile of the instruction is the smallest block that feeds it, and the chain of dependent products of a
 // block grows with the block.  What bounds it: that chain (about 1350 cycles a block of 16 at d_k = 64 with the helpers
 // idle: R, the exchange, U, S, each behind the latency of the one before), and the helpers that share its SIMDs and LDS.
-// Against the recurrence token by token (pf_generic.hip), fp32, us: 32 heads x 2048 tokens, d = 64, r = 1 492 -> 110;
+// Against the recurrence token by token (pf_generic.hip), fp32, us: 32 heads x 2048 tokens, d = 64, r = 1 492 -> 112;
 // drivers of 8 heads x 500 tokens, d_k = 32, d_v = 48, r = 2 127 -> 45; 64 heads x 1000, d = 128, r = 1 335 -> 184;
 // 4 heads x 700, d = 128, r = 3 464 -> 197; 1 head x 64, d = 16 17.5 -> 6.  Error against 64 bits (2-norm of O, S_L): the
 // first of these 2.5e-7, 2.5e-7 -> 1.6e-7, 1.3e-7, because S is rounded once per block.  What a block adds, its sums, is kept
-// down by trees and by U = R + (T - Id) R: 3 % of the time (43.0 -> 44.6 us for the second of these), and without it few tokens
+// down by trees and by U = R + (T - Id) R: 3 % of the time (43.0 -> 45.0 us for the second of these), and without it few tokens
 // were further from 64 bits than token by token (block_pays in pf_generic.hip has what is left of that).
 #pragma once
 #include "pf_generic.h"
@@ -406,30 +406,39 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
         if constexpr (!kDrivers)
             if (lane < 16) smem[o + Ld::oBt + lane] = lane < n ? as_f32(rb) : 0.f;
     };
-    // x y^T over tiles Q0 .. Q1 - 1 of 16 columns, in pairs of pairs: the products of a tile in two sums of eight, their totals in
-    // a tree (in two sums over all of d_k = 128, O of 16 tokens from a zero state was 1.6 times as far from 64 bits as the rows'
-    // body has it, whose sums are trees as well)
-    auto dots = [&](auto self, int ox, int oy, auto Q0c, auto Q1c) -> f32x4 {
-        constexpr int Q0 = decltype(Q0c)::value, Q1 = decltype(Q1c)::value, M = (Q0 + Q1) / 2;
-        if constexpr (Q1 - Q0 > 1) {
-            const f32x4 lo = self(self, ox, oy, Q0c, std::integral_constant<int, M>{});
-            return lo + self(self, ox, oy, std::integral_constant<int, M>{}, Q1c);
-        } else {
-            const f32x4 x = f4(ox + r16 * KP + 16 * Q0 + 4 * g), y = f4(oy + r16 * KP + 16 * Q0 + 4 * g);
-            Sums<DT <= 2 ? 4 : 2> sum;
+    // x y^T over tiles Q0 .. Q1 - 1 of 16 columns: the products of a tile in two or four sums of their own, which meet in a tree.
+    // (In two sums over all of d_k = 128, O of 16 tokens from a zero state was 1.6 times as far from 64 bits as the rows' body
+    // has it, whose sums are trees as well.  One tile after the other instead of all products first: 35 heads x 290 tokens,
+    // d_k = 128, r = 4, 123 us, this 113, the two sums 111.)
+    auto dots = [&](int ox, int oy, auto Q0c, auto Q1c) -> f32x4 {
+        constexpr int Q0 = decltype(Q0c)::value, M = decltype(Q1c)::value - Q0, N = DT <= 2 ? 4 : 2;
+        f32x4 x[M], y[M], sum[M * N];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum.add(e, x[e], y[e]);
-            return sum.total();
+        for (int q = 0; q < M; ++q) {
+            x[q] = f4(ox + r16 * KP + 16 * (Q0 + q) + 4 * g);
+            y[q] = f4(oy + r16 * KP + 16 * (Q0 + q) + 4 * g);
         }
+        LDS_FENCE();
+#pragma unroll
+        for (int i = 0; i < M * N; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int q = 0; q < M; ++q) sum[N * q + e % N] = mfma4(x[q][e], y[q][e], sum[N * q + e % N]);
+#pragma unroll
+        for (int n = M * N; n > 1; n = (n + 1) / 2)
+#pragma unroll
+            for (int i = 0; i < n / 2; ++i) sum[i] += sum[(n + 1) / 2 + i];
+        return sum[0];
     };
     constexpr int H1 = (DT + 1) / 2;
     constexpr std::integral_constant<int, 0> kFirst{};
     constexpr std::integral_constant<int, H1> kHalf{};
     constexpr std::integral_constant<int, DT> kLast{};
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};                      // the first half of the columns, from one interval to the next
-    auto half = [&](int ox, int oy) { acc = dots(dots, ox, oy, kFirst, kHalf); };
+    auto half = [&](int ox, int oy) { acc = dots(ox, oy, kFirst, kHalf); };
     auto whole = [&](int ox, int oy) {
-        if constexpr (H1 < DT) acc += dots(dots, ox, oy, kHalf, kLast);
+        if constexpr (H1 < DT) acc += dots(ox, oy, kHalf, kLast);
     };
     auto put_gram = [&](int o) {                           // the strictly lower part of the system matrix less the identity
         f32x4 b = {-1.f, -1.f, -1.f, -1.f};
