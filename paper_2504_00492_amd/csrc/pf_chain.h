@@ -22,9 +22,11 @@
 // 24 heads x 4096 tokens, d = 64, r = 2 89 -> 65 us, 4 heads x 32768, d = 128 277 -> 240 (both with the flow of
 // pf_flow_wave.h).  The split entry points hand over T itself and take the form without it.
 //
-// What bounds it: at d = 64 the state wave (26 MFMAs a block, and the latencies between the three products).  At d = 128
-// with the readout, 16 rows and 256 workgroups, the loads: a block takes 0.79 us, because its 35 KB come in at 18 bytes a
-// cycle, and the stagers wait to issue while the state wave waits at the barrier.  A compute unit has at most about 128 L2
+// What bounds it: the loads.  At d = 128 with the readout, 16 rows and 256 workgroups a block takes 0.79 us, because its 35 KB
+// come in at 18 bytes a cycle (328 requests of 128 bytes, 114 of them on their way, 667 cycles each); at d = 64 a block of
+// 24 heads x 4096 tokens, d_v = 128, r = 2 takes 0.63 us where its inputs come from HBM, 0.40 where they lie in the last-level
+// cache, and of 32 x 2048, r = 1 0.85 and 0.65: the state wave takes no more than the lower.  The stagers wait to
+// issue while the state wave waits at the barrier.  A compute unit has at most about 128 L2
 // lines on their way: 12 bytes a cycle where they come from HBM, 20 from the last-level cache, 42 from L2; a block's loads
 // alone take 0.79 us, 0.53 and 0.45, the state wave alone less.  Asking for a block's lines ahead of time in part (a wave, or
 // workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more elsewhere.

@@ -409,7 +409,7 @@ __device__ __forceinline__ void generic_block(const GenericArgs<T> &a, int C, fl
     // x y^T over tiles Q0 .. Q1 - 1 of 16 columns: the products of a tile in two or four sums of their own, which meet in a tree.
     // (In two sums over all of d_k = 128, O of 16 tokens from a zero state was 1.6 times as far from 64 bits as the rows' body
     // has it, whose sums are trees as well.  One tile after the other instead of all products first: 35 heads x 290 tokens,
-    // d_k = 128, r = 4, 123 us, this 113, the two sums 111.)
+    // d_k = 128, r = 4 in the product form, 123 us, this 114, the two sums 111.)
     auto dots = [&](int ox, int oy, auto Q0c, auto Q1c) -> f32x4 {
         constexpr int Q0 = decltype(Q0c)::value, M = decltype(Q1c)::value - Q0, N = DT <= 2 ? 4 : 2;
         f32x4 x[M], y[M], sum[M * N];
