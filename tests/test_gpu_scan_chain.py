@@ -52,6 +52,7 @@ def test_segments_cut_once_more(oracle, heads, d, r, L, product):
     print(f"[case] segments cut once more heads={heads} L={L} d={d} r={r} product={product}", flush=True)
     inp = synth.make_inputs(w)
     dev = to_device(w, inp)
+    assert f"pf::segment_maps_kernel<{d}, 64, {64 // r}, 32>" in pf.pf_delta_fwd_describe(1, heads, L, d, d, r, 64, pf.PF_BF16)
     need = pf.pf_delta_fwd_workspace_bytes(1, heads, L, d, d, r, 64, pf.PF_BF16)
     ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
     O, state = torch.empty(1, heads, L, d, dtype=torch.bfloat16, device="cuda:0"), dev["S0"].clone()
@@ -97,10 +98,11 @@ def test_rank_4_in_halves(oracle, blocks, tail, dk, dv):
 def test_two_tiles_beyond_the_compute_units(oracle, heads, dk, dv, r, L):
     """More tiles of 16 rows than compute units, two to a workgroup: one block up to more than the ring holds, tails, d_v apart
     from d_k, halves of rank 4."""
-    _check(oracle, heads, L, dk, dv, r, heads + L)
+    names = _check(oracle, heads, L, dk, dv, r, heads + L)
+    assert f"pf::scan_kernel<{dk}, 64, {64 // r}, 32, true, false, true>" in names
 
 
-@pytest.mark.parametrize("heads,d,L", [(2, 128, 2048), (8, 64, 16384)])
-def test_rank_4_segments(oracle, heads, d, L):
+@pytest.mark.parametrize("heads,d,L,rows", [(2, 128, 2048, 16), (8, 64, 16384, 32)])
+def test_rank_4_segments(oracle, heads, d, L, rows):
     """Segments of halves, with one tile and (cut once more) with two tiles to a workgroup."""
-    assert any(n.startswith("pf::segment_compose_kernel<") for n in _check(oracle, heads, L, d, d, 4, 3))
+    assert f"pf::segment_maps_kernel<{d}, 64, 16, {rows}>" in _check(oracle, heads, L, d, d, 4, 3)

@@ -12,21 +12,28 @@ from test_abi_host import pf  # noqa: F401  (fixture: builds / loads the library
 from test_wait_states import _functions, _listings
 
 
+def _names(pf, heads, L, dk, dv, r):  # noqa: F811
+    return pf.pf_delta_fwd_describe(1, heads, L, dk, dv, r, 64, pf.PF_BF16)
+
+
 def _scan(pf, heads, L, dk, dv, r):  # noqa: F811
-    return next(n for n in pf.pf_delta_fwd_describe(1, heads, L, dk, dv, r, 64, pf.PF_BF16) if n.startswith("pf::scan_kernel"))
+    return next(n for n in _names(pf, heads, L, dk, dv, r) if n.startswith("pf::scan_kernel"))
+
+
+def _cus():
+    try:
+        import torch
+        if torch.cuda.is_available():
+            return torch.cuda.get_device_properties(0).multi_processor_count
+    except ImportError:
+        pass
+    return 256
 
 
 @pytest.mark.parametrize("dk", [64, 128])
 @pytest.mark.parametrize("dv", [48, 64, 112, 128])
 def test_body_by_workgroups(pf, dk, dv):  # noqa: F811
-    cus = 256
-    try:
-        import torch
-        if torch.cuda.is_available():
-            cus = torch.cuda.get_device_properties(0).multi_processor_count
-    except ImportError:
-        pass
-    most = cus // (dv // 16)                     # heads that still give every workgroup a compute unit
+    most = _cus() // (dv // 16)                  # heads that still give every workgroup a compute unit
     for r in (1, 2):
         shape = f"pf::scan_kernel<{dk}, 64, {64 // r}, 16, true, false"
         assert _scan(pf, most, 640, dk, dv, r) == shape + ">"
@@ -36,6 +43,33 @@ def test_body_by_workgroups(pf, dk, dv):  # noqa: F811
         else:
             assert _scan(pf, most + 1, 640, dk, dv, r) == f"pf::scan_kernel<{dk}, 64, {64 // r}, 32, true, false, true>"
     assert _scan(pf, 20 * most, 640, dk, 64, 2) == f"pf::scan_kernel<{dk}, 64, 32, 32, true, false>"
+
+
+@pytest.mark.parametrize("dk", [64, 128])
+@pytest.mark.parametrize("dv", [48, 128])
+def test_rank_4_in_halves_where_the_chain_serves_them(pf, dk, dv):  # noqa: F811
+    halves, whole, most = f"pf::flow_kernel<{dk}, 64, 16, false>", f"pf::flow_kernel<{dk}, 128, 32, false>", _cus() // (dv // 16)
+    assert _names(pf, most, 96, dk, dv, 4) == [halves, f"pf::scan_kernel<{dk}, 64, 16, 16, true, false>"]
+    if dv % 32:
+        assert _names(pf, most + 1, 96, dk, dv, 4) == [whole, f"pf::scan_kernel<{dk}, 128, 32, 16, true, false>"]
+    else:
+        assert _names(pf, most + 1, 96, dk, dv, 4) == [halves, f"pf::scan_kernel<{dk}, 64, 16, 32, true, false, true>"]
+        assert _names(pf, 2 * most, 96, dk, dv, 4) == [whole, f"pf::scan_kernel<{dk}, 128, 32, 32, true, false>"]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("r", [1, 2, 4])
+def test_segments_by_heads_and_blocks(pf, d, r):  # noqa: F811
+    """A quarter of the compute units in use and 32 blocks to cut: four segments a head, cut once more from 32 blocks of 64
+    virtual tokens a segment on; more heads or fewer blocks: none."""
+    most, tokens = _cus() // 4 // (d // 16), 64 // r
+    kinds = lambda heads, L: [re.sub(r"<.*, (\d+)(, true, false(, true)?)?>", r"<\1>", n) for n in _names(pf, heads, L, d, d, r)[1:]]
+    maps = lambda rows: 2 * [f"pf::segment_maps_kernel<{rows}>"]
+    assert [n for n in kinds(most, 8 * 32 * tokens) if "compose" not in n] == maps(32) + ["pf::scan_kernel<32>"]
+    assert [n for n in kinds(most, 8 * 30 * tokens) if "compose" not in n] == maps(16) + ["pf::scan_kernel<16>"]
+    assert kinds(most + 1, 8 * 32 * tokens) == ["pf::scan_kernel<16>"]
+    block = max(tokens, 32)                      # (of 128 virtual tokens at rank 4: they are what is counted)
+    assert len(kinds(most, 32 * block)) == 4 and len(kinds(most, 28 * block)) == 1
 
 
 # every branch of the dispatch: B * H, L, d_k, d_v, r, chunk
