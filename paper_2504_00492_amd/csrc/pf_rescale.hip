@@ -59,9 +59,8 @@ __global__ __launch_bounds__(256) void beta_exponential_kernel(const T *__restri
 // halves the sums a lane still holds, so that a lane ends with the sum of one row and takes one beta: one expm1f for all
 // rows of the wavefront instead of one for every four.
 // What bounds it: HBM, 5.9 TB/s (32 heads x 65536 tokens, r = 2, d_k = 128, bf16).  us, one row per 16 lanes / this:
-//   bf16, d_k = 64     24 heads x 4096, r = 2    9.1 / 4.0      3 x 77, r = 2         3.9 / 3.8
+//   bf16, d_k = 64     24 heads x 4096, r = 2    9.1 / 4.0
 //   bf16, d_k = 128    32 x 4096, r = 2         16.3 / 11.9     32 x 65536, r = 2     229 / 182
-//   fp32, d_k = 64, 32 x 2048, r = 1             4.0 / 3.6      d_k = 32              3.9 / 3.6
 // (64 rows of 16 units a wavefront, 16 loads and sums in registers: 19.5 and 212 at d_k = 128, and 6.6 against 3.9 for 128 rows)
 template <typename T, int G>
 __global__ __launch_bounds__(256) void beta_exponential_kernel(const T *__restrict__ K, const T *beta, T *beta_out,
@@ -120,11 +119,21 @@ hipError_t launch_beta_exponential(const void *K, const void *beta, void *beta_o
             hipLaunchKernelGGL(kern, dim3((unsigned)((rows + per - 1) / per)), dim3(256), 0, stream, k, b, o, rows, G);
         };
         const int bytes = dk * (int)sizeof(T);
-        // rows of 8 or 16 units, at any number of them (figures at the kernel); other widths one row per 16 lanes
-        if (bytes == 128) return wide(std::integral_constant<int, 8>{});
-        if (bytes == 256) return wide(std::integral_constant<int, 16>{});
-        void (*kern)(const T *, const T *, T *, long long, int) = beta_exponential_kernel;
         const long long want = (rows + 15) / 16;
+        // Rows of 8 or 16 units, where 16 rows to a workgroup are more workgroups than the chip holds at once (8 a compute
+        // unit): up to there a row per 16 lanes has all rows on their way as well, and sums less in each lane.  us, one row per
+        // 16 lanes / eight loads a lane, inputs in the last-level cache and cold:
+        //                        2048 rows                 32768                     36864                     65536
+        //   bf16, d_k = 64    2.17 / 2.61, 2.99 / 3.81  2.89 / 2.75, 3.85 / 4.29  3.12 / 2.75, 4.86 / 4.34  4.04 / 2.82, 5.76 / 4.72
+        //         d_k = 128   2.16 / 2.76, 3.01 / 4.06  2.88 / 2.96, 4.46 / 4.77  3.10 / 3.16, 5.38 / 5.29  4.15 / 3.47, 6.57 / 6.10
+        //   fp32, d_k = 32    2.11 / 2.56, 2.81 / 3.68  2.78 / 2.69, 3.64 / 4.09  3.03 / 2.70, 4.67 / 4.16  3.82 / 2.82, 5.56 / 4.74
+        //         d_k = 64    2.10 / 2.74, 2.88 / 4.43  2.78 / 2.99, 4.25 / 5.17  3.02 / 3.15, 5.18 / 5.47  3.95 / 3.46, 6.33 / 6.23
+        // Other widths: one row per 16 lanes.
+        if (want > 8LL * device_cu_count()) {
+            if (bytes == 128) return wide(std::integral_constant<int, 8>{});
+            if (bytes == 256) return wide(std::integral_constant<int, 16>{});
+        }
+        void (*kern)(const T *, const T *, T *, long long, int) = beta_exponential_kernel;
         hipLaunchKernelGGL(kern, dim3((unsigned)(want < 65536 ? want : 65536)), dim3(256), 0, stream, k, b, o, rows, dk);
     };
     if (is_bf16) launch((uint16_t)0);

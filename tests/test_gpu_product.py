@@ -115,8 +115,10 @@ def test_beta_exponential_matches_closed_form(pf, dtype, dk):
 # a wavefront takes 64 rows of 128 bytes or 32 of 256: one row, remainders, whole wavefronts and workgroups, one row more
 @pytest.mark.parametrize("dtype,dk", [("f32", 32), ("f32", 64), ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("rows", [1, 7, 31, 33, 63, 65, 128, 256, 257])
-def test_beta_exponential_rows_of_a_wavefront(pf, dtype, dk, rows):
+@pytest.mark.parametrize("beyond", [False, True])                # (beyond what rows one to 16 lanes can have on the chip at once)
+def test_beta_exponential_rows_of_a_wavefront(pf, dtype, dk, rows, beyond):
     import torch
+    rows += 128 * torch.cuda.get_device_properties(0).multi_processor_count if beyond else 0
     from oracle import chunk_flow_ref as cf
     print(f"[case] beta_exponential dtype={dtype} d_k={dk} rows={rows}", flush=True)
     rng = np.random.default_rng(11 * rows + dk)
@@ -135,6 +137,33 @@ def test_beta_exponential_rows_of_a_wavefront(pf, dtype, dk, rows):
     bar = 2e-6 if dtype == "f32" else 2.0 ** -8
     assert np.all(np.abs(got[:rows] - ref) <= bar * np.abs(ref) + 1e-30)
     assert np.all(np.isnan(got[rows:]))                          # nothing behind the last row
+
+
+@pytest.mark.parametrize("dtype,dk", [("f32", 32), ("f32", 64), ("bf16", 64), ("bf16", 128), ("bf16", 32)])
+def test_beta_exponential_by_rows(pf, dtype, dk):
+    """One row to 16 lanes while the chip holds all of them at once, eight rows a lane beyond, for rows of 128 or 256 bytes:
+    the kernel by the name that a profiler prints, and the same bits on both sides of the line."""
+    import re
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    print(f"[case] beta_exponential by rows dtype={dtype} d_k={dk}", flush=True)
+    most = 128 * torch.cuda.get_device_properties(0).multi_processor_count
+    tdt, dt, size = (torch.float32, pf.PF_F32, 4) if dtype == "f32" else (torch.bfloat16, pf.PF_BF16, 2)
+    gen = torch.Generator(device="cuda:0").manual_seed(dk)
+    K = torch.randn(most + 1, dk, generator=gen, device="cuda:0").to(tdt)
+    beta = (3 * torch.rand(most + 1, generator=gen, device="cuda:0")).to(tdt)
+    ran, out = [], []
+    for rows in (most, most + 1):
+        out.append(torch.empty_like(beta))
+        assert pf.pf_beta_exponential(K, beta, out[-1], 1, 1, rows, dk, 1, dt) == pf.PF_OK      # (looks up the kernel)
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+            assert pf.pf_beta_exponential(K, beta, out[-1], 1, 1, rows, dk, 1, dt) == pf.PF_OK
+            torch.cuda.synchronize()
+        ran += [re.search(r"beta_exponential_kernel<([^>]*)>", e.name).group(1) for e in p.events() if "beta_exponential" in e.name]
+    elem = "float" if dtype == "f32" else "unsigned short"
+    assert ran == [elem, f"{elem}, {dk * size // 16}" if dk * size in (128, 256) else elem]
+    assert torch.equal(out[0][:most], out[1][:most])
 
 
 def test_exponential_product_flow_end_to_end(pf):
