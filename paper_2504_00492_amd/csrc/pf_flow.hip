@@ -65,11 +65,15 @@ struct FlowLds {
     static constexpr size_t total = oUn + szUn;
 };
 
-template <int D, int N, int C, bool GEN>
-__device__ __forceinline__ void flow_workgroup(
+// (The body is the kernel itself: inlined into one that chooses between this and the other, the code for 256 virtual tokens
+// came out a tenth shorter and 3.3 % slower in the middle of 36 shapes: 50 heads x 2816 tokens, d = 64, r = 2 71.8 us, this 68.7.)
+template <int D, int N, int C, bool GEN = false>
+__global__ __launch_bounds__(kFlowThreads) void flow_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
-    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift, char *smem)
+    bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift)
 {
+    static_assert(N != 64, "blocks of 64 virtual tokens: one to a wavefront, below");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     // With GEN, K is the array of B rows and `beta` the array of A rows (n x d, like K); the
     // system matrix is Id - M (.) A B^T and P = Mbar (.) Q B^T (Theorem 3.2 as printed).
     using Ld = FlowLds<D, N, C, GEN>;
@@ -388,18 +392,20 @@ struct FlowBody {
     static constexpr int blocks = kWave ? FlowWavePlan::waves : 1;      // that a workgroup holds at a time
     // (waves a SIMD of the body of one wavefront per block: as its operands in registers allow)
     static constexpr int at_once = kWave ? (GEN && D == 128 ? 1 : 2) : (2 * lds <= kMaxLdsBytes ? 2 : 1);
+    using Arrays = void(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int);
+    using ArraysFold = void(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int, int);
+    using Kernel = std::conditional_t<kWave, ArraysFold, Arrays>;
 };
 
+// (the launches tell the two kernels apart by this one's last parameter; N says which of them a name stands for)
 template <int D, int N, int C, bool GEN = false>
-__global__ __launch_bounds__((FlowBody<D, N, C, GEN>::threads), (FlowBody<D, N, C, GEN>::kWave ? FlowBody<D, N, C, GEN>::at_once : 1)) void flow_kernel(
+__global__ __launch_bounds__(FlowWavePlan::threads, (FlowBody<D, N, C, GEN>::at_once)) void flow_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
     bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail, int mask_shift, int fold)
 {
+    static_assert(N == 64, "other blocks: one to a workgroup, above");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    if constexpr (FlowBody<D, N, C, GEN>::kWave)
-        flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, fold, reinterpret_cast<float *>(smem));
-    else
-        flow_workgroup<D, N, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, smem);
+    flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, fold, reinterpret_cast<float *>(smem));
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -419,11 +425,11 @@ template <int D, int N, int C, bool GEN = false>
 static hipError_t launch_flow_instance(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
                                        size_t nchunks, int NC, int tail, bool product, bool fold, hipStream_t stream)
 {
-    void (*kern)(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int, int) = flow_kernel<D, N, C, GEN>;
+    using Body = FlowBody<D, N, C, GEN>;
+    typename Body::Kernel *kern = flow_kernel<D, N, C, GEN>;
     int mask_shift = 0;
     if (!product)
         while ((1 << mask_shift) < N / C) ++mask_shift;
-    using Body = FlowBody<D, N, C, GEN>;
     static_assert(Body::lds <= kMaxLdsBytes, "flow kernel LDS plan exceeds the CU");
     static std::atomic<uint64_t> armed{0};
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), Body::lds);
@@ -435,8 +441,12 @@ static hipError_t launch_flow_instance(const void *Q, const void *K, const void 
     // 8.6 / 6.3; 1024, d = 128, r = 1 on 256 workgroups of four 9.4, on 512 of two 10.5.)
     const size_t want = nchunks <= resident ? nchunks : (nchunks + Body::blocks - 1) / Body::blocks;
     const unsigned grid = (unsigned)(want < resident ? want : resident);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q,
-                       (const bf16 *)K, (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift, fold ? 1 : 0);
+    auto go = [&](auto... more) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(Body::threads), Body::lds, stream, (const bf16 *)Q, (const bf16 *)K,
+                           (const bf16 *)beta, (bf16 *)Tt, (bf16 *)Pt, (int)nchunks, NC, tail, mask_shift, more...);
+    };
+    if constexpr (Body::kWave) go(fold ? 1 : 0);
+    else go();
     return hipGetLastError();
 }
 
@@ -451,7 +461,7 @@ hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, voi
     const int n = chunk * r;
     if (n == 64 && chunk == 16) {                  // halves of a block of 32 tokens
         using Plan = FlowWavePlan;
-        void (*kern)(const bf16 *, const bf16 *, const bf16 *, bf16 *, bf16 *, int, int, int, int, int) = flow_kernel<128, 64, 16>;
+        FlowBody<128, 64, 16, false>::Kernel *kern = flow_kernel<128, 64, 16>;
         if (d == 64) kern = flow_kernel<64, 64, 16>;
         if ((d != 64 && d != 128) || Plan::lds > 65536) return hipErrorInvalidValue;
         const size_t resident = (size_t)device_cu_count() * 2, want = (nchunks + Plan::waves - 1) / Plan::waves;
