@@ -18,18 +18,20 @@
 // from the copies of S and U_eff that the state waves leave in LDS in operand form.  One barrier per block.
 //
 // The flow kernel of the same call hands over -T diag(beta), rounded once (FOLD): beta and its widening are gone from the
-// state wave, and V enters as a product with -Id: 177 instructions a block at d = 128 where there were 235.  Whole forward,
-// 24 heads x 4096 tokens, d = 64, r = 2 89 -> 65 us, 4 heads x 32768, d = 128 277 -> 240 (both with the flow of
-// pf_flow_wave.h).  The split entry points hand over T itself and take the form without it.
+// state wave, and V enters as a product with -Id: 177 instructions a block at d = 128 where there were 235.  P is not handed
+// over either: the readers hold Q of a block as operands and its K lies in the ring, so they build P of the block that the
+// state is at, the same products in the same order.  The flow then reads K and beta and writes T (22 KB a block of d = 128,
+// r = 2 instead of 33), the chain has 24 requests of 328 fewer.  Whole forward, us, P handed over / built: 32 heads x 65536,
+// d = 128, r = 2 2068 / 1867 (flow 415 / 275, scan 1657 / 1595), 32 x 8192, r = 4 439 / 404, 24 x 4096, d = 64, d_v = 128, r = 2
+// 98.9 / 89.4, 32 x 3001, r = 1 74.2 / 73.6 (its Q then comes from HBM in the scan).  The split entry points hand over T itself
+// and P and take the form without either.
 //
-// What bounds it: the loads.  At d = 128 with the readout, 16 rows and 256 workgroups a block takes 0.79 us, because its 35 KB
-// come in at 18 bytes a cycle (328 requests of 128 bytes, 114 of them on their way, 667 cycles each); at d = 64 a block of
-// 24 heads x 4096 tokens, d_v = 128, r = 2 takes 0.63 us where its inputs come from HBM, 0.40 where they lie in the last-level
-// cache, and of 32 x 2048, r = 1 0.85 and 0.65: the state wave takes no more than the lower.  The stagers wait to
-// issue while the state wave waits at the barrier.  A compute unit has at most about 128 L2
-// lines on their way: 12 bytes a cycle where they come from HBM, 20 from the last-level cache, 42 from L2; a block's loads
-// alone take 0.79 us, 0.53 and 0.45, the state wave alone less.  Asking for a block's lines ahead of time in part (a wave, or
-// workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more elsewhere.
+// What bounds it: the loads.  At d = 128 with the readout, 16 rows and 256 workgroups a block takes 0.78 us, because its 32 KB
+// come in at 17 bytes a cycle (304 requests of 128 bytes, some 114 of them on their way); at d = 64 a block of
+// 24 heads x 4096 tokens, d_v = 128, r = 2 takes 0.57 us.  A compute unit has at most about 128 L2 lines on their way: 12 bytes
+// a cycle where they come from HBM, 20 from the last-level cache, 42 from L2.  Asking for a block's lines ahead of time in
+// part (a wave, or workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more
+// elsewhere.
 //
 // Two tiles to a workgroup (scan_two_tiles and the segments) read K, Q, T, P once for 32 rows: a block takes hardly longer.
 // With at least 256 such workgroups the split of pf_scan.hip is ahead again (64 heads x 4096 tokens, d = 128, r = 2: whole
@@ -273,27 +275,32 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     }
 
     // ------------------------------------------------------------------ helper waves
-    constexpr std::integral_constant<int, 0> k0{};
-    constexpr std::integral_constant<int, 1> k1{};
-    constexpr std::integral_constant<int, 2> k2{};
-    // Blocks in groups of three (one per register set of the readers) without a branch inside: a branch around a load or
-    // store makes every later wait assume the shorter queue.
+    // Blocks in groups of one per register set of the readers, without a branch inside: a branch around a load or store makes
+    // every later wait assume the shorter queue.
+    constexpr int kSets = FOLD ? 4 : 3;                              // blocks of Q (and P) on their way in register sets
     auto for_blocks = [&](auto f) {
         int ch = 0;
 #pragma unroll 1
-        for (; ch + 3 <= NC; ch += 3) {
-            f(ch, k0);
-            f(ch + 1, k1);
-            f(ch + 2, k2);
+        for (; ch + kSets <= NC; ch += kSets) {
+            f(ch, std::integral_constant<int, 0>{});
+            f(ch + 1, std::integral_constant<int, 1>{});
+            f(ch + 2, std::integral_constant<int, 2>{});
+            if constexpr (kSets == 4) f(ch + 3, std::integral_constant<int, 3>{});
         }
-        if (ch < NC) f(ch, k0);
-        if (ch + 1 < NC) f(ch + 1, k1);
+        if (ch < NC) f(ch, std::integral_constant<int, 0>{});
+        if (ch + 1 < NC) f(ch + 1, std::integral_constant<int, 1>{});
+        if constexpr (kSets == 4) {
+            if (ch + 2 < NC) f(ch + 2, std::integral_constant<int, 2>{});
+        }
     };
     auto clamp = [&](int ch) { return c0 + (size_t)(ch < NC ? ch : NC - 1); };
 
-    if (wave < NSS + NSt) {
+    // A workgroup's wavefronts go round the four SIMDs: the readers, who have products of their own, come right behind the state
+    // waves, and the stagers share what SIMDs are left to share.
+    constexpr int NRd = Pl::readers;
+    if (wave >= NSS + NRd) {
         // The stagers' loads go straight to LDS.  Pieces of 64 x 16 bytes, dealt to the stagers one by one.
-        const int H = wave - NSS;
+        const int H = wave - NSS - NRd;
         constexpr int VPR = D / 8, PPR = TV / 8;                     // 16-byte units per row of K, of the V tile
         constexpr int KQ = N * VPR / 64 / NSt, VQ = N * PPR / 64 / NSt, TQ = NT / NSt;
         constexpr int kLoads = KQ + VQ + TQ + (FOLD ? 0 : 1);                     // loads of a stager per block
@@ -359,12 +366,12 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         return;
     }
 
-    // readers: token tiles w and CT - 1 - w (of two tiles: w; of one: one reader), a block behind the state
+    // readers: token tiles w and CT - 1 - w (of two tiles: w; of one: one reader), a block behind the state.  FOLD: P of the
+    // block that the state is at is built from the rows of K in its slot and the Q in registers, else it comes from memory.
     auto reader = [&](auto Wc) {
         constexpr int W = decltype(Wc)::value, TN = CT < 2 ? 1 : CT / 2;
         constexpr auto tok_tile = [](int i) constexpr { return i == 0 ? W : CT - 1 - W; };
-        constexpr int kSets = 3;                                     // blocks of Q and P on their way in register sets
-        bf16x8 bQ[kSets][TN][NKS], bP[kSets][TN][NKT];               // (P tiles above the causal mask do not exist)
+        bf16x8 bQ[kSets][TN][NKS], bP[FOLD ? 1 : kSets][TN][NKT];    // (P tiles above the causal mask do not exist)
         auto fetch = [&](int ch, auto Sc) {
             constexpr int S = decltype(Sc)::value;
             const size_t cid = clamp(ch);
@@ -375,18 +382,63 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                     bQ[S][i][ks] = ld8(Q + cid * (size_t)C * D + (16 * tok_tile(i) + r16) * D + 32 * ks + 8 * g);
 #pragma unroll
                 for (int kt = 0; kt < NKT; ++kt)
-                    if (kt < p_ksteps(R, tok_tile(i))) bP[S][i][kt] = ld8(Pt + cid * (size_t)C * N + full_tile_offset(NKT, tok_tile(i), kt) + lane * 8);
+                    if (!FOLD && kt < p_ksteps(R, tok_tile(i)))
+                        bP[FOLD ? 0 : S][i][kt] = ld8(Pt + cid * (size_t)C * N + full_tile_offset(NKT, tok_tile(i), kt) + lane * 8);
             }
         };
-        if (NC > 0) {
-            fetch(0, k0);
-            fetch(1, k1);
-            fetch(2, k2);
-        }
+        int kr0[NKS];                                                // row operand of K by k-step (as the state waves')
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) kr0[ks] = r16 * D * 2 + ((4 * ks + g) ^ k_swizzle<D>(r16)) * 16;
+        // P = Mbar (.) Q K^T of the block in `base`, from K Q^T: two accumulator tiles, one upon the other, are a tile of P
+        auto build = [&](int base, auto Sc) {
+            constexpr int S = decltype(Sc)::value;
+            constexpr int last = TN > 1 && tok_tile(TN - 1) > tok_tile(0) ? tok_tile(TN - 1) : tok_tile(0);
+            f32x4 p[TN][MT];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                if (16 * mt >= R * (16 * last + 16)) continue;       // later than the last of the tokens
+                bf16x8 k[NKS];
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) k[ks] = ld8(reinterpret_cast<const bf16 *>(smem + base + kr0[ks] + 16 * mt * D * 2));
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    const int tt = tok_tile(i);
+                    if (16 * mt >= R * (16 * tt + 16)) continue;
+                    p[i][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks) p[i][mt] = mfma16(k[ks], bQ[S][i][ks], p[i][mt]);
+                    if (16 * mt + 15 >= R * 16 * tt) {               // readout mask, inclusive in time
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            p[i][mt][e] = (16 * mt + 4 * g + e) / R > 16 * tt + r16 ? 0.0f : p[i][mt][e];
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int kt = 0; kt < NKT; ++kt)
+                    if (kt < p_ksteps(R, tok_tile(i))) {
+                        const bool both = 16 * (2 * kt + 1) < R * (16 * tok_tile(i) + 16);
+                        bP[0][i][kt] = join(cvt4(p[i][2 * kt]), both ? cvt4(p[i][2 * kt + 1]) : cvt4(f32x4{0.f, 0.f, 0.f, 0.f}));
+                    }
+        };
+        auto sets = [&](auto f) {
+            f(0, std::integral_constant<int, 0>{});
+            f(1, std::integral_constant<int, 1>{});
+            f(2, std::integral_constant<int, 2>{});
+            if constexpr (kSets == 4) f(3, std::integral_constant<int, 3>{});
+        };
+        if (NC > 0) sets(fetch);
         __syncthreads();
+        if constexpr (FOLD) {
+            if (NC > 0) build(0, std::integral_constant<int, 0>{});
+        }
+        int slot = 0;
         for_blocks([&](int ch, auto Sc) {
             constexpr int S = decltype(Sc)::value;
             __syncthreads();
+            slot = slot == kRing - 1 ? 0 : slot + 1;                 // of block ch + 1 (beyond the last block: not used)
             bf16 *Oc = O + chain * (size_t)tail * dv + ((c0 + ch) * (size_t)C + r16) * dv + tile * TV + 4 * g;
             const bf16 *X = Xs + (ch & 1) * XB + lane * 8, *U = Us + (ch & 1) * UB + lane * 8;
             f32x4 o[NSS][TN];
@@ -404,7 +456,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                     for (int ks = 0; ks < NKS; ++ks) o[w][i] = mfma16(x[ks], bQ[S][i][ks], o[w][i]);
 #pragma unroll
                     for (int kt = 0; kt < NKT; ++kt)
-                        if (kt < p_ksteps(R, tok_tile(i))) o[w][i] = mfma16(u[kt], bP[S][i][kt], o[w][i]);
+                        if (kt < p_ksteps(R, tok_tile(i))) o[w][i] = mfma16(u[kt], bP[FOLD ? 0 : S][i][kt], o[w][i]);
                 }
             }
             LDS_FENCE();
@@ -415,11 +467,12 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
 #pragma unroll
                 for (int w = 0; w < NSS; ++w) st4(Oc + (size_t)16 * tok_tile(i) * dv + 16 * w, cvt4(o[w][i]));
             LDS_FENCE();
+            if constexpr (FOLD) build(slot * (int)Pl::slot, std::integral_constant<int, (S + 1) % kSets>{});
         });
     };
     if constexpr (RO) {
-        if (Pl::readers == 1 || wave == NSS + NSt) reader(k0);
-        else if constexpr (Pl::readers == 2) reader(k1);
+        if (NRd == 1 || wave == NSS) reader(std::integral_constant<int, 0>{});
+        else if constexpr (NRd == 2) reader(std::integral_constant<int, 1>{});
     }
 }
 

@@ -405,7 +405,11 @@ __global__ __launch_bounds__(FlowWavePlan::threads, (FlowBody<D, N, C, GEN>::at_
 {
     static_assert(N == 64, "other blocks: one to a workgroup, above");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    flow_wave<D, C, GEN>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, fold, reinterpret_cast<float *>(smem));
+    float *const lds = reinterpret_cast<float *>(smem);
+    if constexpr (!GEN) {
+        if (fold) return flow_wave<D, C, false, true>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, lds);
+    }
+    flow_wave<D, C, GEN, false>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, lds);
 }
 
 // ---------------------------------------------------------------------------- host side
