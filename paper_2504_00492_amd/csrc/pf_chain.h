@@ -116,8 +116,9 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
 
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
-    const int tile = blockIdx.x / nchains;             // workgroups of one head: one XCD (see the launcher)
-    const size_t chain = blockIdx.x % nchains;
+    const unsigned tiles = gridDim.x / (unsigned)nchains, work = xcd_consecutive(blockIdx.x, gridDim.x);
+    const int tile = work % tiles;                     // the tiles of a head: one XCD
+    const size_t chain = work / tiles;
     const size_t c0 = PAIR ? chain * (size_t)stride + (size_t)first : chain * (size_t)NC;
     // `tail` tokens of every head belong to another kernel
     Q += chain * (size_t)tail * D;

@@ -56,6 +56,14 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b)
     return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
+// Workgroups go round the eight XCDs, each with an L2 of its own.  Which of `n` pieces of work this workgroup takes, so that
+// every XCD has consecutive ones: what neighbours both read then lies in one L2.
+__device__ __forceinline__ unsigned xcd_consecutive(unsigned b, unsigned n)
+{
+    const unsigned x = b & 7, each = n >> 3, more = n & 7;
+    return x * each + (x < more ? x : more) + (b >> 3);
+}
+
 // fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32 on gfx950).
 __device__ __forceinline__ bf16x4 cvt4(f32x4 v)
 {

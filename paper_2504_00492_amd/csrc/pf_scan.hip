@@ -140,10 +140,10 @@ __device__ __forceinline__ void split_scan(
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane0 = threadIdx.x & 63;
 
-    // Workgroups of one (b, h) are nchains apart in blockIdx, hence on the same XCD (block ids
-    // go round-robin over the 8 XCDs) and share that XCD's L2 for K, Q, T and P, which they all read.
-    const int tile = blockIdx.x / nchains;
-    const size_t chain = blockIdx.x % nchains;
+    // The workgroups of one (b, h) share K, Q, T, P through their XCD's L2.
+    const unsigned tiles = gridDim.x / (unsigned)nchains, work = xcd_consecutive(blockIdx.x, gridDim.x);
+    const int tile = work % tiles;
+    const size_t chain = work / tiles;
     const int dv0 = tile * TV;
     const size_t c0 = chain * (size_t)NC;
     // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: in Q, K,
