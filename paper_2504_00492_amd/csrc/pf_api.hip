@@ -325,13 +325,14 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
     const float *state = S0;                       // state entering the tail
     {
         float *Smid = tail ? reinterpret_cast<float *>(ws + wp.oS) : S_L;
-        const void *Tt = ws + wp.oT, *Pt = ws + wp.oP;
+        const void *Tt = ws + wp.oT;
         const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
         const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
         const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r) || pf::scan_two_tiles(heads, d_v, sub * r);
+        void *const Pt = fold || pf::scan_wide_chain(heads, d_v, sub * r) ? nullptr : ws + wp.oP;   // (nullptr: the scan builds P)
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, Pt, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             // Segment-parallel scan (no tail here, and blocks of 64 virtual tokens: pick_block): every segment of every
             // head is a chain of its own.  What a segment does to a zero state and its propagator, then the composition
@@ -349,7 +350,7 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
                       : pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, Sin, O, nullptr, vh, Ls, d_k, r, sub, s, true);
             return e == hipSuccess ? PF_OK : PF_ERR_LAUNCH;
         } else {
-            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, ws + wp.oP, heads, L, d_k, r, sub, s, product, fold, block);
+            e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, Pt, heads, L, d_k, r, sub, s, product, fold, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;
             e = pf::launch_chunk_scan(Q, K, V, beta, Tt, Pt, S0, O, Smid, heads, L, d_k, r, sub, s, fold, d_v, block);
             if (e != hipSuccess) return PF_ERR_LAUNCH;

@@ -1,6 +1,6 @@
-// Body of the scan kernel for flow blocks of 64 virtual tokens and tiles of 16 rows of S (the delta rule), with at most
-// one workgroup per compute unit (scan_chain, scan_two_tiles in pf_scan.hip): one wavefront runs the whole chain
-// R -> U_eff -> S of 16 rows by itself, out of registers.
+// Body of the scan kernel for flow blocks of 64 virtual tokens (the delta rule): one wavefront runs the whole chain
+// R -> U_eff -> S of 16 rows by itself, out of registers.  A workgroup has one tile of 16 rows or two (scan_chain, scan_two_tiles and
+// scan_wide_chain in pf_scan.hip).
 //
 // With S^T as accumulator tiles (rows d_k, columns the 16 rows of S) every product of a block takes the result of
 // the one before it as its B operand, and an accumulator tile is a B operand lane for lane (pf_common.h):
@@ -33,9 +33,12 @@
 // part (a wave, or workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more
 // elsewhere.
 //
-// Two tiles to a workgroup (scan_two_tiles and the segments) read K, Q, T, P once for 32 rows: a block takes hardly longer.
-// With at least 256 such workgroups the split of pf_scan.hip is ahead again (64 heads x 4096 tokens, d = 128, r = 2: whole
-// forward 172.5 us against 176.8).  With 128 virtual tokens a block the operands of one wave do not fit its registers:
+// Two tiles to a workgroup (scan_two_tiles, scan_wide_chain and the segments) read K, Q, T, P once for 32 rows: a block takes
+// hardly longer (0.98 us at d = 128, r = 2 and 256 workgroups; with every read from L2 0.75, which is LDS: some 165 KB a block).
+// In rounds of one workgroup a compute unit it is ahead of the split of pf_scan.hip, two of which fit a compute unit, as well, since
+// P is built here (64 heads x 4096 tokens, d = 128, r = 2: whole forward 181 us / 161; 128 heads 357 / 320).  Those calls take T
+// itself: -T diag(beta) rounds a product that T R adds to exactly once more, 0.5 % further from 64 bits, and beta costs the
+// state waves 1 % of the time.  With 128 virtual tokens a block the operands of one wave do not fit its registers:
 // blocks of rank 4 run as two halves (32 heads x 8192 tokens, r = 4 529 -> 436 us).
 #pragma once
 #include "pf_common.h"
@@ -103,7 +106,8 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 // beta, no factor, and V goes in as a product with -Id.
 // PAIR: `stride` blocks a chain, of which this call takes NC from `first` on.  The rows of the state are in and out at SL, those
 // of the propagator at SP; from the first block on they start as zeros and as the identity.
-template <int D, int N, int C, int TV, bool RO, bool FOLD, bool PAIR = false>
+// BUILD: P is built by the readers, else Pt holds it.
+template <int D, int N, int C, int TV, bool RO, bool FOLD, bool PAIR = false, bool BUILD = FOLD>
 __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const bf16 *V, const bf16 *beta,
                                            const bf16 *Tt, const bf16 *Pt, const float *S0, bf16 *O, float *SL,
                                            int nchains, int NC, int tail, int dv, char *smem,
@@ -177,7 +181,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         bf16x8 aK[MT][NKS], tA[NT], aT[NKT][MD];
         bf16x4 vt[MT];
         u32x4 bt[FOLD ? 1 : MT];                       // bf16 in the low half
-        f32x4 vneg[FOLD ? 1 : MT], bw[FOLD ? 1 : MT];  // -V and beta, widened
+        f32x4 bw[FOLD ? 1 : MT];                       // beta, widened
         bf16x8 nI[2];                                  // -Id on the first, on the second half of a k-step
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -199,10 +203,8 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         };
         auto widen = [&](int mt) {
             if constexpr (FOLD) return;
-            const u32x2 m = __builtin_bit_cast(u32x2, vt[mt]) ^ 0x80008000u;
-            vneg[mt] = __builtin_bit_cast(f32x4, u32x4{m[0] << 16, m[0] & 0xffff0000u, m[1] << 16, m[1] & 0xffff0000u});
             bw[mt] = __builtin_bit_cast(f32x4, bt[mt] << 16);
-            asm volatile("" : "+v"(vneg[mt]), "+v"(bw[mt]));   // here, not at the use
+            asm volatile("" : "+v"(bw[mt]));               // here, not at the use
         };
         __syncthreads();
 #pragma unroll
@@ -227,10 +229,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 else bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
             };
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                if constexpr (FOLD) acc[mt] = mfma16(nI[mt & 1], join(vt[mt & ~1], vt[mt | 1]), f32x4{0.f, 0.f, 0.f, 0.f});
-                else acc[mt] = vneg[mt];
-            }
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(nI[mt & 1], join(vt[mt & ~1], vt[mt | 1]), f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 const int mt = 2 * (i / (2 * NKS)) + (i & 1), ks = (i / 2) % NKS;
@@ -278,7 +277,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     // ------------------------------------------------------------------ helper waves
     // Blocks in groups of one per register set of the readers, without a branch inside: a branch around a load or store makes
     // every later wait assume the shorter queue.
-    constexpr int kSets = FOLD ? 4 : 3;                              // blocks of Q (and P) on their way in register sets
+    constexpr int kSets = BUILD ? 4 : 3;                              // blocks of Q (and P) on their way in register sets
     auto for_blocks = [&](auto f) {
         int ch = 0;
 #pragma unroll 1
@@ -367,12 +366,12 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         return;
     }
 
-    // readers: token tiles w and CT - 1 - w (of two tiles: w; of one: one reader), a block behind the state.  FOLD: P of the
+    // readers: token tiles w and CT - 1 - w (of two tiles: w; of one: one reader), a block behind the state.  BUILD: P of the
     // block that the state is at is built from the rows of K in its slot and the Q in registers, else it comes from memory.
     auto reader = [&](auto Wc) {
         constexpr int W = decltype(Wc)::value, TN = CT < 2 ? 1 : CT / 2;
         constexpr auto tok_tile = [](int i) constexpr { return i == 0 ? W : CT - 1 - W; };
-        bf16x8 bQ[kSets][TN][NKS], bP[FOLD ? 1 : kSets][TN][NKT];    // (P tiles above the causal mask do not exist)
+        bf16x8 bQ[kSets][TN][NKS], bP[BUILD ? 1 : kSets][TN][NKT];    // (P tiles above the causal mask do not exist)
         auto fetch = [&](int ch, auto Sc) {
             constexpr int S = decltype(Sc)::value;
             const size_t cid = clamp(ch);
@@ -383,8 +382,8 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                     bQ[S][i][ks] = ld8(Q + cid * (size_t)C * D + (16 * tok_tile(i) + r16) * D + 32 * ks + 8 * g);
 #pragma unroll
                 for (int kt = 0; kt < NKT; ++kt)
-                    if (!FOLD && kt < p_ksteps(R, tok_tile(i)))
-                        bP[FOLD ? 0 : S][i][kt] = ld8(Pt + cid * (size_t)C * N + full_tile_offset(NKT, tok_tile(i), kt) + lane * 8);
+                    if (!BUILD && kt < p_ksteps(R, tok_tile(i)))
+                        bP[BUILD ? 0 : S][i][kt] = ld8(Pt + cid * (size_t)C * N + full_tile_offset(NKT, tok_tile(i), kt) + lane * 8);
             }
         };
         int kr0[NKS];                                                // row operand of K by k-step (as the state waves')
@@ -432,7 +431,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         };
         if (NC > 0) sets(fetch);
         __syncthreads();
-        if constexpr (FOLD) {
+        if constexpr (BUILD) {
             if (NC > 0) build(0, std::integral_constant<int, 0>{});
         }
         int slot = 0;
@@ -457,7 +456,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                     for (int ks = 0; ks < NKS; ++ks) o[w][i] = mfma16(x[ks], bQ[S][i][ks], o[w][i]);
 #pragma unroll
                     for (int kt = 0; kt < NKT; ++kt)
-                        if (kt < p_ksteps(R, tok_tile(i))) o[w][i] = mfma16(u[kt], bP[FOLD ? 0 : S][i][kt], o[w][i]);
+                        if (kt < p_ksteps(R, tok_tile(i))) o[w][i] = mfma16(u[kt], bP[BUILD ? 0 : S][i][kt], o[w][i]);
                 }
             }
             LDS_FENCE();
@@ -468,7 +467,7 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
 #pragma unroll
                 for (int w = 0; w < NSS; ++w) st4(Oc + (size_t)16 * tok_tile(i) * dv + 16 * w, cvt4(o[w][i]));
             LDS_FENCE();
-            if constexpr (FOLD) build(slot * (int)Pl::slot, std::integral_constant<int, (S + 1) % kSets>{});
+            if constexpr (BUILD) build(slot * (int)Pl::slot, std::integral_constant<int, (S + 1) % kSets>{});
         });
     };
     if constexpr (RO) {

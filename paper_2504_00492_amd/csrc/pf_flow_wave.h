@@ -88,20 +88,20 @@ __device__ __forceinline__ void substitute_rows(const float (&n)[16], float (&t)
     }
 }
 
-// FOLD: -T diag(beta) is handed over, rounded once, and no P: the chain in one wavefront takes neither beta nor P (pf_chain.h).
-template <int D, int C, bool GEN, bool FOLD>
+// FOLD: -T diag(beta) is handed over, rounded once, in the place of T.  PT: P too (pf_chain.h says who builds it else).
+template <int D, int C, bool GEN, bool FOLD, bool PT>
 __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ beta,
                                           bf16 *__restrict__ Tt, bf16 *__restrict__ Pt, int nchunks, int NC, int tail,
                                           int mask_shift, float *smem)
 {
-    static_assert(!(GEN && FOLD), "the delta rule's form");
+    static_assert(!GEN || (!FOLD && PT), "the delta rule's forms");
     constexpr int N = 64, R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, CT = C / 16, NP = FlowWavePlan::NP;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
     float *Ns = smem + wave * FlowWavePlan::floats, *bs = Ns + 4 * 16 * NP;
     constexpr auto tri = [](int i, int j) constexpr { return i * (i + 1) / 2 + j; };   // tiles on and below the diagonal
 
-    bf16x8 aK[MT][NKS], aA[GEN ? MT : 1][NKS], bQ[FOLD ? 1 : CT][NKS];
+    bf16x8 aK[MT][NKS], aA[GEN ? MT : 1][NKS], bQ[PT ? CT : 1][NKS];
     bf16 breg = (bf16)0.0f;
     // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: block c of the compact
     // numbering starts (c / NC) * tail tokens further on in Q, K, beta.
@@ -116,7 +116,7 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
                 aK[m][ks] = ld8(Kg + at + 16 * m * D + 32 * ks);
                 if constexpr (GEN) aA[m][ks] = ld8(beta + (c * N + skew * R) * D + at + 16 * m * D + 32 * ks);
             }
-        if constexpr (!FOLD) {
+        if constexpr (PT) {
 #pragma unroll
             for (int t = 0; t < CT; ++t)
 #pragma unroll
@@ -159,7 +159,7 @@ __device__ __forceinline__ void flow_wave(const bf16 *__restrict__ Q, const bf16
             }
         // ---- P = Mbar (.) Q K^T, from K Q^T
 #pragma unroll
-        for (int t = 0; t < (FOLD ? 0 : CT); ++t)
+        for (int t = 0; t < (PT ? CT : 0); ++t)
 #pragma unroll
             for (int kt = 0; kt < NKT; ++kt) {
                 if (kt >= p_ksteps(R, t)) continue;

@@ -48,6 +48,7 @@ hipError_t launch_generic_drivers(const void *Q, const void *A, const void *Atil
 bool mfma_instance_exists(int d, int n, int chunk);
 // fold (blocks of 64 virtual tokens): Tt receives -T diag(beta), rounded once, the form that the chain in one wavefront
 // takes (launch_chunk_scan, folded, where scan_chain or scan_two_tiles says that it serves the call) instead of T and beta.
+// Pt: NULL where the scan builds P itself (the same calls, and those of scan_wide_chain).
 hipError_t launch_chunk_flow(const void *Q, const void *K, const void *beta, void *Tt, void *Pt,
                              int heads, int L, int d, int r, int chunk, hipStream_t stream,
                              bool product = false, bool fold = false, int unit = 0);
@@ -82,6 +83,8 @@ int scan_dv_tile(int heads, int dv, int n);
 bool scan_chain(int heads, int dv, int n);
 // whether more tiles of 16 rows than that run it two to a workgroup (launch_chunk_scan, folded)
 bool scan_two_tiles(int heads, int dv, int n);
+// whether still more of them do, in rounds (launch_chunk_scan, T itself and no P)
+bool scan_wide_chain(int heads, int dv, int n);
 
 // ---- fused forward (pf_fused.hip): flow and scan of every block in one kernel, d = d_k = d_v,
 // n = chunk * r in {64, 128}.  Takes the first L / chunk whole blocks of every head.  Tdump / Pdump

@@ -12,8 +12,9 @@
 //
 // Only R -> U_eff -> S_c+1 is a chain from one chunk to the next; the readout O_c hangs off it.
 // Two bodies follow from that.  The chain in one wavefront (pf_chain.h) takes tiles of 16 rows with blocks of 64
-// virtual tokens, one or two to a workgroup, up to one workgroup per compute unit (scan_chain, scan_two_tiles).  The
-// split over several wavefronts below takes the rest: other blocks, general drivers, more workgroups, d_v = 16 mod 32.
+// virtual tokens, one or two to a workgroup (scan_chain, scan_two_tiles, scan_wide_chain).  The split over several
+// wavefronts below takes the rest: other blocks, general drivers, the split entry points with more workgroups than compute units,
+// and d_v = 16 mod 32 with more tiles than those.
 //
 // The workgroup of the split has two kinds of wavefronts, one of each per SIMD:
 //
@@ -668,13 +669,13 @@ __device__ __forceinline__ void split_scan(
     }
 }
 
-// Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for tiles of 16
-// rows and 64 virtual tokens, the split above for the rest; OTHER: the other one, the split at 16 rows, the chain with two
-// tiles at 32 (scan_chain and scan_two_tiles say when).
+// Which body serves an instance, with its LDS and workgroup size: the chain in one wavefront (pf_chain.h) for blocks of 64
+// virtual tokens, one tile of 16 rows to a workgroup or two, the split above for the rest.  OTHER: at 16 rows the split, at 32 the
+// chain on -T diag(beta) instead of T (scan_chain and scan_two_tiles say when).
 template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER = false>
 struct ScanBody {
     using Chain = ChainPlan<D, N, C, TV, RO>;
-    static constexpr bool kChain = !GEN && Chain::kServes && (TV == 16) != OTHER;
+    static constexpr bool kChain = !GEN && Chain::kServes && (TV == 32 || !OTHER);
     static constexpr size_t lds = kChain ? Chain::total : ScanLds<D, N, C, TV, GEN>::total;
     static constexpr int threads = kChain ? Chain::threads : kScanThreads;
 };
@@ -690,12 +691,14 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (ScanBody<D, N, C, TV, RO, GEN>::kChain)
-        chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+        chain_scan<D, N, C, TV, RO, TV == 16, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
         split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
-// the other body of a shape that both serve: the split at 16 rows, the chain with two tiles of 16, a state wave each, at 32
+// 16 rows: the other body, the split.  32: the chain with two tiles on -T diag(beta), which calls with at most one workgroup a compute
+// unit take; those with more take T itself, the form that the split had before them and is as far from 64 bits as that was
+// (with -T diag(beta) O and S_L of 64 heads x 1024 tokens, d = 128, r = 2 0.5 % further).
 template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
@@ -704,7 +707,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(
 {
     static_assert(OTHER && !GEN && ChainPlan<D, N, C, TV, RO>::kServes, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    if constexpr (TV == 32)
+    if constexpr (ScanBody<D, N, C, TV, RO, GEN, true>::kChain)
         chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
         split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
@@ -731,6 +734,18 @@ __global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
     static_assert(ScanBody<D, N, C, 16, true, false>::kChain, "the other shapes take T as it is");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     chain_scan<D, N, C, 16, true, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+}
+
+// and the split at 32 rows on it
+template <int D, int N, int C>
+__global__ __launch_bounds__(kScanThreads) void scan_plain_wide_kernel(
+    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
+    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
+{
+    static_assert(ScanBody<D, N, C, 32, true, false>::kChain, "the other shapes take T as it is");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    split_scan<D, N, C, 32, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -776,6 +791,17 @@ static hipError_t launch_scan_plain(const void *Q, const void *K, const void *V,
                   dv, stream);
 }
 
+template <int D, int N, int C>
+static hipError_t launch_scan_plain_wide(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+                                         const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv, hipStream_t stream)
+{
+    constexpr size_t lds = ScanLds<D, N, C, 32, false>::total;
+    static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
+    static std::atomic<uint64_t> armed{0};
+    return launch(scan_plain_wide_kernel<D, N, C>, armed, 32, kScanThreads, lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail,
+                  dv, stream);
+}
+
 int scan_dv_tile(int heads, int dv, int n)
 {
     // 32 rows when that already gives at least one workgroup per CU, else 16 rows (twice the
@@ -785,17 +811,23 @@ int scan_dv_tile(int heads, int dv, int n)
 }
 
 // A compute unit holds one workgroup of the chain (the ring fills its LDS; at d = 64 a ring of four slots, 75 KB, took
-// the same time within 1 %), but two of the split: the chain where every workgroup has a compute unit of its own, and beyond
-// with two tiles to a workgroup where d_v allows, the split in the rest.  Whole forward, 4096 tokens, us, split / chain of one
-// tile / of two:
+// the same time within 1 %), but two of the split: the chain with one tile where every workgroup has a compute unit of its own, and
+// beyond with two tiles to a workgroup, in rounds where there are more of those than compute units, wherever d_v allows; the
+// split where it does not (d_v = 16 mod 32).  Whole forward, 4096 tokens, us, split / chain of one tile / of two, before P was
+// built by the readers:
 //                              d = 64, r = 2          d = 64, r = 1       d = 128, r = 2         d = 128, r = 1
 //   256 tiles               113 / 110 /  -        30.6 / 29.2 / - (*)   117 /  99 /  -          79 /  74 /  -
 //   288                     142 / 162 / 129         96 /  98 / 70       191 / 202 / 136        135 / 136 /  86
 //   384                     183 / 254 / 153              -              207 / 252 / 150        133 / 137 /  87
 //   480                     234 / 279 / 175         70 /  69 / 49 (*)   288 / 298 / 188        183 / 184 / 122     ((*) 2048 tokens)
-// and r = 4 (the split on blocks of 128 virtual tokens, the chain on halves): d = 128, 288 tiles 498 / 416 / 252, 480
-// 655 / 531 / 309; d = 64, 384 tiles 587 / 438 / 261.  From 256 workgroups of two tiles on (64 heads, d = 128, r = 2) the
-// split of 32 rows is ahead again, 172.5 / 176.8.
+// and now, split (on T itself, with P from the flow) / two tiles:
+//   512                     182 / 151              62.7 / 51.6 (*)     187 / 166              124 / 108
+//   600                     266 / 238              92.4 / 79.7 (*)     300 / 269              203 / 186
+//   800                     307 / 264                  -               324 / 291                  -
+//   1024                    373 / 309             122.3 / 98.4 (*)     357 / 315              252 / 212
+//   1536, 2048                  -                      -           531 / 471, 720 / 643            -
+// r = 4 (the split on blocks of 128 virtual tokens, the chain on halves): d = 128, 288 tiles 498 / 416 / 252, 480
+// 655 / 531 / 309; d = 64, 384 tiles 587 / 438 / 261.
 bool scan_chain(int heads, int dv, int n)
 {
     return n == 64 && scan_dv_tile(heads, dv, n) == 16 && (long long)heads * (dv / 16) <= (long long)device_cu_count();
@@ -806,22 +838,29 @@ bool scan_two_tiles(int heads, int dv, int n)
     return n == 64 && dv % 32 == 0 && scan_dv_tile(heads, dv, n) == 16 && !scan_chain(heads, dv, n);
 }
 
+bool scan_wide_chain(int heads, int dv, int n) { return n == 64 && scan_dv_tile(heads, dv, n) == 32; }
+
 template <int D, int N, int C, int TV>
 static hipError_t launch_scan_instance(const void *Q, const void *K, const void *V, const void *beta,
                                        const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
                                        int heads, int NC, int tail, int dv, bool folded, hipStream_t stream)
 {
-    if constexpr (ScanBody<D, N, C, TV, true, false>::kChain) {
+    if constexpr (!ScanBody<D, N, C, TV, true, false>::kChain) {
+        return folded ? hipErrorInvalidValue
+                      : launch_scan<D, N, C, TV>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    } else if constexpr (TV == 32) {               // a workgroup to a compute unit and more
+        if (folded) return hipErrorInvalidValue;
+        return Pt ? launch_scan_plain_wide<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream)
+                  : launch_scan<D, N, C, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    } else {
         if (folded && scan_two_tiles(heads, dv, N))
             return launch_scan<D, N, C, 32, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
         if (!scan_chain(heads, dv, N))
             return folded ? hipErrorInvalidValue
                           : launch_scan<D, N, C, TV, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
-        if (!folded) return launch_scan_plain<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
-    } else if (folded) {
-        return hipErrorInvalidValue;
+        return folded ? launch_scan<D, N, C, TV>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream)
+                      : launch_scan_plain<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
     }
-    return launch_scan<D, N, C, TV>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
 }
 
 hipError_t launch_chunk_scan(const void *Q, const void *K, const void *V, const void *beta, const void *Tt,

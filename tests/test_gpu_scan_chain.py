@@ -106,3 +106,32 @@ def test_two_tiles_beyond_the_compute_units(oracle, heads, dk, dv, r, L):
 def test_rank_4_segments(oracle, heads, d, L, rows):
     """Segments of halves, with one tile and (cut once more) with two tiles to a workgroup."""
     assert f"pf::segment_maps_kernel<{d}, 64, 16, {rows}>" in _check(oracle, heads, L, d, d, 4, 3)
+
+
+@pytest.mark.parametrize("dk,dv,r,chunk", [(64, 64, 1, 64), (64, 96, 2, 32), (128, 128, 1, 64), (128, 128, 2, 32), (128, 256, 2, 32)])
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("blocks,tail", [(1, 0), (3, 7), (6, 0)])
+def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
+    """As many workgroups of two tiles as there are compute units, and a few more (a last round that is nearly empty, heads that
+    are no multiple of the eight XCDs): T itself is handed over, P built in the scan.  The split entry points give the same."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    heads = -(-cus // (dv // 32)) + more
+    names = _check(oracle, heads, blocks * chunk + tail, dk, dv, r, 10 * blocks + more)
+    assert f"pf::scan_kernel<{dk}, 64, {chunk}, 32, true, false>" in names
+    if tail:
+        return
+    L = blocks * chunk
+    w = synth.Workload("wide", "bf16", 1, heads, L, dk, dv, r, 64, seed=blocks, s0_std=0.2, reflect_frac=0.05)
+    dev = to_device(w, synth.make_inputs(w))
+    O, SL = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64)
+    n = heads * blocks
+    Tt, Pt = (torch.empty(n * m * 64, dtype=torch.bfloat16, device="cuda:0") for m in (64, chunk))
+    O2, SL2 = torch.empty_like(O), torch.empty_like(SL)
+    assert pf.pf_delta_chunk_flow(dev["Q"], dev["K"], dev["beta"], Tt, Pt, 1, heads, L, dk, dv, r, chunk) == pf.PF_OK
+    assert pf.pf_delta_chunk_scan(dev["Q"], dev["K"], dev["V"], dev["beta"], Tt, Pt, dev["S0"], O2, SL2, 1, heads, L, dk, dv, r, chunk) == pf.PF_OK
+    torch.cuda.synchronize()
+    # the same roundings in another order of sums: an ulp of bf16 now and then, which a few blocks carry on
+    for a, b in ((O, O2), (SL, SL2)):
+        assert float((a.float() - b.float()).norm() / b.float().norm()) < 4e-3
