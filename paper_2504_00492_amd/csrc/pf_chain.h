@@ -29,9 +29,8 @@
 // What bounds it: the loads.  At d = 128 with the readout, 16 rows and 256 workgroups a block takes 0.78 us, because its 32 KB
 // come in at 17 bytes a cycle (304 requests of 128 bytes, some 114 of them on their way); at d = 64 a block of
 // 24 heads x 4096 tokens, d_v = 128, r = 2 takes 0.57 us.  A compute unit has at most about 128 L2 lines on their way: 12 bytes
-// a cycle where they come from HBM, 20 from the last-level cache, 42 from L2.  Asking for a block's lines ahead of time in
-// part (a wave, or workgroups of their own, 4 bytes a line) took 402 us instead of 423 where 256 workgroups ran, and 5 % more
-// elsewhere.
+// a cycle where they come from HBM, 20 from the last-level cache, 42 from L2: with every read from L2 a block takes 0.58 us.
+// At d = 128 another wavefront (toucher) asks for lines ahead of time: 0.73 us.
 //
 // Two tiles to a workgroup (scan_two_tiles, scan_wide_chain and the segments) read K, Q, T, P once for 32 rows: a block takes
 // hardly longer (0.98 us at d = 128, r = 2 and 256 workgroups; with every read from L2 0.75, which is LDS: some 165 KB a block).
@@ -68,7 +67,8 @@ __device__ __forceinline__ int k_swizzle(int row)
 template <int D, int N, int C, int TV, bool RO, bool PAIR = false>
 struct ChainPlan {
     static constexpr int states = (PAIR ? 2 : 1) * (TV / 16), stagers = 2, readers = !RO ? 0 : (C >= 32 ? 2 : 1);   // wavefronts of each role
-    static constexpr int threads = 64 * (states + stagers + readers);
+    static constexpr int touchers = RO && D == 128 && TV == 16 ? 1 : 0;
+    static constexpr int threads = 64 * (states + readers + stagers + touchers);
     static constexpr int NT = t_tile_count(N / 16);    // T tiles of a block
     // one ring slot: K, V tile, T tiles, beta (32 bits each)
     static constexpr size_t oV = (size_t)N * D * 2;
@@ -79,22 +79,29 @@ struct ChainPlan {
     static constexpr size_t szU = RO ? (size_t)states * (N / 32) * 1024 : 0;   // U_eff of a block, operand tiles
     // two slots are being read (this block, and the rows and T of the next), the others are on their way from memory
     static constexpr size_t szZ = PAIR ? (size_t)N * TV * 2 : 0;
-    static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU) - szZ) / slot);
+    static constexpr size_t szW = touchers ? 256 : 0;   // what the toucher's loads bring, for nobody
+    static constexpr int fit = (int)((kMaxLdsBytes - 2 * (szX + szU) - szZ - szW) / slot);
     static constexpr int kRing = fit < 6 ? fit : 6;
     static constexpr size_t oX = kRing * slot;
     static constexpr size_t oU = oX + 2 * szX;
     static constexpr size_t oZ = oU + 2 * szU;
-    static constexpr size_t total = oZ + szZ;
+    static constexpr size_t oW = oZ + szZ;
+    static constexpr size_t total = oW + szW;
     static_assert(!(PAIR && RO), "a propagator has no readout");
     static constexpr bool kServes = N == 64 && (TV == 16 || TV == 32) && kRing >= 4;
 };
 
-// 16 bytes (4: 2 bytes, widened to 32 bits) per lane from memory to LDS; the LDS address is the wavefront's, lane l
+// 16 bytes (4; 2, widened to 32 bits) per lane from memory to LDS; the LDS address is the wavefront's, lane l
 // writes behind lane l - 1.
 __device__ __forceinline__ void load_lds16(const bf16 *src, char *dst)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
                                      (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void load_lds4(const char *src, char *dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 4, 0, 0);
 }
 __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 {
@@ -298,6 +305,43 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     // A workgroup's wavefronts go round the four SIMDs: the readers, who have products of their own, come right behind the state
     // waves, and the stagers share what SIMDs are left to share.
     constexpr int NRd = Pl::readers;
+    // The barrier alone, without the wait for every load that __syncthreads brings; to the compiler it does not touch
+    // memory, so the fences keep the loads of a later block, which reuse a slot, behind it.
+    auto barrier = [&] {
+        LDS_FENCE();
+        __builtin_amdgcn_s_barrier();
+        LDS_FENCE();
+    };
+    if (Pl::touchers && wave >= NSS + NRd + NSt) {
+        // The tiles of a head read the same lines at the same time, so that no more of them are on their way from memory than one
+        // of them asks for.  Each asks for its share of a later block's lines of K, V and Q as well, four bytes a line that
+        // nobody waits for: the block's own loads then find them in L2.  Scan, us, without / five to seven blocks ahead / fourteen:
+        // 32 heads x 65536, r = 2 1606 / 1500 / 1616; 32 x 3001, r = 1 55.5 / 52.9 / 52.6; 32 x 8192, r = 4 340 / 336 / 348.
+        // Only V and Q: 1633, 52.1, 347.  With two tiles to a workgroup (64 heads x 4096, r = 2 131 / 142) and at d = 64, where a
+        // block is shorter than the wait for memory (32 x 2048, r = 1 19.1 / 20.0; 24 x 4096, d_v = 128 72.7 / 72), there is none.
+        constexpr int kTouch = 7, KL = N * D / 64, QL = C * D / 64;
+        const int ntiles = dv / TV, VL = N * dv / 64, lines = KL + QL + VL;
+        auto touch = [&](int ch) {
+            const size_t cid = c0 + (size_t)ch;
+            const char *Kg = reinterpret_cast<const char *>(K + cid * (size_t)N * D);
+            const char *Qg = reinterpret_cast<const char *>(Q + cid * (size_t)C * D);
+            const char *Vg = reinterpret_cast<const char *>(V - tile * TV + cid * (size_t)N * dv);
+            for (int first = tile; first < lines; first += 64 * ntiles) {
+                const int i = first + lane * ntiles;
+                if (i < lines)
+                    load_lds4(i < KL ? Kg + 128 * i : i < KL + QL ? Qg + 128 * (i - KL) : Vg + 128 * (i - KL - QL), smem + Pl::oW);
+            }
+        };
+        for (int b = kRing - 1; b < kTouch && b < NC; ++b) touch(b);   // (the stagers ask for those before)
+        barrier();
+#pragma unroll 1
+        for (int ch = 0; ch < NC; ++ch) {
+            if (ch + kTouch < NC) touch(ch + kTouch);
+            barrier();
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // nothing is under way to LDS when the wave ends
+        return;
+    }
     if (wave >= NSS + NRd) {
         // The stagers' loads go straight to LDS.  Pieces of 64 x 16 bytes, dealt to the stagers one by one.
         const int H = wave - NSS - NRd;
@@ -338,13 +382,6 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
         // Loads return in order: all but the newest n blocks have landed.
         auto landed_but = [&](auto Nc) {
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(Nc)::value * kLoads) : "memory");
-        };
-        // The barrier alone, without the wait for every load that __syncthreads brings; to the compiler it does not touch
-        // memory, so the fences keep the loads of a later block, which reuse a slot, behind it.
-        auto barrier = [&] {
-            LDS_FENCE();
-            __builtin_amdgcn_s_barrier();
-            LDS_FENCE();
         };
         if (NC > 0) {
 #pragma unroll

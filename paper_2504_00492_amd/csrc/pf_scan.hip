@@ -778,7 +778,15 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
     if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
     else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    return launch(kern, armed, TV, Body::threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    // The wavefront that asks for lines ahead of time comes last: without it where a head has fewer than four tiles, so that the
+    // share of each would be large (4096 tokens, d = 128, r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48
+    // 137 / 142; 32 heads, d_v = 64 117 / 114, d_v = 128 120 / 115), where workgroups are few (12 heads x 700 32.5 / 33.1, 9 x 4096
+    // 87.2 / 87.3; 17 x 4096 109 / 105), or blocks (32 heads x 256 16.7 / 17.0).
+    int threads = Body::threads;
+    if constexpr (Body::kChain) {
+        if (dv < 4 * TV || (long long)heads * (dv / TV) < device_cu_count() / 2 || NC < 16) threads -= 64 * Body::Chain::touchers;
+    }
+    return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
 }
 
 template <int D, int N, int C>
