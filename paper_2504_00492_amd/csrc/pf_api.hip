@@ -278,7 +278,9 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
                 out += scan + "32" + other;
             } else {
                 const int rows = pf::scan_dv_tile(heads, d_v, n);
-                out += scan + std::to_string(rows) + (n == 64 && rows == 16 && !pf::scan_chain(heads, d_v, n) ? other : usual);
+                const bool split16 = n == 64 && rows == 16 && !pf::scan_chain(heads, d_v, n);
+                const bool split32 = n == 64 && rows == 32 && !pf::scan_wide_chain(heads, L / block, d_k, d_v, n);
+                out += scan + std::to_string(rows) + (split32 ? ", true, false, false>" : split16 ? other : usual);
             }
             if (tail) out += ";" + generic;
         }
@@ -329,7 +331,8 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
         const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
         const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
         const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r) || pf::scan_two_tiles(heads, d_v, sub * r);
-        void *const Pt = fold || pf::scan_wide_chain(heads, d_v, sub * r) ? nullptr : ws + wp.oP;   // (nullptr: the scan builds P)
+        // (nullptr: the scan builds P)
+        void *const Pt = fold || pf::scan_wide_chain(heads, L / block, d_k, d_v, sub * r) ? nullptr : ws + wp.oP;
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, Pt, heads, L, d_k, r, sub, s, product, fold, block);

@@ -83,8 +83,8 @@ int scan_dv_tile(int heads, int dv, int n);
 bool scan_chain(int heads, int dv, int n);
 // whether more tiles of 16 rows than that run it two to a workgroup (launch_chunk_scan, folded)
 bool scan_two_tiles(int heads, int dv, int n);
-// whether still more of them do, in rounds (launch_chunk_scan, T itself and no P)
-bool scan_wide_chain(int heads, int dv, int n);
+// whether still more of them do, in rounds, with so many whole blocks a head (launch_chunk_scan, T itself and no P)
+bool scan_wide_chain(int heads, int blocks, int d, int dv, int n);
 
 // ---- fused forward (pf_fused.hip): flow and scan of every block in one kernel, d = d_k = d_v,
 // n = chunk * r in {64, 128}.  Takes the first L / chunk whole blocks of every head.  Tdump / Pdump

@@ -698,16 +698,17 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: boun
 
 // 16 rows: the other body, the split.  32: the chain with two tiles on -T diag(beta), which calls with at most one workgroup a compute
 // unit take; those with more take T itself, the form that the split had before them and is as far from 64 bits as that was
-// (with -T diag(beta) O and S_L of 64 heads x 1024 tokens, d = 128, r = 2 0.5 % further).
+// (with -T diag(beta) O and S_L of 64 heads x 1024 tokens, d = 128, r = 2 0.5 % further).  32 rows and OTHER = false: the split, for
+// the calls that scan_wide_chain leaves to it and for the split entry points.
 template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
     const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
 {
-    static_assert(OTHER && !GEN && ChainPlan<D, N, C, TV, RO>::kServes, "the other shapes have one body");
+    static_assert((OTHER || TV == 32) && !GEN && ChainPlan<D, N, C, TV, RO>::kServes, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    if constexpr (ScanBody<D, N, C, TV, RO, GEN, true>::kChain)
+    if constexpr (OTHER && ScanBody<D, N, C, TV, RO, GEN, true>::kChain)
         chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
         split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
@@ -734,18 +735,6 @@ __global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
     static_assert(ScanBody<D, N, C, 16, true, false>::kChain, "the other shapes take T as it is");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     chain_scan<D, N, C, 16, true, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
-}
-
-// and the split at 32 rows on it
-template <int D, int N, int C>
-__global__ __launch_bounds__(kScanThreads) void scan_plain_wide_kernel(
-    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
-    const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
-{
-    static_assert(ScanBody<D, N, C, 32, true, false>::kChain, "the other shapes take T as it is");
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    split_scan<D, N, C, 32, false>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
 }
 
 // ---------------------------------------------------------------------------- host side
@@ -800,14 +789,14 @@ static hipError_t launch_scan_plain(const void *Q, const void *K, const void *V,
 }
 
 template <int D, int N, int C>
-static hipError_t launch_scan_plain_wide(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
+static hipError_t launch_scan_wide_split(const void *Q, const void *K, const void *V, const void *beta, const void *Tt, const void *Pt,
                                          const float *S0, void *O, float *SL, int heads, int NC, int tail, int dv, hipStream_t stream)
 {
     constexpr size_t lds = ScanLds<D, N, C, 32, false>::total;
     static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
+    ScanFn *kern = scan_kernel<D, N, C, 32, true, false, false>;
     static std::atomic<uint64_t> armed{0};
-    return launch(scan_plain_wide_kernel<D, N, C>, armed, 32, kScanThreads, lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail,
-                  dv, stream);
+    return launch(kern, armed, 32, kScanThreads, lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
 }
 
 int scan_dv_tile(int heads, int dv, int n)
@@ -846,7 +835,18 @@ bool scan_two_tiles(int heads, int dv, int n)
     return n == 64 && dv % 32 == 0 && scan_dv_tile(heads, dv, n) == 16 && !scan_chain(heads, dv, n);
 }
 
-bool scan_wide_chain(int heads, int dv, int n) { return n == 64 && scan_dv_tile(heads, dv, n) == 32; }
+// More than one round of workgroups costs the chain the fill of its ring once a round (the split has two workgroups to a compute
+// unit), which blocks pay back, at d = 64 the more of them the more of a block's time the scan takes (d_v).  us, split / chain:
+//   d = 128            2 rounds, 4 blocks (r = 2) 21.0 / 21.2   5 31.2 / 30.3   10 33.4 / 30.5    5 rounds, 1 25.8 / 27.5   5 53.6 / 50.1
+//   d = 64, d_v = 64   2 rounds, 8 blocks 22.2 / 23.0   12 26.8 / 27.0   16 33.3 / 33.0   24 57.8 / 55.5    3 rounds, 12 45.8 / 47.5   16 58.6 / 58.1
+//   d_v = 128          2 rounds, 20 37.5 / 35.4   32 58.5 / 61.6   64 115 / 111    3 rounds, 20 55.2 / 60.0   32 86.4 / 87.5   64 172 / 164
+//   d_v = 256          4 rounds, 20 60.6 / 68.8   64 180 / 191   128 365 / 368;   d_v = 192, 128 196 / 199
+bool scan_wide_chain(int heads, int blocks, int d, int dv, int n)
+{
+    if (n != 64 || scan_dv_tile(heads, dv, n) != 32) return false;
+    if ((long long)heads * (dv / 32) <= (long long)device_cu_count()) return true;
+    return d == 128 ? blocks >= 5 : dv <= 64 ? blocks >= 16 : dv <= 128 && blocks >= 64;
+}
 
 template <int D, int N, int C, int TV>
 static hipError_t launch_scan_instance(const void *Q, const void *K, const void *V, const void *beta,
@@ -858,7 +858,7 @@ static hipError_t launch_scan_instance(const void *Q, const void *K, const void 
                       : launch_scan<D, N, C, TV>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
     } else if constexpr (TV == 32) {               // a workgroup to a compute unit and more
         if (folded) return hipErrorInvalidValue;
-        return Pt ? launch_scan_plain_wide<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream)
+        return Pt ? launch_scan_wide_split<D, N, C>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream)
                   : launch_scan<D, N, C, 32>(Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
     } else {
         if (folded && scan_two_tiles(heads, dv, N))

@@ -110,7 +110,7 @@ def test_rank_4_segments(oracle, heads, d, L, rows):
 
 @pytest.mark.parametrize("dk,dv,r,chunk", [(64, 64, 1, 64), (64, 96, 2, 32), (128, 128, 1, 64), (128, 128, 2, 32), (128, 256, 2, 32)])
 @pytest.mark.parametrize("more", [0, 1])
-@pytest.mark.parametrize("blocks,tail", [(1, 0), (3, 7), (6, 0)])
+@pytest.mark.parametrize("blocks,tail", [(1, 0), (3, 7), (5, 0), (16, 3)])
 def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     """As many workgroups of two tiles as there are compute units, and a few more (a last round that is nearly empty, heads that
     are no multiple of the eight XCDs): T itself is handed over, P built in the scan.  The split entry points give the same."""
@@ -119,7 +119,8 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     heads = -(-cus // (dv // 32)) + more
     names = _check(oracle, heads, blocks * chunk + tail, dk, dv, r, 10 * blocks + more)
-    assert f"pf::scan_kernel<{dk}, 64, {chunk}, 32, true, false>" in names
+    chain = heads * (dv // 32) <= cus or blocks >= (5 if dk == 128 else 16 if dv <= 64 else 64)
+    assert f"pf::scan_kernel<{dk}, 64, {chunk}, 32, true, false{'' if chain else ', false'}>" in names
     if tail:
         return
     L = blocks * chunk

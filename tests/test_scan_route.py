@@ -72,8 +72,21 @@ def test_segments_by_heads_and_blocks(pf, d, r):  # noqa: F811
     assert len(kinds(most, 32 * block)) == 4 and len(kinds(most, 28 * block)) == 1
 
 
+@pytest.mark.parametrize("dk,dv,line", [(128, 128, 5), (128, 64, 5), (64, 64, 16), (64, 128, 64), (64, 192, None)])
+@pytest.mark.parametrize("r", [1, 2])
+def test_more_than_a_round_of_two_tiles_by_blocks(pf, dk, dv, line, r):  # noqa: F811
+    """One round: the chain whatever the length.  More: the chain from as many blocks on as pay for the rounds, else the split."""
+    once, block = _cus() // (dv // 32), 64 // r
+    chain, split = (f"pf::scan_kernel<{dk}, 64, {block}, 32, true, false{x}>" for x in ("", ", false"))
+    if _cus() % (dv // 32) == 0:                 # (as many workgroups as compute units: no fewer, which is another form)
+        assert _scan(pf, once, block, dk, dv, r) == chain and _scan(pf, once, 100 * block, dk, dv, r) == chain
+    assert _scan(pf, once + 1, ((line or 500) - 1) * block, dk, dv, r) == split
+    if line:
+        assert _scan(pf, once + 1, line * block, dk, dv, r) == chain and _scan(pf, 10 * once, line * block + 1, dk, dv, r) == chain
+
+
 # every branch of the dispatch: B * H, L, d_k, d_v, r, chunk
-SHAPES = [(32, 2048, 64, 64, 1, 64), (64, 4096, 128, 128, 2, 64), (32, 3001, 128, 128, 1, 64), (33, 256, 128, 128, 2, 64),
+SHAPES = [(65, 96, 128, 128, 2, 64), (32, 2048, 64, 64, 1, 64), (64, 4096, 128, 128, 2, 64), (32, 3001, 128, 128, 1, 64), (33, 256, 128, 128, 2, 64),
           (65, 300, 64, 64, 1, 64), (100, 96, 64, 48, 2, 64), (32, 1024, 128, 128, 4, 128), (40, 96, 64, 128, 4, 64),
           (20, 160, 64, 48, 4, 64), (64, 96, 128, 128, 4, 64), (100, 96, 64, 48, 4, 64), (2, 2048, 128, 128, 1, 64),
           (8, 8192, 128, 128, 2, 64), (2, 2048, 64, 64, 4, 64), (8, 16384, 64, 64, 4, 64), (3, 40, 128, 128, 1, 64)]
