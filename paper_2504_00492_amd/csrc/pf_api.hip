@@ -331,8 +331,8 @@ static pf_status delta_fwd_impl(const void *Q, const void *K, const void *V, con
         const bool halves = run_in_halves(heads, d_v, r, block, wp.segments);
         const int sub = halves ? block / 2 : block;              // tokens of a block as it runs
         const bool fold = wp.segments > 1 || pf::scan_chain(heads, d_v, sub * r) || pf::scan_two_tiles(heads, d_v, sub * r);
-        // (nullptr: the scan builds P)
-        void *const Pt = fold || pf::scan_wide_chain(heads, L / block, d_k, d_v, sub * r) ? nullptr : ws + wp.oP;
+        // (nullptr: the scan builds P; so it does on -T diag(beta), and keeps how far it is there)
+        void *const Pt = !fold && pf::scan_wide_chain(heads, L / block, d_k, d_v, sub * r) ? nullptr : ws + wp.oP;
         hipError_t e = hipSuccess;
         if (wp.segments > 1) {
             e = pf::launch_chunk_flow(Q, K, beta, ws + wp.oT, Pt, heads, L, d_k, r, sub, s, product, fold, block);

@@ -109,6 +109,69 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
                                      (__attribute__((address_space(3))) void *)(uintptr_t)(uint32_t)(uintptr_t)dst, 2, 0, 0);
 }
 
+// A workgroup beyond those of the chain, on a compute unit that they leave idle: asks for the lines of the blocks that the heads of
+// its XCD come to next, four bytes a line that nobody waits for, so that the chain finds them in L2 (a compute unit's reads come
+// back in order: its own wait for memory holds up the chain's, another's does not).  What bounds it: 128 lines on their way at a time.
+// Its first wavefront looks how far the chain is; nothing but time depends on that, and after some 3 ms without progress it gives up.
+// The window: what lies ahead of the chain has to fit an XCD's 4 MB of L2.  Whole forward, us, without / 8, 12, 18 and 24 blocks:
+//   24 heads x 4096, d = 64, r = 2  77.4 / 74.5, 66.4, 65.1, 65.3     20 x 4096, d = 128, r = 2  104 / 99.8, 95.9, 96.4, 96.8
+template <int D, int N, int C, int kRing>
+__device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const bf16 *V, const bf16 *Tt, unsigned *pace,
+                                            unsigned works, unsigned tiles, int NC, int tail, int dv, char *smem)
+{
+    constexpr int R = N / C, NKT = N / 32, NT = t_tile_count(N / 16);
+    constexpr int kWindow = D == 64 ? 18 : 14, kStop = 0x3fffffff, kPatience = 4096;
+    const unsigned x = blockIdx.x & 7, each = works >> 3, more = works & 7;
+    const unsigned count = each + (x < more), first = x * each + (x < more ? x : more);
+    const unsigned groups = (gridDim.x >> 3) + (x < (gridDim.x & 7)) - count, group = (blockIdx.x >> 3) - count;
+    volatile int *const seen = reinterpret_cast<volatile int *>(smem + 256);   // (the loads write below)
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = blockDim.x >> 6, lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) *seen = 0;
+    __syncthreads();
+    if (count == 0) return;
+    if (wave == 0) {
+        int last = 0;
+        for (int idle = 0; last < NC - kWindow && idle < kPatience; ++idle) {
+            const int now = (int)__hip_atomic_load(pace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (now > last) {
+                last = now;
+                idle = 0;
+                *seen = last;
+            }
+            __builtin_amdgcn_s_sleep(4);
+        }
+        *seen = kStop;
+        return;
+    }
+    constexpr int KL = N * D / 64, QL = C * D / 64, TL = 8 * NT;
+    const unsigned h0 = first / tiles, heads = (first + count - 1) / tiles - h0 + 1;
+    const int VL = N * dv / 64, lines = KL + QL + TL + VL;
+    int at = 0;                                            // blocks up to at + kWindow may be asked for
+    for (int b = kRing; b < NC; ++b) {
+        while (b > at + kWindow) {
+            at = *seen;
+            if (b > at + kWindow) __builtin_amdgcn_s_sleep(2);
+        }
+        if (at == kStop) at = b;                           // (the rest is within the window)
+        if (b < at + 2) continue;                          // too late
+        for (unsigned i = ((wave - 1) * groups + group) * 64 + lane; i < heads * lines; i += (waves - 1) * groups * 64) {
+            const size_t head = h0 + i / lines, cid = head * (size_t)NC + b, skew = head * (size_t)tail;
+            int l = i % lines;
+            const char *a;
+            if (l < KL) a = reinterpret_cast<const char *>(K + cid * N * D + skew * R * D) + 128 * l;
+            else if ((l -= KL) < VL) a = reinterpret_cast<const char *>(V + (cid * N + skew * R) * dv) + 128 * l;
+            else if ((l -= VL) < QL) a = reinterpret_cast<const char *>(Q + cid * C * D + skew * D) + 128 * l;
+            else {
+                l -= QL;
+                const int t = l >> 3, mt = t < 1 ? 0 : t < 2 ? 1 : t < 4 ? 2 : 3;
+                a = reinterpret_cast<const char *>(Tt + cid * N * N + full_tile_offset(NKT, mt, t - t_tile_index(mt, 0))) + 128 * (l & 7);
+            }
+            load_lds4(a, smem);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing is under way to LDS when the wave ends
+}
+
 // FOLD: Tt holds -T diag(beta) (launch_chunk_flow), so that the chain takes K S^T - V as it comes out of the products: no
 // beta, no factor, and V goes in as a product with -Id.
 // PAIR: `stride` blocks a chain, of which this call takes NC from `first` on.  The rows of the state are in and out at SL, those
@@ -127,7 +190,18 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
 
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
-    const unsigned tiles = gridDim.x / (unsigned)nchains, work = xcd_consecutive(blockIdx.x, gridDim.x);
+    const unsigned tiles = (unsigned)dv / TV, works = (unsigned)nchains * tiles;
+    // FOLD, one tile to a workgroup: how far the first workgroup of each XCD is, 32 words apart, is kept where P would be (written
+    // to the XCD's L2, by the state wave, which has no other access to memory to wait for; by a reader, whose reads of Q then waited
+    // for it, at every block of every workgroup and through to memory, 24 heads x 4096, d_v = 128 took 333 us instead of 73)
+    constexpr bool kPaced = RO && FOLD && TV == 16;
+    unsigned *const pace = kPaced ? reinterpret_cast<unsigned *>(const_cast<bf16 *>(Pt)) + 32 * (blockIdx.x & 7) : nullptr;
+    if constexpr (kPaced) {
+        if (blockIdx.x >= works)
+            return touch_ahead<D, N, C, Pl::kRing>(Q, K, V, Tt, pace, works, tiles, NC, tail, dv, smem);
+    }
+    const bool paces = kPaced && blockIdx.x < 8 && gridDim.x > works;
+    const unsigned work = xcd_consecutive(blockIdx.x, works);
     const int tile = work % tiles;                     // the tiles of a head: one XCD
     const size_t chain = work / tiles;
     const size_t c0 = PAIR ? chain * (size_t)stride + (size_t)first : chain * (size_t)NC;
@@ -269,6 +343,9 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
                 for (int q = 0; q < kPer; ++q) read_ahead(ahead, kPer * i + q);
                 if (kt == 1 && mt % (MD / MT) == 0) widen(mt / (MD / MT));
                 kInOrder();
+            }
+            if constexpr (kPaced) {
+                if (paces) __hip_atomic_store(pace, (unsigned)ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             __syncthreads();
         }

@@ -407,6 +407,7 @@ __global__ __launch_bounds__(FlowWavePlan::threads, (FlowBody<D, N, C, GEN>::at_
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float *const lds = reinterpret_cast<float *>(smem);
     if constexpr (!GEN) {
+        if (fold && blockIdx.x == 0) reinterpret_cast<unsigned *>(Pt)[threadIdx.x] = 0;   // (pf_chain.h: how far the scan is)
         if (fold) return flow_wave<D, C, false, true, false>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, lds);
         if (!Pt) return flow_wave<D, C, false, false, false>(Q, K, beta, Tt, Pt, nchunks, NC, tail, mask_shift, lds);
     }

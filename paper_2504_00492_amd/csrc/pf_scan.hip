@@ -746,11 +746,11 @@ __global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
 
 static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, int threads, size_t lds, const void *Q, const void *K,
                          const void *V, const void *beta, const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                         int heads, int NC, int tail, int dv, hipStream_t stream)
+                         int heads, int NC, int tail, int dv, hipStream_t stream, int extra = 0)
 {
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / rows)), dim3(threads), lds, stream, (const bf16 *)Q,
+    hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / rows) + extra), dim3(threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
                        (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, dv);
     return hipGetLastError();
@@ -767,15 +767,23 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
     if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
     else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    // The wavefront that asks for lines ahead of time comes last: without it where a head has fewer than four tiles, so that the
-    // share of each would be large (4096 tokens, d = 128, r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48
+    // Compute units that the chain leaves idle ask for its lines ahead of time (touch_ahead), where there are enough of them for what
+    // a block reads, and enough workgroups and blocks for it to matter.  us, without / with:
+    //   d = 128, r = 2, 4096 tokens   9 heads 88.0 / 89.9   12 88.0 / 90.4   16 101 / 95.8   24 107 / 97.8   27 113 / 108   28 112 / 110
+    //             d_v = 64, 30 heads 117 / 101   50 131 / 121       20 heads x 512 20.3 / 20.6   x 1024 31.1 / 30.8
+    //   d = 64, 4096 tokens, r = 2   17 heads 61.3 / 63.6   24 77.4 / 65.3   32 87.2 / 69.5   50 98.4 / 88.8    2048, r = 1   32 24.8 / 23.4
+    // Elsewhere at d = 128 a wavefront of each workgroup, the last, does (chain_scan), but not where a head has fewer than four tiles, so
+    // that the share of each would be large (4096 tokens, r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48
     // 137 / 142; 32 heads, d_v = 64 117 / 114, d_v = 128 120 / 115), where workgroups are few (12 heads x 700 32.5 / 33.1, 9 x 4096
-    // 87.2 / 87.3; 17 x 4096 109 / 105), or blocks (32 heads x 256 16.7 / 17.0).
-    int threads = Body::threads;
-    if constexpr (Body::kChain) {
-        if (dv < 4 * TV || (long long)heads * (dv / TV) < device_cu_count() / 2 || NC < 16) threads -= 64 * Body::Chain::touchers;
+    // 87.2 / 87.3), or blocks (32 heads x 256 16.7 / 17.0).
+    int threads = Body::threads, extra = 0;
+    if constexpr (Body::kChain && TV == 16) {
+        const int cus = device_cu_count(), tiles = dv / TV, works = heads * tiles, idle = cus - works;
+        const long long lines = (N * D + C * D + (long long)N * dv) / 64 + 8 * Body::Chain::NT;      // of a block of one head
+        if (NC >= 24 && works >= cus * (D == 128 ? 4 : 3) / 8 && works * lines <= 350ll * idle * tiles) extra = idle;
+        if (Body::Chain::touchers && (extra || tiles < 4 || works < cus / 2 || NC < 16)) threads -= 64;
     }
-    return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra);
 }
 
 template <int D, int N, int C>

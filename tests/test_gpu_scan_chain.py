@@ -136,3 +136,21 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     # the same roundings in another order of sums: an ulp of bf16 now and then, which a few blocks carry on
     for a, b in ((O, O2), (SL, SL2)):
         assert float((a.float() - b.float()).norm() / b.float().norm()) < 4e-3
+
+
+@pytest.mark.parametrize("heads,dk,dv,r,L", [(24, 64, 64, 2, 24 * 32), (33, 64, 64, 1, 25 * 64 + 5), (13, 64, 128, 2, 70 * 32 + 31), (17, 128, 128, 1, 24 * 64),
+                                             (28, 128, 128, 2, 27 * 32 + 1), (20, 128, 112, 2, 40 * 32), (16, 128, 128, 4, 30 * 32 + 3)])
+def test_idle_compute_units_ask_ahead(oracle, heads, dk, dv, r, L):
+    """Workgroups of the chain on half of the compute units and more, 24 blocks and more: the others ask for its lines ahead of time, by
+    what the chain writes of its progress where P would lie.  Twice, on a workspace full of ones, each to the oracle and bit for bit."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    names = _check(oracle, heads, L, dk, dv, r, heads)
+    assert any(n.startswith(f"pf::scan_kernel<{dk}, 64, {64 // r}, 16, true, false>") for n in names)
+    w = synth.Workload("ahead", "bf16", 1, heads, L, dk, dv, r, 64, seed=heads, s0_std=0.2, reflect_frac=0.05)
+    dev = to_device(w, synth.make_inputs(w))
+    ws = torch.full((pf.pf_delta_fwd_workspace_bytes(1, heads, L, dk, dv, r, 64, pf.PF_BF16),), 255, dtype=torch.uint8, device="cuda:0")
+    a = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
+    b = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
