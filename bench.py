@@ -93,6 +93,11 @@ def kernel_bytes_per_token_head(d, r, e):
     return flow, scan
 
 
+def scan_builds_p(name):
+    """Whether a scan kernel is a chain of blocks of 64 virtual tokens, which builds P = Mbar (.) Q K^T itself."""
+    return re.search(r"scan_kernel<\d+, 64, \d+, (16, true, false|32, true, false(, true)?)>$", name) is not None
+
+
 def kernel_code_digest(csrc=os.path.join(ROOT, "paper_2504_00492_amd", "csrc")):
     """Digest of the code of the flow, scan and fused kernels (comments and white space left out): the name of an
     instantiation does not say which body it has."""
@@ -260,6 +265,9 @@ def run_workload(pf, torch, w, inputs, args, traffic_table):
 
         f_flow, f_scan = kernel_flops_per_token_head(dk, r, block)
         b_flow, b_scan = kernel_bytes_per_token_head(dk, r, e)
+        if len(launched) == 2 and scan_builds_p(launched[1]):          # P, and Q with it, are the scan's
+            f_flow, f_scan = f_flow - dk * r * (block + 1), f_scan + dk * r * (block + 1)
+            b_flow -= e * dk
         us = trace_steps(torch, step, max(10, min(args.steps, 100)), launched) if len(launched) == 2 else None
         if us:                                   # (flow and scan; every workload here launches these two)
             kernels = {"flow_kernel": kinfo(us[0] * 1e-3, f_flow, b_flow, launched[0]),
