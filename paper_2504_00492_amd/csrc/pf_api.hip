@@ -407,8 +407,8 @@ pf_status pf_delta_fwd_static(const void *Q, const void *K, const void *V, const
     if (need > kStaticScratchBytes) return PF_ERR_SCRATCH_LIMIT;
     void *ws = nullptr;
     if (need > 0 && static_scratch(&ws) != hipSuccess) return PF_ERR_LAUNCH;
-    // Nothing in the scratch has to start at zero: every tile of T and P that the scan kernel reads is written by the flow
-    // kernel of the same call, and the states and maps of segments by the pass before the one that reads them.  What an
+    // Nothing in the scratch has to start at zero: every tile of T and P that the scan kernel reads, and the words that say how far
+    // the chain is, are written by the flow kernel of the same call, and the states and maps of segments by the pass before the one that reads them.  What an
     // earlier call left behind is simply overwritten.
     return delta_fwd_impl(Q, K, V, beta, S0, O, S_L, B, H, L, d_k, d_v, r, chunk, dt, ws, need ? kStaticScratchBytes : 0,
                           stream, false);
