@@ -37,8 +37,9 @@
 // In rounds of one workgroup a compute unit it is ahead of the split of pf_scan.hip, two of which fit a compute unit, as well, since
 // P is built here (64 heads x 4096 tokens, d = 128, r = 2: whole forward 181 us / 161; 128 heads 357 / 320).  Those calls take T
 // itself: -T diag(beta) rounds a product that T R adds to exactly once more, 0.5 % further from 64 bits, and beta costs the
-// state waves 1 % of the time.  With 128 virtual tokens a block the operands of one wave do not fit its registers:
-// blocks of rank 4 run as two halves (32 heads x 8192 tokens, r = 4 529 -> 436 us).
+// state waves 1 % of the time.  Nor does V enter as a product with -Id there, so that O and S_L are the split's, bit for bit.
+// With 128 virtual tokens a block the operands of one wave do not fit its registers: blocks of rank 4 run as two halves (32
+// heads x 8192 tokens, r = 4 529 -> 436 us).
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"
@@ -187,6 +188,10 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
     constexpr int NT = Pl::NT, kRing = Pl::kRing;
     constexpr int R = N / C, NKS = D / 32, NKT = N / 32, MT = N / 16, MD = D / 16, CT = C / 16;
     constexpr int NSS = Pl::states, NSt = Pl::stagers;
+    // T itself and P built here: calls that the split of pf_scan.hip had.  R comes out in its order, V - K S^T with the sum of the
+    // products first and the difference on the vector ALU: every bit of O and S_L is what the split gives.  (With -V in the first
+    // product they were 1.2e-3 apart on 64 heads x 4096 tokens, d = 128, r = 2, with -V in the last as well; 159.6 us in each.)
+    constexpr bool kVLast = BUILD && !FOLD;
 
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
@@ -303,14 +308,20 @@ __device__ __forceinline__ void chain_scan(const bf16 *Q, const bf16 *K, const b
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) bS[ks] = join(cvt4(sacc[2 * ks]), cvt4(sacc[2 * ks + 1]));
             kInOrder();
-            // ---- R = beta (.) (V - K S^T), from K S^T - V; the first pair of row tiles is finished inside the second
+            // ---- R = beta (.) (V - K S^T), from K S^T - V (or K S^T: kVLast); the first pair of row tiles is finished inside the second
             f32x4 acc[MT], u[MT];
             auto epilogue = [&](int kt) {
                 if constexpr (FOLD) bR[kt] = join(cvt4(acc[2 * kt]), cvt4(acc[2 * kt + 1]));
-                else bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
+                else if constexpr (kVLast) {
+                    auto row = [&](int mt) { return cvt4((__builtin_convertvector(vt[mt], f32x4) - acc[mt]) * bw[mt]); };
+                    bR[kt] = join(row(2 * kt), row(2 * kt + 1));
+                } else bR[kt] = join(cvt4(acc[2 * kt] * -bw[2 * kt]), cvt4(acc[2 * kt + 1] * -bw[2 * kt + 1]));
             };
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(nI[mt & 1], join(vt[mt & ~1], vt[mt | 1]), f32x4{0.f, 0.f, 0.f, 0.f});
+            for (int mt = 0; mt < MT; ++mt) {
+                acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (!kVLast) acc[mt] = mfma16(nI[mt & 1], join(vt[mt & ~1], vt[mt | 1]), acc[mt]);
+            }
 #pragma unroll
             for (int i = 0; i < NM; ++i) {
                 const int mt = 2 * (i / (2 * NKS)) + (i & 1), ks = (i / 2) % NKS;

@@ -113,7 +113,7 @@ def test_rank_4_segments(oracle, heads, d, L, rows):
 @pytest.mark.parametrize("blocks,tail", [(1, 0), (3, 7), (5, 0), (16, 3)])
 def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     """As many workgroups of two tiles as there are compute units, and a few more (a last round that is nearly empty, heads that
-    are no multiple of the eight XCDs): T itself is handed over, P built in the scan.  The split entry points give the same."""
+    are no multiple of the eight XCDs): T itself is handed over, P built in the scan.  The split entry points give the same bits."""
     import torch
     from paper_2504_00492_amd import binding as pf
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -133,9 +133,8 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     assert pf.pf_delta_chunk_flow(dev["Q"], dev["K"], dev["beta"], Tt, Pt, 1, heads, L, dk, dv, r, chunk) == pf.PF_OK
     assert pf.pf_delta_chunk_scan(dev["Q"], dev["K"], dev["V"], dev["beta"], Tt, Pt, dev["S0"], O2, SL2, 1, heads, L, dk, dv, r, chunk) == pf.PF_OK
     torch.cuda.synchronize()
-    # the same roundings in another order of sums: an ulp of bf16 now and then, which a few blocks carry on
-    for a, b in ((O, O2), (SL, SL2)):
-        assert float((a.float() - b.float()).norm() / b.float().norm()) < 4e-3
+    # the same sums in the same order, rounded at the same places
+    assert torch.equal(O, O2) and torch.equal(SL, SL2)
 
 
 @pytest.mark.parametrize("heads,dk,dv,r,L", [(24, 64, 64, 2, 24 * 32), (33, 64, 64, 1, 25 * 64 + 5), (13, 64, 128, 2, 70 * 32 + 31), (17, 128, 128, 1, 24 * 64),
