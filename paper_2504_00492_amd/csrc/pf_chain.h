@@ -41,6 +41,7 @@
 // With 128 virtual tokens a block the operands of one wave do not fit its registers: blocks of rank 4 run as two halves (32
 // heads x 8192 tokens, r = 4 529 -> 436 us).
 #pragma once
+#include "pf_ahead.h"
 #include "pf_common.h"
 #include "pf_internal.h"
 #include "pf_layout.h"
@@ -113,7 +114,10 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 // A workgroup beyond those of the chain, on a compute unit that they leave idle: asks for the lines of the blocks that the heads of
 // its XCD come to next, four bytes a line that nobody waits for, so that the chain finds them in L2 (a compute unit's reads come
 // back in order: its own wait for memory holds up the chain's, another's does not).  What bounds it: 128 lines on their way at a time.
-// Its first wavefront looks how far the chain is; nothing but time depends on that, and after some 3 ms without progress it gives up.
+// Its first wavefront looks how far the chain is, until the rest of it is within the window; nothing but time depends on that.  The
+// others ask for no block that the chain was seen to have come to (a workgroup that starts late for one or two, until the first has
+// looked), nor, once that has seen no progress for some 3 ms, for any more.  Who waits for the first ends with it: it leaves when
+// no block is beyond the window, or says that it has lost the chain.
 // The window: what lies ahead of the chain has to fit an XCD's 4 MB of L2.  Whole forward, us, without / 8, 12, 18 and 24 blocks:
 //   24 heads x 4096, d = 64, r = 2  77.4 / 74.5, 66.4, 65.1, 65.3     20 x 4096, d = 128, r = 2  104 / 99.8, 95.9, 96.4, 96.8
 template <int D, int N, int C, int kRing>
@@ -121,7 +125,7 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
                                             unsigned works, unsigned tiles, int NC, int tail, int dv, char *smem)
 {
     constexpr int R = N / C, NKT = N / 32, NT = t_tile_count(N / 16);
-    constexpr int kWindow = D == 64 ? 18 : 14, kStop = 0x3fffffff, kPatience = 4096;
+    constexpr int kWindow = ahead_window(D), kPatience = 4096;
     const unsigned x = blockIdx.x & 7, each = works >> 3, more = works & 7;
     const unsigned count = each + (x < more), first = x * each + (x < more ? x : more);
     const unsigned groups = (gridDim.x >> 3) + (x < (gridDim.x & 7)) - count, group = (blockIdx.x >> 3) - count;
@@ -131,8 +135,12 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
     __syncthreads();
     if (count == 0) return;
     if (wave == 0) {
-        int last = 0;
-        for (int idle = 0; last < NC - kWindow && idle < kPatience; ++idle) {
+        int last = 0;                                      // until the rest of the chain is within the window
+        for (int idle = 0; last < NC - kWindow; ++idle) {
+            if (idle == kPatience) {
+                *seen = kAheadLost;
+                return;
+            }
             const int now = (int)__hip_atomic_load(pace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (now > last) {
                 last = now;
@@ -141,20 +149,26 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
             }
             __builtin_amdgcn_s_sleep(4);
         }
-        *seen = kStop;
         return;
     }
     constexpr int KL = N * D / 64, QL = C * D / 64, TL = 8 * NT;
     const unsigned h0 = first / tiles, heads = (first + count - 1) / tiles - h0 + 1;
     const int VL = N * dv / 64, lines = KL + QL + TL + VL;
-    int at = 0;                                            // blocks up to at + kWindow may be asked for
-    for (int b = kRing; b < NC; ++b) {
-        while (b > at + kWindow) {
-            at = *seen;
-            if (b > at + kWindow) __builtin_amdgcn_s_sleep(2);
+    for (int b = kRing; b < NC;) {
+        // (a plain read waits for every load on its way to LDS first: 88.6 us where it takes 73.2, 24 heads x 4096 tokens,
+        // d_v = 128, r = 2, exact product steps)
+        int now;
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(now) : "v"((uint32_t)(uintptr_t)(smem + 256)) : "memory");
+        const int next = ahead_step(b, __builtin_amdgcn_readfirstlane(now), kWindow);
+        if (next == kAheadStop) break;
+        if (next == kAheadWait) {
+            __builtin_amdgcn_s_sleep(2);
+            continue;
         }
-        if (at == kStop) at = b;                           // (the rest is within the window)
-        if (b < at + 2) continue;                          // too late
+        if (next != b) {
+            b = next;
+            continue;
+        }
         for (unsigned i = ((wave - 1) * groups + group) * 64 + lane; i < heads * lines; i += (waves - 1) * groups * 64) {
             const size_t head = h0 + i / lines, cid = head * (size_t)NC + b, skew = head * (size_t)tail;
             int l = i % lines;
@@ -169,6 +183,7 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
             }
             load_lds4(a, smem);
         }
+        ++b;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing is under way to LDS when the wave ends
 }
