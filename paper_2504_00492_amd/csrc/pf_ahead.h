@@ -1,5 +1,5 @@
-// Lines of the chain's later blocks that compute units which it leaves idle ask for ahead of time (touch_ahead, pf_chain.h): plain
-// arithmetic, so that it can be looked at without a GPU.
+// Lines of the chain's later blocks that somebody asks for ahead of time (pf_chain.h): workgroups on compute units that the chain
+// leaves idle (touch_ahead), or at d = 128 a wavefront of each of its own.  Plain arithmetic, so that it can be looked at without a GPU.
 #pragma once
 
 namespace pf {
@@ -19,6 +19,37 @@ constexpr int ahead_step(int b, int seen, int window)
     if (seen == kAheadLost) return kAheadStop;
     if (b > seen + window) return kAheadWait;
     return b < seen + 2 ? seen + window / 2 : b;
+}
+
+// 128-byte lines of a block (64 virtual tokens) of one head: K, Q, V and the six tiles of T
+constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 + dv + 8 * 6; }
+
+// Workgroups of touch_ahead for the chain with tiles of 16 rows, one to a compute unit.  Such a workgroup has the chain's LDS and
+// registers, so that the compute unit is not free for another stream: no more of them than half of those that the chain leaves idle,
+// at d = 128 none where two such calls fit the chip side by side.  Whole forward, 4096 tokens, r = 2, inputs from HBM, us: one call after the other /
+// a pair on two streams / a call of 6 heads x 1024 tokens, d = 64, on another stream, without, with half and with all:
+//   d = 64, 24 heads               81 / 100 / 44    68 /  88 / 43    68 / 104 /  73
+//           32                     87 / 111 / 45    71 / 104 / 45    71 / 115 /  77
+//           40                     90 / 138 / 45    77 / 127 / 56    73 / 124 /  80
+//           44                     94 / 143 / 46    88 / 152 / 57    78 / 132 /  85
+//           24, d_v = 128          86 / 129 / 45    74 / 122 / 56    70 / 119 /  79
+//           26, d_v = 128          89 / 138 / 46    89 / 142 / 91    76 / 132 /  83
+//   d = 128, 16                   101 / 115 / 40    94 / 131 / 42    94 / 168 / 103
+//            20                   105 / 151 / 41    98 / 149 / 52    98 / 174 / 107
+//            24                   107 / 169 / 41    99 / 167 / 55    99 / 180 / 109
+//            26                   111 / 188 / 42   113 / 203 / 127  102 / 187 / 113
+// What one of them has to ask for during a block of the chain (0.5 us at d = 64, 0.75 at 128) bounds how few they may be: it has
+// 128 lines on their way, some 225 a us from HBM, and the chain asks for a part itself.  Lines a block to each, and the gain: d = 64
+// 204 (24 heads, d_v = 128) 14 %, 217 (13, d_v = 256) 5, 229 (44) 6 but 6 lost by the pair, 295 (26, d_v = 128) none; d = 128 153
+// (20) 7 %, 276 (24) 8, 303 (13, d_v = 256, r = 1) 2, 334 (44, d_v = 64) 3 but 7 lost by the pair, 399 (26) -2.  Halves of rank 4 at
+// d = 128: none (20 heads x 3000 145 / 145).  Fewer blocks: none (24 heads x 800 18.8 / 19.1).  And what lies in the window has to fit
+// the XCDs' 4 MB of L2, which narrow d_v with many heads would not (140 heads, d_v = 16 122 / 127).
+constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int blocks)
+{
+    const int works = heads * (dv / 16), some = (cus - works) / 2;
+    if (blocks < 24 || (d == 64 ? 8 * works < 3 * cus : 2 * works <= cus || chunk < 32)) return 0;
+    const long long lines = (long long)heads * ahead_lines(d, dv, chunk);
+    return lines <= (d == 64 ? 205ll : 280ll) * some && lines / 8 * 128 * ahead_window(d) <= 4 << 20 ? some : 0;
 }
 
 }  // namespace pf

@@ -767,20 +767,14 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
     if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
     else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    // Compute units that the chain leaves idle ask for its lines ahead of time (touch_ahead), where there are enough of them for what
-    // a block reads, and enough workgroups and blocks for it to matter.  us, without / with:
-    //   d = 128, r = 2, 4096 tokens   9 heads 88.0 / 89.9   12 88.0 / 90.4   16 101 / 95.8   24 107 / 97.8   27 113 / 108   28 112 / 110
-    //             d_v = 64, 30 heads 117 / 101   50 131 / 121       20 heads x 512 20.3 / 20.6   x 1024 31.1 / 30.8
-    //   d = 64, 4096 tokens, r = 2   17 heads 61.3 / 63.6   24 77.4 / 65.3   32 87.2 / 69.5   50 98.4 / 88.8    2048, r = 1   32 24.8 / 23.4
-    // Elsewhere at d = 128 a wavefront of each workgroup, the last, does (chain_scan), but not where a head has fewer than four tiles, so
-    // that the share of each would be large (4096 tokens, r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48
-    // 137 / 142; 32 heads, d_v = 64 117 / 114, d_v = 128 120 / 115), where workgroups are few (12 heads x 700 32.5 / 33.1, 9 x 4096
-    // 87.2 / 87.3), or blocks (32 heads x 256 16.7 / 17.0).
+    // Where no compute units ask for the chain's lines ahead of time (ahead_workgroups), at d = 128 a wavefront of each workgroup, the
+    // last, does (chain_scan), but not where a head has fewer than four tiles, so that the share of each would be large (4096 tokens,
+    // r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48 137 / 142; 32 heads, d_v = 64 117 / 114, d_v = 128
+    // 120 / 115), where workgroups are few (12 heads x 700 32.5 / 33.1, 9 x 4096 87.2 / 87.3), or blocks (32 heads x 256 16.7 / 17.0).
     int threads = Body::threads, extra = 0;
     if constexpr (Body::kChain && TV == 16) {
-        const int cus = device_cu_count(), tiles = dv / TV, works = heads * tiles, idle = cus - works;
-        const long long lines = (N * D + C * D + (long long)N * dv) / 64 + 8 * Body::Chain::NT;      // of a block of one head
-        if (NC >= 24 && works >= cus * (D == 128 ? 4 : 3) / 8 && works * lines <= 350ll * idle * tiles) extra = idle;
+        const int cus = device_cu_count(), tiles = dv / TV, works = heads * tiles;
+        extra = ahead_workgroups(cus, heads, D, dv, C, NC);
         if (Body::Chain::touchers && (extra || tiles < 4 || works < cus / 2 || NC < 16)) threads -= 64;
     }
     return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra);

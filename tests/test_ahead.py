@@ -15,7 +15,8 @@ def ahead(tmp_path_factory):
     where = tmp_path_factory.mktemp("ahead")
     (where / "ahead.cpp").write_text('#include "pf_ahead.h"\nextern "C" {\n'
                                      "int window(int d) { return pf::ahead_window(d); }\n"
-                                     "int step(int b, int seen, int window) { return pf::ahead_step(b, seen, window); }\n}\n")
+                                     "int step(int b, int seen, int window) { return pf::ahead_step(b, seen, window); }\n"
+                                     "int workgroups(int c, int h, int d, int dv, int chunk, int n) { return pf::ahead_workgroups(c, h, d, dv, chunk, n); }\n}\n")
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(where / "ahead.cpp"), "-o", str(where / "ahead.so")], check=True)
     return ctypes.CDLL(str(where / "ahead.so"))
 
@@ -66,3 +67,31 @@ def test_nothing_more_once_the_chain_is_lost(ahead):
     window = ahead.window(64)
     assert len(_asks(ahead, window, 2048, 1.0, 0.0, 0.5, lost=100.0)) <= 100 + window
     assert _asks(ahead, window, 2048, 1.0, 50.0, 0.5, lost=50.0) == []
+
+
+# compute units, heads, d, d_v, tokens of a block, blocks: workgroups that ask
+@pytest.mark.parametrize("call,some", [((256, 24, 64, 128, 32, 128), 32), ((256, 26, 64, 128, 32, 128), 0),      # too much for each
+                                       ((256, 40, 64, 64, 32, 128), 48), ((256, 44, 64, 64, 32, 128), 0),
+                                       ((256, 24, 64, 64, 32, 24), 80), ((256, 24, 64, 64, 32, 23), 0),          # too few blocks
+                                       ((256, 23, 64, 64, 32, 128), 0),                                          # too few workgroups
+                                       ((256, 17, 128, 128, 32, 128), 60), ((256, 16, 128, 128, 32, 128), 0),    # two calls fit
+                                       ((256, 24, 128, 128, 32, 128), 32), ((256, 25, 128, 128, 32, 128), 0),
+                                       ((256, 20, 128, 128, 16, 256), 0), ((256, 24, 64, 64, 16, 128), 80),      # halves of rank 4
+                                       ((256, 97, 64, 16, 32, 128), 0), ((256, 140, 64, 16, 32, 128), 0),        # L2
+                                       ((256, 32, 128, 128, 64, 1000), 0), ((256, 300, 64, 64, 64, 1000), 0)])   # none idle
+def test_who_asks(ahead, call, some):
+    assert ahead.workgroups(*call) == some
+
+
+def test_half_of_the_idle_compute_units_stay_free(ahead):
+    for cus in (64, 80, 256, 304):
+        for d in (64, 128):
+            for dv in (16, 32, 48, 64, 112, 128, 256):
+                for heads in range(1, cus // (dv // 16) + 2):
+                    works = heads * (dv // 16)
+                    for chunk in (16, 32, 64):
+                        some = ahead.workgroups(cus, heads, d, dv, chunk, 500)
+                        assert 0 <= 2 * some <= max(0, cus - works)
+                        if some:
+                            assert d == 64 or 2 * works > cus
+                            assert heads * (d + chunk * d // 64 + dv + 48) * 128 * ahead.window(d) <= 8 * (4 << 20)
