@@ -52,4 +52,18 @@ constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int
     return lines <= (d == 64 ? 205ll : 280ll) * some && lines / 8 * 128 * ahead_window(d) <= 4 << 20 ? some : 0;
 }
 
+// Whether the last wavefront of each workgroup of the chain with tiles of 16 rows at d = 128 asks for lines ahead of time, where no
+// compute units do.  Not where a head has few tiles, so that the share of each is large, where workgroups are few, or blocks.
+// P built in the chain, whole forward, 4096 tokens, r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48
+// 136 / 140; 32 heads, d_v = 64 117 / 112, d_v = 128 121 / 114; 12 heads x 700 32.5 / 33.1, 9 x 4096 from the last-level cache 87.2 / 87.3,
+// 32 heads x 256 16.7 / 17.0.
+// P handed over (the split entry points: more lines that it does not ask for), scan alone, inputs from HBM: 64 heads, d_v = 32 111 /
+// 126, 60, d_v = 48 116 / 122, 32, d_v = 64 111.2 / 112.6, 32, d_v = 80 110.9 / 110.9, 32, d_v = 96 112 / 110, d_v = 128 112.5 / 108.6; 9 heads
+// 104.9 / 100.8, 4 heads 79.5 / 79.8, 3, r = 1 57.2 / 59.2; 32 heads x 256 10.0 / 9.8.
+constexpr bool ahead_wavefront(int cus, int heads, int dv, int blocks, bool handed_over)
+{
+    const int tiles = dv / 16, works = heads * tiles;
+    return handed_over ? tiles >= 5 && works >= cus / 4 : tiles >= 4 && works >= cus / 2 && blocks >= 16;
+}
+
 }  // namespace pf

@@ -767,15 +767,11 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
     if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
     else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    // Where no compute units ask for the chain's lines ahead of time (ahead_workgroups), at d = 128 a wavefront of each workgroup, the
-    // last, does (chain_scan), but not where a head has fewer than four tiles, so that the share of each would be large (4096 tokens,
-    // r = 2, us, without / with: 64 heads, d_v = 32 130 / 147, 60 heads, d_v = 48 137 / 142; 32 heads, d_v = 64 117 / 114, d_v = 128
-    // 120 / 115), where workgroups are few (12 heads x 700 32.5 / 33.1, 9 x 4096 87.2 / 87.3), or blocks (32 heads x 256 16.7 / 17.0).
     int threads = Body::threads, extra = 0;
     if constexpr (Body::kChain && TV == 16) {
-        const int cus = device_cu_count(), tiles = dv / TV, works = heads * tiles;
+        const int cus = device_cu_count();
         extra = ahead_workgroups(cus, heads, D, dv, C, NC);
-        if (Body::Chain::touchers && (extra || tiles < 4 || works < cus / 2 || NC < 16)) threads -= 64;
+        if (Body::Chain::touchers && (extra || !ahead_wavefront(cus, heads, dv, NC, false))) threads -= 64;
     }
     return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra);
 }
@@ -786,7 +782,8 @@ static hipError_t launch_scan_plain(const void *Q, const void *K, const void *V,
 {
     using Pl = ChainPlan<D, N, C, 16, true>;
     static std::atomic<uint64_t> armed{0};
-    return launch(scan_plain_kernel<D, N, C>, armed, 16, Pl::threads, Pl::total, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail,
+    const int threads = Pl::threads - (Pl::touchers && !ahead_wavefront(device_cu_count(), heads, dv, NC, true) ? 64 : 0);
+    return launch(scan_plain_kernel<D, N, C>, armed, 16, threads, Pl::total, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail,
                   dv, stream);
 }
 

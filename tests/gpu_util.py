@@ -144,3 +144,22 @@ def untile_acc4(t, mt, dt):
         for j in range(dt):
             out[16 * i + 4 * g[:, None] + e[None, :], (16 * j + r16)[:, None]] = t[i, j]
     return out
+
+
+def launches(call):
+    """[name, grid, threads] of the kernels of this library that `call` launches, in order, out of a trace."""
+    import json
+    import os
+    import re
+    import tempfile
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        call()
+        torch.cuda.synchronize()
+    with tempfile.TemporaryDirectory() as where:
+        p.export_chrome_trace(os.path.join(where, "trace.json"))
+        with open(os.path.join(where, "trace.json")) as f:
+            events = [e for e in json.load(f)["traceEvents"] if "pf::" in e.get("name", "") and "grid" in e.get("args", {})]
+    return [[re.sub(r"^void ", "", re.match(r"[^(]*", e["name"]).group(0)), e["args"]["grid"][0], e["args"]["block"][0]]
+            for e in sorted(events, key=lambda e: e["ts"])]

@@ -16,7 +16,8 @@ def ahead(tmp_path_factory):
     (where / "ahead.cpp").write_text('#include "pf_ahead.h"\nextern "C" {\n'
                                      "int window(int d) { return pf::ahead_window(d); }\n"
                                      "int step(int b, int seen, int window) { return pf::ahead_step(b, seen, window); }\n"
-                                     "int workgroups(int c, int h, int d, int dv, int chunk, int n) { return pf::ahead_workgroups(c, h, d, dv, chunk, n); }\n}\n")
+                                     "int workgroups(int c, int h, int d, int dv, int chunk, int n) { return pf::ahead_workgroups(c, h, d, dv, chunk, n); }\n"
+                                     "int wavefront(int c, int h, int dv, int n, int p) { return pf::ahead_wavefront(c, h, dv, n, p); }\n}\n")
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(where / "ahead.cpp"), "-o", str(where / "ahead.so")], check=True)
     return ctypes.CDLL(str(where / "ahead.so"))
 
@@ -81,6 +82,14 @@ def test_nothing_more_once_the_chain_is_lost(ahead):
                                        ((256, 32, 128, 128, 64, 1000), 0), ((256, 300, 64, 64, 64, 1000), 0)])   # none idle
 def test_who_asks(ahead, call, some):
     assert ahead.workgroups(*call) == some
+
+
+# compute units, heads, d_v, blocks, P handed over
+@pytest.mark.parametrize("call,asks", [((256, 32, 64, 16, 0), 1), ((256, 32, 64, 15, 0), 0), ((256, 31, 64, 16, 0), 0), ((256, 60, 48, 128, 0), 0),
+                                       ((256, 60, 48, 128, 1), 0), ((256, 64, 64, 128, 1), 0), ((256, 32, 80, 128, 1), 1),
+                                       ((256, 8, 128, 1, 1), 1), ((256, 7, 128, 128, 1), 0)])
+def test_which_workgroups_ask_themselves(ahead, call, asks):
+    assert ahead.wavefront(*call) == asks
 
 
 def test_half_of_the_idle_compute_units_stay_free(ahead):

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2504_00492_amd import synth
-from gpu_util import assert_parity, flat_heads, output_stats, rel_l2, to_device
+from gpu_util import assert_parity, flat_heads, launches, output_stats, rel_l2, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -153,3 +153,25 @@ def test_idle_compute_units_ask_ahead(oracle, heads, dk, dv, r, L):
     b = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("heads,dv,r,blocks,wavefront", [(32, 64, 2, 6, 0), (36, 48, 1, 20, 0), (13, 80, 2, 9, 1), (8, 128, 2, 3, 1), (7, 128, 1, 17, 0)])
+def test_split_scan_with_and_without_the_wavefront_that_asks(oracle, heads, dv, r, blocks, wavefront):
+    """pf_delta_chunk_scan on the chain with one tile: the wavefront is there where it pays, and O and S_L are right either way."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    chunk, L = 64 // r, blocks * (64 // r)
+    w = synth.Workload("split", "bf16", 1, heads, L, 128, dv, r, chunk, seed=heads, s0_std=0.2, reflect_frac=0.05)
+    print(f"[case] split scan heads={heads} L={L} dv={dv} r={r}", flush=True)
+    inp = synth.make_inputs(w)
+    dev = to_device(w, inp)
+    Tt, Pt = (torch.empty(heads * blocks * m * 64, dtype=torch.bfloat16, device="cuda:0") for m in (64, chunk))
+    O, SL = torch.empty(1, heads, L, dv, dtype=torch.bfloat16, device="cuda:0"), torch.empty(1, heads, dv, 128, device="cuda:0")
+    assert pf.pf_delta_chunk_flow(dev["Q"], dev["K"], dev["beta"], Tt, Pt, 1, heads, L, 128, dv, r, chunk) == pf.PF_OK
+    scan = lambda: pf.pf_delta_chunk_scan(dev["Q"], dev["K"], dev["V"], dev["beta"], Tt, Pt, dev["S0"], O, SL, 1, heads, L, 128, dv, r, chunk)
+    (name, grid, threads), = launches(lambda: scan())
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (name, grid, threads) == (f"pf::scan_plain_kernel<128, 64, {chunk}>", heads * (dv // 16), 64 * (5 + wavefront))
+    Oref, SLref = oracle.delta_fwd(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    SLn, SLref = SL.cpu().numpy().reshape(heads, dv, 128), np.asarray(SLref).reshape(heads, dv, 128)
+    assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
