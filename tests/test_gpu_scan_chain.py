@@ -137,20 +137,33 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     assert torch.equal(O, O2) and torch.equal(SL, SL2)
 
 
-@pytest.mark.parametrize("heads,dk,dv,r,L", [(24, 64, 64, 2, 24 * 32), (33, 64, 64, 1, 25 * 64 + 5), (13, 64, 128, 2, 70 * 32 + 31), (17, 128, 128, 1, 24 * 64),
-                                             (28, 128, 128, 2, 27 * 32 + 1), (20, 128, 112, 2, 40 * 32), (16, 128, 128, 4, 30 * 32 + 3)])
-def test_idle_compute_units_ask_ahead(oracle, heads, dk, dv, r, L):
-    """Workgroups of the chain on half of the compute units and more, 24 blocks and more: the others ask for its lines ahead of time, by
-    what the chain writes of its progress where P would lie.  Twice, on a workspace full of ones, each to the oracle and bit for bit."""
+# what a call with d_k, d_v, r, L takes besides the workgroups of the chain, on 256 compute units: other workgroups that ask for lines
+# ahead of time, or a wavefront of its own for it
+AHEAD = [(24, 64, 64, 2, 24 * 32, 80, 0), (33, 64, 64, 1, 25 * 64 + 5, 62, 0), (13, 64, 128, 2, 70 * 32 + 31, 76, 0), (17, 128, 128, 1, 24 * 64, 60, 0),
+         (24, 128, 128, 2, 27 * 32 + 1, 32, 0), (20, 128, 112, 2, 40 * 32, 58, 0), (24, 64, 64, 4, 30 * 32 + 3, 80, 0),
+         (28, 128, 128, 2, 27 * 32 + 1, 0, 1), (16, 128, 128, 4, 30 * 32 + 3, 0, 1), (16, 128, 128, 2, 24 * 32, 0, 1),
+         (24, 64, 64, 2, 23 * 32, 0, 0), (60, 128, 48, 2, 24 * 32, 0, 0)]
+
+
+@pytest.mark.parametrize("heads,dk,dv,r,L,workgroups,wavefront", AHEAD)
+def test_idle_compute_units_ask_ahead(oracle, heads, dk, dv, r, L, workgroups, wavefront):
+    """Workgroups of the chain on a part of the compute units, 24 blocks and more: some of the others ask for its lines ahead of time, by
+    what the chain writes of its progress where P would lie; else, at d = 128, a wavefront of its own may.  That they run is seen in a
+    trace; then twice, on a workspace full of ones, each to the oracle and bit for bit."""
     import torch
     from paper_2504_00492_amd import binding as pf
     names = _check(oracle, heads, L, dk, dv, r, heads)
-    assert any(n.startswith(f"pf::scan_kernel<{dk}, 64, {64 // r}, 16, true, false>") for n in names)
+    scan = next(n for n in names if n.startswith("pf::scan_kernel"))
+    assert scan == f"pf::scan_kernel<{dk}, 64, {64 // r}, 16, true, false>"
     w = synth.Workload("ahead", "bf16", 1, heads, L, dk, dv, r, 64, seed=heads, s0_std=0.2, reflect_frac=0.05)
     dev = to_device(w, synth.make_inputs(w))
+    call = lambda ws=None: pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        _, grid, threads = next(k for k in launches(call) if k[0] == scan)
+        roles = 4 if r == 4 else 5                   # state wave, two stagers, one reader or two
+        assert grid == heads * (dv // 16) + workgroups and threads == 64 * (roles + wavefront), (grid, threads)
     ws = torch.full((pf.pf_delta_fwd_workspace_bytes(1, heads, L, dk, dv, r, 64, pf.PF_BF16),), 255, dtype=torch.uint8, device="cuda:0")
-    a = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
-    b = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws)
+    a, b = call(ws), call(ws)
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(a, b))
 
