@@ -114,6 +114,17 @@ def test_rank_4_segments(oracle, heads, d, L, rows):
 def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     """As many workgroups of two tiles as there are compute units, and a few more (a last round that is nearly empty, heads that
     are no multiple of the eight XCDs): T itself is handed over, P built in the scan.  The split entry points give the same bits."""
+    _wide_chain(oracle, dk, dv, r, chunk, more, blocks, tail)
+
+
+@pytest.mark.parametrize("dk,dv,r,chunk", [(64, 96, 2, 32), (64, 128, 1, 64), (64, 64, 2, 32)])
+@pytest.mark.parametrize("blocks,tail", [(64, 0), (65, 9)])
+def test_wide_chain_of_64_blocks_in_rounds(oracle, dk, dv, r, chunk, blocks, tail):
+    """The same at d = 64, where wide d_v takes the chain in more than one round from 64 blocks on."""
+    assert _wide_chain(oracle, dk, dv, r, chunk, 1, blocks, tail)
+
+
+def _wide_chain(oracle, dk, dv, r, chunk, more, blocks, tail):
     import torch
     from paper_2504_00492_amd import binding as pf
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -122,7 +133,7 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     chain = heads * (dv // 32) <= cus or blocks >= (5 if dk == 128 else 16 if dv <= 64 else 64)
     assert f"pf::scan_kernel<{dk}, 64, {chunk}, 32, true, false{'' if chain else ', false'}>" in names
     if tail:
-        return
+        return chain
     L = blocks * chunk
     w = synth.Workload("wide", "bf16", 1, heads, L, dk, dv, r, 64, seed=blocks, s0_std=0.2, reflect_frac=0.05)
     dev = to_device(w, synth.make_inputs(w))
@@ -135,6 +146,7 @@ def test_wide_chain_in_rounds(oracle, dk, dv, r, chunk, more, blocks, tail):
     torch.cuda.synchronize()
     # the same sums in the same order, rounded at the same places
     assert torch.equal(O, O2) and torch.equal(SL, SL2)
+    return chain
 
 
 # what a call with d_k, d_v, r, L takes besides the workgroups of the chain, on 256 compute units: other workgroups that ask for lines
