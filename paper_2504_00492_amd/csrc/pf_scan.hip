@@ -91,7 +91,7 @@ __device__ __forceinline__ void split_scan(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
     const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv,
-    char *smem)
+    int apart, char *smem)
 {
     // With GEN, K is the array of B rows, `beta` the array of A rows (n x d each) and V the array
     // of Atil rows: R = Atil + A S^T, U_eff = T R, S += U_eff^T B, O = Q S^T + P U_eff.
@@ -141,10 +141,10 @@ __device__ __forceinline__ void split_scan(
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane0 = threadIdx.x & 63;
 
-    // The workgroups of one (b, h) share K, Q, T, P through their XCD's L2.
+    // The workgroups of one (b, h) share K, Q, T, P through their XCD's L2: consecutive ones of an XCD, or `apart` (tiles_apart) by nchains.
     const unsigned tiles = gridDim.x / (unsigned)nchains, work = xcd_consecutive(blockIdx.x, gridDim.x);
-    const int tile = work % tiles;
-    const size_t chain = work / tiles;
+    const int tile = apart ? blockIdx.x / nchains : work % tiles;
+    const size_t chain = apart ? blockIdx.x % nchains : work / tiles;
     const int dv0 = tile * TV;
     const size_t c0 = chain * (size_t)NC;
     // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: in Q, K,
@@ -681,19 +681,19 @@ struct ScanBody {
 };
 
 typedef void ScanFn(const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const bf16 *, const float *, bf16 *,
-                    float *, int, int, int, int);
+                    float *, int, int, int, int, int);
 
 template <int D, int N, int C, int TV, bool RO, bool GEN>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(   // (at most: bounds of 256 and below bring in AGPR copies)
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, int apart)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (ScanBody<D, N, C, TV, RO, GEN>::kChain)
         chain_scan<D, N, C, TV, RO, TV == 16, false, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
-        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, apart, smem);
 }
 
 // 16 rows: the other body, the split.  32: the chain with two tiles on -T diag(beta), which calls with at most one workgroup a compute
@@ -704,14 +704,14 @@ template <int D, int N, int C, int TV, bool RO, bool GEN, bool OTHER>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, int apart)
 {
     static_assert((OTHER || TV == 32) && !GEN && ChainPlan<D, N, C, TV, RO>::kServes, "the other shapes have one body");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if constexpr (OTHER && ScanBody<D, N, C, TV, RO, GEN, true>::kChain)
         chain_scan<D, N, C, TV, RO, true>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
     else
-        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, smem);
+        split_scan<D, N, C, TV, GEN>(Q, K, V, beta, Tt, Pt, S0, O, SL, nchains, NC, tail, dv, apart, smem);
 }
 
 // the state of a segment from zero and its propagator side by side (ChainPlan, PAIR), TV rows of each to a workgroup
@@ -730,7 +730,7 @@ template <int D, int N, int C>
 __global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
     const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
     const bf16 *__restrict__ beta, const bf16 *__restrict__ Tt, const bf16 *__restrict__ Pt,
-    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv)
+    const float *S0, bf16 *__restrict__ O, float *SL, int nchains, int NC, int tail, int dv, int apart)
 {
     static_assert(ScanBody<D, N, C, 16, true, false>::kChain, "the other shapes take T as it is");
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -746,14 +746,33 @@ __global__ __launch_bounds__(kScanThreads) void scan_plain_kernel(
 
 static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, int threads, size_t lds, const void *Q, const void *K,
                          const void *V, const void *beta, const void *Tt, const void *Pt, const float *S0, void *O, float *SL,
-                         int heads, int NC, int tail, int dv, hipStream_t stream, int extra = 0)
+                         int heads, int NC, int tail, int dv, hipStream_t stream, int extra = 0, int apart = 0)
 {
     hipError_t e = arm_dynamic_lds(armed, reinterpret_cast<const void *>(kern), lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)heads * (dv / rows) + extra), dim3(threads), lds, stream, (const bf16 *)Q,
                        (const bf16 *)K, (const bf16 *)V, (const bf16 *)beta, (const bf16 *)Tt,
-                       (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, dv);
+                       (const bf16 *)Pt, S0, (bf16 *)O, SL, heads, NC, tail, dv, apart);
     return hipGetLastError();
+}
+
+// Whether tiles of 16 rows of the split lie as many as there are heads apart in blockIdx, which keeps a head on an XCD for multiples of
+// eight heads only, instead of side by side.  Where few compute units have a second workgroup, that is then one of the last tiles of
+// every head, which find their lines in L2, else all tiles of a few heads, which the call waits for; with more of them, and in
+// rounds, tiles side by side keep in step.  Whole forward, 1000 tokens, us, side by side / apart (drivers; delta rule alike):
+//   256 compute units, workgroups of                      288          312         320          384          480
+//   d = 64, r = 2    d_v = 48                        58.6 / 54.2   64.8 / 59.7               70.4 / 66.9   83.8 / 84.6
+//                    d_v = 128                                                 48.2 / 45.4   52.7 / 48.0
+//   d = 128, r = 2   d_v = 48                         106 / 96.4    113 / 102                118.5 / 116    131 / 150
+//                    d_v = 128                                                 80.2 / 78.2   81.6 / 81.2
+//   d = 128, r = 4   d_v = 48                         227 / 217                                263 / 320    302 / 386
+//                    d_v = 128                                                  159 / 152      172 / 169
+//   d = 128, r = 1   d_v = 48                        76.2 / 76.9   78.0 / 78.2               87.2 / 89.9    102 / 113
+//                    d_v = 128                                                 63.2 / 64.3   64.9 / 65.4
+static bool tiles_apart(int cus, int heads, int tiles, int n, int chunk)
+{
+    const long long works = (long long)heads * tiles;
+    return heads % 8 == 0 && n > chunk && works > cus && 4 * works <= (n == 64 ? 6ll : 5ll) * cus;
 }
 
 // the body that is usual for TV rows to a workgroup, or (OTHER) the other one
@@ -767,13 +786,14 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
     if constexpr (OTHER) kern = scan_kernel<D, N, C, TV, true, GEN, true>;
     else kern = scan_kernel<D, N, C, TV, true, GEN>;
     static std::atomic<uint64_t> armed{0};
-    int threads = Body::threads, extra = 0;
+    int threads = Body::threads, extra = 0, apart = 0;
     if constexpr (Body::kChain && TV == 16) {
         const int cus = device_cu_count();
         extra = ahead_workgroups(cus, heads, D, dv, C, NC);
         if (Body::Chain::touchers && (extra || !ahead_wavefront(cus, heads, dv, NC, false))) threads -= 64;
     }
-    return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra);
+    if constexpr (!Body::kChain && TV == 16) apart = tiles_apart(device_cu_count(), heads, dv / TV, N, C);
+    return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra, apart);
 }
 
 template <int D, int N, int C>

@@ -150,3 +150,34 @@ def test_parity_beyond_the_compute_units(oracle, heads, L, dk, dv, r):
     Oref, SLref = oracle.delta_fwd(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
     SLn, SLref = SL.cpu().numpy().reshape(heads, dv, dk), np.asarray(SLref).reshape(heads, dv, dk)
     assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("drivers", [False, True])
+@pytest.mark.parametrize("heads,dk,dv,r,L", [(88, 64, 48, 2, 70), (96, 64, 48, 2, 64), (97, 128, 48, 2, 64), (128, 64, 48, 2, 45), (136, 128, 48, 2, 40),
+                                             (104, 128, 48, 4, 40), (112, 64, 48, 4, 64), (96, 128, 48, 1, 64)])
+def test_parity_of_both_orders_of_tiles(oracle, heads, dk, dv, r, L, drivers):
+    """Workgroups of the split with 16 rows around the lines between the two orders of its tiles: as many as compute units and a few
+    more, one and a quarter times and one and a half times as many, heads that are no multiple of eight."""
+    import torch
+    from gpu_util import assert_parity, flat_heads, output_stats, rel_l2, to_device
+    from paper_2504_00492_amd import binding as pf  # noqa: F811
+    w = synth.Workload("order", "bf16", 1, heads, L, dk, dv, r, 64, seed=heads + r, s0_std=0.2, reflect_frac=0.05)
+    print(f"[case] order of tiles heads={heads} L={L} d=({dk},{dv}) r={r} drivers={drivers}", flush=True)
+    inp = synth.make_inputs(w)
+    dev = to_device(w, inp)
+    if drivers:
+        A, Bm = (dev["beta"][..., None] * dev["K"]).contiguous(), (-dev["K"]).contiguous()
+        O, SL = torch.empty(1, heads, L, dv, dtype=torch.bfloat16, device="cuda:0"), torch.empty(1, heads, dv, dk, device="cuda:0")
+        need = pf.pf_flow_fwd_mfma_workspace_bytes(1, heads, L, dk, dv, r, 64, pf.PF_BF16)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        assert pf.pf_flow_fwd_mfma(dev["Q"], A, dev["V"], Bm, dev["S0"], O, SL, 1, heads, L, dk, dv, r, 64, pf.PF_BF16, ws, need) == pf.PF_OK
+        f = lambda x: flat_heads(x.float().cpu().numpy())
+        heads_of = zip(f(A), f(dev["V"]), f(Bm), f(dev["Q"]), f(dev["S0"]))
+        Oref, SLref = (np.stack(x) for x in zip(*(oracle.flow_head(*x) for x in heads_of)))
+    else:
+        O, SL = pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64)
+        Oref, SLref = oracle.delta_fwd(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
+    torch.cuda.synchronize()
+    SLn, SLref = SL.cpu().numpy().reshape(heads, dv, dk), np.asarray(SLref).reshape(heads, dv, dk)
+    assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
