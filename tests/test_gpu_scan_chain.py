@@ -200,3 +200,28 @@ def test_split_scan_with_and_without_the_wavefront_that_asks(oracle, heads, dv, 
     Oref, SLref = oracle.delta_fwd(inp["Q"], inp["K"], inp["V"], inp["beta"], inp["S0"])
     SLn, SLref = SL.cpu().numpy().reshape(heads, dv, 128), np.asarray(SLref).reshape(heads, dv, 128)
     assert_parity(output_stats(flat_heads(O.float().cpu().numpy()), Oref), [rel_l2(SLn[h], SLref[h]) for h in range(heads)], "bf16")
+
+
+@pytest.mark.parametrize("heads,dk,dv,r,L", [(24, 64, 64, 2, 30 * 32 + 5), (20, 128, 128, 2, 40 * 32), (16, 128, 128, 2, 26 * 32)])
+def test_pairs_on_two_streams(heads, dk, dv, r, L):
+    """Two calls at a time, on two streams, with and without workgroups that ask ahead, each with a workspace of its own: the same bits
+    as one after the other."""
+    import torch
+    from paper_2504_00492_amd import binding as pf
+    print(f"[case] two streams heads={heads} L={L} d=({dk},{dv}) r={r}", flush=True)
+    need = pf.pf_delta_fwd_workspace_bytes(1, heads, L, dk, dv, r, 64, pf.PF_BF16)
+    calls = []
+    for seed in (1, 2):
+        w = synth.Workload("pair", "bf16", 1, heads, L, dk, dv, r, 64, seed=seed, s0_std=0.2, reflect_frac=0.05)
+        dev, ws = to_device(w, synth.make_inputs(w)), torch.empty(need, dtype=torch.uint8, device="cuda:0")
+        calls.append(lambda dev=dev, ws=ws: pf.delta_fwd(dev["Q"], dev["K"], dev["V"], dev["beta"], dev["S0"], chunk=64, workspace=ws))
+    alone = [call() for call in calls]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(5):
+        beside = []
+        for stream, call in zip(streams, calls):
+            with torch.cuda.stream(stream):
+                beside.append(call())
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for a, b in zip(alone, beside) for x, y in zip(a, b))
