@@ -104,9 +104,10 @@ size_t pf_delta_fwd_workspace_bytes(int B, int H, int L, int d_k, int d_v, int r
  * "pf::flow_kernel<128, 64, 32, false>;pf::scan_kernel<128, 64, 32, 32, true, false>".  Template
  * arguments: d_k, virtual tokens and tokens of a block as it runs (with r = 4 a block of pf_delta_fwd_block
  * tokens may run as two halves); for the scan and segment kernels then the rows one workgroup owns; for the
- * scan kernel whether it reads out O, whether the instance is the one for general drivers, and a seventh, true,
- * where the other of its two bodies runs: at 16 rows the one of eight wavefronts instead of the chain in one
- * wavefront, at 32 rows the chain, two tiles of 16, instead of that one.  A name stands for one kernel of the
+ * scan kernel whether it reads out O, whether the instance is the one for general drivers, and a seventh where
+ * two bodies serve the shape and the name without it is not the one that runs: at 16 rows true, the body of eight
+ * wavefronts instead of the chain in one wavefront; at 32 rows, where the name without it is the chain with two tiles of
+ * 16, on T, true for the same chain on -T diag(beta) and false for the body of eight wavefronts.  A name stands for one kernel of the
  * library, but for the generic kernel: its bodies share theirs, because the choice depends on the form
  * (pf_delta_fwd or pf_delta_product_fwd) as well, which is not an argument here.  At most cap - 1
  * characters and a terminating NUL are written to buf (buf may be NULL); the return value is the

@@ -39,9 +39,10 @@ struct WorkspacePlan {
 // Segments per head for the segment-parallel scan: 1 (plain hand-over chain per head) unless
 // the chains of the plain scan (heads x d_v tiles) would leave three quarters of the CUs idle
 // and there are enough blocks to cut.  Two passes of the scan kernel (launch_segment_maps, then the readout) then run with
-// `segments` times as many chains.  A block costs 0.6 us in the first, 0.67 with the readout and 0.75 in the plain scan, so
-// G segments pay from 1.27 / G + composition < 0.75 on: two would by little, and only with three quarters of the compute
-// units idle is the gain worth what a call's workspace grows by; powers of two, on whole blocks that divide evenly.
+// `segments` times as many chains.  4 heads x 4096 tokens, d = 128, r = 2: a block costs 1.2 us in the first (two sets of rows), 1.0
+// with the readout and 0.66 in the plain scan, the composition 11 us; so G segments pay from 2.2 / G + composition < 0.66 on: two
+// would lose, four pay by little, and only with three quarters of the compute units idle is the gain worth what a call's workspace
+// grows by; powers of two, on whole blocks that divide evenly.
 int scan_segments(int heads, int L, int d, int dv, int r, int chunk)
 {
     if (L % chunk != 0 || d != dv) return 1;     // (the composition kernel takes square states)
@@ -114,9 +115,9 @@ int tail_chunk(int d, int dv, int r)
 // Tokens per flow block on the MFMA path: the requested chunk or chunk / 2^j (the flow over a
 // chunk is the composition of the flows over its pieces, Section 3.1).  Small blocks are preferred
 // where an instance exists: the hand-over array T grows with the square of the block and every d_v
-// tile of a head reads all of it.  Measured (us per forward; 64 / 128 / 256 virtual tokens per
-// block), d = 128: 64 heads x 4096 tokens, r = 2: 180 / 225 / 461; 32 heads x 65536, r = 2: 2065 / 2378 / 3227; 32 heads x 8192,
-// r = 4: 438 (as halves of 128: run_in_halves) / 530 / 755; 32 heads x 2048, d = 64, r = 1: 28 / 37 / -.  Blocks of 16 tokens
+// tile of a head reads all of it.  Measured (us per forward, inputs from HBM; 64 / 128 / 256 virtual tokens per
+// block, those through the split entry points), d = 128: 64 heads x 4096 tokens, r = 2: 160 / 257 / 444; 32 heads x 65536, r = 2: 1785 /
+// 2417 / 3238; 32 heads x 8192, r = 4: 394 (as halves of 128: run_in_halves) / 534 / 756; 32 heads x 2048, d = 64, r = 1: 23 / 43 / -.  Blocks of 16 tokens
 // have no instance of their own.  So: 64 virtual tokens if that is at least 32 tokens, else at most 128 virtual tokens,
 // else the largest block that has an instance.  0 when no instance serves these dimensions.
 template <typename Exists>

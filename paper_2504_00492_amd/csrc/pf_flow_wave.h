@@ -15,14 +15,15 @@
 // the rows of G_jj come in 16 reads and go round by DPP (as operands that all lanes read out of LDS, 40 reads of 16 bytes,
 // 32 x 2944 below took 18.0 us: the chain of one block is all it has).
 //
-// What bounds it: HBM (64 heads x 4096 tokens, d = 128, r = 2: 278 MB in 45 us, 6.2 TB/s; 32 heads x 65536: 2.2 GB in
-// 433 us).  The rows of the next block are asked for as soon as the block before has had its two sets of products, and
+// What bounds it: HBM.  Where the scan builds P (pf_chain.h) it reads K and beta and writes T: 64 heads x 4096 tokens, d = 128, r = 2
+// 187 MB in 37 us, 5.1 TB/s, 32 heads x 65536 1.49 GB in 275 us, 5.4 TB/s.  With P (and Q) 278 MB in 45 us, 2.2 GB in 433 us.
+// The rows of the next block are asked for as soon as the block before has had its two sets of products, and
 // eight wavefronts a compute unit at different steps keep the loads going (at d = 64 a third workgroup a compute unit
 // would spill).  The workgroup of eight wavefronts per block that serves the larger blocks (pf_flow.hip) had work for
-// two to four of them here and six barriers; flow alone, us, that body / this one:
-//   64 heads x 4096, d = 128, r = 2    70.2 / 44.7        32 x 2048, d = 64, r = 1    11.2 / 7.9
-//   32 x 65536, d = 128, r = 2          533 / 432         24 x 4096, d = 64, r = 2    26.1 / 13.6
-//   4 x 32768, d = 128, r = 2          36.6 / 23.8        32 x 2944, d = 128, r = 1   18.1 / 14.9 (one block a wavefront)
+// two to four of them here and six barriers; flow alone, us, that body / this one with P, when it was built / without P:
+//   64 heads x 4096, d = 128, r = 2    70.2 / 44.7 / 37      32 x 2048, d = 64, r = 1    11.2 / 7.9 / 6.4
+//   32 x 65536, d = 128, r = 2          533 / 432 / 275      24 x 4096, d = 64, r = 2    26.1 / 13.6 / 10.6
+//   4 x 32768, d = 128, r = 2          36.6 / 23.8 / 20.8    32 x 2944, d = 128, r = 1   18.1 / 14.9 / 11 (one block a wavefront)
 #pragma once
 #include "pf_common.h"
 #include "pf_internal.h"
