@@ -7,49 +7,44 @@ namespace pf {
 // Blocks ahead of the chain that may be asked for (touch_ahead says what other numbers cost).
 constexpr int ahead_window(int d) { return d == 64 ? 18 : 14; }
 
-// What a wavefront that has come to block b does next, with the chain last seen at block `seen`: b, to ask for block b now; a later
-// block, to go on there, because the chain comes to b too soon; or one of
-constexpr int kAheadWait = -1;                   // block b is beyond the window
-constexpr int kAheadStop = -2;                   // nobody watches the chain any more
-constexpr int kAheadLost = -1;                   // (`seen`, then)
-// A wavefront that has fallen behind goes on in the middle of the window: two blocks ahead of the chain it is late again at once
-// (24 heads x 4096 tokens, d = 64, d_v = 128, r = 2, inputs from HBM, all idle compute units: 73.5 us, in the middle 70.2).
-constexpr int ahead_step(int b, int seen, int window)
-{
-    if (seen == kAheadLost) return kAheadStop;
-    if (b > seen + window) return kAheadWait;
-    return b < seen + 2 ? seen + window / 2 : b;
-}
+// A wavefront that has come to block b and last saw the chain at block `at` waits and looks again, or leaves block b out.
+constexpr int kAheadLost = -0x40000000;          // (`at`: nobody watches the chain any more)
+constexpr bool ahead_beyond(int b, int at, int window) { return b > at + window; }
+constexpr bool ahead_late(int b, int at) { return b < at + 2; }
 
 // 128-byte lines of a block (64 virtual tokens) of one head: K, Q, V and the six tiles of T
 constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 + dv + 8 * 6; }
 
 // Workgroups of touch_ahead for the chain with tiles of 16 rows, one to a compute unit.  Such a workgroup has the chain's LDS and
-// registers, so that the compute unit is not free for another stream: no more of them than half of those that the chain leaves idle,
-// at d = 128 none where two such calls fit the chip side by side.  Whole forward, 4096 tokens, r = 2, inputs from HBM, us: one call after the other /
-// a pair on two streams / a call of 6 heads x 1024 tokens, d = 64, on another stream, without, with half and with all:
-//   d = 64, 24 heads               81 / 100 / 44    68 /  88 / 43    68 / 104 /  73
-//           32                     87 / 111 / 45    71 / 104 / 45    71 / 115 /  77
-//           40                     90 / 138 / 45    77 / 127 / 56    73 / 124 /  80
-//           44                     94 / 143 / 46    88 / 152 / 57    78 / 132 /  85
-//           24, d_v = 128          86 / 129 / 45    74 / 122 / 56    70 / 119 /  79
-//           26, d_v = 128          89 / 138 / 46    89 / 142 / 91    76 / 132 /  83
-//   d = 128, 16                   101 / 115 / 40    94 / 131 / 42    94 / 168 / 103
-//            20                   105 / 151 / 41    98 / 149 / 52    98 / 174 / 107
-//            24                   107 / 169 / 41    99 / 167 / 55    99 / 180 / 109
-//            26                   111 / 188 / 42   113 / 203 / 127  102 / 187 / 113
-// What one of them has to ask for during a block of the chain (0.5 us at d = 64, 0.75 at 128) bounds how few they may be: it has
-// 128 lines on their way, some 225 a us from HBM, and the chain asks for a part itself.  Lines a block to each, and the gain: d = 64
-// 204 (24 heads, d_v = 128) 14 %, 217 (13, d_v = 256) 5, 229 (44) 6 but 6 lost by the pair, 295 (26, d_v = 128) none; d = 128 153
-// (20) 7 %, 276 (24) 8, 303 (13, d_v = 256, r = 1) 2, 334 (44, d_v = 64) 3 but 7 lost by the pair, 399 (26) -2.  Halves of rank 4 at
-// d = 128: none (20 heads x 3000 145 / 145).  Fewer blocks: none (24 heads x 800 18.8 / 19.1).  And what lies in the window has to fit
-// the XCDs' 4 MB of L2, which narrow d_v with many heads would not (140 heads, d_v = 16 122 / 127).
+// registers, so that the compute unit is not free for another stream: no more of them than are of use, and at d = 128 none where two
+// such calls fit the chip side by side.  Whole forward, 4096 tokens, r = 2, inputs from HBM, us: one call after the other / a pair on two
+// streams / a call of 6 heads x 1024 tokens, d = 64, on another stream, without, as here, and with all idle compute units:
+//   d = 64, 24 heads (56 of 160)             81 / 103 / 42     67 /  88 / 41     67 / 105 / 73
+//           32 (72 of 128)                   87 / 109 / 44     71 / 108 / 42     71 / 117 / 77
+//           40 (88 of 96)                    90 / 139 / 45     73 / 127 / 82     73 / 127 / 82
+//           44 (all 80)                      94 / 145 / 46     77 / 132 / 86
+//           24, d_v = 128 (all 64)           87 / 130 / 45     68 / 120 / 78
+//           26, d_v = 128 (all 48)           90 / 139 / 46     75 / 133 / 86
+//   d = 128, 16 (none of 128)               101 / 116 / 41                       93 / 166 / 103
+//            20 (40 of 96)                  105 / 149 / 41     97 / 147 / 40     97 / 174 / 108
+//            24 (48 of 64)                  107 / 170 / 41     98 / 170 / 47     99 / 179 / 110
+//            26 (all 48)                    112 / 188 / 42    101 / 185 / 115
+//            28 (all 32)                    112 / 194 / 43    110 / 214 / 125
+// How many are of use: 24 heads, d = 64 (4992 lines a block) 32 of them 69.0 us, 48 67.0, 160 66.9; 32 heads (6656) 32 77.9, 48 71.7, 64
+// 70.8, 128 70.7; 20 heads, d = 128 (7360) 27 101, 32 96.7, 96 97.2.  So one for 100 lines or 220 of a block, in which a compute unit with 128
+// lines on their way from HBM gets about as many (225 a us; 0.5 us at d = 64, 0.75 at 128), and eight at a time, one for each XCD.
+// Where even all of them would have 350 lines each the gain ends: 54 heads, d = 64 (281) 101 / 169 / 48 without, 100 / 177 / 106 with; 28, d = 128
+// (322) above.  Halves of rank 4 at d = 128: 24 heads x 3000 150 / 230 / 43, 148 / 261 / 142.  Few blocks: 24 heads x 800, d = 64 18.8 / 19.1.
+// What lies in the window has to fit the XCDs' L2, 4 MB each, of which the chain has passed a part: to 5 MB.  From the last-level
+// cache ~ from HBM, without / with: 60 heads, d = 128, d_v = 48, r = 1 (4.5 MB) 71 ~ 91 / 75 ~ 78; 110 heads, d = 64, d_v = 16, r = 2 (4.8)
+// 96 ~ 103 / 93 ~ 97; 97 heads, r = 1 (5.1) 48 ~ 63 / 60 ~ 58; 130 heads, d = 128, d_v = 16, r = 1 (8.9) 103 ~ 112 / 124 ~ 122.
 constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int blocks)
 {
-    const int works = heads * (dv / 16), some = (cus - works) / 2;
+    const int works = heads * (dv / 16), idle = cus - works, full = d == 64 ? 100 : 220;
     if (blocks < 24 || (d == 64 ? 8 * works < 3 * cus : 2 * works <= cus || chunk < 32)) return 0;
-    const long long lines = (long long)heads * ahead_lines(d, dv, chunk);
-    return lines <= (d == 64 ? 205ll : 280ll) * some && lines / 8 * 128 * ahead_window(d) <= 4 << 20 ? some : 0;
+    const long long lines = (long long)heads * ahead_lines(d, dv, chunk), need = (lines + 8 * full - 1) / (8 * full) * 8;
+    if (lines > 350ll * idle || lines / 8 * 128 * ahead_window(d) > 5 << 20) return 0;
+    return need < idle ? (int)need : idle;
 }
 
 // Whether the last wavefront of each workgroup of the chain with tiles of 16 rows at d = 128 asks for lines ahead of time, where no

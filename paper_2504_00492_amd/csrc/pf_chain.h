@@ -115,9 +115,10 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 // its XCD come to next, four bytes a line that nobody waits for, so that the chain finds them in L2 (a compute unit's reads come
 // back in order: its own wait for memory holds up the chain's, another's does not).  What bounds it: 128 lines on their way at a time.
 // Its first wavefront looks how far the chain is, until the rest of it is within the window; nothing but time depends on that.  The
-// others ask for no block that the chain was seen to have come to (a workgroup that starts late for one or two, until the first has
-// looked), nor, once that has seen no progress for some 3 ms, for any more.  Who waits for the first ends with it: it leaves when
-// no block is beyond the window, or says that it has lost the chain.
+// others look there when they are through the window that they last saw (at every block, or going on in its middle once late, they are up
+// to 10 % slower: 16 heads x 64967 tokens, d = 64, d_v = 192, r = 2 963 us, so 912), and leave out what the chain had come to then;
+// once the first has seen no progress for some 3 ms, they leave.  Who waits for the first ends with it: it leaves when no block is
+// beyond the window, or says that it has lost the chain.
 // The window: what lies ahead of the chain has to fit an XCD's 4 MB of L2.  Whole forward, us, without / 8, 12, 18 and 24 blocks:
 //   24 heads x 4096, d = 64, r = 2  77.4 / 74.5, 66.4, 65.1, 65.3     20 x 4096, d = 128, r = 2  104 / 99.8, 95.9, 96.4, 96.8
 template <int D, int N, int C, int kRing>
@@ -154,21 +155,17 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
     constexpr int KL = N * D / 64, QL = C * D / 64, TL = 8 * NT;
     const unsigned h0 = first / tiles, heads = (first + count - 1) / tiles - h0 + 1;
     const int VL = N * dv / 64, lines = KL + QL + TL + VL;
-    for (int b = kRing; b < NC;) {
-        // (a plain read waits for every load on its way to LDS first: 88.6 us where it takes 73.2, 24 heads x 4096 tokens,
-        // d_v = 128, r = 2, exact product steps)
-        int now;
-        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(now) : "v"((uint32_t)(uintptr_t)(smem + 256)) : "memory");
-        const int next = ahead_step(b, __builtin_amdgcn_readfirstlane(now), kWindow);
-        if (next == kAheadStop) break;
-        if (next == kAheadWait) {
-            __builtin_amdgcn_s_sleep(2);
-            continue;
+    int at = kRing - kWindow;                              // (so that a workgroup that starts late looks after its first block)
+    for (int b = kRing; b < NC; ++b) {
+        while (ahead_beyond(b, at, kWindow)) {
+            at = *seen;
+            if (at == kAheadLost) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                return;
+            }
+            if (ahead_beyond(b, at, kWindow)) __builtin_amdgcn_s_sleep(2);
         }
-        if (next != b) {
-            b = next;
-            continue;
-        }
+        if (ahead_late(b, at)) continue;
         for (unsigned i = ((wave - 1) * groups + group) * 64 + lane; i < heads * lines; i += (waves - 1) * groups * 64) {
             const size_t head = h0 + i / lines, cid = head * (size_t)NC + b, skew = head * (size_t)tail;
             int l = i % lines;
@@ -183,7 +180,6 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
             }
             load_lds4(a, smem);
         }
-        ++b;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing is under way to LDS when the wave ends
 }
