@@ -142,9 +142,10 @@ __device__ __forceinline__ void split_scan(
     const int lane0 = threadIdx.x & 63;
 
     // The workgroups of one (b, h) share K, Q, T, P through their XCD's L2: consecutive ones of an XCD, or `apart` (tiles_apart) by nchains.
-    const unsigned tiles = gridDim.x / (unsigned)nchains, work = xcd_consecutive(blockIdx.x, gridDim.x);
-    const int tile = apart ? blockIdx.x / nchains : work % tiles;
-    const size_t chain = apart ? blockIdx.x % nchains : work / tiles;
+    const unsigned work = apart ? blockIdx.x : xcd_consecutive(blockIdx.x, gridDim.x), side = apart ? (unsigned)nchains : gridDim.x / (unsigned)nchains;
+    const unsigned over = work / side, in = work % side;
+    const int tile = apart ? over : in;
+    const size_t chain = apart ? in : over;
     const int dv0 = tile * TV;
     const size_t c0 = chain * (size_t)NC;
     // A head holds NC whole blocks followed by `tail` tokens that another kernel takes: in Q, K,
