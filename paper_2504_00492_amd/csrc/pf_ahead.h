@@ -16,8 +16,7 @@ constexpr bool ahead_late(int b, int at) { return b < at + 2; }
 constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 + dv + 8 * 6; }
 
 // Workgroups of touch_ahead for the chain with tiles of 16 rows, one to a compute unit.  Such a workgroup has the chain's LDS and
-// registers, so that the compute unit is not free for another stream: no more of them than are of use, and at d = 128 none where two
-// such calls fit the chip side by side.  Whole forward, 4096 tokens, r = 2, inputs from HBM, us: one call after the other / a pair on two
+// registers, so that the compute unit is not free for another stream: no more of them than are of use.  Whole forward, 4096 tokens, r = 2, inputs from HBM, us: one call after the other / a pair on two
 // streams / a call of 6 heads x 1024 tokens, d = 64, on another stream, without, as here, and with all idle compute units:
 //   d = 64, 24 heads (56 of 160)             81 / 103 / 42     67 /  88 / 41     67 / 105 / 73
 //           32 (72 of 128)                   87 / 109 / 44     71 / 108 / 42     71 / 117 / 77
@@ -25,7 +24,7 @@ constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 
 //           44 (all 80)                      94 / 145 / 46     77 / 132 / 86
 //           24, d_v = 128 (all 64)           87 / 130 / 45     68 / 120 / 78
 //           26, d_v = 128 (all 48)           90 / 139 / 46     75 / 133 / 86
-//   d = 128, 16 (none of 128)               101 / 116 / 41                       93 / 166 / 103
+//   d = 128, 16 (32 of 128)                 101 / 116 / 41     92 / 125 / 40     93 / 166 / 103
 //            20 (40 of 96)                  105 / 149 / 41     97 / 147 / 40     97 / 174 / 108
 //            24 (48 of 64)                  107 / 170 / 41     98 / 170 / 47     99 / 179 / 110
 //            26 (all 48)                    112 / 188 / 42    101 / 185 / 115
@@ -35,13 +34,15 @@ constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 
 // lines on their way from HBM gets about as many (225 a us; 0.5 us at d = 64, 0.75 at 128), and eight at a time, one for each XCD.
 // Where even all of them would have 350 lines each the gain ends: 54 heads, d = 64 (281) 101 / 169 / 48 without, 100 / 177 / 106 with; 28, d = 128
 // (322) above.  Halves of rank 4 at d = 128: 24 heads x 3000 150 / 230 / 43, 148 / 261 / 142.  Few blocks: 24 heads x 800, d = 64 18.8 / 19.1.
+// Few workgroups, from the last-level cache ~ from HBM, without / with: 12 heads, d = 128 90 ~ 102 / 91 ~ 93, 17 heads, d = 64 63 ~ 78 / 64 ~ 66:
+// the lines, at a half and three eighths of the compute units, lie where the first of the two begins to gain.
 // What lies in the window has to fit the XCDs' L2, 4 MB each, of which the chain has passed a part: to 5 MB.  From the last-level
 // cache ~ from HBM, without / with: 60 heads, d = 128, d_v = 48, r = 1 (4.5 MB) 71 ~ 91 / 75 ~ 78; 110 heads, d = 64, d_v = 16, r = 2 (4.8)
 // 96 ~ 103 / 93 ~ 97; 97 heads, r = 1 (5.1) 48 ~ 63 / 60 ~ 58; 130 heads, d = 128, d_v = 16, r = 1 (8.9) 103 ~ 112 / 124 ~ 122.
 constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int blocks)
 {
     const int works = heads * (dv / 16), idle = cus - works, full = d == 64 ? 100 : 220;
-    if (blocks < 24 || (d == 64 ? 8 * works < 3 * cus : 2 * works <= cus || chunk < 32)) return 0;
+    if (blocks < 24 || (d == 64 ? 8 * works < 3 * cus : 2 * works < cus || chunk < 32)) return 0;
     const long long lines = (long long)heads * ahead_lines(d, dv, chunk), need = (lines + 8 * full - 1) / (8 * full) * 8;
     if (lines > 350ll * idle || lines / 8 * 128 * ahead_window(d) > 5 << 20) return 0;
     return need < idle ? (int)need : idle;
