@@ -116,7 +116,7 @@ __device__ __forceinline__ void load_lds2(const bf16 *src, char *dst)
 // back in order: its own wait for memory holds up the chain's, another's does not).  What bounds it: 128 lines on their way at a time.
 // Its first wavefront looks how far the chain is, until the rest of it is within the window; nothing but time depends on that.  The
 // others look there when they are through the window that they last saw (at every block, or going on in its middle once late, they are up
-// to 10 % slower: 16 heads x 64967 tokens, d = 64, d_v = 192, r = 2 963 us, so 912), and leave out what the chain had come to then;
+// to 10 % slower: 16 heads x 64967 tokens, d = 64, d_v = 192, r = 2 963 us, so 880), and leave out what the chain had come to then;
 // once the first has seen no progress for some 3 ms, they leave.  Who waits for the first ends with it: it leaves when no block is
 // beyond the window, or says that it has lost the chain.
 // The window: what lies ahead of the chain has to fit an XCD's 4 MB of L2.  Whole forward, us, without / 8, 12, 18 and 24 blocks:
@@ -158,7 +158,10 @@ __device__ __forceinline__ void touch_ahead(const bf16 *Q, const bf16 *K, const 
     int at = kRing - kWindow;                              // (so that a workgroup that starts late looks after its first block)
     for (int b = kRing; b < NC; ++b) {
         while (ahead_beyond(b, at, kWindow)) {
-            at = *seen;
+            // (the plain read waits for all that is on its way to LDS first, which pays with the many lines of r = 1: 30 heads x 34581
+            // tokens, d = 64, d_v = 96 319 us, else 330; with r = 2, 35 heads x 38963, d = 64 623, else 586, r = 4, 30 x 10624 310 / 297)
+            if constexpr (C < 64) asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(at) : "v"((uint32_t)(uintptr_t)(smem + 256)) : "memory");
+            else at = *seen;
             if (at == kAheadLost) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 return;
