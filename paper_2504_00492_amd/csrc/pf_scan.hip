@@ -757,11 +757,11 @@ static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, i
     return hipGetLastError();
 }
 
-// Whether tiles of 16 rows of the split lie as many as there are heads apart in blockIdx, which keeps a head on an XCD for multiples of
-// eight heads only, instead of side by side.  Where few compute units have a second workgroup, that is then one of the last tiles of
+// Whether the tiles of a head lie as many as there are heads apart in blockIdx in the split, which keeps a head on an XCD for multiples
+// of eight heads only, instead of side by side.  Where few compute units have a second workgroup, that is then one of the last tiles of
 // every head, which find their lines in L2, else all tiles of a few heads, which the call waits for; with more of them, and in
 // rounds, tiles side by side keep in step.  Whole forward, 1000 tokens, us, side by side / apart (drivers; delta rule alike):
-//   256 compute units, workgroups of                      288          312         320          384          480
+//   tiles of 16 rows, workgroups to 256 compute units     288          312         320          384          480
 //   d = 64, r = 2    d_v = 48                        58.6 / 54.2   64.8 / 59.7               70.4 / 66.9   83.8 / 84.6
 //                    d_v = 128                                                 48.2 / 45.4   52.7 / 48.0
 //   d = 128, r = 2   d_v = 48                         106 / 96.4    113 / 102                118.5 / 116    131 / 150
@@ -770,10 +770,27 @@ static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, i
 //                    d_v = 128                                                  159 / 152      172 / 169
 //   d = 128, r = 1   d_v = 48                        76.2 / 76.9   78.0 / 78.2               87.2 / 89.9    102 / 113
 //                    d_v = 128                                                 63.2 / 64.3   64.9 / 65.4
-static bool tiles_apart(int cus, int heads, int tiles, int n, int chunk)
+// Tiles of 32 rows, inputs from HBM (those from the last-level cache: within 5 %, but 160 heads, d = 64, d_v = 64, 69.7 / 79.7):
+//   workgroups                                            272          288          320          352          384
+//   d = 64, r = 2    d_v = 64                        85.0 / 76.0  87.3 / 77.7  91.7 / 82.4  97.8 / 94.6   99.6 / 95.8
+//                    d_v = 128                                    67.2 / 62.1  68.6 / 63.4  70.4 / 72.1   72.7 / 73.5
+//            r = 1   d_v = 64                                     67.5 / 64.0  69.0 / 66.4                75.4 / 75.8
+//   d = 128, r = 2   d_v = 64                         126 / 120                 138 / 137    148 / 155    155 / 173
+//                    d_v = 128, 96 (264, 312, 336)                 103 / 98.0   108 / 102    112 / 104     114 / 111
+//                                                     104 / 99.5                120 / 109    120 / 111
+//                    d_v = 160 (280), 256                         90.6 / 89.8  95.9 / 97.8, 89.8 / 90.7
+//            r = 1   d_v = 128                                    82.4 / 81.9  83.2 / 83.4                85.6 / 88.1
+//   d = 128, r = 4   d_v = 128                                     234 / 229    120 / 117 (512 tokens)  251 / 265   260 / 281
+//   d = 64, r = 4    d_v = 64                                      193 / 193    205 / 218
+static bool tiles_apart(int cus, int heads, int tiles, int rows, int d, int n, int chunk)
 {
     const long long works = (long long)heads * tiles;
-    return heads % 8 == 0 && n > chunk && works > cus && 4 * works <= (n == 64 ? 6ll : 5ll) * cus;
+    if (heads % 8 != 0 || works <= cus) return false;
+    if (rows == 32) {
+        if (d == 128 && tiles > 4) return false;
+        return 8 * works <= (n != 64 || (d == 128 && n == chunk) ? 9ll : d == 128 && tiles > 2 ? 12ll : 10ll) * cus;
+    }
+    return n > chunk && 4 * works <= (n == 64 ? 6ll : 5ll) * cus;
 }
 
 // the body that is usual for TV rows to a workgroup, or (OTHER) the other one
@@ -793,7 +810,7 @@ static hipError_t launch_scan(const void *Q, const void *K, const void *V, const
         extra = ahead_workgroups(cus, heads, D, dv, C, NC);
         if (Body::Chain::touchers && (extra || !ahead_wavefront(cus, heads, dv, NC, false))) threads -= 64;
     }
-    if constexpr (!Body::kChain && TV == 16) apart = tiles_apart(device_cu_count(), heads, dv / TV, N, C);
+    if constexpr (!Body::kChain) apart = tiles_apart(device_cu_count(), heads, dv / TV, TV, D, N, C);
     return launch(kern, armed, TV, threads, Body::lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, extra, apart);
 }
 
@@ -816,7 +833,8 @@ static hipError_t launch_scan_wide_split(const void *Q, const void *K, const voi
     static_assert(lds <= kMaxLdsBytes, "scan kernel LDS plan exceeds the CU");
     ScanFn *kern = scan_kernel<D, N, C, 32, true, false, false>;
     static std::atomic<uint64_t> armed{0};
-    return launch(kern, armed, 32, kScanThreads, lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream);
+    const int apart = tiles_apart(device_cu_count(), heads, dv / 32, 32, D, N, C);
+    return launch(kern, armed, 32, kScanThreads, lds, Q, K, V, beta, Tt, Pt, S0, O, SL, heads, NC, tail, dv, stream, 0, apart);
 }
 
 int scan_dv_tile(int heads, int dv, int n)

@@ -155,10 +155,12 @@ def test_parity_beyond_the_compute_units(oracle, heads, L, dk, dv, r):
 @pytest.mark.gpu
 @pytest.mark.parametrize("drivers", [False, True])
 @pytest.mark.parametrize("heads,dk,dv,r,L", [(88, 64, 48, 2, 70), (96, 64, 48, 2, 64), (97, 128, 48, 2, 64), (128, 64, 48, 2, 45), (136, 128, 48, 2, 40),
-                                             (104, 128, 48, 4, 40), (112, 64, 48, 4, 64), (96, 128, 48, 1, 64)])
+                                             (104, 128, 48, 4, 40), (112, 64, 48, 4, 64), (96, 128, 48, 1, 64),
+                                             (136, 64, 64, 2, 70), (160, 64, 64, 2, 40), (168, 64, 64, 1, 64), (96, 128, 128, 2, 40), (104, 128, 128, 2, 64), (73, 128, 128, 2, 64),
+                                             (176, 128, 64, 2, 40), (64, 128, 160, 2, 40), (72, 128, 128, 1, 70), (72, 128, 128, 4, 40), (80, 64, 128, 4, 64)])
 def test_parity_of_both_orders_of_tiles(oracle, heads, dk, dv, r, L, drivers):
-    """Workgroups of the split with 16 rows around the lines between the two orders of its tiles: as many as compute units and a few
-    more, one and a quarter times and one and a half times as many, heads that are no multiple of eight."""
+    """Workgroups of the split, with 16 rows and with 32, around the lines between the two orders of its tiles: as many as compute units
+    and a few more, one and a quarter times and one and a half times as many, heads that are no multiple of eight."""
     import torch
     from gpu_util import assert_parity, flat_heads, output_stats, rel_l2, to_device
     from paper_2504_00492_amd import binding as pf  # noqa: F811
