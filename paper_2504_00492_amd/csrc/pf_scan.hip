@@ -780,15 +780,15 @@ static hipError_t launch(ScanFn *kern, std::atomic<uint64_t> &armed, int rows, i
 //                                                     104 / 99.5                120 / 109    120 / 111
 //                    d_v = 160 (280), 256                         90.6 / 89.8  95.9 / 97.8, 89.8 / 90.7
 //            r = 1   d_v = 128                                    82.4 / 81.9  83.2 / 83.4                85.6 / 88.1
-//   d = 128, r = 4   d_v = 128                                     234 / 229    120 / 117 (512 tokens)  251 / 265   260 / 281
-//   d = 64, r = 4    d_v = 64                                      193 / 193    205 / 218
+//   r = 4            d = 128, d_v = 128, d_v = 96 (1443 tokens)    234 / 229, 365 / 372                   260 / 281
+//                    d = 64, d_v = 64                              193 / 193    205 / 218
 static bool tiles_apart(int cus, int heads, int tiles, int rows, int d, int n, int chunk)
 {
     const long long works = (long long)heads * tiles;
     if (heads % 8 != 0 || works <= cus) return false;
     if (rows == 32) {
-        if (d == 128 && tiles > 4) return false;
-        return 8 * works <= (n != 64 || (d == 128 && n == chunk) ? 9ll : d == 128 && tiles > 2 ? 12ll : 10ll) * cus;
+        if (n != 64 || (d == 128 && tiles > 4)) return false;
+        return 8 * works <= (d == 64 ? 10ll : n == chunk ? 9ll : tiles > 2 ? 12ll : 10ll) * cus;
     }
     return n > chunk && 4 * works <= (n == 64 ? 6ll : 5ll) * cus;
 }
