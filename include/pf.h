@@ -138,9 +138,9 @@ size_t pf_delta_fwd_describe(int B, int H, int L, int d_k, int d_v, int r, int c
  * Returns PF_OK after enqueueing, else the first failed check (see pf_status).
  * L == 0 is valid: the five sequence pointers may then be NULL, nothing is written to O and
  * S_L receives S0 (or zeros).
- * Calls on several streams run side by side as far as their kernels fit the GPU.  Where the scan of a bf16 call occupies more
- * than half of the compute units (d_k = 64: more than three eighths), up to all of the others load for it ahead of time until
- * shortly before its end, so that a small call on another stream may have to wait for that.
+ * Calls on several streams run side by side as far as their kernels fit the GPU.  Where the scan of a bf16 call occupies an
+ * eighth of the compute units or more, some of the others, the more the wider it is and up to all of them, load for it ahead of
+ * time until shortly before its end, so that a small call on another stream may have to wait for that.
  */
 pf_status pf_delta_fwd(const void *Q, const void *K, const void *V, const void *beta,
                        const float *S0, void *O, float *S_L,

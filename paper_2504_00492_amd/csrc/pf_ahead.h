@@ -32,17 +32,26 @@ constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 
 // How many are of use: 24 heads, d = 64 (4992 lines a block) 32 of them 69.0 us, 48 67.0, 160 66.9; 32 heads (6656) 32 77.9, 48 71.7, 64
 // 70.8, 128 70.7; 20 heads, d = 128 (7360) 27 101, 32 96.7, 96 97.2.  So one for 100 lines or 220 of a block, in which a compute unit with 128
 // lines on their way from HBM gets about as many (225 a us; 0.5 us at d = 64, 0.75 at 128), and eight at a time, one for each XCD.
+// Halves of rank 4 take 0.6 us a block, one for 150 lines: 25 heads x 7263, d = 128 (56 of 56) 326 us, 40 of them 337, none 347.
 // Where even all of them would have 350 lines each the gain ends: 54 heads, d = 64 (281) 101 / 169 / 48 without, 100 / 177 / 106 with; 28, d = 128
-// (322) above.  Halves of rank 4 at d = 128: 24 heads x 3000 150 / 230 / 43, 148 / 261 / 142.  Few blocks: 24 heads x 800, d = 64 18.8 / 19.1.
-// Few workgroups, from the last-level cache ~ from HBM, without / with: 12 heads, d = 128 90 ~ 102 / 91 ~ 93, 17 heads, d = 64 63 ~ 78 / 64 ~ 66:
-// the lines, at a half and three eighths of the compute units, lie where the first of the two begins to gain.
+// (322) above.  Few blocks: 24 heads x 800, d = 64 18.8 / 19.1.
+// Halves of rank 4, from HBM, without / with, one after the other, pairs: 16 heads x 8000, d = 128 327 / 324, 20 x 4096 303 / 296 (a pair),
+// 24 x 3000 149 / 147, 262 / 289, 24 x 6000 275 / 264, 25 x 7263 347 / 326, 634 / 628, 40 x 3000, d_v = 64 169 / 158; 16 x 3000 140 / 142, 8 x 3001 137 /
+// 139: from half of the compute units on (d = 64: three eighths).
+// Rank 1 and 2 with few workgroups: from HBM the chain's own reads (Q among them since P is built there) hold it up as they do many; from an
+// eighth of the compute units on.  3001 tokens, from the last-level cache ~ from HBM, without / with:
+//   d = 128, r = 1   4 heads 52.0 ~ 58.3 / 49.9 ~ 51.0   12, d_v = 64 56.6 ~ 68.2 / 52.8 ~ 54.4   16, d_v = 32 55.1 ~ 65.1 / 53.3 ~ 54.8
+//            r = 2   4 heads 74.0 ~ 81.3 / 75.3 ~ 76.3   8, d_v = 64 75.1 ~ 85.6 / 76.6 ~ 77.6    10 x 20001 467 ~ 482 / 405 ~ 408
+//   d = 64,  r = 1   8 heads 35.7 ~ 42.4 / 34.7 ~ 35.2   16 38.7 ~ 48.4 / 36.8 ~ 37.5             10 x 20001 172 ~ 233 / 148 ~ 153
+//            r = 2   8 heads 53.1 ~ 60.9 / 54.2 ~ 54.4   12 55.1 ~ 64.9 / 55.9 ~ 56.5             12 x 900, d = 128 31.8 ~ 34.5 / 32.2 ~ 33.3
+// and pairs on two streams, 4096 tokens, from HBM: d = 128 12 heads 125 / 115, r = 1 88 / 71, 8 heads 122 / 125, d = 64 12 heads 79 / 82, 16, r = 1 63 / 66.
 // What lies in the window has to fit the XCDs' L2, 4 MB each, of which the chain has passed a part: to 5 MB.  From the last-level
 // cache ~ from HBM, without / with: 60 heads, d = 128, d_v = 48, r = 1 (4.5 MB) 71 ~ 91 / 75 ~ 78; 110 heads, d = 64, d_v = 16, r = 2 (4.8)
 // 96 ~ 103 / 93 ~ 97; 97 heads, r = 1 (5.1) 48 ~ 63 / 60 ~ 58; 130 heads, d = 128, d_v = 16, r = 1 (8.9) 103 ~ 112 / 124 ~ 122.
 constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int blocks)
 {
-    const int works = heads * (dv / 16), idle = cus - works, full = d == 64 ? 100 : 220;
-    if (blocks < 24 || (d == 64 ? 8 * works < 3 * cus : 2 * works < cus || chunk < 32)) return 0;
+    const int works = heads * (dv / 16), idle = cus - works, full = d == 64 ? 100 : chunk < 32 ? 150 : 220;
+    if (blocks < 24 || 8 * works < (chunk >= 32 ? 1 : d == 64 ? 3 : 4) * cus) return 0;
     const long long lines = (long long)heads * ahead_lines(d, dv, chunk), need = (lines + 8 * full - 1) / (8 * full) * 8;
     if (lines > 350ll * idle || lines / 8 * 128 * ahead_window(d) > 5 << 20) return 0;
     return need < idle ? (int)need : idle;
