@@ -38,12 +38,13 @@ constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 
 // Halves of rank 4, from HBM, without / with, one after the other, pairs: 16 heads x 8000, d = 128 327 / 324, 20 x 4096 303 / 296 (a pair),
 // 24 x 3000 149 / 147, 262 / 289, 24 x 6000 275 / 264, 25 x 7263 347 / 326, 634 / 628, 40 x 3000, d_v = 64 169 / 158; 16 x 3000 140 / 142, 8 x 3001 137 /
 // 139: from half of the compute units on (d = 64: three eighths).
-// Rank 1 and 2 with few workgroups: from HBM the chain's own reads (Q among them since P is built there) hold it up as they do many; from an
-// eighth of the compute units on.  3001 tokens, from the last-level cache ~ from HBM, without / with:
+// Rank 1 and 2 with fewer workgroups: from HBM the chain's own reads (Q among them since P is built there) hold it up as they do many; from an
+// eighth of the compute units on.  At rank 2 it loses 1 % where the inputs lie in the 256 MB of the last-level cache: from 64 MB on, which
+// hardly lie there whole.  3001 tokens, from the last-level cache ~ from HBM, without / with:
 //   d = 128, r = 1   4 heads 52.0 ~ 58.3 / 49.9 ~ 51.0   12, d_v = 64 56.6 ~ 68.2 / 52.8 ~ 54.4   16, d_v = 32 55.1 ~ 65.1 / 53.3 ~ 54.8
-//            r = 2   4 heads 74.0 ~ 81.3 / 75.3 ~ 76.3   8, d_v = 64 75.1 ~ 85.6 / 76.6 ~ 77.6    10 x 20001 467 ~ 482 / 405 ~ 408
+//            r = 2   12 x 4096 87.6 ~ 102 / 88.6 ~ 90.9  8, d_v = 64 75.2 ~ 85.6 / 76.3 ~ 77.5    10 x 20001 467 ~ 482 / 405 ~ 408
 //   d = 64,  r = 1   8 heads 35.7 ~ 42.4 / 34.7 ~ 35.2   16 38.7 ~ 48.4 / 36.8 ~ 37.5             10 x 20001 172 ~ 233 / 148 ~ 153
-//            r = 2   8 heads 53.1 ~ 60.9 / 54.2 ~ 54.4   12 55.1 ~ 64.9 / 55.9 ~ 56.5             12 x 900, d = 128 31.8 ~ 34.5 / 32.2 ~ 33.3
+//            r = 2   8 heads 53.1 ~ 60.9 / 54.2 ~ 54.4   12 55.1 ~ 64.9 / 55.9 ~ 56.5
 // and pairs on two streams, 4096 tokens, from HBM: d = 128 12 heads 125 / 115, r = 1 88 / 71, 8 heads 122 / 125, d = 64 12 heads 79 / 82, 16, r = 1 63 / 66.
 // What lies in the window has to fit the XCDs' L2, 4 MB each, of which the chain has passed a part: to 5 MB.  From the last-level
 // cache ~ from HBM, without / with: 60 heads, d = 128, d_v = 48, r = 1 (4.5 MB) 71 ~ 91 / 75 ~ 78; 110 heads, d = 64, d_v = 16, r = 2 (4.8)
@@ -51,8 +52,9 @@ constexpr int ahead_lines(int d, int dv, int chunk) { return d + chunk * d / 64 
 constexpr int ahead_workgroups(int cus, int heads, int d, int dv, int chunk, int blocks)
 {
     const int works = heads * (dv / 16), idle = cus - works, full = d == 64 ? 100 : chunk < 32 ? 150 : 220;
-    if (blocks < 24 || 8 * works < (chunk >= 32 ? 1 : d == 64 ? 3 : 4) * cus) return 0;
     const long long lines = (long long)heads * ahead_lines(d, dv, chunk), need = (lines + 8 * full - 1) / (8 * full) * 8;
+    const bool few = 8 * works < (d == 64 ? 3 : 4) * cus;
+    if (blocks < 24 || 8 * works < cus || (few && (chunk < 32 || (chunk < 64 && lines * blocks * 128 < 64ll << 20)))) return 0;
     if (lines > 350ll * idle || lines / 8 * 128 * ahead_window(d) > 5 << 20) return 0;
     return need < idle ? (int)need : idle;
 }

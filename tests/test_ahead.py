@@ -76,7 +76,8 @@ def test_nothing_more_once_the_chain_is_lost(ahead):
                                        ((256, 55, 64, 64, 32, 128), 36), ((256, 56, 64, 64, 32, 128), 0),          # too much for each
                                        ((256, 28, 128, 128, 32, 128), 32), ((256, 29, 128, 128, 32, 128), 0),
                                        ((256, 24, 64, 64, 32, 24), 56), ((256, 24, 64, 64, 32, 23), 0),            # too few blocks
-                                       ((256, 4, 128, 128, 32, 128), 8), ((256, 3, 128, 128, 32, 128), 0), ((256, 8, 64, 64, 64, 128), 24), ((256, 7, 64, 64, 64, 128), 0),   # too few workgroups
+                                       ((256, 4, 128, 128, 64, 128), 8), ((256, 3, 128, 128, 64, 128), 0), ((256, 8, 64, 64, 64, 128), 24), ((256, 7, 64, 64, 64, 128), 0),   # too few workgroups
+                                       ((256, 4, 128, 128, 32, 357), 8), ((256, 4, 128, 128, 32, 356), 0), ((256, 23, 64, 64, 32, 110), 48), ((256, 23, 64, 64, 32, 109), 0),   # few and small
                                        ((256, 16, 128, 128, 32, 128), 32), ((256, 12, 128, 128, 64, 128), 24),
                                        ((256, 20, 128, 128, 16, 256), 48), ((256, 16, 128, 128, 16, 256), 40), ((256, 15, 128, 128, 16, 256), 0),   # halves of rank 4
                                        ((256, 24, 64, 64, 16, 128), 48), ((256, 23, 64, 64, 16, 128), 0),
@@ -107,4 +108,5 @@ def test_no_more_than_idle_compute_units_and_what_fits_their_l2(ahead):
                         assert some < 8 + lines / (100 if d == 64 else 220 if chunk >= 32 else 150)
                         if some:
                             assert 8 * works >= (1 if chunk >= 32 else 3 if d == 64 else 4) * cus
+                            assert chunk != 32 or 8 * works >= (3 if d == 64 else 4) * cus or lines * 500 * 128 >= 64 << 20
                             assert lines * 128 * ahead.window(d) <= 8 * (5 << 20) + 8 * 128 * ahead.window(d)

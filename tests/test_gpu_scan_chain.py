@@ -155,7 +155,7 @@ AHEAD = [(24, 64, 64, 2, 24 * 32, 56, 0), (33, 64, 64, 1, 25 * 64 + 5, 80, 0), (
          (24, 128, 128, 2, 27 * 32 + 1, 48, 0), (28, 128, 128, 2, 27 * 32 + 1, 32, 0), (20, 128, 112, 2, 40 * 32, 32, 0), (24, 64, 64, 4, 30 * 32 + 3, 48, 0),
          (44, 64, 64, 2, 24 * 32, 80, 0), (30, 128, 128, 2, 27 * 32 + 1, 0, 1), (16, 128, 128, 4, 30 * 32 + 3, 40, 0), (20, 128, 128, 4, 60 * 32, 48, 0),
          (15, 128, 128, 4, 30 * 32 + 3, 0, 0), (16, 128, 128, 2, 24 * 32, 32, 0), (16, 128, 128, 2, 23 * 32, 0, 1), (5, 128, 128, 1, 24 * 64 + 7, 16, 0),
-         (4, 64, 128, 2, 30 * 32, 16, 0), (33, 64, 16, 1, 24 * 64 + 63, 64, 0), (24, 64, 64, 2, 23 * 32, 0, 0), (70, 128, 48, 2, 24 * 32, 0, 0)]
+         (4, 64, 128, 1, 30 * 64, 16, 0), (8, 128, 64, 2, 24 * 32, 0, 0), (33, 64, 16, 1, 24 * 64 + 63, 64, 0), (24, 64, 64, 2, 23 * 32, 0, 0), (70, 128, 48, 2, 24 * 32, 0, 0)]
 
 
 @pytest.mark.parametrize("heads,dk,dv,r,L,workgroups,wavefront", AHEAD)
